@@ -9,7 +9,8 @@ namespace conef {
 // Device-resident copy of a plan: descriptor array and work tables.
 struct DevicePlan {
     const MatDesc *mats = nullptr;
-    const WorkItem *p_items = nullptr, *q_items = nullptr, *err_items = nullptr;          // generic family
+    const WorkItem *p_items = nullptr, *q_items = nullptr, *err_s_items = nullptr;        // strip kernels (any shape)
+    const WorkItem *err_items = nullptr;        // err pass of blocks the strip kernel does not take
     const WorkItem *p_f_items = nullptr, *q_f_items = nullptr, *err_f_items = nullptr;    // octet family
     const WorkItem *err_t_items = nullptr;      // octet family, err pass with the residual on the fp32 matrix cores
     const WorkItem *p_m_items = nullptr, *q_m_items = nullptr, *err_m_items = nullptr;    // MFMA family
@@ -39,6 +40,10 @@ struct DevicePlan {
     int n_upd = 0;
     int n_pred = 0, n_gram = 0, n_apply = 0, n_qred = 0, n_elem = 0;
     int rank = 0, rpad = 0, bits = 0, block = 0, dtype = 0;
+    int n_err_s = 0, es_lds = 0;    // strip err pass: items, floats of LDS per workgroup
+    int wshift = 0, lb_shift = 0;   // log2(code fields per word), log2(block / 8)
+    float inv_s = 0.0f;             // fl32(1 / s)
+    uint64_t bmagic = 0;            // j / block = mulhi64(j, bmagic) for j < 2^35
     uint32_t seed_lo = 0, seed_hi = 0;
     long long q_elems = 0;
     // Improved contractive error feedback around the rank-r compressor: the FIRST error vector, laid out like the
@@ -124,10 +129,18 @@ void pack_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes,
                  hipStream_t st);
 void pack_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Phat,
                  double *ws, float *Qout, hipStream_t st);
-void generic_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
-                    const float *Q, float *P, hipStream_t st);
-void generic_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
-                    const float *Phat, double *ws, hipStream_t st);
+// any shape, a lane per column (kernels_strip.hip); dp.i_codes as in mfma_pass_p
+void strip_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Q, float *P,
+                  double *ws, hipStream_t st);
+void strip_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Phat,
+                  double *ws, float *Qout, hipStream_t st);
+void strip_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, const float *Phat, const float *Qn,
+                    uint64_t step, hipStream_t st);
+void strip_pass_err_two(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, uint32_t *codes2, float *scales2,
+                        const float *Phat, const float *Qn, uint64_t step, hipStream_t st);
+void strip_cs_pass_p(const DevicePlan &dp, const void *grads, const void *table, const float *Q, float *P, double *ws, hipStream_t st);
+void strip_cs_pass_q(const DevicePlan &dp, const void *grads, const void *table, const float *Phat, double *ws, float *Qout,
+                     hipStream_t st);
 void generic_p_reduce(const DevicePlan &dp, double *ws, float *P, hipStream_t st);       // adds the column-chunk partials of P
 void generic_q_reduce(const DevicePlan &dp, double *ws, float *Qout, hipStream_t st);   // adds the row-tile partials of Q+
 void generic_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, const float *Phat,

@@ -60,67 +60,7 @@ __device__ __forceinline__ double ordered_sum(const double *src, int T, int64_t 
     return T <= 8 ? ordered_sum_batches<8>(src, T, stride) : ordered_sum_batches<32>(src, T, stride);
 }
 
-// ---------------------------------------------------------------- pass 1: P = p * Q
-// One wave per row; lanes stride along the row; wave-level tree sum.
-template <int RP>
-__global__ __launch_bounds__(256) void k_pass_p_generic(DevicePlan dp, const void *grads, const uint32_t *codes,
-                                                        const float *scales, const float *Q, float *P)
-{
-    const WorkItem it = dp.p_items[blockIdx.x];
-    const MatDesc d = dp.mats[it.mat];
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)it.a + (threadIdx.x >> 6);
-    if (row >= d.n) return;
-    const int r = dp.rank;
-    double acc[RP];
-#pragma unroll
-    for (int c = 0; c < RP; ++c) acc[c] = 0.0;
-    for (int64_t k = lane; k < d.m; k += 64) {
-        const double pv = (double)form_p(dp, d, grads, codes, scales, row * d.m + k, dp.omb);
-        const float *qrow = Q + d.q_off + k * r;
-#pragma unroll
-        for (int c = 0; c < RP; ++c)
-            if (c < r) acc[c] = __builtin_fma(pv, (double)qrow[c], acc[c]);
-    }
-#pragma unroll
-    for (int c = 0; c < RP; ++c) acc[c] = wave_sum(acc[c]);
-    if (lane == 0) {
-#pragma unroll
-        for (int c = 0; c < RP; ++c)
-            if (c < r) P[d.p_off + row * r + c] = (float)acc[c];
-    }
-}
-
-// ---------------------------------------------------------------- pass 2: Q+ = p^T * P^
-// One thread per column, one workgroup per (column tile, row tile); partial sums per row
-// tile go to the workspace and are added in row-tile order by k_q_reduce.
-template <int RP>
-__global__ __launch_bounds__(kGenQCols) void k_pass_q_generic(DevicePlan dp, const void *grads, const uint32_t *codes,
-                                                              const float *scales, const float *Phat, double *ws)
-{
-    const WorkItem it = dp.q_items[blockIdx.x];
-    const MatDesc d = dp.mats[it.mat];
-    const int r = dp.rank;
-    const int64_t k = (int64_t)it.a * kGenQCols + threadIdx.x;
-    const int64_t row0 = (int64_t)it.b * d.q_tile_rows;
-    const int64_t row1 = (row0 + d.q_tile_rows < d.n) ? row0 + d.q_tile_rows : d.n;
-    if (k >= d.m) return;
-    double acc[RP];
-#pragma unroll
-    for (int c = 0; c < RP; ++c) acc[c] = 0.0;
-    for (int64_t i = row0; i < row1; ++i) {
-        const double pv = (double)form_p(dp, d, grads, codes, scales, i * d.m + k, dp.omb);
-        const float *prow = Phat + d.p_off + i * r;
-#pragma unroll
-        for (int c = 0; c < RP; ++c)
-            if (c < r) acc[c] = __builtin_fma(pv, (double)prow[c], acc[c]);
-    }
-    double *out = ws + d.qpart_off + ((int64_t)it.b * d.m + k) * r;
-#pragma unroll
-    for (int c = 0; c < RP; ++c)
-        if (c < r) out[c] = acc[c];
-}
-
+// ---------------------------------------------------------------- reduction of the partial sums of Q+
 // Adds the row-tile partial sums of Q+ and rounds once to fp32.  item.c = 0: 256 entries, a thread per entry, the tiles
 // in order.  item.c = 1 (a tall matrix: kQredManyTiles tiles or more): 16 entries; thread (entry, part) adds the tiles
 // part, part + 16, ... in that order, then the 16 parts are added in order (the order of k_gram_reduce).
@@ -548,29 +488,6 @@ __global__ __launch_bounds__(256) void k_zero(uint32_t *a, size_t na, uint32_t *
 
 }  // namespace
 
-#define CONEF_DISPATCH_RP(KERNEL, GRID, BLOCK, ST, ...)                                          \
-    do {                                                                                          \
-        switch (dp.rpad) {                                                                        \
-        case 4: hipLaunchKernelGGL(KERNEL<4>, GRID, BLOCK, 0, ST, __VA_ARGS__); break;            \
-        case 8: hipLaunchKernelGGL(KERNEL<8>, GRID, BLOCK, 0, ST, __VA_ARGS__); break;            \
-        case 16: hipLaunchKernelGGL(KERNEL<16>, GRID, BLOCK, 0, ST, __VA_ARGS__); break;          \
-        default: hipLaunchKernelGGL(KERNEL<32>, GRID, BLOCK, 0, ST, __VA_ARGS__); break;          \
-        }                                                                                         \
-    } while (0)
-
-void generic_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
-                    const float *Q, float *P, hipStream_t st)
-{
-    if (dp.n_p > 0) CONEF_DISPATCH_RP(k_pass_p_generic, dim3(dp.n_p), dim3(256), st, dp, grads, codes, scales, Q, P);
-}
-
-void generic_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
-                    const float *Phat, double *ws, hipStream_t st)
-{
-    if (dp.n_q > 0)
-        CONEF_DISPATCH_RP(k_pass_q_generic, dim3(dp.n_q), dim3(kGenQCols), st, dp, grads, codes, scales, Phat, ws);
-}
-
 void generic_p_reduce(const DevicePlan &dp, double *ws, float *P, hipStream_t st)
 {
     if (dp.n_pred > 0) hipLaunchKernelGGL(k_p_reduce, dim3(dp.n_pred), dim3(256), 0, st, dp, (const double *)ws, P);
@@ -608,6 +525,7 @@ hipError_t launch_pass_err_two(const DevicePlan &dp, const void *grads, uint32_t
     if (span.begin) (void)hipEventRecord(span.begin, st);
     mfma_pass_err_two(dp, grads, codes, scales, codes2, scales2, Phat, ws, step, st);
     octet_pass_err_two(dp, grads, codes, scales, codes2, scales2, Phat, Qn, step, st);
+    strip_pass_err_two(dp, grads, codes, scales, codes2, scales2, Phat, Qn, step, st);
     if (dp.n_err > 0) {
         const uint32_t lo = (uint32_t)step, hi = (uint32_t)(step >> 32);
         switch (dp.rpad) {
@@ -629,7 +547,7 @@ hipError_t launch_pass_p(const DevicePlan &dp, const void *grads, const uint32_t
     mfma_pass_p(dp, grads, codes, scales, Q, P, st);
     pack_pass_p(dp, grads, codes, scales, Q, P, st);
     octet_pass_p(dp, grads, codes, scales, Q, P, ws, st);
-    generic_pass_p(dp, grads, codes, scales, Q, P, st);
+    strip_pass_p(dp, grads, codes, scales, Q, P, ws, st);
     if (span.end) (void)hipEventRecord(span.end, st);
     generic_p_reduce(dp, ws, P, st);
     return hipGetLastError();
@@ -648,7 +566,7 @@ hipError_t launch_pass_q(const DevicePlan &dp, const void *grads, const uint32_t
     mfma_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
     pack_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
     octet_pass_q(dp, grads, codes, scales, Phat, ws, st);
-    generic_pass_q(dp, grads, codes, scales, Phat, ws, st);
+    strip_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
     if (span.end) (void)hipEventRecord(span.end, st);
     // the reduction also writes the matrix-core family's operand splits of Q+
     generic_q_reduce(dp, ws, Qout, st);
@@ -667,6 +585,7 @@ hipError_t launch_pass_err(const DevicePlan &dp, const void *grads, uint32_t *co
     if (span.begin) (void)hipEventRecord(span.begin, st);
     mfma_pass_err(dp, grads, codes, scales, Phat, ws, step, st);
     octet_pass_err(dp, grads, codes, scales, Phat, Qn, step, st);
+    strip_pass_err(dp, grads, codes, scales, Phat, Qn, step, st);
     generic_pass_err(dp, grads, codes, scales, Phat, Qn, step, st);
     if (span.end) (void)hipEventRecord(span.end, st);
     return hipGetLastError();

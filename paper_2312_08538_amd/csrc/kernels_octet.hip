@@ -125,33 +125,6 @@ __device__ __forceinline__ void decode_octet(const RawOctet<BF16, BITS> &r, floa
     }
 }
 
-// Fixed-point stochastic rounding of an octet (quantise_field on each of its 8 values) straight into packed
-// BITS-wide two's-complement fields: 8-bit codes give two words (elements 0..3, 4..7), 4- and 2-bit codes the low
-// 32 / 16 bits of w[0].  Magnitudes and sign bits are gathered field by field and the negation is done on the
-// whole word: with s the sign bit of a field, ((mag ^ (s - (s >> (BITS-1)))) + (s >> (BITS-1))) ^ s is
-// 2^BITS - mag for a negative field with mag >= 1 and 0 for mag = 0; no carry leaves a field.
-template <int BITS>
-__device__ __forceinline__ void quantise_octet(const float x[8], float inv16, const uint32_t rnd[4], uint32_t w[2])
-{
-    constexpr int kPerWord = BITS == 8 ? 4 : 8;
-    constexpr uint32_t kSignBits = BITS == 8 ? 0x80808080u : (BITS == 4 ? 0x88888888u : 0x0000AAAAu);
-#pragma unroll
-    for (int h = 0; h < 8 / kPerWord; ++h) {
-        uint32_t mags = 0, sg = 0;
-#pragma unroll
-        for (int k = kPerWord - 1; k >= 0; --k) {
-            const int e = h * kPerWord + k;
-            const uint32_t U = (uint32_t)(fabsf(x[e]) * inv16);
-            mags = (mags << BITS) | ((U + draw16(rnd, e)) >> 16);
-            sg = __builtin_amdgcn_alignbit(sg, __float_as_uint(x[e]), 32 - BITS);     // (sg << BITS) | top BITS bits of x
-        }
-        sg &= kSignBits;
-        const uint32_t s1 = sg >> (BITS - 1), sm = sg - s1;
-        w[h] = ((mags ^ sm) + s1) ^ sg;
-    }
-    if (BITS != 8) w[1] = 0;
-}
-
 template <int BITS>
 __device__ __forceinline__ void store_code_words(const MatDesc &d, uint32_t *codes, int64_t o, const uint32_t w[2])
 {
@@ -167,19 +140,6 @@ __device__ __forceinline__ void store_code_pair(const MatDesc &d, uint32_t *code
     if (BITS == 8) *reinterpret_cast<uint4 *>(codes + d.word_off + o * 2) = make_uint4(w0[0], w0[1], w1[0], w1[1]);
     else if (BITS == 4) *reinterpret_cast<uint2 *>(codes + d.word_off + o) = make_uint2(w0[0], w1[0]);
     else codes[d.word_off + (o >> 1)] = (w0[0] & 0xFFFFu) | (w1[0] << 16);
-}
-
-// max over the 2^lb_shift lanes of a scale block (aligned group of lanes)
-__device__ __forceinline__ float block_max(float a, int lb_shift)
-{
-    // quad_perm [1,0,3,2] = 0xB1, [2,3,0,1] = 0x4E, row_half_mirror = 0x141, row_mirror = 0x140
-    if (lb_shift >= 1) a = fmaxf(a, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(a), 0xB1, 0xF, 0xF, true)));
-    if (lb_shift >= 2) a = fmaxf(a, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(a), 0x4E, 0xF, 0xF, true)));
-    if (lb_shift >= 3) a = fmaxf(a, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(a), 0x141, 0xF, 0xF, true)));
-    if (lb_shift >= 4) a = fmaxf(a, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(a), 0x140, 0xF, 0xF, true)));
-    if (lb_shift >= 5) a = fmaxf(a, __shfl_xor(a, 16, 64));
-    if (lb_shift >= 6) a = fmaxf(a, __shfl_xor(a, 32, 64));
-    return a;
 }
 
 // One row (RP = rank floats, 8- or 16-byte aligned) of a factor matrix; zeros if !valid.

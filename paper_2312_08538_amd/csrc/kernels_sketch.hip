@@ -41,79 +41,6 @@ __device__ __forceinline__ void table_store(void *table, int f16, int64_t idx, f
 // (1 - beta) with the sign of the row folded in: fma(-(1 - beta), t, g) is fma(1 - beta, -t, g) exactly
 __device__ __forceinline__ float signed_omb(const DevicePlan &dp, int32_t hv) { return hv < 0 ? -dp.omb : dp.omb; }
 
-// ---------------------------------------------------------------- pass 1: P = p * Q
-// One wave per row; lanes stride along the row; wave-level tree sum.
-template <int RP>
-__global__ __launch_bounds__(256) void k_cs_p_generic(DevicePlan dp, const void *grads, const void *table, const float *Q,
-                                                      float *P)
-{
-    const WorkItem it = dp.p_items[blockIdx.x];
-    const MatDesc d = dp.mats[it.mat];
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)it.a + (threadIdx.x >> 6);
-    if (row >= d.n) return;
-    const int r = dp.rank;
-    // row form: the row's bucket and sign; column form (cs_cols_mode): the column's, the table row is the matrix row's
-    const bool colm = dp.cs_cols_mode != 0;
-    const int32_t hv_row = colm ? 0 : dp.row_hash[d.hash_off + row];
-    const int64_t trow = colm ? d.table_off + row * d.w : d.table_off + (int64_t)(hv_row & INT32_MAX) * d.m;
-    double acc[RP];
-#pragma unroll
-    for (int c = 0; c < RP; ++c) acc[c] = 0.0;
-    for (int64_t k = lane; k < d.m; k += 64) {
-        const int32_t hv = colm ? dp.row_hash[d.hash_off + k] : hv_row;
-        const float somb = signed_omb(dp, hv);
-        const float t = table_load(table, dp.table_dtype, colm ? trow + (hv & INT32_MAX) : trow + k);
-        const double pv = (double)__builtin_fmaf(somb, t, load_grad(grads, dp.dtype, d.grad_off + row * d.m + k));
-        const float *qrow = Q + d.q_off + k * r;
-#pragma unroll
-        for (int c = 0; c < RP; ++c)
-            if (c < r) acc[c] = __builtin_fma(pv, (double)qrow[c], acc[c]);
-    }
-#pragma unroll
-    for (int c = 0; c < RP; ++c) acc[c] = wave_sum(acc[c]);
-    if (lane == 0) {
-#pragma unroll
-        for (int c = 0; c < RP; ++c)
-            if (c < r) P[d.p_off + row * r + c] = (float)acc[c];
-    }
-}
-
-// ---------------------------------------------------------------- pass 2: Q+ = p^T * P^
-// One thread per column, one workgroup per (column tile, row tile); partial sums per row tile go to
-// the workspace and are added in row-tile order by the reduction kernel.
-template <int RP>
-__global__ __launch_bounds__(kGenQCols) void k_cs_q_generic(DevicePlan dp, const void *grads, const void *table,
-                                                            const float *Phat, double *ws)
-{
-    const WorkItem it = dp.q_items[blockIdx.x];
-    const MatDesc d = dp.mats[it.mat];
-    const int r = dp.rank;
-    const int64_t k = (int64_t)it.a * kGenQCols + threadIdx.x;
-    const int64_t row0 = (int64_t)it.b * d.q_tile_rows;
-    const int64_t row1 = (row0 + d.q_tile_rows < d.n) ? row0 + d.q_tile_rows : d.n;
-    if (k >= d.m) return;
-    double acc[RP];
-#pragma unroll
-    for (int c = 0; c < RP; ++c) acc[c] = 0.0;
-    const bool colm = dp.cs_cols_mode != 0;
-    const int32_t hv_col = colm ? dp.row_hash[d.hash_off + k] : 0;
-    for (int64_t i = row0; i < row1; ++i) {
-        const int32_t hv = colm ? hv_col : dp.row_hash[d.hash_off + i];
-        const float t = table_load(table, dp.table_dtype, colm ? d.table_off + i * d.w + (hv & INT32_MAX)
-                                                                : d.table_off + (int64_t)(hv & INT32_MAX) * d.m + k);
-        const double pv = (double)__builtin_fmaf(signed_omb(dp, hv), t, load_grad(grads, dp.dtype, d.grad_off + i * d.m + k));
-        const float *prow = Phat + d.p_off + i * r;
-#pragma unroll
-        for (int c = 0; c < RP; ++c)
-            if (c < r) acc[c] = __builtin_fma(pv, (double)prow[c], acc[c]);
-    }
-    double *out = ws + d.qpart_off + ((int64_t)it.b * d.m + k) * r;
-#pragma unroll
-    for (int c = 0; c < RP; ++c)
-        if (c < r) out[c] = acc[c];
-}
-
 // ---------------------------------------------------------------- pass 3: S <- beta S + C(p - P^ Q+^T)
 // One thread per column of a column tile, a run of buckets per workgroup.  The thread keeps its row of
 // Q+ in registers; P^ rows and the bucket lists are uniform over the workgroup.
@@ -1131,7 +1058,7 @@ hipError_t launch_cs_pass_p(const DevicePlan &dp, const void *grads, const void 
     if (span.begin) (void)hipEventRecord(span.begin, st);
     mfma_cs_pass_p(dp, grads, table, Q, P, ws, st);
     if (dp.n_p_f > 0) CONEF_CS_OCTET_DISPATCH(k_cs_p_octet, dim3(dp.n_p_f), st, dp, grads, table, Q, P, ws);
-    if (dp.n_p > 0) CONEF_CS_DISPATCH_RP(k_cs_p_generic, dim3(dp.n_p), dim3(256), st, dp, grads, table, Q, P);
+    strip_cs_pass_p(dp, grads, table, Q, P, ws, st);
     if (span.end) (void)hipEventRecord(span.end, st);
     generic_p_reduce(dp, ws, P, st);
     return hipGetLastError();
@@ -1144,7 +1071,7 @@ hipError_t launch_cs_pass_q(const DevicePlan &dp, const void *grads, const void 
     if (span.begin) (void)hipEventRecord(span.begin, st);
     mfma_cs_pass_q(dp, grads, table, Phat, ws, st);
     if (dp.n_q_f > 0) CONEF_CS_OCTET_DISPATCH(k_cs_q_octet, dim3((dp.n_q_f + 3) / 4), st, dp, grads, table, Phat, ws);
-    if (dp.n_q > 0) CONEF_CS_DISPATCH_RP(k_cs_q_generic, dim3(dp.n_q), dim3(kGenQCols), st, dp, grads, table, Phat, ws);
+    strip_cs_pass_q(dp, grads, table, Phat, ws, Qout, st);
     if (span.end) (void)hipEventRecord(span.end, st);
     generic_q_reduce(dp, ws, Qout, st);
     return hipGetLastError();

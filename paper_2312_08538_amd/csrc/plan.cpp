@@ -382,6 +382,12 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         plan = Plan();
         plan.rank = rank; plan.bits = bits; plan.block = block; plan.dtype = dtype; plan.seed = seed;
         plan.rpad = rank <= 4 ? 4 : rank <= 8 ? 8 : rank <= 16 ? 16 : 32;
+        plan.wshift = log2i(W);
+        plan.inv_s = 1.0f / (float)((1 << (bits - 1)) - 1);
+        plan.bmagic = is_pow2(block) ? ((uint64_t)1 << 63) / (uint64_t)(block >> 1) : ~(uint64_t)0 / (uint64_t)block + 1;
+        // blocks that a power-of-two number of lanes, at most a wave, holds in octets: the strip err pass takes them
+        const bool octet_blocks = block % 8 == 0 && is_pow2(block / 8) && block / 8 <= 64;
+        plan.lb_shift = octet_blocks ? log2i(block / 8) : 0;
         plan.mats.resize(n_mats);
 
         // The octet family needs whole scale blocks per row, a power-of-two number of lanes (8 elements
@@ -405,7 +411,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         // (1024 / bits columns) and of every block size of the family
         const int p_cols = 512;
 
-        int64_t g = 0, w = 0, s = 0, p = 0, q = 0, wd = 0;
+        int64_t g = 0, w = 0, s = 0, p = 0, q = 0, wd = 0, strip_elems = 0;
         for (int l = 0; l < n_mats; ++l) {
             MatDesc &d = plan.mats[l];
             d = MatDesc();
@@ -442,7 +448,19 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                       d.m % 128 == 0 && d.m <= (1 << 24)) ? 1 : 0;
             if (d.path == kPathOctet) plan.any_octet = true;
             else if (d.path == kPathMfma) plan.any_mfma = true;
-            else plan.any_generic = true;
+            else {
+                plan.any_generic = true;
+                strip_elems += d.N;
+            }
+        }
+        // The strip kernels: about 1536 workgroups per launch (six per CU) where the model is large enough, with limits that
+        // keep a workgroup's fixed part (operand set-up, the sum over its waves, partial sums to be added later) small
+        // against its share of the elements.
+        const int64_t strip_chunk = std::min<int64_t>(2048, std::max<int64_t>(256, round_up(strip_elems / (kStripRows * 1536), 256)));
+        const int64_t strip_q_rows = std::min<int64_t>(512, std::max<int64_t>(32, round_up(strip_elems / (64 * 1536), 32)));
+        const int64_t strip_err = strip_elems / 8192 >= 1024 ? 8192 : strip_elems / 4096 >= 768 ? 4096 : 2048;
+        for (int l = 0; l < n_mats; ++l) {
+            MatDesc &d = plan.mats[l];
             if (d.path == kPathMfma) {
                 d.scT_off = wd; wd += round_up((d.m / 128) * d.n * 4 / 8 + 1, 32);
                 d.scT2_off = wd; wd += round_up((d.m / 128) * d.n * 4 / 8 + 1, 32);
@@ -454,21 +472,39 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
             d.gram_off = wd; wd += (int64_t)d.n_gram_tiles * rank * rank;
             d.gsum_off = wd; wd += rank * rank;
             d.rinv_off = wd; wd += rank * rank;
-            // generic family: short row tiles for small matrices (their workgroups are latency bound,
-            // so parallelism has to come from the number of tiles)
-            const int gen_q_rows = d.n <= 1024 ? 16 : kGenQRows;
-            d.q_tile_rows = d.cs_lin ? 2048 : d.pack ? kPackQRows : d.path == kPathOctet ? q_rows : (d.path == kPathMfma && (kMfmaPasses & 2)) ? 2048 : gen_q_rows;
+            d.q_tile_rows = d.cs_lin ? 2048 : d.pack ? kPackQRows : d.path == kPathOctet ? q_rows : (d.path == kPathMfma && (kMfmaPasses & 2)) ? 2048 : (int32_t)strip_q_rows;
             d.n_q_tiles = (int32_t)ceil_div(d.n, d.q_tile_rows);
             d.qpart_off = wd; wd += round_up((int64_t)d.n_q_tiles * d.m * rank, 32);
             d.n_p_chunks = 1;
             d.p_chunk_cols = (int32_t)d.m;
-            if (d.path == kPathOctet && !d.cs_lin && !d.pack) {
-                d.p_chunk_cols = p_cols;
+            const bool strip = d.path == kPathGeneric;
+            if ((d.path == kPathOctet && !d.cs_lin && !d.pack) || strip) {
+                // strip kernels: chunks of one size, a multiple of a strip
+                d.p_chunk_cols = strip ? (int32_t)round_up(ceil_div(d.m, ceil_div(d.m, strip_chunk)), 64) : p_cols;
                 d.n_p_chunks = (int32_t)ceil_div(d.m, d.p_chunk_cols);
                 if (d.n_p_chunks > 1) {
                     d.ppart_off = wd; wd += round_up((int64_t)d.n_p_chunks * d.n * rank, 32);
                     plan.any_p_chunks = true;
                 }
+            }
+        }
+        // The strip err pass: runs of the flat index of strip_err elements where that is at least eight rows (a wave's row of
+        // Q+ per lane serves all rows of a run), else eight rows of a column segment.
+        for (int l = 0; l < n_mats && !sketch && octet_blocks; ++l) {
+            MatDesc &d = plan.mats[l];
+            if (d.path != kPathGeneric) continue;
+            if (d.m <= 1024) {
+                int64_t tile = strip_err;
+                while (tile < 8192 && tile < 8 * d.m) tile *= 2;
+                d.es_tile = (int32_t)round_up(tile, block);
+                plan.es_lds = std::max(plan.es_lds, d.es_tile + 8);
+            } else {
+                const bool whole = d.m % block == 0;
+                const int64_t cols_want = std::max<int64_t>(strip_err / 8, whole ? block : 2 * block);
+                d.es_seg = (int32_t)(whole ? round_up(cols_want, block) : ceil_div(d.m, ceil_div(d.m, cols_want)));
+                d.es_over = whole ? 0 : block;
+                d.es_pitch = (int32_t)round_up(d.es_seg + d.es_over, 8);
+                plan.es_lds = std::max(plan.es_lds, 8 * d.es_pitch + 8);
             }
         }
         // Stream tables of the element-wise gradient compressors (random block, scaled sign) for the quantiser:
@@ -526,14 +562,26 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
             }
             if (d.path == kPathGeneric || mf) {
                 if (!mf_p)
-                    for (int64_t r0 = 0; r0 < d.n; r0 += 4) plan.p_items.push_back({l, (int32_t)r0, 0, 0});
-                const int32_t nct = (int32_t)ceil_div(d.m, kGenQCols);
+                    for (int64_t r0 = 0; r0 < d.n; r0 += kStripRows)
+                        for (int32_t cc = 0; cc < d.n_p_chunks; ++cc) plan.p_items.push_back({l, (int32_t)r0, cc, 0});
+                const int32_t nct = (int32_t)ceil_div(d.m, 64);
                 if (!mf_q)
                     for (int32_t rt = 0; rt < d.n_q_tiles; ++rt)
                         for (int32_t ct = 0; ct < nct; ++ct) plan.q_items.push_back({l, ct, rt, 0});
+                if (!mf_p && d.n_p_chunks > 1)
+                    for (int64_t e0 = 0; e0 < d.n * rank; e0 += 256) plan.pred_items.push_back({l, (int32_t)e0, 0, 0});
+                if (!mf_e && !sketch && d.es_tile > 0)
+                    for (int64_t t = 0; t * d.es_tile < d.N; ++t) {
+                        const int64_t i0 = t * d.es_tile / d.m, i1 = (std::min<int64_t>((t + 1) * d.es_tile, d.N) - 1) / d.m;
+                        plan.err_s_items.push_back({l, (int32_t)t, (int32_t)i0, (int32_t)(i1 - i0 + 1)});
+                    }
+                if (!mf_e && !sketch && d.es_seg > 0)
+                    for (int64_t r0 = 0; r0 < d.n; r0 += 8)
+                        for (int32_t sg = 0; sg < (int32_t)ceil_div(d.m, d.es_seg); ++sg)
+                            plan.err_s_items.push_back({l, (int32_t)r0, sg, (int32_t)std::min<int64_t>(8, d.n - r0)});
                 // 4 waves per workgroup, each wave takes blocks b0+wave, b0+wave+4, ...: 16 per wave, or
                 // one per wave for small matrices (a: first block, b: blocks per wave)
-                if (!mf_e && !sketch) {
+                if (!mf_e && !sketch && d.es_tile == 0 && d.es_seg == 0) {
                     const int32_t per_wave = d.nblk <= 16384 ? 1 : 16;
                     for (int64_t b0 = 0; b0 < d.nblk; b0 += 4 * per_wave)
                         plan.err_items.push_back({l, (int32_t)b0, per_wave, 0});
@@ -572,7 +620,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
             for (int32_t t = 0; t < d.n_gram_tiles; ++t) plan.gram_items.push_back({l, t, 0, 0});
             for (int64_t r0 = 0; r0 < d.n; r0 += 64) plan.apply_items.push_back({l, (int32_t)r0, 0, 0});
             // a matrix-core matrix with a single row tile gets its Q+ straight from the Q+ pass
-            if (!((mf_q || d.pack) && d.n_q_tiles == 1) || d.cs_lin)
+            if (!((mf_q || d.pack || d.path == kPathGeneric) && d.n_q_tiles == 1) || d.cs_lin)
             {
                 // 256 entries per workgroup, a thread per entry; with kQredManyTiles partial sums or more per entry, 16
                 // entries per workgroup and 16 threads per entry (item.c = 1)
@@ -733,7 +781,8 @@ bool check_plan(const Plan &plan)
     // pass 1: P = p Q
     {
         Cover c(nm);
-        for (const WorkItem &it : plan.p_items) c.add(plan, it, it.a, 4, 0, INT64_MAX);
+        for (const WorkItem &it : plan.p_items)
+            c.add(plan, it, it.a, kStripRows, (int64_t)it.b * plan.mats[it.mat].p_chunk_cols, plan.mats[it.mat].p_chunk_cols);
         for (const WorkItem &it : plan.p_f_items)
             c.add(plan, it, it.a, kPTileRows, (int64_t)it.b * plan.mats[it.mat].p_chunk_cols, plan.mats[it.mat].p_chunk_cols);
         if (plan.p_m_items.size() % 8 != 0) return false;                  // eight lists of one length
@@ -751,7 +800,7 @@ bool check_plan(const Plan &plan)
     {
         Cover c(nm);
         for (const WorkItem &it : plan.q_items)
-            c.add(plan, it, (int64_t)it.b * plan.mats[it.mat].q_tile_rows, plan.mats[it.mat].q_tile_rows, (int64_t)it.a * kGenQCols, kGenQCols);
+            c.add(plan, it, (int64_t)it.b * plan.mats[it.mat].q_tile_rows, plan.mats[it.mat].q_tile_rows, (int64_t)it.a * 64, 64);
         for (const WorkItem &it : plan.q_f_items)
             c.add(plan, it, (int64_t)it.b * plan.mats[it.mat].q_tile_rows, plan.mats[it.mat].q_tile_rows, (int64_t)it.a * 64, 64);
         for (const WorkItem &it : plan.q_m_items)
@@ -818,6 +867,21 @@ bool check_plan(const Plan &plan)
     {
         Cover c(nm);
         for (const WorkItem &it : plan.err_items) c.add_elems(plan, it, (int64_t)it.a * plan.block, (int64_t)4 * it.b * plan.block);
+        for (const WorkItem &it : plan.err_s_items) {
+            const MatDesc &d = plan.mats[it.mat];
+            if (d.es_seg > 0) {
+                // the blocks that start in this rectangle: up to es_over columns more per row, inside the pitch
+                if (d.es_pitch < d.es_seg + d.es_over || (d.m % plan.block != 0 && d.es_over < plan.block) ||
+                    (d.m % plan.block == 0 && d.es_seg % plan.block != 0) || 8 * d.es_pitch > plan.es_lds || it.c > 8)
+                    return false;
+                c.add(plan, it, it.a, it.c, (int64_t)it.b * d.es_seg, d.es_seg);
+            } else {
+                const int64_t j0 = (int64_t)it.a * d.es_tile, j1 = std::min<int64_t>(j0 + d.es_tile, d.N);
+                if (d.es_tile % plan.block != 0 || d.es_tile > plan.es_lds || it.b != j0 / d.m || it.b + it.c - 1 != (j1 - 1) / d.m)
+                    return false;
+                c.add_elems(plan, it, j0, d.es_tile);
+            }
+        }
         for (const WorkItem &it : plan.err_f_items) {
             const int64_t strip = (int64_t)8 << plan.mats[it.mat].lr_shift;
             c.add(plan, it, it.b, it.c, (int64_t)it.a * strip, strip);
@@ -847,7 +911,7 @@ bool check_plan(const Plan &plan)
     for (size_t l = 0; l < nm; ++l) {
         const MatDesc &d = plan.mats[l];
         if (gram[l] != d.n_gram_tiles || apply[l] != (d.n + 63) / 64) return false;
-        const bool direct_q = (d.path == kPathMfma || d.pack) && d.n_q_tiles == 1;
+        const bool direct_q = (d.path == kPathMfma || d.path == kPathGeneric || d.pack) && d.n_q_tiles == 1;
         if (d.pack && (d.path != kPathOctet || d.n_p_chunks != 1 || (d.m & 127) != 0 || plan.block < 128 || plan.dtype != 1 ||
                        (plan.bits != 2 && plan.bits != 4)))
             return false;

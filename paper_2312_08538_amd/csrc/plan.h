@@ -11,8 +11,7 @@ constexpr int kAlign = 64;          // every per-matrix offset is a multiple of 
 constexpr int kMaxRank = 32;
 constexpr int kGramRows = 256;      // rows per LDS piece of the Gram kernel
 constexpr int kQredManyTiles = 32;  // partial sums of Q+ per entry from which 16 threads share an entry's sum
-constexpr int kGenQRows = 128;      // rows per partial of Q+ in the generic pass 2
-constexpr int kGenQCols = 256;      // columns per workgroup in the generic pass 2
+constexpr int kStripRows = 32;      // rows per workgroup item of the strip P pass
 constexpr int kFastMaxRank = 8;     // the octet family holds rank <= 8 in registers
 constexpr int kPTileRows = 64;      // rows per workgroup item of the octet P pass
 
@@ -40,6 +39,9 @@ struct MatDesc {
     int32_t q_tile_rows;            // rows per partial of Q+
     int32_t p_chunk_cols;           // columns per partial of P
     int32_t path;                   // kernel family chosen for this matrix
+    // strip err pass: a run of es_tile elements of the flat index per item, or (es_seg > 0) rows of a column segment of es_seg
+    // columns, es_over columns past it that the segment's last blocks may reach, es_pitch floats of LDS per row
+    int32_t es_tile, es_seg, es_over, es_pitch;
     // octet family: a lane owns 8 consecutive elements of a row; lr lanes share a row
     int32_t lr_shift;               // log2(lanes per row segment), 3..6
     int32_t lb_shift;               // log2(lanes per scale block) = log2(block/8)
@@ -109,10 +111,15 @@ struct Plan {
     bool any_octet = false, any_generic = false, any_p_chunks = false, any_mfma = false;
     size_t ws_doubles = 0;
     size_t workspace_bytes = 0;
-    // generic family
-    std::vector<WorkItem> p_items;      // pass 1: (mat, first row)            4 rows per workgroup
-    std::vector<WorkItem> q_items;      // pass 2: (mat, column tile, row tile)
-    std::vector<WorkItem> err_items;    // pass 3: (mat, first block, blocks per wave)
+    // strip kernels (any shape)
+    std::vector<WorkItem> p_items;      // pass 1: (mat, first row of kStripRows, column chunk)
+    std::vector<WorkItem> q_items;      // pass 2: (mat, strip of 64 columns, row tile)
+    std::vector<WorkItem> err_s_items;  // pass 3: (mat, tile, its first row, rows it spans), or with segments (mat, first row, segment, rows)
+    std::vector<WorkItem> err_items;    // pass 3, blocks that are not 8 * 2^j elements (j <= 6): (mat, first block, blocks per wave)
+    int es_lds = 0;                     // floats of LDS of the strip err pass
+    int wshift = 0, lb_shift = 0;       // log2(code fields per word); log2(block / 8) for power-of-two blocks of 8 elements or more
+    float inv_s = 0.0f;                 // fl32(1 / s)
+    uint64_t bmagic = 0;                // floor(2^64 / block) + 1 (exactly 2^64 / block for a power of two)
     // octet family (one item per wave for p and err, per workgroup for q)
     std::vector<WorkItem> p_f_items;    // (mat, first row, column chunk), one workgroup each
     std::vector<WorkItem> q_f_items;    // (mat, 64-column strip, row tile)
