@@ -42,6 +42,7 @@ struct DevicePlan {
     int rank = 0, rpad = 0, bits = 0, block = 0, dtype = 0;
     int n_err_s = 0, es_lds = 0;    // strip err pass: items, floats of LDS per workgroup
     int wshift = 0, lb_shift = 0;   // log2(code fields per word), log2(block / 8)
+    int block_shift = -1;           // log2(block), -1 if it is not a power of two
     float inv_s = 0.0f;             // fl32(1 / s)
     uint64_t bmagic = 0;            // j / block = mulhi64(j, bmagic) for j < 2^35
     uint32_t seed_lo = 0, seed_hi = 0;

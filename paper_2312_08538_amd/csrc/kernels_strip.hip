@@ -36,7 +36,7 @@ template <int SRC>
 struct Raw {
     uint32_t g;                 // gradient bits (fp32, or bf16 in the low half)
     uint32_t c, c2;             // code words (c2: the second vector), or the table entry's bits in c
-    float s, s2;                // block scales
+    float s, s2;                // block scales, or (sketch) the signed 1 - beta in s
 };
 
 struct Source {
@@ -49,49 +49,84 @@ struct Source {
 // (1 - beta) with the sign of a hashed row or column folded in
 __device__ __forceinline__ float signed_omb(float omb, int32_t hv) { return hv < 0 ? -omb : omb; }
 
-// Loads the elements (row[u], col0 + lc) of U rows; rows and col0 are uniform over the wave, lc is the lane's offset
-// (the caller keeps it inside the matrix; below 64 unless FAR, which needs octet blocks).  hv_col: the lane's column hash in
-// the column form of the sketch.
-template <int SRC, int U, bool FAR = false>
-__device__ __forceinline__ void load_rows(const DevicePlan &dp, const MatDesc &d, const Source &src, const int64_t (&row)[U],
-                                          int64_t col0, const uint32_t (&lc)[U], int32_t hv_col, Raw<SRC> (&o)[U])
+// Where a wave's elements lie: the arrays from the scale block on that holds the element the wave starts from, so that a
+// lane needs only its 32-bit distance `rel` from that block's first element: code word rel >> wshift, bit rel * bits mod
+// 32, block rel / block, and every load is a scalar base plus a 32-bit offset.  (Per-row 64-bit addresses and divisions on
+// the scalar side, a quarter of the vector issue rate, took twice as long as everything else in these kernels.)  The plan
+// keeps a workgroup's rows within 2^29 elements.
+template <int SRC>
+struct Base {
+    const void *g;
+    const uint32_t *c, *c2;     // first (or only) and second vector
+    const float *s, *s2;
+    int64_t j;                  // the element the arrays start at (sketch: the starting element itself)
+};
+
+template <int SRC>
+__device__ __forceinline__ Base<SRC> make_base(const DevicePlan &dp, const MatDesc &d, const Source &src, int64_t start, uint32_t *rel0)
 {
-    int64_t j0[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) j0[u] = row[u] * d.m + col0;
+    Base<SRC> b;
+    int64_t blk = 0;
+    b.j = start;
+    if (SRC == kSrcOne || SRC == kSrcTwo) {
+        blk = (int64_t)__umul64hi((uint64_t)start, dp.bmagic);
+        b.j = blk * dp.block;
+        const int64_t w = d.word_off + (b.j >> dp.wshift);
+        b.c = (SRC == kSrcTwo ? dp.i_codes : src.codes) + w;
+        b.s = (SRC == kSrcTwo ? dp.i_scales : src.scales) + d.scale_off + blk;
+        b.c2 = src.codes + w;
+        b.s2 = src.scales + d.scale_off + blk;
+    } else {
+        b.c = b.c2 = nullptr;
+        b.s = b.s2 = nullptr;
+    }
+    b.g = dp.dtype == 0 ? (const void *)(reinterpret_cast<const float *>(src.grads) + d.grad_off + b.j)
+                        : (const void *)(reinterpret_cast<const uint16_t *>(src.grads) + d.grad_off + b.j);
+    *rel0 = (uint32_t)(start - b.j);
+    return b;
+}
+
+// Loads U elements of a lane, at distances rel[u] from the base; row[u] / col are their matrix row (uniform) and first
+// column of the strip (lc: the lane's offset from it), hv_col the lane's column hash: used by the sketch forms only.
+template <int SRC, int U>
+__device__ __forceinline__ void load_rows(const DevicePlan &dp, const MatDesc &d, const Source &src, const Base<SRC> &b,
+                                          const uint32_t (&rel)[U], const int64_t (&row)[U], int64_t col, uint32_t lc, int32_t hv_col,
+                                          Raw<SRC> (&o)[U])
+{
     if (dp.dtype == 0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) o[u].g = (reinterpret_cast<const uint32_t *>(src.grads) + (d.grad_off + j0[u]))[lc[u]];
+        for (int u = 0; u < U; ++u) o[u].g = reinterpret_cast<const uint32_t *>(b.g)[rel[u]];
     } else {
 #pragma unroll
-        for (int u = 0; u < U; ++u) o[u].g = (reinterpret_cast<const uint16_t *>(src.grads) + (d.grad_off + j0[u]))[lc[u]];
+        for (int u = 0; u < U; ++u) o[u].g = reinterpret_cast<const uint16_t *>(b.g)[rel[u]];
     }
     if (SRC == kSrcOne || SRC == kSrcTwo) {
-        const uint32_t W1 = (1u << dp.wshift) - 1u;
-        const uint32_t *cw = SRC == kSrcTwo ? dp.i_codes : src.codes;
-        const float *sc = SRC == kSrcTwo ? dp.i_scales : src.scales;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t w0 = d.word_off + (j0[u] >> dp.wshift);
-            const uint32_t wi = (((uint32_t)j0[u] & W1) + lc[u]) >> dp.wshift;
-            o[u].c = (cw + w0)[wi];
-            if (SRC == kSrcTwo) o[u].c2 = (src.codes + w0)[wi];
+            o[u].c = b.c[rel[u] >> dp.wshift];
+            if (SRC == kSrcTwo) o[u].c2 = b.c2[rel[u] >> dp.wshift];
         }
+        if (dp.block_shift >= 0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t blk = (int64_t)__umul64hi((uint64_t)j0[u], dp.bmagic);
-            const uint32_t e = (uint32_t)(j0[u] - blk * dp.block) + lc[u];
-            const uint32_t bi = FAR ? e >> (dp.lb_shift + 3) : dp.block >= 64 ? (e >= (uint32_t)dp.block ? 1u : 0u) : e / (uint32_t)dp.block;
-            o[u].s = (sc + (d.scale_off + blk))[bi];
-            if (SRC == kSrcTwo) o[u].s2 = (src.scales + (d.scale_off + blk))[bi];
+            for (int u = 0; u < U; ++u) {
+                o[u].s = b.s[rel[u] >> dp.block_shift];
+                if (SRC == kSrcTwo) o[u].s2 = b.s2[rel[u] >> dp.block_shift];
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t blk = rel[u] / (uint32_t)dp.block;
+                o[u].s = b.s[blk];
+                if (SRC == kSrcTwo) o[u].s2 = b.s2[blk];
+            }
         }
     } else {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             // row form: the row's bucket; column form: the column's
             const int32_t hv = SRC == kSrcRow ? dp.row_hash[d.hash_off + row[u]] : hv_col;
-            const int64_t base = SRC == kSrcRow ? d.table_off + (int64_t)(hv & INT32_MAX) * d.m + col0 : d.table_off + row[u] * d.w;
-            const uint32_t off = SRC == kSrcRow ? lc[u] : (uint32_t)(hv & INT32_MAX);
+            const int64_t base = SRC == kSrcRow ? d.table_off + (int64_t)(hv & INT32_MAX) * d.m + col : d.table_off + row[u] * d.w;
+            const uint32_t off = SRC == kSrcRow ? lc : (uint32_t)(hv & INT32_MAX);
             if (dp.table_dtype == 1) o[u].c = (reinterpret_cast<const uint16_t *>(src.table) + base)[off];
             else o[u].c = (reinterpret_cast<const uint32_t *>(src.table) + base)[off];
             o[u].s = signed_omb(dp.omb, hv);
@@ -99,14 +134,13 @@ __device__ __forceinline__ void load_rows(const DevicePlan &dp, const MatDesc &d
     }
 }
 
-// p of a loaded element; flat0 + lc is its flat index.
+// p of a loaded element at distance rel.
 template <int SRC>
-__device__ __forceinline__ float form_p(const DevicePlan &dp, const Raw<SRC> &o, int64_t flat0, uint32_t lc, float omb)
+__device__ __forceinline__ float form_p(const DevicePlan &dp, const Raw<SRC> &o, uint32_t rel, float omb)
 {
     const float g = dp.dtype == 0 ? __uint_as_float(o.g) : bf16_bits_to_f32(o.g);
     if (SRC == kSrcOne || SRC == kSrcTwo) {
-        const uint32_t W1 = (1u << dp.wshift) - 1u;
-        const uint32_t sh = (((uint32_t)flat0 + lc) & W1) * (uint32_t)dp.bits;
+        const uint32_t sh = (rel * (uint32_t)dp.bits) & 31u;
         const int q = __builtin_amdgcn_sbfe((int)o.c, sh, (uint32_t)dp.bits);
         const float step = o.s * dp.inv_s * omb;
         const float p1 = __builtin_fmaf(step, (float)q, g);
@@ -159,11 +193,14 @@ __global__ __launch_bounds__(256) void k_p_strip(DevicePlan dp, Source src, cons
         bc[h] = c < r ? c : r - 1;
     }
     const int n_strips = (c_end - c_begin + 63) >> 6;
+    const int rows = it.c;
+    uint32_t rel0;
+    const Base<SRC> base = make_base<SRC>(dp, d, src, row0 * d.m + c_begin, &rel0);
     for (int s = wave; s < n_strips; s += 4) {
         const int col0 = c_begin + 64 * s;
         const int ncol = (c_end - col0 < 64) ? c_end - col0 : 64;
-        const uint32_t l0 = (uint32_t)(lane < ncol ? lane : ncol - 1);
-        const int32_t hv_col = SRC == kSrcCol ? dp.row_hash[d.hash_off + col0 + l0] : 0;
+        const uint32_t lc = (uint32_t)(lane < ncol ? lane : ncol - 1);
+        const int32_t hv_col = SRC == kSrcCol ? dp.row_hash[d.hash_off + col0 + lc] : 0;
         float bq[16][BN];
         const float *qbase = Q + d.q_off + (int64_t)col0 * r;
 #pragma unroll
@@ -172,20 +209,22 @@ __global__ __launch_bounds__(256) void k_p_strip(DevicePlan dp, Source src, cons
 #pragma unroll
             for (int h = 0; h < BN; ++h) bq[j][h] = qbase[(uint32_t)(k * r + bc[h])];
         }
+        const uint32_t rel_s = rel0 + 64u * (uint32_t)s + lc;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
+            uint32_t rel[16];
             int64_t row[16];
-            uint32_t lc[16];
             Raw<SRC> o[16];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                row[u] = row0 + 16 * half + u < d.n ? row0 + 16 * half + u : d.n - 1;
-                lc[u] = l0;
+            for (int u = 0; u < 16; ++u) {                      // rows beyond the item re-read its last one (not stored)
+                const int rr = 16 * half + u < rows ? 16 * half + u : rows - 1;
+                rel[u] = rel_s + (uint32_t)rr * (uint32_t)d.m;
+                row[u] = row0 + rr;
             }
-            load_rows<SRC, 16>(dp, d, src, row, col0, lc, hv_col, o);
+            load_rows<SRC, 16>(dp, d, src, base, rel, row, col0, lc, hv_col, o);
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
-                const float p = form_p<SRC>(dp, o[u], row[u] * d.m + col0, l0, dp.omb);
+                const float p = form_p<SRC>(dp, o[u], rel[u], dp.omb);
                 T[(16 * half + u) * kPPitch + lane] = lane < ncol ? p : 0.0f;
             }
         }
@@ -224,7 +263,7 @@ __global__ __launch_bounds__(256) void k_p_strip(DevicePlan dp, Source src, cons
     for (int idx = tid; idx < kStripRows * RC; idx += 256) {
         const int rr = idx / RC, c = idx % RC;
         const int64_t row = row0 + rr;
-        if (c < r && row < d.n) {
+        if (c < r && rr < rows) {
             double sum = red[idx];
 #pragma unroll
             for (int w = 1; w < 4; ++w) sum += red[w * kStripRows * RC + idx];
@@ -261,35 +300,41 @@ __global__ __launch_bounds__(256) void k_q_strip(DevicePlan dp, Source src, cons
     const int r = EXACT ? R : dp.rank;
     const int64_t col0 = (int64_t)it.a * 64;
     const int ncol = (int)((d.m - col0 < 64) ? d.m - col0 : 64);
-    const uint32_t l0 = (uint32_t)(lane < ncol ? lane : ncol - 1);
+    const uint32_t lc = (uint32_t)(lane < ncol ? lane : ncol - 1);
     const int64_t t0 = (int64_t)it.b * d.q_tile_rows + (int64_t)wave * (d.q_tile_rows >> 2);
     const int64_t t1 = (t0 + (d.q_tile_rows >> 2) < d.n) ? t0 + (d.q_tile_rows >> 2) : d.n;
-    const int32_t hv_col = SRC == kSrcCol ? dp.row_hash[d.hash_off + col0 + l0] : 0;
+    const int32_t hv_col = SRC == kSrcCol ? dp.row_hash[d.hash_off + col0 + lc] : 0;
     double acc[R];
 #pragma unroll
     for (int c = 0; c < R; ++c) acc[c] = 0.0;
     if (t0 < t1) {
-        uint32_t lc[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) lc[u] = l0;
+        uint32_t rel0;
+        const Base<SRC> base = make_base<SRC>(dp, d, src, t0 * d.m + col0, &rel0);
+        rel0 += lc;
         Raw<SRC> cur[U];
-        auto load_trip = [&](Raw<SRC> (&o)[U], int64_t i0) {
+        const int rows = (int)(t1 - t0);
+        auto rel_of = [&](int i) { return rel0 + (uint32_t)(i < rows ? i : rows - 1) * (uint32_t)d.m; };
+        auto load_trip = [&](Raw<SRC> (&o)[U], int i0) {
+            uint32_t rel[U];
             int64_t row[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) row[u] = i0 + u < t1 ? i0 + u : t1 - 1;
-            load_rows<SRC, U>(dp, d, src, row, col0, lc, hv_col, o);
+            for (int u = 0; u < U; ++u) {
+                rel[u] = rel_of(i0 + u);
+                row[u] = t0 + (i0 + u < rows ? i0 + u : rows - 1);
+            }
+            load_rows<SRC, U>(dp, d, src, base, rel, row, col0, lc, hv_col, o);
         };
-        load_trip(cur, t0);
-        for (int64_t i0 = t0; i0 < t1; i0 += U) {
+        load_trip(cur, 0);
+        for (int i0 = 0; i0 < rows; i0 += U) {
             float p[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) p[u] = form_p<SRC>(dp, cur[u], (i0 + u < t1 ? i0 + u : t1 - 1) * d.m + col0, l0, dp.omb);
-            load_trip(cur, i0 + U < t1 ? i0 + U : i0);
+            for (int u = 0; u < U; ++u) p[u] = form_p<SRC>(dp, cur[u], rel_of(i0 + u), dp.omb);
+            load_trip(cur, i0 + U < rows ? i0 + U : i0);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if (i0 + u < t1) {                              // uniform
+                if (i0 + u < rows) {                            // uniform
                     float ph[R];
-                    uniform_row<R, EXACT>(Phat + d.p_off + (i0 + u) * r, r, ph);
+                    uniform_row<R, EXACT>(Phat + d.p_off + (t0 + i0 + u) * r, r, ph);
                     const double pd = (double)p[u];
 #pragma unroll
                     for (int c = 0; c < R; ++c) acc[c] = __builtin_fma(pd, (double)ph[c], acc[c]);
@@ -423,20 +468,26 @@ __global__ __launch_bounds__(256) void k_err_strip(DevicePlan dp, const void *__
     Source src;
     src.grads = grads; src.codes = TWO ? codes2 : codes; src.scales = TWO ? scales2 : scales; src.table = nullptr;
 
-    // window of row i, relative to c0
-    auto window = [&](int64_t i, int &lo, int &hi) {
-        const int64_t f = i * d.m + c0;
+    // All indices are relative to the first owned block of the run (its first element: jb); row rl of the run owns the
+    // elements [ws, we) and its (virtual) column 64 st + lane is element rel_row(rl) + 64 st + lane.
+    const int64_t f0 = i_first * d.m + c0;
+    const int64_t jb = seg ? ((f0 + B - 1) & ~(B - 1)) : j0;
+    const int rel_f0 = (int)(f0 - jb);                          // (negative: the run's first row starts before its first block)
+    auto rel_row = [&](int rl) { return rel_f0 + rl * (int)d.m; };
+    const int last = (int)(seg ? (d.N - jb < INT32_MAX ? d.N - jb : INT32_MAX) : j1 - jb);
+    auto window = [&](int rl, int &ws, int &we) {
+        const int f = rel_row(rl);
         if (seg) {
-            const int64_t e = i * d.m + c1;
-            int64_t t = (e + B - 1) & ~(B - 1);
-            t = t < d.N ? t : d.N;
-            lo = (int)(((f + B - 1) & ~(B - 1)) - f);
-            hi = (int)(t - f);
+            ws = (f + (int)B - 1) & ~((int)B - 1);
+            we = (f + (int)(c1 - c0) + (int)B - 1) & ~((int)B - 1);
         } else {
-            lo = j0 > f ? (int)(j0 - f) : 0;
-            hi = j1 - f < d.m ? (int)(j1 - f) : (int)d.m;
+            ws = f > 0 ? f : 0;
+            we = f + (int)d.m;
         }
+        we = we < last ? we : last;
     };
+    uint32_t rel_unused;
+    const Base<SRC> base = make_base<SRC>(dp, d, src, jb < d.N ? jb : d.N - 1, &rel_unused);
 
     const int n_strips = (width + 63) >> 6, n_groups = (n_rows + U - 1) / U;
     const int n_units = n_strips * n_groups;
@@ -445,28 +496,28 @@ __global__ __launch_bounds__(256) void k_err_strip(DevicePlan dp, const void *__
     struct Unit {
         Raw<SRC> o[U];
     };
-    // lane's column relative to c0, kept inside the row's window
-    auto lane_col = [&](int st, int lo, int hi) {
-        int k = 64 * st + lane;
-        k = k > lo ? k : lo;
-        k = k < hi ? k : hi - 1;
-        return k > 0 ? k : 0;           // (an empty window: nothing is stored, the load stays inside the matrix)
+    // the lane's element of a row, kept inside the row's window (an empty window: inside the matrix)
+    auto clamped = [&](int rl, int st) {
+        int ws, we;
+        window(rl, ws, we);
+        int e = rel_row(rl) + 64 * st + lane;
+        e = e > ws ? e : ws;
+        e = e < we ? e : we - 1;
+        return (uint32_t)(e > 0 ? e : 0);
     };
     auto row_of = [&](int g, int u) {
         const int rl = g * U + u;
         return rl < n_rows ? rl : n_rows - 1;
     };
     auto load_unit = [&](Unit &un, int st, int g) {
+        uint32_t rel[U];
         int64_t row[U];
-        uint32_t lc[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            row[u] = i_first + row_of(g, u);
-            int lo, hi;
-            window(row[u], lo, hi);
-            lc[u] = (uint32_t)lane_col(st, lo, hi);
+            rel[u] = clamped(row_of(g, u), st);
+            row[u] = 0;
         }
-        load_rows<SRC, U, true>(dp, d, src, row, c0, lc, 0, un.o);
+        load_rows<SRC, U>(dp, d, src, base, rel, row, 0, 0, 0, un.o);
     };
     float q[R];
 #pragma unroll
@@ -496,16 +547,17 @@ __global__ __launch_bounds__(256) void k_err_strip(DevicePlan dp, const void *__
         int n_strip = strip, n_group = group + 1;
         if (n_group == n_groups) { n_group = 0; ++n_strip; }
         if (un + 1 < u_end) load_unit(nxt, n_strip, n_group);
-        const bool wraps = c0 + 64 * strip + 63 >= d.m && seg;  // uniform: some lanes may belong to the next row
+        const bool wraps = seg && c0 + 64 * strip + 63 >= d.m;  // uniform: some lanes may belong to the next row
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (group * U + u < n_rows) {                       // uniform
                 const int rl = group * U + u;
                 const int64_t i = i_first + rl;
-                int lo, hi;
-                window(i, lo, hi);
-                const int k = 64 * strip + lane;
-                const float p = form_p<SRC>(dp, cur.o[u], i * d.m + c0, (uint32_t)lane_col(strip, lo, hi), 1.0f);
+                int ws, we;
+                window(rl, ws, we);
+                const int e = rel_row(rl) + 64 * strip + lane;
+                // (lanes outside the window work on another element's inputs and store nothing)
+                const float p = form_p<SRC>(dp, cur.o[u], (uint32_t)e, 1.0f);
                 float ph[R];
                 uniform_row<R, EXACT>(Phat + d.p_off + i * r, r, ph);
                 float acc = 0.0f;
@@ -518,8 +570,7 @@ __global__ __launch_bounds__(256) void k_err_strip(DevicePlan dp, const void *__
 #pragma unroll
                     for (int c = 0; c < R; ++c) acc = __builtin_fmaf(kk < d.m ? ph[c] : pn[c], q[c], acc);
                 }
-                const int pos = seg ? rl * d.es_pitch + (k - lo) : (int)(i * d.m + k - j0);
-                if (k >= lo && k < hi) X[pos] = p - acc;
+                if (e >= ws && e < we) X[seg ? rl * d.es_pitch + (e - ws) : e] = p - acc;
             }
         }
         cur = nxt;
@@ -535,10 +586,10 @@ __global__ __launch_bounds__(256) void k_err_strip(DevicePlan dp, const void *__
                                     codes2, scales2);
         } else {
             for (int rl = wave; rl < n_rows; rl += 4) {
-                int lo, hi;
-                window(i_first + rl, lo, hi);
-                const int count = hi - lo;
-                quantise_run<BITS, TWO>(dp, d, it.mat, step_lo, step_hi, X + rl * d.es_pitch, (i_first + rl) * d.m + c0 + lo, count,
+                int ws, we;
+                window(rl, ws, we);
+                const int count = we - ws;
+                quantise_run<BITS, TWO>(dp, d, it.mat, step_lo, step_hi, X + rl * d.es_pitch, jb + ws, count,
                                         (count + 7) >> 3, 0, 64, codes, scales, codes2, scales2);
             }
         }

@@ -388,6 +388,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         // blocks that a power-of-two number of lanes, at most a wave, holds in octets: the strip err pass takes them
         const bool octet_blocks = block % 8 == 0 && is_pow2(block / 8) && block / 8 <= 64;
         plan.lb_shift = octet_blocks ? log2i(block / 8) : 0;
+        plan.block_shift = is_pow2(block) ? log2i(block) : -1;
         plan.mats.resize(n_mats);
 
         // The octet family needs whole scale blocks per row, a power-of-two number of lanes (8 elements
@@ -472,7 +473,8 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
             d.gram_off = wd; wd += (int64_t)d.n_gram_tiles * rank * rank;
             d.gsum_off = wd; wd += rank * rank;
             d.rinv_off = wd; wd += rank * rank;
-            d.q_tile_rows = d.cs_lin ? 2048 : d.pack ? kPackQRows : d.path == kPathOctet ? q_rows : (d.path == kPathMfma && (kMfmaPasses & 2)) ? 2048 : (int32_t)strip_q_rows;
+            d.q_tile_rows = d.cs_lin ? 2048 : d.pack ? kPackQRows : d.path == kPathOctet ? q_rows : (d.path == kPathMfma && (kMfmaPasses & 2)) ? 2048
+                            : (int32_t)std::min<int64_t>(strip_q_rows, 4 * std::max<int64_t>(1, kStripSpan / d.m));
             d.n_q_tiles = (int32_t)ceil_div(d.n, d.q_tile_rows);
             d.qpart_off = wd; wd += round_up((int64_t)d.n_q_tiles * d.m * rank, 32);
             d.n_p_chunks = 1;
@@ -561,9 +563,11 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                         plan.err_m_items.push_back({l, (int32_t)r0, cb0, std::min<int32_t>(kErrRun, ncb - cb0)});
             }
             if (d.path == kPathGeneric || mf) {
+                const int64_t prow = std::min<int64_t>(kStripRows, std::max<int64_t>(1, kStripSpan / d.m));
                 if (!mf_p)
-                    for (int64_t r0 = 0; r0 < d.n; r0 += kStripRows)
-                        for (int32_t cc = 0; cc < d.n_p_chunks; ++cc) plan.p_items.push_back({l, (int32_t)r0, cc, 0});
+                    for (int64_t r0 = 0; r0 < d.n; r0 += prow)
+                        for (int32_t cc = 0; cc < d.n_p_chunks; ++cc)
+                            plan.p_items.push_back({l, (int32_t)r0, cc, (int32_t)std::min<int64_t>(prow, d.n - r0)});
                 const int32_t nct = (int32_t)ceil_div(d.m, 64);
                 if (!mf_q)
                     for (int32_t rt = 0; rt < d.n_q_tiles; ++rt)
@@ -575,10 +579,11 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                         const int64_t i0 = t * d.es_tile / d.m, i1 = (std::min<int64_t>((t + 1) * d.es_tile, d.N) - 1) / d.m;
                         plan.err_s_items.push_back({l, (int32_t)t, (int32_t)i0, (int32_t)(i1 - i0 + 1)});
                     }
+                const int64_t erow = std::min<int64_t>(8, std::max<int64_t>(1, kStripSpan / d.m));
                 if (!mf_e && !sketch && d.es_seg > 0)
-                    for (int64_t r0 = 0; r0 < d.n; r0 += 8)
+                    for (int64_t r0 = 0; r0 < d.n; r0 += erow)
                         for (int32_t sg = 0; sg < (int32_t)ceil_div(d.m, d.es_seg); ++sg)
-                            plan.err_s_items.push_back({l, (int32_t)r0, sg, (int32_t)std::min<int64_t>(8, d.n - r0)});
+                            plan.err_s_items.push_back({l, (int32_t)r0, sg, (int32_t)std::min<int64_t>(erow, d.n - r0)});
                 // 4 waves per workgroup, each wave takes blocks b0+wave, b0+wave+4, ...: 16 per wave, or
                 // one per wave for small matrices (a: first block, b: blocks per wave)
                 if (!mf_e && !sketch && d.es_tile == 0 && d.es_seg == 0) {
@@ -782,7 +787,8 @@ bool check_plan(const Plan &plan)
     {
         Cover c(nm);
         for (const WorkItem &it : plan.p_items)
-            c.add(plan, it, it.a, kStripRows, (int64_t)it.b * plan.mats[it.mat].p_chunk_cols, plan.mats[it.mat].p_chunk_cols);
+            c.add(plan, it, it.a, it.c <= kStripRows && it.c * plan.mats[it.mat].m < 2 * kStripSpan * 2 ? it.c : 0,
+                  (int64_t)it.b * plan.mats[it.mat].p_chunk_cols, plan.mats[it.mat].p_chunk_cols);
         for (const WorkItem &it : plan.p_f_items)
             c.add(plan, it, it.a, kPTileRows, (int64_t)it.b * plan.mats[it.mat].p_chunk_cols, plan.mats[it.mat].p_chunk_cols);
         if (plan.p_m_items.size() % 8 != 0) return false;                  // eight lists of one length

@@ -12,6 +12,7 @@ constexpr int kMaxRank = 32;
 constexpr int kGramRows = 256;      // rows per LDS piece of the Gram kernel
 constexpr int kQredManyTiles = 32;  // partial sums of Q+ per entry from which 16 threads share an entry's sum
 constexpr int kStripRows = 32;      // rows per workgroup item of the strip P pass
+constexpr int64_t kStripSpan = (int64_t)1 << 29;    // elements a strip workgroup's rows may span (32-bit byte offsets)
 constexpr int kFastMaxRank = 8;     // the octet family holds rank <= 8 in registers
 constexpr int kPTileRows = 64;      // rows per workgroup item of the octet P pass
 
@@ -112,12 +113,13 @@ struct Plan {
     size_t ws_doubles = 0;
     size_t workspace_bytes = 0;
     // strip kernels (any shape)
-    std::vector<WorkItem> p_items;      // pass 1: (mat, first row of kStripRows, column chunk)
+    std::vector<WorkItem> p_items;      // pass 1: (mat, first row, column chunk, rows: kStripRows or fewer)
     std::vector<WorkItem> q_items;      // pass 2: (mat, strip of 64 columns, row tile)
     std::vector<WorkItem> err_s_items;  // pass 3: (mat, tile, its first row, rows it spans), or with segments (mat, first row, segment, rows)
     std::vector<WorkItem> err_items;    // pass 3, blocks that are not 8 * 2^j elements (j <= 6): (mat, first block, blocks per wave)
     int es_lds = 0;                     // floats of LDS of the strip err pass
     int wshift = 0, lb_shift = 0;       // log2(code fields per word); log2(block / 8) for power-of-two blocks of 8 elements or more
+    int block_shift = -1;               // log2(block), -1 if it is not a power of two
     float inv_s = 0.0f;                 // fl32(1 / s)
     uint64_t bmagic = 0;                // floor(2^64 / block) + 1 (exactly 2^64 / block for a power of two)
     // octet family (one item per wave for p and err, per workgroup for q)
