@@ -100,8 +100,9 @@ int ensure_uploaded(conef_ctx *ctx)
     d.n_cs_u = (int)pl.cs_u_items.size();
     d.n_cs_lin = (int)pl.cs_lin_items.size();
     d.cs_cols_mode = pl.sketch_cols ? 1 : 0;
-    d.cs_max_cols = 0;
-    for (const MatDesc &m : pl.mats) d.cs_max_cols = std::max<int>(d.cs_max_cols, (int)std::min<int64_t>(m.m, kCscMaxCols));
+    d.csc_lds = 0;
+    for (const MatDesc &m : pl.mats)
+        if (pl.sketch_cols) d.csc_lds = std::max<int>(d.csc_lds, (int)(m.cs_cols * (m.m + m.w)));
     d.n_cs_err_f_old = 0;
     for (const MatDesc &m : pl.mats)
         if (pl.sketch && m.path == kPathOctet && !m.cs_lin) d.n_cs_err_f_old += 1;

@@ -247,9 +247,11 @@ int make_sketch_plan_columns(Plan &plan, const int64_t *rows, const int64_t *col
                 const int32_t hv = plan.row_hash[(size_t)(d.hash_off + k)];
                 plan.bucket_rows[(size_t)(d.hash_off + fill[hv & INT32_MAX]++)] = (int32_t)k | (hv & INT32_MIN);
             }
-            d.cs_cols = (int32_t)d.m;
+            d.cs_cols = 8;
+            while (d.cs_cols > 1 && d.cs_cols * (d.m + d.w) > kCscLds) d.cs_cols /= 2;
             d.st_first = (int32_t)plan.cs_err_items.size();
-            for (int64_t i = 0; i < d.n; ++i) plan.cs_err_items.push_back({l, (int32_t)i, 1, 0});
+            for (int64_t i = 0; i < d.n; i += d.cs_cols)
+                plan.cs_err_items.push_back({l, (int32_t)i, (int32_t)std::min<int64_t>(d.cs_cols, d.n - i), 0});
             d.st_slots = 0;
         }
     } catch (const std::bad_alloc &) {
@@ -819,8 +821,8 @@ bool check_plan(const Plan &plan)
     if (plan.sketch && plan.sketch_cols) {
         std::vector<int64_t> rows_seen(nm, 0);
         for (const WorkItem &it : plan.cs_err_items) {
-            if (it.mat < 0 || it.mat >= (int)nm || it.a < 0 || it.a >= plan.mats[it.mat].n || it.b != 1) return false;
-            rows_seen[it.mat] += 1;
+            if (it.mat < 0 || it.mat >= (int)nm || it.a != rows_seen[it.mat] || it.b < 1 || it.b > plan.mats[it.mat].cs_cols) return false;
+            rows_seen[it.mat] += it.b;
         }
         for (size_t l = 0; l < nm; ++l) {
             const MatDesc &d = plan.mats[l];

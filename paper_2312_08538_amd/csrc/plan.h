@@ -56,7 +56,7 @@ struct MatDesc {
     int64_t table_off;              // element offset of the w x m table in the flat table buffer
     int64_t hash_off;               // offset of the matrix's n entries in row_hash and bucket_rows
     int64_t bptr_off;               // offset of its w + 1 entries in bucket_ptr
-    int32_t cs_cols;                // columns per item of the sketch update pass
+    int32_t cs_cols;                // columns per item of the sketch update pass; column form: rows per item (1, 2, 4 or 8)
     // count sketch in its linear form (rank 32, bf16 gradients, fp16 table, columns a multiple of 128): the sketch is
     // never decoded per element; T = S Q and U = (signed bucket sums of P^) carry its share of the factors
     int32_t cs_lin;                 // 1: this matrix takes the linear form
@@ -102,7 +102,7 @@ struct Plan {
     std::vector<int32_t> row_hash;      // per row: bucket, bit 31 set for sign -1
     std::vector<int32_t> bucket_ptr;    // per matrix w + 1 entries: rows of bucket b are bucket_rows[ptr[b] .. ptr[b+1])
     std::vector<int32_t> bucket_rows;   // per matrix n entries: row index (bit 31: sign -1), ascending within a bucket
-    std::vector<WorkItem> cs_err_items; // sketch update: (mat, first bucket, buckets, column tile of cs_cols)
+    std::vector<WorkItem> cs_err_items; // sketch update: (mat, first bucket, buckets, column tile of cs_cols); column form: (mat, first row, rows, 0)
     std::vector<WorkItem> cs_err_f_items;  // the same for matrices of the octet path (wider tiles)
     // linear form: (mat, first table row, 0, 0) tiles of 128 table rows for T = S Q; (mat, pair of column blocks, table row
     // tile, 0) for S^T U; (mat, first bucket, buckets, 0) for U; (mat, strip of 128 columns, first bucket, buckets) for the update
@@ -172,7 +172,9 @@ int make_plan(Plan &plan, const int64_t *rows, const int64_t *cols, int n_mats, 
 // columns: the column form (sketch_rows then holds the number of buckets per matrix, at most its columns)
 int make_sketch_plan(Plan &plan, const int64_t *rows, const int64_t *cols, const int64_t *sketch_rows, int n_mats,
                      int rank, float beta, int table_dtype, int dtype, uint64_t seed, bool columns = false);
-constexpr int kCscMaxCols = 16384;  // column form: a row of the residual is staged in LDS
+constexpr int kCscMaxCols = 16384;  // column form: a row of the residual and one of the table are staged in LDS
+constexpr int kCscThreads = 512;
+constexpr int kCscLds = 20 * 1024;  // LDS floats that several rows of a workgroup may take: two workgroups per CU
 
 // Random-block gradient compressor: keep[l] coordinates of matrix l per step (1 .. rows * cols).  Sets the
 // per-matrix fields, the Delta layout and (for a quantiser plan) the work tables.  Returns 0 or a negative code.
