@@ -23,6 +23,29 @@ __device__ __forceinline__ int code_field(uint32_t w, int e, int bits)
     return (int)(w << (32 - bits * (e + 1))) >> (32 - bits);
 }
 
+// signed 4-bit field in the low nibble of byte `byte` of w, divided by 16 (exact), as fp32: the
+// conversion instruction reads the nibble through its byte selector, so no shift or mask is spent
+template <int byte>
+__device__ __forceinline__ float nibble_over_16(uint32_t w)
+{
+    float r;
+    if constexpr (byte == 0) asm("v_cvt_off_f32_i4_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0" : "=v"(r) : "v"(w));
+    else if constexpr (byte == 1) asm("v_cvt_off_f32_i4_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1" : "=v"(r) : "v"(w));
+    else if constexpr (byte == 2) asm("v_cvt_off_f32_i4_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2" : "=v"(r) : "v"(w));
+    else asm("v_cvt_off_f32_i4_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3" : "=v"(r) : "v"(w));
+    return r;
+}
+
+// the eight fields of a code word, each divided by 16
+__device__ __forceinline__ void fields_over_16(uint32_t w, float q[8])
+{
+    const uint32_t w4 = w >> 4;
+    q[0] = nibble_over_16<0>(w); q[1] = nibble_over_16<0>(w4);
+    q[2] = nibble_over_16<1>(w); q[3] = nibble_over_16<1>(w4);
+    q[4] = nibble_over_16<2>(w); q[5] = nibble_over_16<2>(w4);
+    q[6] = nibble_over_16<3>(w); q[7] = nibble_over_16<3>(w4);
+}
+
 __device__ __forceinline__ float inv_levels(int bits)
 {
     // fl32(1/s) for s = 2^(b-1)-1: 1, 1/7, 1/127
@@ -33,6 +56,23 @@ __device__ __forceinline__ float inv_levels(int bits)
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
 {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+// The eight fields of an octet (8-bit codes: c0 elements 0..3, c1 elements 4..7; else all in c0) as fp32, divided by
+// code_unit<BITS>(): 4-bit fields come over 16, one instruction each.  A step size times the unit is exact, so
+// fma(step unit, field over unit, g) and (step unit) (field over unit) have the bits of fma(step, field, g) and step field.
+template <int BITS>
+__device__ __forceinline__ constexpr float code_unit() { return BITS == 4 ? 16.0f : 1.0f; }
+
+template <int BITS>
+__device__ __forceinline__ void code_values(uint32_t c0, uint32_t c1, float q[8])
+{
+    if constexpr (BITS == 4) {
+        fields_over_16(c0, q);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) q[e] = (float)(BITS == 8 ? code_field(e < 4 ? c0 : c1, e & 3, 8) : code_field(c0, e, BITS));
+    }
 }
 
 // Philox4x32-10 (Salmon et al., SC'11): 10 rounds of two 32x32->64 multiplies and xors.
@@ -82,7 +122,7 @@ __device__ __forceinline__ int64_t i2_block_start(uint32_t mat, uint32_t step_lo
 // coordinates (the last one may be shorter) and one coordinate of every stratum is kept:
 //   stratum i keeps  i g + floor(u_i len_i / 2^32),  len_i = min(g, N - i g),
 //   u_i = word i % 4 of the Philox call with counter (i / 4, matrix + 2^30, step), which no other draw uses.
-// N < 2^32.  strata_kept_octet looks at the 8 consecutive coordinates j0 .. j0 + 7 (all below N): bit e of the
+// N < 2^32.  strata_kept_octet looks at the 8 consecutive coordinates j0 .. j0 + 7 (those below N): bit e of the
 // result is set if j0 + e is kept; the kept ones belong to consecutive strata, the first of which is *first.
 __device__ __forceinline__ uint32_t stratum_of(uint32_t j, uint32_t g, uint64_t magic)
 {
@@ -93,7 +133,7 @@ __device__ __forceinline__ uint32_t strata_kept_octet(uint32_t j0, uint32_t N, u
                                                       uint32_t step_lo, uint32_t step_hi, uint32_t seed_lo, uint32_t seed_hi,
                                                       uint32_t *first)
 {
-    const uint32_t ia = stratum_of(j0, g, magic), ib = stratum_of(j0 + 7u, g, magic);
+    const uint32_t ia = stratum_of(j0, g, magic), ib = stratum_of(N - 1u - j0 < 7u ? N - 1u : j0 + 7u, g, magic);
     uint32_t bits = 0, first_i = 0, cached = 0xFFFFFFFFu;
     uint32_t out[4] = {0u, 0u, 0u, 0u};
     for (uint32_t i = ia; i <= ib; ++i) {
@@ -199,29 +239,49 @@ __device__ __forceinline__ uint32_t quantise_field(float x, float inv16, uint32_
 
 // Fixed-point stochastic rounding of an octet (quantise_field on each of its 8 values) straight into packed
 // BITS-wide two's-complement fields: 8-bit codes give two words (elements 0..3, 4..7), 4- and 2-bit codes the low
-// 32 / 16 bits of w[0].  Magnitudes and sign bits are gathered field by field and the negation is done on the
-// whole word: with s the sign bit of a field, ((mag ^ (s - (s >> (BITS-1)))) + (s >> (BITS-1))) ^ s is
-// 2^BITS - mag for a negative field with mag >= 1 and 0 for mag = 0; no carry leaves a field.
+// 32 / 16 bits of w[0].  U + draw stays below 2^23, so its byte 2 is the magnitude, and byte permutes gather the magnitudes
+// of an octet (7 - 10 instructions; a shift and an insertion per element were 16).  Sign bits are gathered field by field
+// and the negation is done on the whole word: with s the sign bit of a field,
+// ((mag ^ (s - (s >> (BITS-1)))) + (s >> (BITS-1))) ^ s is 2^BITS - mag for a negative field with mag >= 1 and 0 for mag = 0;
+// no carry leaves a field.
 template <int BITS>
 __device__ __forceinline__ void quantise_octet(const float x[8], float inv16, const uint32_t rnd[4], uint32_t w[2])
 {
-    constexpr int kPerWord = BITS == 8 ? 4 : 8;
     constexpr uint32_t kSignBits = BITS == 8 ? 0x80808080u : (BITS == 4 ? 0x88888888u : 0x0000AAAAu);
+    uint32_t t[8], sg[2] = {0, 0}, mags[2] = {0, 0};
 #pragma unroll
-    for (int h = 0; h < 8 / kPerWord; ++h) {
-        uint32_t mags = 0, sg = 0;
+    for (int e = 7; e >= 0; --e) {
+        const uint32_t U = (uint32_t)(fabsf(x[e]) * inv16);
+        t[e] = U + draw16(rnd, e);
+        uint32_t &s = sg[BITS == 8 ? e >> 2 : 0];
+        s = __builtin_amdgcn_alignbit(s, __float_as_uint(x[e]), 32 - BITS);       // (s << BITS) | top BITS bits of x
+    }
+    // __builtin_amdgcn_perm(hi, lo, sel): result byte i is byte sel_i of {hi, lo} (0..3 lo, 4..7 hi, 12: zero)
+    auto low2 = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x0C0C0602u); };     // byte 0: a's, byte 1: b's
+    auto high2 = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x06020C0Cu); };    // bytes 2 and 3
+    if (BITS == 8) {
+        mags[0] = low2(t[0], t[1]) | high2(t[2], t[3]);
+        mags[1] = low2(t[4], t[5]) | high2(t[6], t[7]);
+    } else if (BITS == 4) {
+        mags[0] = ((low2(t[1], t[3]) | high2(t[5], t[7])) << 4) | (low2(t[0], t[2]) | high2(t[4], t[6]));
+    } else {
+        mags[0] = low2(t[0], t[4]) | (low2(t[1], t[5]) << 2) | (low2(t[2], t[6]) << 4) | (low2(t[3], t[7]) << 6);
+    }
 #pragma unroll
-        for (int k = kPerWord - 1; k >= 0; --k) {
-            const int e = h * kPerWord + k;
-            const uint32_t U = (uint32_t)(fabsf(x[e]) * inv16);
-            mags = (mags << BITS) | ((U + draw16(rnd, e)) >> 16);
-            sg = __builtin_amdgcn_alignbit(sg, __float_as_uint(x[e]), 32 - BITS);     // (sg << BITS) | top BITS bits of x
-        }
-        sg &= kSignBits;
-        const uint32_t s1 = sg >> (BITS - 1), sm = sg - s1;
-        w[h] = ((mags ^ sm) + s1) ^ sg;
+    for (int h = 0; h < (BITS == 8 ? 2 : 1); ++h) {
+        const uint32_t s = sg[h] & kSignBits;
+        const uint32_t s1 = s >> (BITS - 1), sm = s - s1;
+        w[h] = ((mags[h] ^ sm) + s1) ^ s;
     }
     if (BITS != 8) w[1] = 0;
+}
+
+// LDS of a wave's own: its instructions are executed in order, so what is needed between one lane's write and another lane's
+// read is that the compiler keeps their order
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
 }
 
 // max over the 2^lb_shift lanes of a scale block (aligned group of lanes)

@@ -424,20 +424,28 @@ __global__ __launch_bounds__(256) void k_rb_generic(DevicePlan dp, const void *g
     }
 }
 
-// c = fl32(||p||_1 / N) of every matrix from the partial sums of the norm pass: thread t adds a contiguous share of
-// the matrix's partials in order, thread 0 the 256 shares in order.
-__global__ __launch_bounds__(256) void k_ss_scale(DevicePlan dp, const double *ws, float *c_scale)
+// c = fl32(||p||_1 / N) of every matrix from the partial sums of the norm pass: thread t adds partials t, t + 1024, ..., then the
+// 1024 sums are added over the lanes of each wave and over the waves in order.  (Thousands of partials per matrix: a chain of
+// loads per thread and then one thread's chain over the threads were 10 us; neighbouring threads' loads are neighbouring now.)
+__global__ __launch_bounds__(1024) void k_ss_scale(DevicePlan dp, const double *ws, float *c_scale)
 {
-    __shared__ double share[256];
+    __shared__ double share[16];
     const MatDesc d = dp.mats[blockIdx.x];
-    const int per = (d.st_slots + 255) / 256;
+    const double *src = ws + d.st_part_off;
     double s = 0.0;
-    for (int i = threadIdx.x * per; i < (int)(threadIdx.x + 1) * per && i < d.st_slots; ++i) s += ws[d.st_part_off + i];
-    share[threadIdx.x] = s;
+    int i = threadIdx.x;
+    for (; i + 3 * 1024 < d.st_slots; i += 4 * 1024) {
+        const double v0 = src[i], v1 = src[i + 1024], v2 = src[i + 2048], v3 = src[i + 3072];
+        s = ((s + v0) + v1) + v2;
+        s += v3;
+    }
+    for (; i < d.st_slots; i += 1024) s += src[i];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) share[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
-        double tot = 0.0;
-        for (int i = 0; i < 256; ++i) tot += share[i];
+        double tot = share[0];
+        for (int w = 1; w < 16; ++w) tot += share[w];
         c_scale[blockIdx.x] = (float)(tot / (double)d.N);
     }
 }
@@ -618,7 +626,7 @@ hipError_t launch_rb_step(const DevicePlan &dp, const void *grads, uint32_t *cod
 
 void launch_ss_scale(const DevicePlan &dp, const double *ws, float *c_scale, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_ss_scale, dim3(dp.n_mats), dim3(256), 0, st, dp, ws, c_scale);
+    hipLaunchKernelGGL(k_ss_scale, dim3(dp.n_mats), dim3(1024), 0, st, dp, ws, c_scale);
 }
 
 void launch_ss_clear(const DevicePlan &dp, uint32_t *sign_words, hipStream_t st)

@@ -756,31 +756,6 @@ struct ErrIn {
     float s1[TWO ? 4 : 1];
 };
 
-// Fixed-point stochastic rounding of an octet into a word of eight 4-bit two's-complement fields.
-// U + draw is below 2^19 for finite input, so byte 2 of the sum is the magnitude (0..7) and nothing
-// else: byte permutes gather the eight magnitudes (even elements into the low nibbles of a word's
-// bytes, odd ones into the high nibbles).  Sign bits are gathered nibble by nibble; the negation is
-// done on the whole word: for a negative field ((mag ^ 7) + 1) ^ 8 = 16 - mag for mag = 1..7 and 0
-// for mag = 0, without carries between fields.
-__device__ __forceinline__ uint32_t quantise_octet4(const float x[8], float inv16, const uint32_t rnd[4])
-{
-    uint32_t t[8], sg = 0;
-#pragma unroll
-    for (int e = 7; e >= 0; --e) {
-        const uint32_t U = (uint32_t)(fabsf(x[e]) * inv16);
-        const uint32_t r16 = (e & 1) ? (rnd[e >> 1] >> 16) : (rnd[e >> 1] & 0xFFFFu);
-        t[e] = U + r16;
-        sg = __builtin_amdgcn_alignbit(sg, __float_as_uint(x[e]), 28);      // (sg << 4) | top nibble of x
-    }
-    // __builtin_amdgcn_perm(hi, lo, sel): result byte i is byte sel_i of {hi, lo} (0..3 lo, 4..7 hi, 12: zero)
-    const uint32_t ev = __builtin_amdgcn_perm(t[2], t[0], 0x0C0C0602u) | __builtin_amdgcn_perm(t[6], t[4], 0x06020C0Cu);
-    const uint32_t od = __builtin_amdgcn_perm(t[3], t[1], 0x0C0C0602u) | __builtin_amdgcn_perm(t[7], t[5], 0x06020C0Cu);
-    const uint32_t mags = (od << 4) | ev;
-    sg &= 0x88888888u;
-    const uint32_t s1 = sg >> 3, s7 = sg - s1;
-    return ((mags ^ s7) + s1) ^ sg;
-}
-
 // the value of lane (lane ^ 1) / (lane ^ 2) of the quad, and of the lanes 4 and 8 further on in the row of 16
 __device__ __forceinline__ uint32_t dpp_quad_xor1(uint32_t a) { return __builtin_amdgcn_update_dpp(0, a, 0xB1, 0xF, 0xF, true); }
 __device__ __forceinline__ uint32_t dpp_quad_xor2(uint32_t a) { return __builtin_amdgcn_update_dpp(0, a, 0x4E, 0xF, 0xF, true); }
@@ -1025,7 +1000,9 @@ __global__ __launch_bounds__(512, TWO ? 2 : 4) void k_err_mfma(DevicePlan dp, co
                 const uint32_t o = octet0[v] + (uint32_t)(cb * 16);
                 uint32_t rnd[4];
                 philox4x32_10(o, (uint32_t)it.mat, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
-                const uint32_t word = quantise_octet4(x, inv16v[v], rnd);
+                uint32_t qw[2];
+                quantise_octet<4>(x, inv16v[v], rnd, qw);
+                const uint32_t word = qw[0];
                 if (valid[v]) *reinterpret_cast<uint32_t *>(cw1_out + ooff[v]) = word;
                 fields_over_16(word, q16);
 #pragma unroll
@@ -1048,7 +1025,9 @@ __global__ __launch_bounds__(512, TWO ? 2 : 4) void k_err_mfma(DevicePlan dp, co
             const uint32_t o = octet0[v] + (uint32_t)(cb * 16);
             uint32_t rnd[4];
             philox4x32_10(o, TWO ? ((uint32_t)it.mat | 0x80000000u) : (uint32_t)it.mat, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
-            const uint32_t word = quantise_octet4(x, inv16v[v], rnd);
+            uint32_t qw[2];
+            quantise_octet<4>(x, inv16v[v], rnd, qw);
+            const uint32_t word = qw[0];
             if (valid[v]) *reinterpret_cast<uint32_t *>(cw_out + ooff[v]) = word;
         }
         __syncthreads();        // the next block's splits are in LDS; everybody is done with this block's

@@ -18,6 +18,8 @@
 //             Ranks 4 and 8 with blocks up to 256: the same chain on the fp32 matrix cores (k_err_tile).
 //
 // All sums are combined in a fixed order: results do not depend on scheduling.
+#include <type_traits>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -90,12 +92,11 @@ __device__ __forceinline__ RawCodes<BITS> load_codes_always(const MatDesc &d, co
 template <int BITS>
 __device__ __forceinline__ void add_codes(const RawCodes<BITS> &r, float p[8])
 {
-    const float step = r.scale * inv_levels(BITS);
+    const float step = r.scale * inv_levels(BITS) * code_unit<BITS>();
+    float q[8];
+    code_values<BITS>(r.c0, r.c1, q);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int q = BITS == 8 ? code_field(e < 4 ? r.c0 : r.c1, e & 3, 8) : code_field(r.c0, e, BITS);
-        p[e] = __builtin_fmaf(step, (float)q, p[e]);
-    }
+    for (int e = 0; e < 8; ++e) p[e] = __builtin_fmaf(step, q[e], p[e]);
 }
 
 // omb: 1 - beta of the partial update in the P and Q+ passes (Algorithm 4 line 5), 1 in the err pass
@@ -115,13 +116,26 @@ __device__ __forceinline__ void decode_octet(const RawOctet<BF16, BITS> &r, floa
         g[3] = __uint_as_float(r.g0.w); g[4] = __uint_as_float(r.g1.x); g[5] = __uint_as_float(r.g1.y);
         g[6] = __uint_as_float(r.g1.z); g[7] = __uint_as_float(r.g1.w);
     }
-    const float step = r.scale * inv_levels(BITS) * omb;
+    const float step = r.scale * inv_levels(BITS) * omb * code_unit<BITS>();
+    float q[8];
+    code_values<BITS>(r.c0, r.c1, q);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        int q;
-        if (BITS == 8) q = code_field(e < 4 ? r.c0 : r.c1, e & 3, 8);
-        else q = code_field(r.c0, e, BITS);
-        p[e] = __builtin_fmaf(step, (float)q, g[e]);
+    for (int e = 0; e < 8; ++e) p[e] = __builtin_fmaf(step, q[e], g[e]);
+}
+
+// The last octet of a matrix that ends inside it or inside its word: nothing is stored beyond the matrix's last word, and that
+// one whole.
+template <int BITS>
+__device__ __forceinline__ void store_code_words_end(const MatDesc &d, uint32_t *codes, int64_t o, int tail, const uint32_t w[2])
+{
+    if (BITS == 8) {
+        codes[d.word_off + o * 2] = w[0];
+        if (tail > 4) codes[d.word_off + o * 2 + 1] = w[1];
+    } else if (BITS == 4) {
+        codes[d.word_off + o] = w[0];
+    } else {
+        reinterpret_cast<uint16_t *>(codes + d.word_off)[o] = (uint16_t)w[0];
+        if ((o & 1) == 0) reinterpret_cast<uint16_t *>(codes + d.word_off)[o + 1] = 0;
     }
 }
 
@@ -214,12 +228,12 @@ __global__ __launch_bounds__(256) void k_err_octet(DevicePlan dp, const void *__
             if ((lc & ((1 << d.lb_shift) - 1)) == 0) (TWO ? scales_first : scales)[d.scale_off + (o >> d.lb_shift)] = a;
         }
         if (TWO) {
-            const float dnew = a * inv_levels(BITS);
-            float a2 = 0.0f;
+            const float dnew = a * inv_levels(BITS) * code_unit<BITS>();
+            float a2 = 0.0f, qn[8];
+            code_values<BITS>(w[0], w[1], qn);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int qn = BITS == 8 ? code_field(w[e >> 2], e & 3, 8) : code_field(w[0], e, BITS);
-                x[e] = x[e] - dnew * (float)qn;
+                x[e] = x[e] - dnew * qn[e];
                 a2 = fmaxf(a2, fabsf(x[e]));
             }
             a2 = block_max(a2, d.lb_shift);
@@ -388,7 +402,7 @@ __global__ __launch_bounds__(256, 2) void k_err_tile(DevicePlan dp, const void *
             }
             a = block_max(a, lb);
             const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
-            const float dnew = a * inv_levels(BITS);
+            const float dnew = a * inv_levels(BITS) * code_unit<BITS>();
             float a2 = 0.0f;
             uint32_t w[NT][2];
 #pragma unroll
@@ -402,10 +416,11 @@ __global__ __launch_bounds__(256, 2) void k_err_tile(DevicePlan dp, const void *
                     if (h == 0 && (cc & ((1 << lb) - 1)) == 0) (TWO ? scales_first : scales)[d.scale_off + (o >> d.lb_shift)] = a;
                 }
                 if (TWO) {
+                    float qn[8];
+                    code_values<BITS>(w[h][0], w[h][1], qn);
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
-                        const int qn = BITS == 8 ? code_field(w[h][e >> 2], e & 3, 8) : code_field(w[h][0], e, BITS);
-                        x[h][e] = x[h][e] - dnew * (float)qn;
+                        x[h][e] = x[h][e] - dnew * qn[e];
                         a2 = fmaxf(a2, fabsf(x[h][e]));
                     }
                 }
@@ -814,7 +829,7 @@ void k_p_octet(DevicePlan dp, const void *__restrict__ grads, const uint32_t *__
 // e~+ = C(p - Delta) as before and the second q+ = C(p - Delta - e~+): the decoded e~+ (rounded to fp32) is
 // subtracted, the block maximum taken again and the difference rounded with random numbers of its own (matrix
 // word of the Philox counter + 2^31), all in registers.
-// MODE 3, random-k (stratified: one coordinate kept per stratum of rk_g consecutive ones, see strata_kept_octet):
+// MODE 3, random-k (stratified: one coordinate kept per stratum of rk_g consecutive ones, see strata_kept):
 // as MODE 0 with the kept coordinates scattered; the kept values go to the Delta buffer in stratum order.
 // MODE 4, random-k as a uniformly drawn subset (see rku_perm): the same; coordinate j is kept iff pi(j) < rk_uk and its value
 // goes to slot pi(j).  Eight evaluations of the keyed permutation per octet: several times the arithmetic of MODE 3.
@@ -846,22 +861,30 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
     }
     RkuKeys ku = {};
     if (MODE == kModeUniform) ku = rku_keys((uint32_t)it.mat, step_lo, step_hi, dp.seed_lo, dp.seed_hi);
+    __shared__ __attribute__((aligned(16))) float s_val[MODE == kModeStrata ? 4 : 1][MODE == kModeStrata ? 512 : 4];
+    __shared__ uint32_t s_kept[MODE == kModeStrata ? 4 : 1][64];
     double l1 = 0.0;
     const float s_f = (float)((1 << (BITS - 1)) - 1);
-    // The last run of a matrix may be short: octets at or beyond the end re-read the last octet and store
-    // nothing.  They make up whole scale blocks (the matrix is a whole number of blocks), so they do not
-    // enter the block maximum of a stored block.
-    const int64_t n_oct = d.N >> 3;
+    // The last run of a matrix may be short: octets beyond the end re-read the last octet and store nothing (where they share
+    // its block, they repeat what it brings to the block's maximum).  The last octet may hold fewer than eight elements (tail):
+    // the rest of it is read from the padding behind the matrix and counts as zero.
+    const int64_t n_oct = (d.N + 7) >> 3;
+    const int tail = (int)(d.N - ((n_oct - 1) << 3));
+    // does the last octet end its code word and (sign mode) its sign word?
+    const bool ends = tail != 8 || (BITS == 2 && (n_oct & 1) != 0) || (MODE == kModeSign && (n_oct & 3) != 0);
     auto clamp = [&](int64_t o) { return o < n_oct ? o : n_oct - 1; };
     RawOctet<BF16, BITS> cur = load_octet_always<BF16, BITS>(d, grads, codes, scales, clamp((int64_t)it.a * 64 + lane));
     RawCodes<BITS> cur2 = {0u, 0u, 0.0f};
     if (TWO) cur2 = load_codes_always<BITS>(d, codes2, scales2, clamp((int64_t)it.a * 64 + lane));
-    for (int rr = 0; rr < it.b; ++rr) {
+    // TAIL: the run that holds the last octet of a matrix that ends inside that octet or inside its word
+    auto run = [&](int rr, auto tail_tag) {
+        constexpr bool TAIL = decltype(tail_tag)::value;
         const int64_t o_raw = ((int64_t)it.a + rr) * 64 + lane;
         const bool valid = o_raw < n_oct;
         const int64_t o = clamp(o_raw);
-        const RawOctet<BF16, BITS> r = cur;
-        const RawCodes<BITS> r2 = cur2;
+        RawOctet<BF16, BITS> r = cur;
+        RawCodes<BITS> r2 = cur2;
+        const bool cut = TAIL && o == n_oct - 1;
         // the next run is requested before this one is worked on (the last one re-reads itself)
         cur = load_octet_always<BF16, BITS>(d, grads, codes, scales, clamp(o_raw + (rr + 1 < it.b ? 64 : 0)));
         if (TWO) cur2 = load_codes_always<BITS>(d, codes2, scales2, clamp(o_raw + (rr + 1 < it.b ? 64 : 0)));
@@ -878,12 +901,21 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
             g[3] = __uint_as_float(r.g0.w); g[4] = __uint_as_float(r.g1.x); g[5] = __uint_as_float(r.g1.y);
             g[6] = __uint_as_float(r.g1.z); g[7] = __uint_as_float(r.g1.w);
         }
-        const float dstep = r.scale * inv_levels(BITS);
-        const float dpart = TWO ? dstep : dstep * dp.omb;
-        const float dstep2 = r2.scale * inv_levels(BITS);
-        auto code_of = [&](int e) {
-            return (float)(BITS == 8 ? code_field(e < 4 ? r.c0 : r.c1, e & 3, 8) : code_field(r.c0, e, BITS));
-        };
+        if (TAIL) {
+            const uint32_t lo = BITS == 8 && tail >= 4 ? ~0u : (1u << (BITS * tail)) - 1u;
+            const uint32_t hi = BITS == 8 && tail > 4 ? (1u << (BITS * (tail - 4))) - 1u : 0u;
+            if (cut) {
+                r.c0 &= lo; r.c1 &= hi; r2.c0 &= lo; r2.c1 &= hi;
+#pragma unroll
+                for (int e = 1; e < 8; ++e) g[e] = e < tail ? g[e] : 0.0f;
+            }
+        }
+        const float dstep1 = r.scale * inv_levels(BITS), dstep = dstep1 * code_unit<BITS>();
+        const float dpart = TWO ? dstep : dstep1 * dp.omb * code_unit<BITS>();
+        const float dstep2 = r2.scale * inv_levels(BITS) * code_unit<BITS>();
+        float qf[8], qf2[8];
+        code_values<BITS>(r.c0, r.c1, qf);
+        if (TWO) code_values<BITS>(r2.c0, r2.c1, qf2);
         // Which of the octet's coordinates does the gradient compressor keep as they are (bit e of kbits), and where
         // does the first of them go in the Delta buffer (the others follow it)?  Most octets of a random block keep none.
         uint32_t kbits = 0;
@@ -895,19 +927,15 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                 kbits = ((1u << h8) - 1u) & ~((1u << l8) - 1u);
                 kslot = d.rb_delta_off + (l8 - lo);
             }
-        } else if (MODE == kModeStrata) {
-            uint32_t kfirst;
-            kbits = strata_kept_octet((uint32_t)(o * 8), (uint32_t)d.N, d.rk_g, d.rk_magic, (uint32_t)it.mat, step_lo, step_hi,
-                                      dp.seed_lo, dp.seed_hi, &kfirst);
-            kslot = d.rk_delta_off + kfirst;
         }
         uint32_t kpos[8];                                               // MODE 4: pi of the octet's coordinates
         if (MODE == kModeUniform) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                kpos[e] = rku_perm((uint32_t)(o * 8 + e), (uint32_t)d.N, d.rk_ua, d.rk_ub, d.rk_umagic, ku);
+                kpos[e] = rku_perm((uint32_t)(o * 8 + (cut && e >= tail ? 0 : e)), (uint32_t)d.N, d.rk_ua, d.rk_ub, d.rk_umagic, ku);
                 kbits |= (kpos[e] < d.rk_uk ? 1u : 0u) << e;
             }
+            if (cut) kbits &= (1u << tail) - 1u;
             kslot = d.rk_delta_off;
         }
         // x: the argument of the error compressor.  First as if nothing were kept: g + e (= beta e + p), or p = g + e~ + q
@@ -915,13 +943,9 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
         uint32_t neg_bits = 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float qf = code_of(e);
-            float ge = __builtin_fmaf(dstep, qf, g[e]);
-            float pv = TWO ? ge : __builtin_fmaf(dpart, qf, g[e]);        // p = g + (1 - beta) e
-            if (TWO) {
-                const int q2 = BITS == 8 ? code_field(e < 4 ? r2.c0 : r2.c1, e & 3, 8) : code_field(r2.c0, e, BITS);
-                pv = ge = __builtin_fmaf(dstep2, (float)q2, ge);
-            }
+            float ge = __builtin_fmaf(dstep, qf[e], g[e]);
+            float pv = TWO ? ge : __builtin_fmaf(dpart, qf[e], g[e]);     // p = g + (1 - beta) e
+            if (TWO) pv = ge = __builtin_fmaf(dstep2, qf2[e], ge);
             if (MODE == kModeNorm) {
                 l1 += valid ? (double)fabsf(pv) : 0.0;
                 x[e] = 0.0f;
@@ -933,7 +957,12 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                 x[e] = ge;
             }
         }
-        if (MODE == kModeNorm) continue;
+        if (MODE == kModeNorm) return;
+        if (MODE == kModeSign && TAIL && cut) {
+            neg_bits &= (1u << tail) - 1u;
+#pragma unroll
+            for (int e = 1; e < 8; ++e) x[e] = e < tail ? x[e] : 0.0f;
+        }
         if (V2) {
             // + e~ where it was taken from
             const int64_t lo = e_from - o * 8, hi = lo + d.i2_k;
@@ -945,7 +974,55 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
             }
         }
         // ... then the kept coordinates: Delta = p there, and beta e (plain) or nothing (two vectors) is left
-        if (SPARSE && kbits != 0) {
+        if (MODE == kModeStrata) {
+            // The run's values of p go through LDS, and the lanes take the run's strata: each draws its stratum's coordinate,
+            // passes the value on and marks it in its octet's word.  (An octet looking for its strata's coordinates evaluated
+            // two Philox calls and a branch per element: half of the pass.)  With short strata a lane takes the four of a call.
+            float *sp = s_val[threadIdx.x >> 6];
+            uint32_t *sk = s_kept[threadIdx.x >> 6];
+            float p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = (TWO || V2) ? x[e] : __builtin_fmaf(dpart, qf[e], g[e]);
+            reinterpret_cast<float4 *>(sp + lane * 8)[0] = make_float4(p[0], p[1], p[2], p[3]);
+            reinterpret_cast<float4 *>(sp + lane * 8)[1] = make_float4(p[4], p[5], p[6], p[7]);
+            sk[lane] = 0;
+            wave_lds_sync();
+            const uint32_t N = (uint32_t)d.N, j0 = (uint32_t)(((int64_t)it.a + rr) << 9);
+            const uint32_t s0 = stratum_of(j0, d.rk_g, d.rk_magic), s1 = stratum_of(N - 1u - j0 < 511u ? N - 1u : j0 + 511u, d.rk_g, d.rk_magic);
+            auto take = [&](uint32_t s, uint32_t u) {
+                const uint32_t base = s * d.rk_g;
+                const uint32_t len = N - base < d.rk_g ? N - base : d.rk_g;
+                const uint32_t rel = base + __umulhi(u, len) - j0;            // wraps to a large value before the run
+                if (rel < 512u) {
+                    delta[d.rk_delta_off + s] = sp[rel];
+                    __hip_atomic_fetch_or(sk + (rel >> 3), 1u << (rel & 7u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            };
+            uint32_t out[4];
+            if (d.rk_g >= 8) {
+                for (uint32_t s = s0 + lane; s <= s1; s += 64) {
+                    philox4x32_10(s >> 2, (uint32_t)it.mat + 0x40000000u, step_lo, step_hi, dp.seed_lo, dp.seed_hi, out);
+                    const uint32_t w = s & 3u;
+                    take(s, w == 0 ? out[0] : (w == 1 ? out[1] : (w == 2 ? out[2] : out[3])));
+                }
+            } else {
+                for (uint32_t q = (s0 >> 2) + lane; q <= (s1 >> 2); q += 64) {
+                    philox4x32_10(q, (uint32_t)it.mat + 0x40000000u, step_lo, step_hi, dp.seed_lo, dp.seed_hi, out);
+#pragma unroll
+                    for (uint32_t w = 0; w < 4; ++w)
+                        if (q * 4 + w >= s0 && q * 4 + w <= s1) take(q * 4 + w, out[w]);
+                }
+            }
+            wave_lds_sync();
+            const uint32_t left = ~sk[lane];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t keep = (uint32_t)((int32_t)(left << (31 - e)) >> 31);        // all ones where nothing was taken
+                if (TWO || V2) x[e] = __uint_as_float(__float_as_uint(x[e]) & keep);
+                else x[e] = keep ? x[e] : dp.beta * (dstep * qf[e]);
+            }
+            wave_lds_sync();                // the next run's values may not overtake these reads
+        } else if (SPARSE && kbits != 0) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 if ((kbits >> e) & 1u) {
@@ -954,9 +1031,8 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                         if (valid) delta[slot] = x[e];
                         x[e] = 0.0f;
                     } else {
-                        const float qf = code_of(e);
-                        if (valid) delta[slot] = __builtin_fmaf(dpart, qf, g[e]);
-                        x[e] = dp.beta * (dstep * qf);
+                        if (valid) delta[slot] = __builtin_fmaf(dpart, qf[e], g[e]);
+                        x[e] = dp.beta * (dstep * qf[e]);
                     }
                 }
             }
@@ -975,7 +1051,12 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                 }
             }
         }
-        if (MODE == kModeSign && valid) reinterpret_cast<uint8_t *>(sign_words + d.sign_off)[o] = (uint8_t)neg_bits;
+        if (MODE == kModeSign && valid) {
+            uint8_t *sb = reinterpret_cast<uint8_t *>(sign_words + d.sign_off);
+            sb[o] = (uint8_t)neg_bits;
+            if (TAIL && o == n_oct - 1)
+                for (int64_t b = o + 1; (b & 3) != 0; ++b) sb[b] = 0;          // the rest of the last word
+        }
         float a = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) a = fmaxf(a, fabsf(x[e]));
@@ -985,17 +1066,18 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
         philox4x32_10((uint32_t)o, (uint32_t)it.mat, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
         quantise_octet<BITS>(x, inv16, rnd, w);
         if (valid) {
-            store_code_words<BITS>(d, codes, o, w);
+            if (cut) store_code_words_end<BITS>(d, codes, o, tail, w);
+            else store_code_words<BITS>(d, codes, o, w);
             if ((lane & ((1 << d.lb_shift) - 1)) == 0) scales[d.scale_off + (o >> d.lb_shift)] = a;
         }
         if (TWO) {
             // q+ = C(x - e~+): what the first rounding left, one level finer
-            const float dnew = a * inv_levels(BITS);
-            float a2 = 0.0f;
+            const float dnew = a * inv_levels(BITS) * code_unit<BITS>();
+            float a2 = 0.0f, qn[8];
+            code_values<BITS>(w[0], w[1], qn);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int qn = BITS == 8 ? code_field(w[e >> 2], e & 3, 8) : code_field(w[0], e, BITS);
-                x[e] = x[e] - dnew * (float)qn;
+                x[e] = x[e] - dnew * qn[e];
                 a2 = fmaxf(a2, fabsf(x[e]));
             }
             a2 = block_max(a2, d.lb_shift);
@@ -1003,11 +1085,15 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
             philox4x32_10((uint32_t)o, (uint32_t)it.mat | 0x80000000u, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
             quantise_octet<BITS>(x, inv16_2, rnd, w);
             if (valid) {
-                store_code_words<BITS>(d, codes2, o, w);
+                if (cut) store_code_words_end<BITS>(d, codes2, o, tail, w);
+                else store_code_words<BITS>(d, codes2, o, w);
                 if ((lane & ((1 << d.lb_shift) - 1)) == 0) scales2[d.scale_off + (o >> d.lb_shift)] = a2;
             }
         }
-    }
+    };
+    const int whole = ends && (((int64_t)it.a + it.b) << 6) >= n_oct ? it.b - 1 : it.b;
+    for (int rr = 0; rr < whole; ++rr) run(rr, std::false_type{});
+    if (whole < it.b) run(whole, std::true_type{});
     if (MODE == kModeNorm) {
         l1 = wave_sum(l1);
         if (lane == 0) ws[d.st_part_off + (item - d.st_first)] = l1;

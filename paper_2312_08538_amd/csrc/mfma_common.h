@@ -57,29 +57,6 @@ __device__ __forceinline__ uint4 lds_read_tr16x8(const uint16_t *p, int pitch)
     return make_uint4(lo.u.x, lo.u.y, hi.u.x, hi.u.y);
 }
 
-// signed 4-bit field in the low nibble of byte `byte` of w, divided by 16 (exact), as fp32: the
-// conversion instruction reads the nibble through its byte selector, so no shift or mask is spent
-template <int byte>
-__device__ __forceinline__ float nibble_over_16(uint32_t w)
-{
-    float r;
-    if constexpr (byte == 0) asm("v_cvt_off_f32_i4_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0" : "=v"(r) : "v"(w));
-    else if constexpr (byte == 1) asm("v_cvt_off_f32_i4_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1" : "=v"(r) : "v"(w));
-    else if constexpr (byte == 2) asm("v_cvt_off_f32_i4_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_2" : "=v"(r) : "v"(w));
-    else asm("v_cvt_off_f32_i4_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3" : "=v"(r) : "v"(w));
-    return r;
-}
-
-// the eight fields of a code word, each divided by 16
-__device__ __forceinline__ void fields_over_16(uint32_t w, float q[8])
-{
-    const uint32_t w4 = w >> 4;
-    q[0] = nibble_over_16<0>(w); q[1] = nibble_over_16<0>(w4);
-    q[2] = nibble_over_16<1>(w); q[3] = nibble_over_16<1>(w4);
-    q[4] = nibble_over_16<2>(w); q[5] = nibble_over_16<2>(w4);
-    q[6] = nibble_over_16<3>(w); q[7] = nibble_over_16<3>(w4);
-}
-
 // the eight signed 2-bit fields of the low half of h as bf16 integers (-1, 0, 1; exact), two per word
 __device__ __forceinline__ uint4 fields2_bf16(uint32_t h)
 {

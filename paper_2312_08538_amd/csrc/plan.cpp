@@ -512,16 +512,17 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
             }
         }
         // Stream tables of the element-wise gradient compressors (random block, scaled sign) for the quantiser:
-        // the wave-per-run kernel needs blocks of 8 * 2^j elements (j <= 6) that fill the matrix (no short last block)
+        // the wave-per-run kernel needs blocks of 8 * 2^j elements (j <= 6).  A wave takes eight runs of 512 elements, fewer where
+        // that would leave the chip with fewer than eight waves per SIMD (a wave's items are one serial chain of loads).
         int64_t sw = 0;
         const bool stream_ok = block % 8 == 0 && is_pow2(block / 8) && block / 8 <= 64;
         for (int l = 0; l < n_mats; ++l) {
             MatDesc &d = plan.mats[l];
             d.sign_off = sw; sw += round_up(ceil_div(d.N, 32), kAlign);
             if (sketch) continue;                   // the count-sketch mode walks its bucket lists
-            if (stream_ok && d.N % block == 0) {
+            if (stream_ok) {
                 d.lb_shift = log2i(block / 8);
-                const int64_t runs = ceil_div(d.N, 512), per_item = 8;        // the last run may be short
+                const int64_t runs = ceil_div(d.N, 512), per_item = std::min<int64_t>(8, std::max<int64_t>(1, total_elems / (512 * 8192)));
                 d.st_first = (int32_t)plan.rb_items.size();
                 for (int64_t r0 = 0; r0 < runs; r0 += per_item)
                     plan.rb_items.push_back({l, (int32_t)r0, (int32_t)std::min<int64_t>(per_item, runs - r0), 0});
