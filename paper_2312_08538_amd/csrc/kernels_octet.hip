@@ -1014,12 +1014,14 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                 }
             }
             wave_lds_sync();
-            const uint32_t left = ~sk[lane];
+            // (an octet beyond the end is marked nowhere: it must not bring the last octet's kept coordinates to the maximum)
+            const uint32_t left = valid ? ~sk[lane] : 0u;
+            const float back = valid ? dp.beta : 0.0f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const uint32_t keep = (uint32_t)((int32_t)(left << (31 - e)) >> 31);        // all ones where nothing was taken
                 if (TWO || V2) x[e] = __uint_as_float(__float_as_uint(x[e]) & keep);
-                else x[e] = keep ? x[e] : dp.beta * (dstep * qf[e]);
+                else x[e] = keep ? x[e] : back * (dstep * qf[e]);
             }
             wave_lds_sync();                // the next run's values may not overtake these reads
         } else if (SPARSE && kbits != 0) {
