@@ -462,6 +462,11 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         const int64_t strip_chunk = std::min<int64_t>(2048, std::max<int64_t>(256, round_up(strip_elems / (kStripRows * 1536), 256)));
         const int64_t strip_q_rows = std::min<int64_t>(512, std::max<int64_t>(32, round_up(strip_elems / (64 * 1536), 32)));
         const int64_t strip_err = strip_elems / 8192 >= 1024 ? 8192 : strip_elems / 4096 >= 768 ? 4096 : 2048;
+        // decompress / update: row tiles per item.  On the matrix cores a workgroup keeps its strip of Q+ for several of
+        // them, as many as leave about 4096 workgroups
+        int64_t upd_tiles = 0;
+        for (int l = 0; l < n_mats; ++l) upd_tiles += ceil_div(plan.mats[l].n, kUpdRows) * ceil_div(plan.mats[l].m, kUpdCols);
+        upd_tiles = update_on_cores(rank) ? std::min<int64_t>(8, std::max<int64_t>(1, upd_tiles / 4096)) : 1;
         for (int l = 0; l < n_mats; ++l) {
             MatDesc &d = plan.mats[l];
             if (d.path == kPathMfma) {
@@ -637,9 +642,10 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                     plan.qred_items.push_back({l, (int32_t)e0, 0, per == 16 ? 1 : 0});
             }
             for (int64_t e0 = 0; e0 < d.N; e0 += 1024) plan.elem_items.push_back({l, (int32_t)(e0 >> 10), 0, 0});
-            for (int64_t r0 = 0; r0 < d.n; r0 += kUpdRows)
+            for (int64_t r0 = 0; r0 < d.n; r0 += upd_tiles * kUpdRows)
                 for (int64_t c0 = 0; c0 < d.m; c0 += kUpdCols)
-                    plan.upd_items.push_back({l, (int32_t)(r0 / kUpdRows), (int32_t)(c0 / kUpdCols), 0});
+                    plan.upd_items.push_back({l, (int32_t)(r0 / kUpdRows), (int32_t)(c0 / kUpdCols),
+                                              (int32_t)std::min<int64_t>(upd_tiles, ceil_div(d.n - r0, kUpdRows))});
         }
         // The P pass of the matrix-core family: workgroups are dealt to the eight XCDs in turn (workgroup b runs on
         // XCD b % 8), and a pass streams faster when every XCD stays inside an address range of its own (measured
@@ -907,7 +913,7 @@ bool check_plan(const Plan &plan)
     {
         Cover c(nm);
         for (const WorkItem &it : plan.upd_items)
-            c.add(plan, it, (int64_t)it.a * kUpdRows, kUpdRows, (int64_t)it.b * kUpdCols, kUpdCols);
+            c.add(plan, it, (int64_t)it.a * kUpdRows, (int64_t)it.c * kUpdRows, (int64_t)it.b * kUpdCols, kUpdCols);
         if (!c.complete(plan)) return false;
     }
     // per-matrix helpers, and the workspace map

@@ -20,6 +20,8 @@ enum Path { kPathGeneric = 0, kPathOctet = 1, kPathMfma = 2 };
 constexpr int kMfmaRows = 128;      // rows per workgroup item of the MFMA P pass
 constexpr int kUpdRows = 64;        // tile of the decompress / update kernel
 constexpr int kUpdCols = 128;
+// ranks for which that kernel is the one on the fp32 matrix cores (elsewhere the vector ALU keeps up with the memory)
+constexpr bool update_on_cores(int rank) { return rank > 8 && (rank & 3) == 0; }
 constexpr int kErrRows = 128;       // rows per workgroup item of the MFMA err pass (8 waves x 16)
 constexpr int kErrRun = 16;         // column blocks of 128 per item of the MFMA err pass (at most 16)
 constexpr int kCsCols = 256;        // columns per workgroup item of the count-sketch update pass
