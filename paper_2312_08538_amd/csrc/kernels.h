@@ -146,6 +146,14 @@ void generic_p_reduce(const DevicePlan &dp, double *ws, float *P, hipStream_t st
 void generic_q_reduce(const DevicePlan &dp, double *ws, float *Qout, hipStream_t st);   // adds the row-tile partials of Q+
 void generic_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, const float *Phat,
                       const float *Qn, uint64_t step, hipStream_t st);
+// The octet family's and the strip family's workgroups in one launch (kernels_mixed.hip), where that is the faster way:
+// false if it is not, and then nothing has been enqueued.  The err pass takes the plan's err_t_items and err_s_items.
+bool mixed_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Q, float *P,
+                  double *ws, hipStream_t st);
+bool mixed_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Phat, double *ws,
+                  float *Qout, hipStream_t st);
+bool mixed_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, const float *Phat, const float *Qn,
+                    uint64_t step, hipStream_t st);
 void octet_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
                   const float *Q, float *P, double *ws, hipStream_t st);
 void octet_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,

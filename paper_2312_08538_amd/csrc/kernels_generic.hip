@@ -554,8 +554,10 @@ hipError_t launch_pass_p(const DevicePlan &dp, const void *grads, const uint32_t
     if (span.begin) (void)hipEventRecord(span.begin, st);
     mfma_pass_p(dp, grads, codes, scales, Q, P, st);
     pack_pass_p(dp, grads, codes, scales, Q, P, st);
-    octet_pass_p(dp, grads, codes, scales, Q, P, ws, st);
-    strip_pass_p(dp, grads, codes, scales, Q, P, ws, st);
+    if (!mixed_pass_p(dp, grads, codes, scales, Q, P, ws, st)) {
+        octet_pass_p(dp, grads, codes, scales, Q, P, ws, st);
+        strip_pass_p(dp, grads, codes, scales, Q, P, ws, st);
+    }
     if (span.end) (void)hipEventRecord(span.end, st);
     generic_p_reduce(dp, ws, P, st);
     return hipGetLastError();
@@ -573,8 +575,10 @@ hipError_t launch_pass_q(const DevicePlan &dp, const void *grads, const uint32_t
     if (span.begin) (void)hipEventRecord(span.begin, st);
     mfma_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
     pack_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
-    octet_pass_q(dp, grads, codes, scales, Phat, ws, st);
-    strip_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
+    if (!mixed_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st)) {
+        octet_pass_q(dp, grads, codes, scales, Phat, ws, st);
+        strip_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
+    }
     if (span.end) (void)hipEventRecord(span.end, st);
     // the reduction also writes the matrix-core family's operand splits of Q+
     generic_q_reduce(dp, ws, Qout, st);
@@ -592,8 +596,10 @@ hipError_t launch_pass_err(const DevicePlan &dp, const void *grads, uint32_t *co
     }
     if (span.begin) (void)hipEventRecord(span.begin, st);
     mfma_pass_err(dp, grads, codes, scales, Phat, ws, step, st);
-    octet_pass_err(dp, grads, codes, scales, Phat, Qn, step, st);
-    strip_pass_err(dp, grads, codes, scales, Phat, Qn, step, st);
+    DevicePlan rest = dp;
+    if (mixed_pass_err(dp, grads, codes, scales, Phat, Qn, step, st)) rest.n_err_t = rest.n_err_s = 0;
+    octet_pass_err(rest, grads, codes, scales, Phat, Qn, step, st);
+    strip_pass_err(rest, grads, codes, scales, Phat, Qn, step, st);
     generic_pass_err(dp, grads, codes, scales, Phat, Qn, step, st);
     if (span.end) (void)hipEventRecord(span.end, st);
     return hipGetLastError();

@@ -504,7 +504,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
             if (d.path != kPathGeneric) continue;
             if (d.m <= 1024) {
                 int64_t tile = strip_err;
-                while (tile < 8192 && tile < 8 * d.m) tile *= 2;
+                while (tile < 8192 && tile < 8 * d.m && strip_elems / tile >= 512) tile *= 2;      // (shorter runs rather than an empty chip)
                 d.es_tile = (int32_t)round_up(tile, block);
                 plan.es_lds = std::max(plan.es_lds, d.es_tile + 8);
             } else {
