@@ -1,0 +1,62 @@
+"""GPU tests of the strip kernels (any layout), of the launches that carry octet and strip workgroups together, and of
+the update's row tiles, at the sizes where a rule or a tile ends.  All of them reproduce the oracle bit for bit."""
+import numpy as np
+import pytest
+
+from paper_2312_08538_amd import workloads as wl
+from test_gpu_parity import _run_model, env  # noqa: F401  (the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rank,bits,block,dtype", [(1, 4, 128, wl.F32), (3, 8, 64, wl.BF16), (4, 2, 512, wl.F32), (6, 4, 8, wl.F32),
+                                                   (8, 4, 256, wl.BF16), (12, 4, 24, wl.F32), (16, 8, 128, wl.BF16), (32, 2, 64, wl.F32)])
+def test_strip_kernels_at_the_ends_of_their_tiles(env, rank, bits, block, dtype):
+    """Columns one below, at and above a strip (64), a P chunk (256) and the limit between runs of the flat index and
+    column segments in the err pass (1024); rows one below, at and above a row tile (32).  Blocks of 24 take the err pass
+    for any block."""
+    layout = [(33, 63), (32, 65), (31, 255), (65, 257), (40, 1023), (33, 1025), (64, 1029), (35, 2560), (70, 2047)]
+    layout = [(max(n, rank), m) for n, m in layout]
+    w = wl.Workload("strip-edges", 11, tuple(layout), rank, bits, block, dtype, "normal", 1.0, 0x57819)
+    _run_model(env, w, layout, 2, f"strip-r{rank}-b{bits}-B{block}-dt{dtype}")
+
+
+@pytest.mark.parametrize("rank,bits,block,dtype", [(2, 4, 64, wl.F32), (4, 8, 128, wl.BF16), (4, 4, 256, wl.F32), (8, 2, 128, wl.F32),
+                                                   (8, 8, 256, wl.BF16)])
+@pytest.mark.parametrize("strips", [1, 7, 24])
+def test_octet_and_strip_matrices_in_one_launch(env, rank, bits, block, dtype, strips):
+    """A few strip matrices (their workgroups lead the launch, padded to eight) among octet matrices, and more of them
+    than the joint launch takes (the two families then run in launches of their own)."""
+    layout = [(100, 512), (64, 147)] + [(40, 768), (33 + 2 * strips, 163 if strips < 24 else 2049)] * strips
+    w = wl.Workload("mixed", 12, tuple(layout), rank, bits, block, dtype, "normal", 1.0, 0x313D)
+    assert _run_model(env, w, layout, 2, f"mixed-r{rank}-b{bits}-B{block}-dt{dtype}-{strips}") == 0
+
+
+@pytest.mark.parametrize("rank,tiles", [(12, 2), (32, 3), (16, 8)])
+def test_update_over_several_row_tiles_per_workgroup(env, rank, tiles):
+    """The update on the fp32 matrix cores where a workgroup walks several 64-row tiles: the last item ragged in tiles and
+    rows, columns not a multiple of its strip.  Sampled rows (the ends of tiles, items and the matrix) bit for bit."""
+    R, B, U = env
+    import torch
+
+    m = 1000
+    n = tiles * 4096 // 8 * 64 + 64 + 37
+    print(f"[update rank {rank} tiles {tiles}] {n} x {m}: launching", flush=True)
+    model = B.Model([(n, m)], rank, 4, 128, B.F32, 7)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(rank)
+    P = torch.randn(model.sizes["p_elems"], device="cuda:0", generator=gen)
+    Q = torch.randn(model.sizes["q_elems"], device="cuda:0", generator=gen)
+    x = torch.randn(model.sizes["grad_elems"], device="cuda:0", generator=gen)
+    rows = np.unique(np.concatenate([np.arange(0, 66), np.arange(64 * tiles - 2, 64 * tiles + 3), np.arange(n // 2 - 40, n // 2 + 40),
+                                     np.arange(n - 170, n)]))
+    pick = torch.from_numpy(rows).cuda()
+    x0 = x[:n * m].view(n, m)[pick].cpu().numpy()
+    tail = x[n * m:].clone()
+    B.conef_apply_update(model.ctx, P, Q, x, model.stream_handle())
+    torch.cuda.synchronize()
+    want = R.apply_update(x0, P[:n * rank].view(n, rank)[pick].cpu().numpy(), Q[:m * rank].view(m, rank).cpu().numpy())
+    got = x[:n * m].view(n, m)[pick].cpu().numpy()
+    assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+    assert torch.equal(x[n * m:], tail)
+    model.close()
