@@ -195,6 +195,12 @@ __device__ __forceinline__ void p_strip(const DevicePlan &dp, int block, float *
 #pragma unroll
             for (int h = 0; h < BN; ++h) bq[j][h] = qbase[(uint32_t)(k * r + bc[h])];
         }
+        if (ncol & 3) {                                         // uniform; zero, so that 0 x inf does not reach a sum
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+#pragma unroll
+                for (int h = 0; h < BN; ++h) bq[j][h] = 4 * j + mk < ncol ? bq[j][h] : 0.0f;
+        }
         const uint32_t rel_s = rel0 + 64u * (uint32_t)s + lc;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {

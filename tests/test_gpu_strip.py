@@ -60,3 +60,28 @@ def test_update_over_several_row_tiles_per_workgroup(env, rank, tiles):
     assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
     assert torch.equal(x[n * m:], tail)
     model.close()
+
+
+def test_an_infinite_factor_entry_stays_in_its_products(env):
+    """P pass with an infinity in the last row of Q, columns that do not fill the last operand of four: p Q is infinite
+    there with the sign of the product, not NaN from the operand's empty places."""
+    R, B, U = env
+    import torch
+
+    layout, rank = [(64, 147), (33, 129), (40, 126)], 3
+    model = B.Model(layout, rank, 4, 128, B.F32, 5)
+    buf = model.alloc("cuda:0")
+    rng = np.random.default_rng(5)
+    g = [rng.standard_normal((n, m)).astype(np.float32) for n, m in layout]
+    for x, (n, m), o in zip(g, layout, model.offsets):
+        buf["grads"][o["grad_off"]:o["grad_off"] + n * m] = torch.from_numpy(x.ravel()).cuda()
+        q = rng.standard_normal((m, rank)).astype(np.float32)
+        q[m - 1, 1] = np.inf
+        buf["Q"][o["q_off"]:o["q_off"] + m * rank] = torch.from_numpy(q.ravel()).cuda()
+    B.conef_step_p(model.ctx, buf["grads"], buf["codes"], buf["scales"], buf["Q"], buf["P"], buf["ws"], model.stream_handle())
+    torch.cuda.synchronize()
+    for x, (n, m), o in zip(g, layout, model.offsets):
+        P = buf["P"][o["p_off"]:o["p_off"] + n * rank].cpu().numpy().reshape(n, rank)
+        assert np.array_equal(P[:, 1], np.where(x[:, m - 1] > 0, np.inf, -np.inf).astype(np.float32))
+        assert np.all(np.isfinite(P[:, [0, 2]]))
+    model.close()
