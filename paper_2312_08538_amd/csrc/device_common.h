@@ -239,8 +239,9 @@ __device__ __forceinline__ uint32_t quantise_field(float x, float inv16, uint32_
 
 // Fixed-point stochastic rounding of an octet (quantise_field on each of its 8 values) straight into packed
 // BITS-wide two's-complement fields: 8-bit codes give two words (elements 0..3, 4..7), 4- and 2-bit codes the low
-// 32 / 16 bits of w[0].  U + draw stays below 2^23, so its byte 2 is the magnitude, and byte permutes gather the magnitudes
-// of an octet (7 - 10 instructions; a shift and an insertion per element were 16).  Sign bits are gathered field by field
+// 32 / 16 bits of w[0].  Byte 2 of U + draw is the magnitude, and byte permutes gather the magnitudes of an octet (8 - 13
+// instructions; a shift and an insertion per element were 16).  U + draw stays below 2^23, unless the block is so small that
+// inv16 is infinite: then a byte may be 0xFF, and a field keeps its own bits of it, as in quantise_field.  Sign bits are gathered field by field
 // and the negation is done on the whole word: with s the sign bit of a field,
 // ((mag ^ (s - (s >> (BITS-1)))) + (s >> (BITS-1))) ^ s is 2^BITS - mag for a negative field with mag >= 1 and 0 for mag = 0;
 // no carry leaves a field.
@@ -259,13 +260,16 @@ __device__ __forceinline__ void quantise_octet(const float x[8], float inv16, co
     // __builtin_amdgcn_perm(hi, lo, sel): result byte i is byte sel_i of {hi, lo} (0..3 lo, 4..7 hi, 12: zero)
     auto low2 = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x0C0C0602u); };     // byte 0: a's, byte 1: b's
     auto high2 = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x06020C0Cu); };    // bytes 2 and 3
+    auto fields = [](uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); };                          // one v_bfi
     if (BITS == 8) {
         mags[0] = low2(t[0], t[1]) | high2(t[2], t[3]);
         mags[1] = low2(t[4], t[5]) | high2(t[6], t[7]);
     } else if (BITS == 4) {
-        mags[0] = ((low2(t[1], t[3]) | high2(t[5], t[7])) << 4) | (low2(t[0], t[2]) | high2(t[4], t[6]));
+        mags[0] = fields(0x0F0F0F0Fu, low2(t[0], t[2]) | high2(t[4], t[6]), (low2(t[1], t[3]) | high2(t[5], t[7])) << 4);
     } else {
-        mags[0] = low2(t[0], t[4]) | (low2(t[1], t[5]) << 2) | (low2(t[2], t[6]) << 4) | (low2(t[3], t[7]) << 6);
+        mags[0] = fields(0x0303u, low2(t[0], t[4]), low2(t[1], t[5]) << 2);
+        mags[0] = fields(0x0F0Fu, mags[0], low2(t[2], t[6]) << 4);
+        mags[0] = fields(0x3F3Fu, mags[0], low2(t[3], t[7]) << 6) & 0xFFFFu;
     }
 #pragma unroll
     for (int h = 0; h < (BITS == 8 ? 2 : 1); ++h) {

@@ -85,3 +85,29 @@ def test_an_infinite_factor_entry_stays_in_its_products(env):
         assert np.array_equal(P[:, 1], np.where(x[:, m - 1] > 0, np.inf, -np.inf).astype(np.float32))
         assert np.all(np.isfinite(P[:, [0, 2]]))
     model.close()
+
+
+@pytest.mark.parametrize("rank", [3, 4])
+@pytest.mark.parametrize("bits,block", [(2, 64), (4, 128), (8, 64)])
+def test_blocks_too_small_to_divide_by_keep_their_codes_apart(env, rank, bits, block):
+    """Residuals of 1e-41: levels / max-norm is infinite, so the fixed-point product saturates and the draw wraps it.  What
+    comes out for such a value is of no use, but the field of its neighbour (here zero) stays zero.  Strip and octet
+    matrices; one value in 65536 draws the zero that gives an all-ones magnitude."""
+    R, B, U = env
+    import torch
+
+    layout = [(1500, 1026), (1500, 1024)]
+    model = B.Model(layout, rank, bits, block, B.F32, 5)
+    buf = model.alloc("cuda:0")
+    for (n, m), o in zip(layout, model.offsets):
+        g = torch.full((n, m), 1e-41)
+        g[::2] = -1e-41
+        g[:, 1::2] = 0.0
+        buf["grads"][o["grad_off"]:o["grad_off"] + n * m] = g.view(-1).cuda()
+    P, Q = torch.zeros_like(buf["P"]), torch.zeros_like(buf["Q"])
+    B.conef_step_err(model.ctx, buf["grads"], buf["codes"], buf["scales"], P, Q, buf["ws"], 3, model.stream_handle())
+    torch.cuda.synchronize()
+    for (n, m), o in zip(layout, model.offsets):
+        words = buf["codes"][o["word_off"]:o["word_off"] + R.n_words(n * m, bits)].cpu().numpy().view(np.uint32)
+        assert not U.unpack(words, n * m, bits).reshape(n, m)[:, 1::2].any()
+    model.close()
