@@ -1,5 +1,7 @@
 #include "plan.h"
 
+#include "../../include/conef.h"
+
 #include <array>
 #include <climits>
 #include <cmath>
@@ -467,35 +469,50 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         int64_t upd_tiles = 0;
         for (int l = 0; l < n_mats; ++l) upd_tiles += ceil_div(plan.mats[l].n, kUpdRows) * ceil_div(plan.mats[l].m, kUpdCols);
         upd_tiles = update_on_cores(rank) ? std::min<int64_t>(8, std::max<int64_t>(1, upd_tiles / 4096)) : 1;
-        for (int l = 0; l < n_mats; ++l) {
-            MatDesc &d = plan.mats[l];
-            if (d.path == kPathMfma) {
-                d.scT_off = wd; wd += round_up((d.m / 128) * d.n * 4 / 8 + 1, 32);
-                d.scT2_off = wd; wd += round_up((d.m / 128) * d.n * 4 / 8 + 1, 32);
-                d.qs_off = wd;  wd += round_up(3 * 32 * d.m * 2 / 8, 32);
-            }
+        auto lay_out = [&](int64_t chunk_cols, int64_t tile_rows) {
+            wd = 0;
+            plan.any_p_chunks = false;
+            for (int l = 0; l < n_mats; ++l) {
+                MatDesc &d = plan.mats[l];
+                if (d.path == kPathMfma) {
+                    d.scT_off = wd; wd += round_up((d.m / 128) * d.n * 4 / 8 + 1, 32);
+                    d.scT2_off = wd; wd += round_up((d.m / 128) * d.n * 4 / 8 + 1, 32);
+                    d.qs_off = wd;  wd += round_up(3 * 32 * d.m * 2 / 8, 32);
+                }
 
-            d.gram_tile_rows = d.n > 8192 ? 2 * kGramRows : kGramRows;
-            d.n_gram_tiles = (int32_t)ceil_div(d.n, d.gram_tile_rows);
-            d.gram_off = wd; wd += (int64_t)d.n_gram_tiles * rank * rank;
-            d.gsum_off = wd; wd += rank * rank;
-            d.rinv_off = wd; wd += rank * rank;
-            d.q_tile_rows = d.cs_lin ? 2048 : d.pack ? kPackQRows : d.path == kPathOctet ? q_rows : (d.path == kPathMfma && (kMfmaPasses & 2)) ? 2048
-                            : (int32_t)std::min<int64_t>(strip_q_rows, 4 * std::max<int64_t>(1, kStripSpan / d.m));
-            d.n_q_tiles = (int32_t)ceil_div(d.n, d.q_tile_rows);
-            d.qpart_off = wd; wd += round_up((int64_t)d.n_q_tiles * d.m * rank, 32);
-            d.n_p_chunks = 1;
-            d.p_chunk_cols = (int32_t)d.m;
-            const bool strip = d.path == kPathGeneric;
-            if ((d.path == kPathOctet && !d.cs_lin && !d.pack) || strip) {
-                // strip kernels: chunks of one size, a multiple of a strip
-                d.p_chunk_cols = strip ? (int32_t)round_up(ceil_div(d.m, ceil_div(d.m, strip_chunk)), 64) : p_cols;
-                d.n_p_chunks = (int32_t)ceil_div(d.m, d.p_chunk_cols);
-                if (d.n_p_chunks > 1) {
-                    d.ppart_off = wd; wd += round_up((int64_t)d.n_p_chunks * d.n * rank, 32);
-                    plan.any_p_chunks = true;
+                d.gram_tile_rows = d.n > 8192 ? 2 * kGramRows : kGramRows;
+                d.n_gram_tiles = (int32_t)ceil_div(d.n, d.gram_tile_rows);
+                d.gram_off = wd; wd += (int64_t)d.n_gram_tiles * rank * rank;
+                d.gsum_off = wd; wd += rank * rank;
+                d.rinv_off = wd; wd += rank * rank;
+                d.q_tile_rows = d.cs_lin ? 2048 : d.pack ? kPackQRows : d.path == kPathOctet ? q_rows : (d.path == kPathMfma && (kMfmaPasses & 2)) ? 2048
+                                : (int32_t)std::min<int64_t>(tile_rows, 4 * std::max<int64_t>(1, kStripSpan / d.m));
+                d.n_q_tiles = (int32_t)ceil_div(d.n, d.q_tile_rows);
+                d.qpart_off = wd; wd += round_up((int64_t)d.n_q_tiles * d.m * rank, 32);
+                d.n_p_chunks = 1;
+                d.p_chunk_cols = (int32_t)d.m;
+                const bool strip = d.path == kPathGeneric;
+                if ((d.path == kPathOctet && !d.cs_lin && !d.pack) || strip) {
+                    // strip kernels: chunks of one size, a multiple of a strip
+                    d.p_chunk_cols = strip ? (int32_t)round_up(ceil_div(d.m, ceil_div(d.m, chunk_cols)), 64) : p_cols;
+                    d.n_p_chunks = (int32_t)ceil_div(d.m, d.p_chunk_cols);
+                    if (d.n_p_chunks > 1) {
+                        d.ppart_off = wd; wd += round_up((int64_t)d.n_p_chunks * d.n * rank, 32);
+                        plan.any_p_chunks = true;
+                    }
                 }
             }
+        };
+        lay_out(strip_chunk, strip_q_rows);
+        // Partial sums of small and middle-sized models at high ranks can take the workspace beyond the static one of
+        // conef_step_static (98304 wave-rows x 32 entries: 25 MB).  They are split more coarsely until it fits (with 1 MB left for
+        // what follows); whole rows of P and 512 rows per partial of Q+ are the least.  Where that does not fit either, nothing
+        // is gained by a coarser split.
+        const int64_t fits = ((int64_t)CONEF_STATIC_WORKSPACE_BYTES - (1 << 20)) / 8;
+        if (!sketch && strip_elems > 0 && wd > fits) {
+            for (int64_t k = 2; k <= 16 && wd > fits; k *= 2) lay_out(strip_chunk * k, std::min<int64_t>(512, strip_q_rows * k));
+            if (wd > fits) lay_out(INT32_MAX, 512);
+            if (wd > (int64_t)CONEF_STATIC_WORKSPACE_BYTES / 8) lay_out(strip_chunk, strip_q_rows);
         }
         // The strip err pass: runs of the flat index of strip_err elements where that is at least eight rows (a wave's row of
         // Q+ per lane serves all rows of a run), else eight rows of a column segment.

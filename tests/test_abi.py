@@ -504,3 +504,13 @@ def test_element_wise_and_iconef_calls_validate_their_arguments_before_any_launc
     assert L.conef_i_step(q, A, A, A, 512, 512, A, A, A, A, 0, 0) == B.ESTATE
     for ctx in (q, qb, sk):
         B.conef_destroy(ctx)
+
+
+@pytest.mark.parametrize("layout,rank", [([(16384, 700)], 32), ([(9000, 333)] * 5, 32), ([(33278, 650)] + [(2600, 650)] * 4, 16)])
+def test_high_rank_strip_models_keep_to_the_static_workspace(layout, rank):
+    """Models for any shape whose partial sums of P and Q+, split as finely as the chip would like, exceed the static
+    workspace: the planner splits them more coarsely, and the tables still cover everything once."""
+    model = B.Model(layout, rank, 4, 128, B.F32, 1)
+    assert model.sizes["workspace_bytes"] <= 32 << 20
+    B.conef_check_plan(model.ctx)
+    model.close()

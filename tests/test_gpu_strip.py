@@ -111,3 +111,9 @@ def test_blocks_too_small_to_divide_by_keep_their_codes_apart(env, rank, bits, b
         words = buf["codes"][o["word_off"]:o["word_off"] + R.n_words(n * m, bits)].cpu().numpy().view(np.uint32)
         assert not U.unpack(words, n * m, bits).reshape(n, m)[:, 1::2].any()
     model.close()
+
+
+def test_high_rank_matrix_with_a_coarser_split(env):
+    """A matrix whose finely split partial sums would not fit the static workspace: fewer, larger partials of P and Q+."""
+    w = wl.Workload("coarse", 13, ((16384, 700),), 32, 4, 128, wl.F32, "normal", 1.0, 0xC0A25E)
+    _run_model(env, w, [(16384, 700)], 1, "coarse-split")
