@@ -1,6 +1,6 @@
-// Generic kernel family: correct for every layout the plan accepts (any cols, any block
-// that is a multiple of 32/bits, any rank <= 32, fp32 or bf16 gradients).  One element per
-// lane and per access; the shape-specialised families replace it where their conditions hold.
+// The kernels for any block (a multiple of 32/bits): error pass and element-wise compressors, one element per lane and
+// access, used where no power-of-two number of lanes holds a block in octets.  Beside them the reductions of the partial
+// sums, decode, decompress / update, and the choice of launches of the three passes.
 //
 // All reductions run in a fixed order (no floating-point atomics), so results are
 // reproducible from run to run.
