@@ -58,17 +58,16 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-// The eight fields of an octet (8-bit codes: c0 elements 0..3, c1 elements 4..7; else all in c0) as fp32, divided by
-// code_unit<BITS>(): 4-bit fields come over 16, one instruction each.  A step size times the unit is exact, so
-// fma(step unit, field over unit, g) and (step unit) (field over unit) have the bits of fma(step, field, g) and step field.
-template <int BITS>
-__device__ __forceinline__ constexpr float code_unit() { return BITS == 4 ? 16.0f : 1.0f; }
-
+// The eight fields of an octet (8-bit codes: c0 elements 0..3, c1 elements 4..7; else all in c0) as fp32.  4-bit fields come
+// over 16 and are multiplied back, two instructions each; the factor is not moved into the step size, which would overflow
+// for scales above 1.5e38.
 template <int BITS>
 __device__ __forceinline__ void code_values(uint32_t c0, uint32_t c1, float q[8])
 {
     if constexpr (BITS == 4) {
         fields_over_16(c0, q);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) q[e] *= 16.0f;
     } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) q[e] = (float)(BITS == 8 ? code_field(e < 4 ? c0 : c1, e & 3, 8) : code_field(c0, e, BITS));

@@ -153,9 +153,9 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                 for (int e = 1; e < 8; ++e) g[e] = e < tail ? g[e] : 0.0f;
             }
         }
-        const float dstep1 = r.scale * inv_levels(BITS), dstep = dstep1 * code_unit<BITS>();
-        const float dpart = TWO ? dstep : dstep1 * dp.omb * code_unit<BITS>();
-        const float dstep2 = r2.scale * inv_levels(BITS) * code_unit<BITS>();
+        const float dstep1 = r.scale * inv_levels(BITS), dstep = dstep1;
+        const float dpart = TWO ? dstep : dstep1 * dp.omb;
+        const float dstep2 = r2.scale * inv_levels(BITS);
         float qf[8], qf2[8];
         code_values<BITS>(r.c0, r.c1, qf);
         if (TWO) code_values<BITS>(r2.c0, r2.c1, qf2);
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
         }
         if (TWO) {
             // q+ = C(x - e~+): what the first rounding left, one level finer
-            const float dnew = a * inv_levels(BITS) * code_unit<BITS>();
+            const float dnew = a * inv_levels(BITS);
             float a2 = 0.0f, qn[8];
             code_values<BITS>(w[0], w[1], qn);
 #pragma unroll

@@ -75,7 +75,7 @@ __device__ __forceinline__ RawCodes<BITS> load_codes_always(const MatDesc &d, co
 template <int BITS>
 __device__ __forceinline__ void add_codes(const RawCodes<BITS> &r, float p[8])
 {
-    const float step = r.scale * inv_levels(BITS) * code_unit<BITS>();
+    const float step = r.scale * inv_levels(BITS);
     float q[8];
     code_values<BITS>(r.c0, r.c1, q);
 #pragma unroll
@@ -99,7 +99,7 @@ __device__ __forceinline__ void decode_octet(const RawOctet<BF16, BITS> &r, floa
         g[3] = __uint_as_float(r.g0.w); g[4] = __uint_as_float(r.g1.x); g[5] = __uint_as_float(r.g1.y);
         g[6] = __uint_as_float(r.g1.z); g[7] = __uint_as_float(r.g1.w);
     }
-    const float step = r.scale * inv_levels(BITS) * omb * code_unit<BITS>();
+    const float step = r.scale * inv_levels(BITS) * omb;
     float q[8];
     code_values<BITS>(r.c0, r.c1, q);
 #pragma unroll
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void k_err_octet(DevicePlan dp, const void *__
             if ((lc & ((1 << d.lb_shift) - 1)) == 0) (TWO ? scales_first : scales)[d.scale_off + (o >> d.lb_shift)] = a;
         }
         if (TWO) {
-            const float dnew = a * inv_levels(BITS) * code_unit<BITS>();
+            const float dnew = a * inv_levels(BITS);
             float a2 = 0.0f, qn[8];
             code_values<BITS>(w[0], w[1], qn);
 #pragma unroll
@@ -388,7 +388,7 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
             }
             a = block_max(a, lb);
             const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
-            const float dnew = a * inv_levels(BITS) * code_unit<BITS>();
+            const float dnew = a * inv_levels(BITS);
             float a2 = 0.0f;
             uint32_t w[NT][2];
 #pragma unroll

@@ -117,3 +117,22 @@ def test_high_rank_matrix_with_a_coarser_split(env):
     """A matrix whose finely split partial sums would not fit the static workspace: fewer, larger partials of P and Q+."""
     w = wl.Workload("coarse", 13, ((16384, 700),), 32, 4, 128, wl.F32, "normal", 1.0, 0xC0A25E)
     _run_model(env, w, [(16384, 700)], 1, "coarse-split")
+
+
+def test_scales_near_the_largest_value_decode_finite(env):
+    """Residuals up to 3e38 with 4-bit codes: the second vector of Algorithm 3 takes what the first rounding leaves, at most
+    one level of it, and stays finite."""
+    R, B, U = env
+    import torch
+
+    layout = [(64, 147), (100, 512)]
+    model = B.Model(layout, 4, 4, 128, B.F32, 5)
+    buf = model.alloc("cuda:0")
+    buf["grads"].copy_(torch.from_numpy(np.random.default_rng(6).uniform(-3e38, 3e38, buf["grads"].numel()).astype(np.float32)))
+    B.conef_rk_configure(model.ctx, [10, 10])
+    delta = torch.zeros(B.conef_rk_sizes(model.ctx)["delta_elems"], device="cuda:0")
+    codes2, scales2 = torch.zeros_like(buf["codes"]), torch.zeros_like(buf["scales"])
+    B.conef_i_rk_step(model.ctx, buf["grads"], buf["codes"], buf["scales"], codes2, scales2, delta, 1, model.stream_handle())
+    torch.cuda.synchronize()
+    assert 0 < float(scales2.max()) <= float(buf["scales"].max()) / 7 * 1.0001
+    model.close()
