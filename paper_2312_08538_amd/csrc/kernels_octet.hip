@@ -145,8 +145,9 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
             g[6] = __uint_as_float(r.g1.z); g[7] = __uint_as_float(r.g1.w);
         }
         if (TAIL) {
-            const uint32_t lo = BITS == 8 && tail >= 4 ? ~0u : (1u << (BITS * tail)) - 1u;
-            const uint32_t hi = BITS == 8 && tail > 4 ? (1u << (BITS * (tail - 4))) - 1u : 0u;
+            // the code fields of a full octet (here because its word ends a code or sign word) all count: no shift by a word's width
+            const uint64_t fields = tail < 8 ? (1ull << (BITS * tail)) - 1ull : ~0ull;
+            const uint32_t lo = (uint32_t)fields, hi = (uint32_t)(fields >> 32);
             if (cut) {
                 r.c0 &= lo; r.c1 &= hi; r2.c0 &= lo; r2.c1 &= hi;
 #pragma unroll
