@@ -384,7 +384,7 @@ void k_cs_p_octet(DevicePlan dp, const void *__restrict__ grads, const void *__r
         float bn[8][BN];
         load_b(bn, col0 + kCsStepCols);
         load_tile(cur, col0 + kCsStepCols);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         if (col0 < c_end) {             // a ragged last step leaves the upper waves without columns
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -403,7 +403,7 @@ void k_cs_p_octet(DevicePlan dp, const void *__restrict__ grads, const void *__r
         for (int j = 0; j < 8; ++j)
 #pragma unroll
             for (int h = 0; h < BN; ++h) bq[j][h] = bn[j][h];
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
     }
     // the four waves' sums, added in wave order.  D of block (lane % 16) / 4, entry [lane / 16][lane % 4]:
     // row 16 t + 4 ((lane % 16) / 4) + lane / 16 of the tile, factor column lane % 4 + 4 h
@@ -548,7 +548,7 @@ void k_cs_q_octet(DevicePlan dp, const void *__restrict__ grads, const void *__r
 #pragma unroll
             for (int h = 0; h < BN; ++h) b[g][h] = (double)cur.ph[g][h];
         load_step(cur, i0 + kCsQStepRows);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
 #pragma unroll
@@ -561,7 +561,7 @@ void k_cs_q_octet(DevicePlan dp, const void *__restrict__ grads, const void *__r
                 }
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
     }
     // D of block (lane % 16) / 4, entry [lane / 16][lane % 4]: column 16 t + 4 ((lane % 16) / 4) + lane / 16 of the strip
     const int dcol = 4 * (mi >> 2) + mk;
@@ -806,9 +806,7 @@ __global__ __launch_bounds__(256) void k_cs_lin_update(DevicePlan dp, const uint
             const int idx = i * 64 + lane, col = idx >> 5, c = idx & 31;
             sq[(((col & 7) * 8 + (c >> 2)) * 4 + (c & 3)) * 16 + (col >> 3)] = src[idx];
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_sync();
     }
     const int64_t col0 = (int64_t)it.a * 128 + 8 * cc;
     const int b_end = it.b + it.c;

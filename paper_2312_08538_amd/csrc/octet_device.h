@@ -536,7 +536,7 @@ __device__ __forceinline__ void q_octet(const DevicePlan &dp, int block, float *
 #pragma unroll
             for (int h = 0; h < RH; ++h) b[g][h] = cur.ph[g][h];
         load_step(cur, i0 + kQStepRows);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
 #pragma unroll
@@ -547,7 +547,7 @@ __device__ __forceinline__ void q_octet(const DevicePlan &dp, int block, float *
                     acc[t][h] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, (double)b[g][h], acc[t][h], 0, 0, 0);
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
     }
     // D of block (lane % 16) / 4, entry [lane / 16][lane % 4]: column 16 t + 4 ((lane % 16) / 4) + lane / 16 of the strip
     const int dcol = 4 * (mi >> 2) + mk;
@@ -765,7 +765,7 @@ __device__ __forceinline__ void p_octet(const DevicePlan &dp, int block, float *
         // issue the loads of this wave's next sub-tile
         load_b(bn, col0 + kStepCols);
         load_grads(cur, col0 + kStepCols);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         if (col0 < c_end) {             // a ragged last step leaves the upper waves without columns
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -778,7 +778,7 @@ __device__ __forceinline__ void p_octet(const DevicePlan &dp, int block, float *
                 }
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
 #pragma unroll
         for (int j = 0; j < 8; ++j)
 #pragma unroll

@@ -220,7 +220,7 @@ __device__ __forceinline__ void p_strip(const DevicePlan &dp, int block, float *
                 T[(16 * half + u) * kPPitch + lane] = lane < ncol ? p : 0.0f;
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             if (4 * j < ncol) {                                 // uniform
@@ -235,7 +235,7 @@ __device__ __forceinline__ void p_strip(const DevicePlan &dp, int block, float *
                 }
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
     }
     __syncthreads();
     double *red = reinterpret_cast<double *>(lds);      // [wave][row][factor column]
