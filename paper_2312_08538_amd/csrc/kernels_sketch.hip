@@ -312,7 +312,7 @@ void k_cs_p_octet(DevicePlan dp, const void *__restrict__ grads, const void *__r
     const int r = dp.rank;
     const int64_t row0 = it.a;
     const int c_begin = it.b * d.p_chunk_cols;
-    const int c_end = (c_begin + d.p_chunk_cols < d.m) ? c_begin + d.p_chunk_cols : (int)d.m;
+    const int c_end = chunk_end(d.m, d.p_chunk_cols, c_begin);
     const int lrow = lane >> 2, loct = lane & 3;      // load layout: 4 lanes per row, 16 rows per load
     const int mi = lane & 15, mk = lane >> 4;         // matrix-core roles
     const int mc = lane & 3;                          // factor column of this lane's B and D entries (+ 4 h)

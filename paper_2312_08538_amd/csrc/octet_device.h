@@ -619,7 +619,7 @@ __device__ __forceinline__ void p_octet(const DevicePlan &dp, int block, float *
     const int r = dp.rank;
     const int64_t row0 = it.a;
     const int c_begin = it.b * d.p_chunk_cols;
-    const int c_end = (c_begin + d.p_chunk_cols < d.m) ? c_begin + d.p_chunk_cols : (int)d.m;
+    const int c_end = chunk_end(d.m, d.p_chunk_cols, c_begin);
     const int lrow = lane >> 2, loct = lane & 3;      // load layout: 4 lanes per row, 16 rows per load
     const int mi = lane & 15, mk = lane >> 4;         // matrix-core roles
     const int lb = d.lb_shift + 3;                    // log2(block)

@@ -427,11 +427,11 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
             d.scale_off = s; s += round_up(d.nblk, kAlign);
             d.p_off = p;     p += round_up(d.n * rank, kAlign);
             d.q_off = q;     q += round_up(d.m * rank, kAlign);
-            d.path = (!sketch && block_ok && (rank == 2 || rank == 4 || rank == 8) && d.m % 64 == 0 && d.m % block == 0) ? kPathOctet
+            d.path = (!sketch && block_ok && (rank == 2 || rank == 4 || rank == 8) && d.m % 64 == 0 && d.m % block == 0 && d.m <= kOctetMaxCols) ? kPathOctet
                                                                                              : kPathGeneric;
             // count-sketch mode: the octet path needs whole octets per row only (16-byte aligned rows of
             // the gradient and of the table), at any rank
-            const bool sketch_octet = sketch && !all_generic && d.m % 8 == 0;
+            const bool sketch_octet = sketch && !all_generic && d.m % 8 == 0 && d.m <= kOctetMaxCols;
             d.m8 = (int32_t)(d.m / 8);
             d.lb_shift = block_ok ? log2i(block / 8) : 0;
             d.cs_lin = (sketch && cs_lin_ok && rank == 32 && dtype == 1 && d.m % 128 == 0 && d.m <= (1 << 24)) ? 1 : 0;
@@ -494,7 +494,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 const bool strip = d.path == kPathGeneric;
                 if ((d.path == kPathOctet && !d.cs_lin && !d.pack) || strip) {
                     // strip kernels: chunks of one size, a multiple of a strip
-                    d.p_chunk_cols = strip ? (int32_t)round_up(ceil_div(d.m, ceil_div(d.m, chunk_cols)), 64) : p_cols;
+                    d.p_chunk_cols = strip ? (int32_t)std::min<int64_t>(round_up(ceil_div(d.m, ceil_div(d.m, chunk_cols)), 64), INT32_MAX / 64 * 64) : p_cols;
                     d.n_p_chunks = (int32_t)ceil_div(d.m, d.p_chunk_cols);
                     if (d.n_p_chunks > 1) {
                         d.ppart_off = wd; wd += round_up((int64_t)d.n_p_chunks * d.n * rank, 32);
@@ -812,6 +812,11 @@ bool check_plan(const Plan &plan)
     // pass 1: P = p Q
     {
         Cover c(nm);
+        // the kernels' own end of a chunk, on the last chunk of every row
+        for (const MatDesc &d : plan.mats) {
+            const int64_t c_begin = (int64_t)(d.n_p_chunks - 1) * d.p_chunk_cols;
+            if (d.n_p_chunks < 1 || c_begin < 0 || c_begin >= d.m || chunk_end(d.m, d.p_chunk_cols, (int)c_begin) != d.m) return false;
+        }
         for (const WorkItem &it : plan.p_items)
             c.add(plan, it, it.a, it.c <= kStripRows && it.c * plan.mats[it.mat].m < 2 * kStripSpan * 2 ? it.c : 0,
                   (int64_t)it.b * plan.mats[it.mat].p_chunk_cols, plan.mats[it.mat].p_chunk_cols);

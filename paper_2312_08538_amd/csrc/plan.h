@@ -22,6 +22,10 @@ constexpr int kUpdRows = 64;        // tile of the decompress / update kernel
 constexpr int kUpdCols = 128;
 // ranks for which that kernel is the one on the fp32 matrix cores (elsewhere the vector ALU keeps up with the memory)
 constexpr bool update_on_cores(int rank) { return rank > 8 && (rank & 3) == 0; }
+// End of the chunk of columns that starts at c_begin (the last chunk may be short, and c_begin + chunk beyond 2^31).
+constexpr int chunk_end(int64_t m, int chunk, int c_begin) { return m - c_begin > chunk ? c_begin + chunk : (int)m; }
+// Widest matrix of the octet kernels, whose column indices run ahead of a row's end in 32 bits; the strip kernels take wider ones.
+constexpr int64_t kOctetMaxCols = ((int64_t)1 << 31) - 4096;
 constexpr int kErrRows = 128;       // rows per workgroup item of the MFMA err pass (8 waves x 16)
 constexpr int kErrRun = 16;         // column blocks of 128 per item of the MFMA err pass (at most 16)
 constexpr int kCsCols = 256;        // columns per workgroup item of the count-sketch update pass

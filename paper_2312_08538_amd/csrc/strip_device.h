@@ -160,7 +160,7 @@ __device__ __forceinline__ void p_strip(const DevicePlan &dp, int block, float *
     const int r = dp.rank;
     const int64_t row0 = it.a;
     const int c_begin = it.b * d.p_chunk_cols;
-    const int c_end = (c_begin + d.p_chunk_cols < d.m) ? c_begin + d.p_chunk_cols : (int)d.m;
+    const int c_end = chunk_end(d.m, d.p_chunk_cols, c_begin);
     const int mi = lane & 15, mk = lane >> 4, mc = lane & 3;
     double acc[2][WIDE ? 1 : RH];
     f64x4 accw[2][WIDE ? BN : 1];

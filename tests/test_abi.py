@@ -256,6 +256,16 @@ def test_sketch_plans_of_the_full_workloads_are_consistent():
             m.close()
 
 
+@pytest.mark.parametrize("layout,rank", [([(1, 2 ** 31 - 1)], 1), ([(2, 2 ** 31 - 64)], 2)])
+def test_plans_of_the_widest_matrices_are_consistent(layout, rank):
+    """The last column chunk of the P pass ends at the last column although its start plus a chunk is beyond 2^31 (the
+    plan's self-check takes the end from the function that the kernels call)."""
+    ctx = B.conef_init(layout, rank, 4, 128, B.F32, 0)
+    B.conef_check_plan(ctx)
+    assert B.conef_matrix_family(ctx, 0) == B.FAMILY_GENERIC
+    B.conef_destroy(ctx)
+
+
 def test_set_beta_validates_its_argument():
     ctx = B.conef_init([(64, 64)], 4, 4, 64, B.F32, 0)
     L = B.lib()
