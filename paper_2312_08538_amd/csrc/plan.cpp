@@ -503,16 +503,36 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 }
             }
         };
+        // Stream kernels of the element-wise gradient compressors for the quantiser: the wave-per-run kernel needs blocks of
+        // 8 * 2^j elements (j <= 6).  A wave takes eight runs of 512 elements, fewer where that would leave the chip with fewer
+        // than eight waves per SIMD (a wave's items are one serial chain of loads), and leaves one partial sum; elsewhere a
+        // wave takes 16 blocks, or one of a small matrix.
+        const bool stream_ok = block % 8 == 0 && is_pow2(block / 8) && block / 8 <= 64;
+        const int64_t stream_runs_rule = std::min<int64_t>(8, std::max<int64_t>(1, total_elems / (512 * 8192)));
+        int64_t stream_runs = stream_runs_rule;
+        auto blocks_per_wave = [](const MatDesc &d) { return d.nblk <= 16384 ? 1 : 16; };
+        auto stream_slots = [&](const MatDesc &d) {
+            return stream_ok ? ceil_div(ceil_div(d.N, 512), stream_runs) : 4 * ceil_div(d.nblk, 4 * blocks_per_wave(d));
+        };
         lay_out(strip_chunk, strip_q_rows);
         // Partial sums of small and middle-sized models at high ranks can take the workspace beyond the static one of
-        // conef_step_static (98304 wave-rows x 32 entries: 25 MB).  They are split more coarsely until it fits (with 1 MB left for
-        // what follows); whole rows of P and 512 rows per partial of Q+ are the least.  Where that does not fit either, nothing
-        // is gained by a coarser split.
-        const int64_t fits = ((int64_t)CONEF_STATIC_WORKSPACE_BYTES - (1 << 20)) / 8;
-        if (!sketch && strip_elems > 0 && wd > fits) {
-            for (int64_t k = 2; k <= 16 && wd > fits; k *= 2) lay_out(strip_chunk * k, std::min<int64_t>(512, strip_q_rows * k));
-            if (wd > fits) lay_out(INT32_MAX, 512);
-            if (wd > (int64_t)CONEF_STATIC_WORKSPACE_BYTES / 8) lay_out(strip_chunk, strip_q_rows);
+        // conef_step_static (98304 wave-rows x 32 entries: 25 MB).  They are split more coarsely until it fits: whole rows of P
+        // and 512 rows per partial of Q+ are the least, then longer items of the stream kernels.  Where that does not fit
+        // either, nothing is gained by a coarser split.
+        auto fits = [&]() {
+            int64_t all = wd;
+            for (const MatDesc &d : plan.mats) all += stream_slots(d);
+            return all <= (int64_t)CONEF_STATIC_WORKSPACE_BYTES / 8;
+        };
+        if (!sketch && !fits()) {
+            for (int64_t k = 2; k <= 16 && strip_elems > 0 && !fits(); k *= 2)
+                lay_out(strip_chunk * k, std::min<int64_t>(512, strip_q_rows * k));
+            if (strip_elems > 0 && !fits()) lay_out(INT32_MAX, 512);
+            while (stream_ok && stream_runs < 64 && !fits()) stream_runs *= 2;
+            if (!fits()) {
+                stream_runs = stream_runs_rule;
+                lay_out(strip_chunk, strip_q_rows);
+            }
         }
         // The strip err pass: runs of the flat index of strip_err elements where that is at least eight rows (a wave's row of
         // Q+ per lane serves all rows of a run), else eight rows of a column segment.
@@ -533,29 +553,25 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 plan.es_lds = std::max(plan.es_lds, 8 * d.es_pitch + 8);
             }
         }
-        // Stream tables of the element-wise gradient compressors (random block, scaled sign) for the quantiser:
-        // the wave-per-run kernel needs blocks of 8 * 2^j elements (j <= 6).  A wave takes eight runs of 512 elements, fewer where
-        // that would leave the chip with fewer than eight waves per SIMD (a wave's items are one serial chain of loads).
+        // Stream tables of the element-wise gradient compressors
         int64_t sw = 0;
-        const bool stream_ok = block % 8 == 0 && is_pow2(block / 8) && block / 8 <= 64;
         for (int l = 0; l < n_mats; ++l) {
             MatDesc &d = plan.mats[l];
             d.sign_off = sw; sw += round_up(ceil_div(d.N, 32), kAlign);
             if (sketch) continue;                   // the count-sketch mode walks its bucket lists
             if (stream_ok) {
                 d.lb_shift = log2i(block / 8);
-                const int64_t runs = ceil_div(d.N, 512), per_item = std::min<int64_t>(8, std::max<int64_t>(1, total_elems / (512 * 8192)));
+                const int64_t runs = ceil_div(d.N, 512);
                 d.st_first = (int32_t)plan.rb_items.size();
-                for (int64_t r0 = 0; r0 < runs; r0 += per_item)
-                    plan.rb_items.push_back({l, (int32_t)r0, (int32_t)std::min<int64_t>(per_item, runs - r0), 0});
-                d.st_slots = (int32_t)plan.rb_items.size() - d.st_first;      // one wave per item
+                for (int64_t r0 = 0; r0 < runs; r0 += stream_runs)
+                    plan.rb_items.push_back({l, (int32_t)r0, (int32_t)std::min<int64_t>(stream_runs, runs - r0), 0});
             } else {
-                const int32_t per_wave = d.nblk <= 16384 ? 1 : 16;
+                const int32_t per_wave = blocks_per_wave(d);
                 d.st_first = (int32_t)plan.rb_g_items.size();
                 for (int64_t b0 = 0; b0 < d.nblk; b0 += 4 * per_wave) plan.rb_g_items.push_back({l, (int32_t)b0, per_wave, 0});
-                d.st_slots = 4 * ((int32_t)plan.rb_g_items.size() - d.st_first);   // four waves per item
                 d.st_atomic = 1;
             }
+            d.st_slots = (int32_t)stream_slots(d);       // one per wave (four waves per item of the second kind)
             d.st_part_off = wd; wd += d.st_slots;
         }
         plan.sign_words = (size_t)sw;

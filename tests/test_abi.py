@@ -524,3 +524,14 @@ def test_high_rank_strip_models_keep_to_the_static_workspace(layout, rank):
     assert model.sizes["workspace_bytes"] <= 32 << 20
     B.conef_check_plan(model.ctx)
     model.close()
+
+
+@pytest.mark.parametrize("layout,rank,bits,block", [
+    ([(593, 70), (2369, 26002)], 32, 8, 64), ([(403, 355), (10087, 162), (5939, 437), (59, 7138), (69, 26011), (660, 6651), (716, 23053), (8641, 1573)], 32, 2, 512)])
+def test_the_static_workspace_counts_the_stream_kernels_partial_sums(layout, rank, bits, block):
+    """The coarse split alone fits here by less than the scaled sign's partial sums, one per wave of its kernels: these
+    are part of what has to fit."""
+    ctx = B.conef_init(layout, rank, bits, block, B.F32, 0)
+    assert B.conef_sizes(ctx)["workspace_bytes"] <= B.STATIC_WORKSPACE_BYTES
+    B.conef_check_plan(ctx)
+    B.conef_destroy(ctx)
