@@ -37,7 +37,7 @@ struct DevicePlan {
     int n_p = 0, n_q = 0, n_err = 0, n_p_f = 0, n_q_f = 0, n_err_f = 0, n_err_t = 0;
     int n_p_m = 0, n_q_m = 0, n_err_m = 0, n_split_p = 0, n_split_qn = 0;
     int n_p_k = 0, n_q_k = 0;
-    int n_upd = 0;
+    int n_upd = 0, upd_many = 0;    // upd_many: its items may be of several row tiles
     int n_pred = 0, n_gram = 0, n_apply = 0, n_qred = 0, n_elem = 0;
     int rank = 0, rpad = 0, bits = 0, block = 0, dtype = 0;
     int n_err_s = 0, es_lds = 0;    // strip err pass: items, floats of LDS per workgroup

@@ -771,17 +771,21 @@ __global__ __launch_bounds__(256) void k_update(DevicePlan dp, const float *__re
 // of the sequential fp32 fma chain (checked against the chain on random operands: no difference in
 // any entry, where an unfused or a wider accumulation differs in about half of them).
 //   operand layout: lane l holds A[l%16][l/16], B[l/16][l%16] and D[4(l/16) + v][l%16], v = 0..3.
-// One workgroup per strip of 128 columns and a range of rows, walked 64 rows at a time, wave w rows 16w..16w+15 of them.
 // Tile t (0..7) of the matrix cores takes column 8 cc + t of every octet cc = l % 16, so after eight tiles lane
 // (cc, kg = l / 16) holds rows 4 kg + v, columns 8 cc .. 8 cc + 7: two 16-byte accesses per row.  The strip's rows of Q+
-// go through LDS once ([cc][kg][t][q], c = 4 q + kg) into registers, and the next 64 rows' parameters and rows of P^ are
-// on their way while the current ones are worked on.  Bound by memory: parameters in and out.
-// Measured, 1.31 G parameters at rank 32: 2143 us, 4.9 TB/s, what a large copy reaches; 2592 us with a workgroup per
-// 64 x 128 tile, which staged a 16 KB piece of Q+ per 64 KB of parameters and fetched the parameters only at the end.
+// go through LDS ([cc][kg][t][q], c = 4 q + kg).  Bound by memory: parameters in and out.
+//   MANY      one workgroup per strip of 128 columns and up to 512 rows, walked 64 at a time, wave w rows 16w..16w+15 of
+//             them: Q+ stays in registers, and the next 64 rows' parameters and rows of P^ are on their way while the
+//             current ones are worked on.
+//   otherwise one workgroup per 64 x 128 tile, its parameters fetched first, Q+ read from LDS tile by tile: half the
+//             registers, so twice the waves that hide one another's latency where a workgroup has no next rows.
+// Measured, 1.31 G parameters at rank 32: 2145 us, 4.9 TB/s of read and write (2.6 ms with a tile per workgroup and the
+// parameters fetched last).  8000 x 8100 at rank 32: 104 us (182 us where MANY took single tiles).  The planner's rule
+// (upd_many) and the figures on either side of it: plan.cpp.
 typedef float upd_f32x4 __attribute__((ext_vector_type(4)));
 
 // NQ: a quarter of the rank
-template <bool SUBTRACT, int NQ>
+template <bool SUBTRACT, int NQ, bool MANY>
 __global__ __launch_bounds__(256, 2) void k_update_mfma(DevicePlan dp, const float *__restrict__ Phat,
                                                         const float *__restrict__ Qn, float *x)
 {
@@ -829,22 +833,26 @@ __global__ __launch_bounds__(256, 2) void k_update_mfma(DevicePlan dp, const flo
         }
     }
     __syncthreads();
-    float b[8][NQ];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
+    auto load_b = [&](int t, float (&b)[NQ]) {
         const float *src = sbq + (cc * 4 + kg) * kLanePitch + t * 8;
         const float4 b0 = *reinterpret_cast<const float4 *>(src), b1 = *reinterpret_cast<const float4 *>(src + 4);
         const float bv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) b[t][q] = bv[q];
+        for (int q = 0; q < NQ; ++q) b[q] = bv[q];
+    };
+    float b[MANY ? 8 : 1][NQ];
+    if (MANY) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) load_b(t, b[MANY ? t : 0]);
     }
     auto process = [&](const Trip &tr, int r0) {
         upd_f32x4 acc[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
+            if (!MANY) load_b(t, b[0]);
             acc[t] = upd_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(tr.a[q], b[t][q], acc[t], 0, 0, 0);
+            for (int q = 0; q < NQ; ++q) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(tr.a[q], b[MANY ? t : 0][q], acc[t], 0, 0, 0);
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -870,6 +878,10 @@ __global__ __launch_bounds__(256, 2) void k_update_mfma(DevicePlan dp, const flo
             }
         }
     };
+    if (!MANY) {
+        process(ta, 16 * wave);
+        return;
+    }
     // two register sets take turns
     for (int r0 = 16 * wave; r0 < rows; r0 += 128) {
         load_trip(tb, r0 + 64);
@@ -889,8 +901,13 @@ hipError_t launch_update(const DevicePlan &dp, const float *Phat, const float *Q
         if (update_on_cores(dp.rank)) {
             auto go = [&](auto nq) {
                 constexpr int NQ = decltype(nq)::value;
-                if (subtract) hipLaunchKernelGGL((k_update_mfma<true, NQ>), dim3(dp.n_upd), dim3(256), 0, st, dp, Phat, Qn, x);
-                else hipLaunchKernelGGL((k_update_mfma<false, NQ>), dim3(dp.n_upd), dim3(256), 0, st, dp, Phat, Qn, x);
+                auto launch = [&](auto many) {
+                    constexpr bool MANY = decltype(many)::value;
+                    if (subtract) hipLaunchKernelGGL((k_update_mfma<true, NQ, MANY>), dim3(dp.n_upd), dim3(256), 0, st, dp, Phat, Qn, x);
+                    else hipLaunchKernelGGL((k_update_mfma<false, NQ, MANY>), dim3(dp.n_upd), dim3(256), 0, st, dp, Phat, Qn, x);
+                };
+                if (dp.upd_many) launch(std::true_type{});
+                else launch(std::false_type{});
             };
             switch (dp.rank >> 2) {
             case 3: go(std::integral_constant<int, 3>{}); break;

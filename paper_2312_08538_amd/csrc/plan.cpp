@@ -464,11 +464,6 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         const int64_t strip_chunk = std::min<int64_t>(2048, std::max<int64_t>(256, round_up(strip_elems / (kStripRows * 1536), 256)));
         const int64_t strip_q_rows = std::min<int64_t>(512, std::max<int64_t>(32, round_up(strip_elems / (64 * 1536), 32)));
         const int64_t strip_err = strip_elems / 8192 >= 1024 ? 8192 : strip_elems / 4096 >= 768 ? 4096 : 2048;
-        // decompress / update: row tiles per item.  On the matrix cores a workgroup keeps its strip of Q+ for several of
-        // them, as many as leave about 4096 workgroups
-        int64_t upd_tiles = 0;
-        for (int l = 0; l < n_mats; ++l) upd_tiles += ceil_div(plan.mats[l].n, kUpdRows) * ceil_div(plan.mats[l].m, kUpdCols);
-        upd_tiles = update_on_cores(rank) ? std::min<int64_t>(8, std::max<int64_t>(1, upd_tiles / 4096)) : 1;
         auto lay_out = [&](int64_t chunk_cols, int64_t tile_rows) {
             wd = 0;
             plan.any_p_chunks = false;
@@ -675,10 +670,29 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                     plan.qred_items.push_back({l, (int32_t)e0, 0, per == 16 ? 1 : 0});
             }
             for (int64_t e0 = 0; e0 < d.N; e0 += 1024) plan.elem_items.push_back({l, (int32_t)(e0 >> 10), 0, 0});
-            for (int64_t r0 = 0; r0 < d.n; r0 += upd_tiles * kUpdRows)
+        }
+        // Decompress / update: row tiles per workgroup.  On the matrix cores a workgroup keeps its strip of Q+ for several of
+        // them (a matrix's tiles in equal shares), where that leaves enough workgroups.  Measured, rank 32, a tile / 4 / 8 tiles
+        // per workgroup: 4096 x 8192 (4096 tiles) 64 / 54 / 52 us, 4096 x 4096 35 / 32 / 28, 15.7 M elements in ten matrices
+        // (1920 tiles) 34 / 32 / 51, 2048 x 2048 (512 tiles) 11.6 / 14.7 / 21.  Rows that do not start on 16-byte boundaries
+        // cannot be fetched ahead: a tile per workgroup (33278 x 650, rank 16: 103 us, four tiles 129), and models with more
+        // than an eighth of such tiles stay with the kernel for one tile, whose waves are twice as many.
+        int64_t upd_total = 0, upd_odd = 0;
+        for (const MatDesc &d : plan.mats) {
+            const int64_t tiles = ceil_div(d.n, kUpdRows) * ceil_div(d.m, kUpdCols);
+            upd_total += tiles;
+            if (d.m % 4 != 0) upd_odd += tiles;
+        }
+        plan.upd_many = update_on_cores(rank) && upd_total >= 1024 && 8 * upd_odd <= upd_total ? 1 : 0;
+        // (up to rank 16 the strip of Q+ is paid for by four tiles, and shorter items end more evenly: 124 M elements 216 us, eight
+        // tiles 232; rank 32: 257 and 249)
+        const int64_t upd_most = plan.upd_many ? std::min<int64_t>(rank <= 16 ? 4 : 8, std::max<int64_t>(4, upd_total / 512)) : 1;
+        for (int l = 0; l < n_mats; ++l) {
+            const MatDesc &d = plan.mats[l];
+            const int64_t tiles = ceil_div(d.n, kUpdRows), per = d.m % 4 == 0 ? ceil_div(tiles, ceil_div(tiles, upd_most)) : 1;
+            for (int64_t t = 0; t < tiles; t += per)
                 for (int64_t c0 = 0; c0 < d.m; c0 += kUpdCols)
-                    plan.upd_items.push_back({l, (int32_t)(r0 / kUpdRows), (int32_t)(c0 / kUpdCols),
-                                              (int32_t)std::min<int64_t>(upd_tiles, ceil_div(d.n - r0, kUpdRows))});
+                    plan.upd_items.push_back({l, (int32_t)t, (int32_t)(c0 / kUpdCols), (int32_t)std::min<int64_t>(per, tiles - t)});
         }
         // The P pass of the matrix-core family: workgroups are dealt to the eight XCDs in turn (workgroup b runs on
         // XCD b % 8), and a pass streams faster when every XCD stays inside an address range of its own (measured
@@ -950,8 +964,10 @@ bool check_plan(const Plan &plan)
     // decompression / update
     {
         Cover c(nm);
-        for (const WorkItem &it : plan.upd_items)
+        for (const WorkItem &it : plan.upd_items) {
+            if (it.c < 1 || it.c > (plan.upd_many ? 8 : 1)) return false;
             c.add(plan, it, (int64_t)it.a * kUpdRows, (int64_t)it.c * kUpdRows, (int64_t)it.b * kUpdCols, kUpdCols);
+        }
         if (!c.complete(plan)) return false;
     }
     // per-matrix helpers, and the workspace map

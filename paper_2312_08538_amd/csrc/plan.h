@@ -149,7 +149,8 @@ struct Plan {
     std::vector<WorkItem> apply_items;  // (mat, first row)                    64 rows per workgroup
     std::vector<WorkItem> qred_items;   // reduce partial Q+: (mat, first entry of m*r)
     std::vector<WorkItem> elem_items;   // element-wise helpers: (mat, first element / 1024)
-    std::vector<WorkItem> upd_items;    // decompress / update: (mat, row tile of 64, column tile of 128)
+    std::vector<WorkItem> upd_items;    // decompress / update: (mat, row tile of 64, column tile of 128, row tiles)
+    int upd_many = 0;                   // 1: the kernel that walks several row tiles takes them (else all are of one tile)
     // element-wise gradient compressors with the quantiser: stream tables (made with the plan)
     size_t sign_words = 0;
     size_t rb_delta_elems = 0;      // set by configure_random_block

@@ -62,6 +62,42 @@ def test_update_over_several_row_tiles_per_workgroup(env, rank, tiles):
     model.close()
 
 
+@pytest.mark.parametrize("rank,layout", [
+    (12, [(2100, 4100), (64, 147), (70, 131)]),        # 1089 tiles of rows on 16-byte boundaries: four row tiles per workgroup, two matrices one
+    (32, [(4165, 4096), (300, 4100)]),                 # 2277 tiles: four at rank 32; a matrix of five row tiles in shares of three and two
+    (20, [(8256, 4100)]),                              # 4290 tiles: eight, 130 row tiles in 17 shares
+    (16, [(1000, 1500), (129, 650)]),                  # few tiles: one per workgroup
+    (24, [(2100, 4099), (65, 128)])])                  # nearly all rows off 16-byte boundaries: a tile per workgroup
+def test_update_and_decompression_on_either_side_of_the_row_tile_rule(env, rank, layout):
+    """Whole matrices, bit for bit: one row tile per workgroup (few tiles, or rows that do not start on 16-byte boundaries)
+    and several, the last share ragged in tiles and rows."""
+    R, B, U = env
+    import torch
+
+    print(f"[update rank {rank}] {layout}: launching", flush=True)
+    model = B.Model(layout, rank, 4, 128, B.F32, 7)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(rank)
+    P = torch.randn(model.sizes["p_elems"], device="cuda:0", generator=gen)
+    Q = torch.randn(model.sizes["q_elems"], device="cuda:0", generator=gen)
+    x = torch.randn(model.sizes["grad_elems"], device="cuda:0", generator=gen)
+    x0, delta = x.clone(), torch.full_like(x, 7.0)
+    B.conef_apply_update(model.ctx, P, Q, x, model.stream_handle())
+    B.conef_decompress(model.ctx, P, Q, delta, model.stream_handle())
+    torch.cuda.synchronize()
+    inside = torch.zeros_like(x, dtype=torch.bool)
+    for (n, m), o in zip(layout, model.offsets):
+        s = slice(o["grad_off"], o["grad_off"] + n * m)
+        inside[s] = True
+        p = P[o["p_off"]:o["p_off"] + n * rank].view(n, rank).cpu().numpy()
+        q = Q[o["q_off"]:o["q_off"] + m * rank].view(m, rank).cpu().numpy()
+        want = R.apply_update(x0[s].view(n, m).cpu().numpy(), p, q)
+        assert np.array_equal(x[s].view(n, m).cpu().numpy().view(np.uint32), want.view(np.uint32)), f"{n} x {m}: update"
+        assert np.array_equal(delta[s].view(n, m).cpu().numpy().view(np.uint32), R.decompress(p, q).view(np.uint32)), f"{n} x {m}: delta"
+    assert torch.equal(x[~inside], x0[~inside]) and bool((delta[~inside] == 7.0).all())
+    model.close()
+
+
 def test_an_infinite_factor_entry_stays_in_its_products(env):
     """P pass with an infinity in the last row of Q, columns that do not fill the last operand of four: p Q is infinite
     there with the sign of the product, not NaN from the operand's empty places."""
