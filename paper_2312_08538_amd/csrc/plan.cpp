@@ -488,8 +488,10 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 d.p_chunk_cols = (int32_t)d.m;
                 const bool strip = d.path == kPathGeneric;
                 if ((d.path == kPathOctet && !d.cs_lin && !d.pack) || strip) {
-                    // strip kernels: chunks of one size, a multiple of a strip
-                    d.p_chunk_cols = strip ? (int32_t)std::min<int64_t>(round_up(ceil_div(d.m, ceil_div(d.m, chunk_cols)), 64), INT32_MAX / 64 * 64) : p_cols;
+                    // strip kernels: chunks of one size, a multiple of a strip.  Up to 512 columns stay together: a wave has
+                    // two strips then, and the launch that adds the chunks costs more (600 x 300 at rank 4: 9.3 us in two
+                    // chunks, 7.8 in one)
+                    d.p_chunk_cols = strip ? (int32_t)std::min<int64_t>(round_up(ceil_div(d.m, d.m <= 512 ? 1 : ceil_div(d.m, chunk_cols)), 64), INT32_MAX / 64 * 64) : p_cols;
                     d.n_p_chunks = (int32_t)ceil_div(d.m, d.p_chunk_cols);
                     if (d.n_p_chunks > 1) {
                         d.ppart_off = wd; wd += round_up((int64_t)d.n_p_chunks * d.n * rank, 32);
