@@ -579,6 +579,7 @@ hipError_t launch_pass_q(const DevicePlan &dp, const void *grads, const uint32_t
         octet_pass_q(dp, grads, codes, scales, Phat, ws, st);
         strip_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
     }
+    strip_pass_q_flat(dp, grads, codes, scales, Phat, Qout, st);
     if (span.end) (void)hipEventRecord(span.end, st);
     // the reduction also writes the matrix-core family's operand splits of Q+
     generic_q_reduce(dp, ws, Qout, st);

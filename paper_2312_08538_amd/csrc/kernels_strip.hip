@@ -42,6 +42,12 @@ __global__ __launch_bounds__(256) void k_q_strip(DevicePlan dp, Source src, cons
     q_strip<SRC, R, EXACT>(dp, blockIdx.x, red, src, Phat, ws, Qout);
 }
 
+template <int SRC, int R, bool EXACT>
+__global__ __launch_bounds__(256) void k_q_flat(DevicePlan dp, Source src, const float *__restrict__ Phat, float *Qout)
+{
+    q_flat<SRC, R, EXACT>(dp, blockIdx.x, src, Phat, Qout);
+}
+
 template <int R, bool EXACT, bool TWO>
 __global__ __launch_bounds__(256) void k_err_strip(DevicePlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
                                                    uint32_t *codes2, float *scales2, const float *__restrict__ Phat,
@@ -63,25 +69,45 @@ void pass_p(const DevicePlan &dp, const Source &src, const float *Q, float *P, d
     }
 }
 
+// go(rank or the next of 4, 8, 16, 32 as a constant, is it the rank itself)
+template <typename F>
+void by_rank(int rank, F &&go)
+{
+    switch (rank) {
+    case 1: go(std::integral_constant<int, 1>{}, std::true_type{}); break;
+    case 2: go(std::integral_constant<int, 2>{}, std::true_type{}); break;
+    case 4: go(std::integral_constant<int, 4>{}, std::true_type{}); break;
+    case 8: go(std::integral_constant<int, 8>{}, std::true_type{}); break;
+    case 16: go(std::integral_constant<int, 16>{}, std::true_type{}); break;
+    case 32: go(std::integral_constant<int, 32>{}, std::true_type{}); break;
+    default:
+        if (rank < 4) go(std::integral_constant<int, 4>{}, std::false_type{});
+        else if (rank < 8) go(std::integral_constant<int, 8>{}, std::false_type{});
+        else if (rank < 16) go(std::integral_constant<int, 16>{}, std::false_type{});
+        else go(std::integral_constant<int, 32>{}, std::false_type{});
+    }
+}
+
 template <int SRC>
 void pass_q(const DevicePlan &dp, const Source &src, const float *Phat, double *ws, float *Qout, hipStream_t st)
 {
-    const dim3 grid(dp.n_q), block(256);
-#define CONEF_STRIP_Q(R, EXACT) hipLaunchKernelGGL((k_q_strip<SRC, R, EXACT>), grid, block, 0, st, dp, src, Phat, ws, Qout)
-    switch (dp.rank) {
-    case 1: CONEF_STRIP_Q(1, true); break;
-    case 2: CONEF_STRIP_Q(2, true); break;
-    case 4: CONEF_STRIP_Q(4, true); break;
-    case 8: CONEF_STRIP_Q(8, true); break;
-    case 16: CONEF_STRIP_Q(16, true); break;
-    case 32: CONEF_STRIP_Q(32, true); break;
-    default:
-        if (dp.rank < 4) CONEF_STRIP_Q(4, false);
-        else if (dp.rank < 8) CONEF_STRIP_Q(8, false);
-        else if (dp.rank < 16) CONEF_STRIP_Q(16, false);
-        else CONEF_STRIP_Q(32, false);
-    }
-#undef CONEF_STRIP_Q
+    if (dp.n_q > 0)
+        by_rank(dp.rank, [&](auto rank, auto exact) {
+            hipLaunchKernelGGL((k_q_strip<SRC, decltype(rank)::value, decltype(exact)::value>), dim3(dp.n_q), dim3(256), 0, st, dp, src,
+                               Phat, ws, Qout);
+        });
+}
+
+// the matrices of up to kFlatRows rows (ranks up to 8: a matrix has at least as many rows)
+template <int SRC>
+void pass_q_flat(const DevicePlan &dp, const Source &src, const float *Phat, float *Qout, hipStream_t st)
+{
+    if (dp.n_q_flat > 0)
+        by_rank(dp.rank, [&](auto rank, auto exact) {
+            constexpr int R = decltype(rank)::value;
+            if constexpr (R <= kFlatRows)
+                hipLaunchKernelGGL((k_q_flat<SRC, R, decltype(exact)::value>), dim3(dp.n_q_flat), dim3(256), 0, st, dp, src, Phat, Qout);
+        });
 }
 
 template <bool TWO>
@@ -90,23 +116,10 @@ void pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *s
 {
     if (dp.n_err_s <= 0) return;
     const uint32_t lo = (uint32_t)step, hi = (uint32_t)(step >> 32);
-#define CONEF_STRIP_ERR(R, EXACT)                                                                                                    \
-    hipLaunchKernelGGL((k_err_strip<R, EXACT, TWO>), dim3(dp.n_err_s), dim3(256), (size_t)dp.es_lds * 4, st, dp, grads, codes, scales, \
-                       codes2, scales2, Phat, Qn, lo, hi)
-    switch (dp.rank) {
-    case 1: CONEF_STRIP_ERR(1, true); break;
-    case 2: CONEF_STRIP_ERR(2, true); break;
-    case 4: CONEF_STRIP_ERR(4, true); break;
-    case 8: CONEF_STRIP_ERR(8, true); break;
-    case 16: CONEF_STRIP_ERR(16, true); break;
-    case 32: CONEF_STRIP_ERR(32, true); break;
-    default:
-        if (dp.rank < 4) CONEF_STRIP_ERR(4, false);
-        else if (dp.rank < 8) CONEF_STRIP_ERR(8, false);
-        else if (dp.rank < 16) CONEF_STRIP_ERR(16, false);
-        else CONEF_STRIP_ERR(32, false);
-    }
-#undef CONEF_STRIP_ERR
+    by_rank(dp.rank, [&](auto rank, auto exact) {
+        hipLaunchKernelGGL((k_err_strip<decltype(rank)::value, decltype(exact)::value, TWO>), dim3(dp.n_err_s), dim3(256),
+                           (size_t)dp.es_lds * 4, st, dp, grads, codes, scales, codes2, scales2, Phat, Qn, lo, hi);
+    });
 }
 
 }  // namespace
@@ -123,10 +136,17 @@ void strip_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes
 void strip_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Phat, double *ws,
                   float *Qout, hipStream_t st)
 {
-    if (dp.n_q <= 0) return;
     const Source src = {grads, codes, scales, nullptr};
     if (dp.i_codes) pass_q<kSrcTwo>(dp, src, Phat, ws, Qout, st);
     else pass_q<kSrcOne>(dp, src, Phat, ws, Qout, st);
+}
+
+void strip_pass_q_flat(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Phat,
+                       float *Qout, hipStream_t st)
+{
+    const Source src = {grads, codes, scales, nullptr};
+    if (dp.i_codes) pass_q_flat<kSrcTwo>(dp, src, Phat, Qout, st);
+    else pass_q_flat<kSrcOne>(dp, src, Phat, Qout, st);
 }
 
 void strip_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, const float *Phat, const float *Qn,
@@ -152,10 +172,14 @@ void strip_cs_pass_p(const DevicePlan &dp, const void *grads, const void *table,
 void strip_cs_pass_q(const DevicePlan &dp, const void *grads, const void *table, const float *Phat, double *ws, float *Qout,
                      hipStream_t st)
 {
-    if (dp.n_q <= 0) return;
     const Source src = {grads, nullptr, nullptr, table};
-    if (dp.cs_cols_mode) pass_q<kSrcCol>(dp, src, Phat, ws, Qout, st);
-    else pass_q<kSrcRow>(dp, src, Phat, ws, Qout, st);
+    if (dp.cs_cols_mode) {
+        pass_q<kSrcCol>(dp, src, Phat, ws, Qout, st);
+        pass_q_flat<kSrcCol>(dp, src, Phat, Qout, st);
+    } else {
+        pass_q<kSrcRow>(dp, src, Phat, ws, Qout, st);
+        pass_q_flat<kSrcRow>(dp, src, Phat, Qout, st);
+    }
 }
 
 }  // namespace conef

@@ -607,7 +607,9 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                         for (int32_t cc = 0; cc < d.n_p_chunks; ++cc)
                             plan.p_items.push_back({l, (int32_t)r0, cc, (int32_t)std::min<int64_t>(prow, d.n - r0)});
                 const int32_t nct = (int32_t)ceil_div(d.m, 64);
-                if (!mf_q)
+                if (!mf_q && d.n <= kFlatRows && d.n_q_tiles == 1 && d.N <= kStripSpan)
+                    for (int32_t ct = 0; ct < nct; ct += 4) plan.q_flat_items.push_back({l, ct / 4, 0, 0});
+                else if (!mf_q)
                     for (int32_t rt = 0; rt < d.n_q_tiles; ++rt)
                         for (int32_t ct = 0; ct < nct; ++ct) plan.q_items.push_back({l, ct, rt, 0});
                 if (!mf_p && d.n_p_chunks > 1)
@@ -870,6 +872,11 @@ bool check_plan(const Plan &plan)
         Cover c(nm);
         for (const WorkItem &it : plan.q_items)
             c.add(plan, it, (int64_t)it.b * plan.mats[it.mat].q_tile_rows, plan.mats[it.mat].q_tile_rows, (int64_t)it.a * 64, 64);
+        for (const WorkItem &it : plan.q_flat_items) {
+            const MatDesc &d = plan.mats[it.mat];
+            if (d.n > kFlatRows || plan.rank > kFlatRows || d.n_q_tiles != 1 || d.N > kStripSpan) return false;
+            c.add(plan, it, 0, d.n, (int64_t)it.a * 256, 256);
+        }
         for (const WorkItem &it : plan.q_f_items)
             c.add(plan, it, (int64_t)it.b * plan.mats[it.mat].q_tile_rows, plan.mats[it.mat].q_tile_rows, (int64_t)it.a * 64, 64);
         for (const WorkItem &it : plan.q_m_items)

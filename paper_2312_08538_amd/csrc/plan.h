@@ -13,6 +13,7 @@ constexpr int kGramRows = 256;      // rows per LDS piece of the Gram kernel
 constexpr int kQredManyTiles = 32;  // partial sums of Q+ per entry from which 16 threads share an entry's sum
 constexpr int kStripRows = 32;      // rows per workgroup item of the strip P pass
 constexpr int64_t kStripSpan = (int64_t)1 << 29;    // elements a strip workgroup's rows may span (32-bit byte offsets)
+constexpr int kFlatRows = 8;        // matrices of at most so many rows: a wave of the strip Q+ pass takes all of them
 constexpr int kFastMaxRank = 8;     // the octet family holds rank <= 8 in registers
 constexpr int kPTileRows = 64;      // rows per workgroup item of the octet P pass
 
@@ -121,6 +122,7 @@ struct Plan {
     // strip kernels (any shape)
     std::vector<WorkItem> p_items;      // pass 1: (mat, first row, column chunk, rows: kStripRows or fewer)
     std::vector<WorkItem> q_items;      // pass 2: (mat, strip of 64 columns, row tile)
+    std::vector<WorkItem> q_flat_items; // pass 2, few rows: (mat, four strips)
     std::vector<WorkItem> err_s_items;  // pass 3: (mat, tile, its first row, rows it spans), or with segments (mat, first row, segment, rows)
     std::vector<WorkItem> err_items;    // pass 3, blocks that are not 8 * 2^j elements (j <= 6): (mat, first block, blocks per wave)
     int es_lds = 0;                     // floats of LDS of the strip err pass

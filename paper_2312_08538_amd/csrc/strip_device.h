@@ -363,6 +363,57 @@ __device__ __forceinline__ void q_strip(const DevicePlan &dp, int block, double 
     }
 }
 
+// Matrices of up to kFlatRows rows: a strip per wave, which has all rows (item: four strips).  In q_strip three waves of four
+// have no rows then, and a trip repeats what rows there are: 1 x 1000000, rank 1, 16.7 us (31 with two vectors) against 7.5
+// here; a thread per column without strips took 11.9.
+template <int SRC, int R, bool EXACT>
+__device__ __forceinline__ void q_flat(const DevicePlan &dp, int block, const Source &src, const float *__restrict__ Phat, float *Qout)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const WorkItem it = dp.q_flat_items[block];
+    const MatDesc d = dp.mats[it.mat];
+    const int r = EXACT ? R : dp.rank;
+    const int64_t col0 = ((int64_t)it.a * 4 + wave) * 64;
+    if (col0 >= d.m) return;
+    const int ncol = (int)((d.m - col0 < 64) ? d.m - col0 : 64);
+    const uint32_t lc = (uint32_t)(lane < ncol ? lane : ncol - 1);
+    const int32_t hv_col = SRC == kSrcCol ? dp.row_hash[d.hash_off + col0 + lc] : 0;
+    uint32_t rel0;
+    const Base<SRC> base = make_base<SRC>(dp, d, src, col0, &rel0);
+    const int rows = (int)d.n;
+    double acc[R];
+#pragma unroll
+    for (int c = 0; c < R; ++c) acc[c] = 0.0;
+    for (int i0 = 0; i0 < rows; i0 += 2) {
+        uint32_t rel[2];
+        int64_t row[2];
+        Raw<SRC> o[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            row[u] = i0 + u < rows ? i0 + u : rows - 1;
+            rel[u] = rel0 + lc + (uint32_t)row[u] * (uint32_t)d.m;
+        }
+        load_rows<SRC, 2>(dp, d, src, base, rel, row, col0, lc, hv_col, o);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (i0 + u < rows) {                                // uniform
+                float ph[R];
+                uniform_row<R, EXACT>(Phat + d.p_off + (i0 + u) * r, r, ph);
+                const double pd = (double)form_p<SRC>(dp, o[u], rel[u], dp.omb);
+#pragma unroll
+                for (int c = 0; c < R; ++c) acc[c] = __builtin_fma(pd, (double)ph[c], acc[c]);
+            }
+        }
+    }
+    if (lane < ncol) {
+        float *out = Qout + d.q_off + (col0 + lane) * r;
+#pragma unroll
+        for (int c = 0; c < R; ++c)
+            if (EXACT || c < r) out[c] = (float)acc[c];
+    }
+}
+
 // ------------------------------------------------------------------ err pass
 // The workgroup's run of scale blocks is either a piece of the flat index (d.es_seg == 0: es_tile elements from
 // it.a * es_tile on, spanning it.c rows from row it.b), or, for matrices too wide for several rows to fit into LDS, for
