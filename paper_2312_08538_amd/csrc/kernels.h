@@ -10,7 +10,7 @@ namespace conef {
 struct DevicePlan {
     const MatDesc *mats = nullptr;
     const WorkItem *p_items = nullptr, *q_items = nullptr, *err_s_items = nullptr;        // strip kernels (any shape)
-    const WorkItem *q_flat_items = nullptr;     // the same, matrices of few rows
+    const WorkItem *q_flat_items = nullptr, *err_g_items = nullptr;     // few rows (Q+ pass), few columns (err pass)
     const WorkItem *err_items = nullptr;        // err pass of blocks the strip kernel does not take
     const WorkItem *p_f_items = nullptr, *q_f_items = nullptr, *err_f_items = nullptr;    // octet family
     const WorkItem *err_t_items = nullptr;      // octet family, err pass with the residual on the fp32 matrix cores
@@ -41,7 +41,7 @@ struct DevicePlan {
     int n_upd = 0, upd_many = 0;    // upd_many: its items may be of several row tiles
     int n_pred = 0, n_gram = 0, n_apply = 0, n_qred = 0, n_elem = 0;
     int rank = 0, rpad = 0, bits = 0, block = 0, dtype = 0;
-    int n_q_flat = 0;
+    int n_q_flat = 0, n_err_g = 0;
     int n_err_s = 0, es_lds = 0;    // strip err pass: items, floats of LDS per workgroup
     int wshift = 0, lb_shift = 0;   // log2(code fields per word), log2(block / 8)
     int block_shift = -1;           // log2(block), -1 if it is not a power of two

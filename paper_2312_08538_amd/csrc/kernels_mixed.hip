@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256, 2) void k_err_mixed(DevicePlan dp, int lead, c
     if (b >= lead)
         err_tile<BF16, BITS, R, WIDE, false>(dp, b - lead, lds, grads, codes, scales, Phat, Qn, step_lo, step_hi, nullptr, nullptr);
     else if (b < dp.n_err_s)
-        err_strip<R, true, false>(dp, b, lds, grads, codes, scales, nullptr, nullptr, Phat, Qn, step_lo, step_hi);
+        err_strip<R, true, false, false>(dp, b, lds, grads, codes, scales, nullptr, nullptr, Phat, Qn, step_lo, step_hi);
 }
 
 // At most two strip workgroups per CU: with more, the strip kernels fill the chip by themselves, and their own launch

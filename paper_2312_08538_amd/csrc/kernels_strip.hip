@@ -48,13 +48,13 @@ __global__ __launch_bounds__(256) void k_q_flat(DevicePlan dp, Source src, const
     q_flat<SRC, R, EXACT>(dp, blockIdx.x, src, Phat, Qout);
 }
 
-template <int R, bool EXACT, bool TWO>
+template <int R, bool EXACT, bool TWO, bool GROUP>
 __global__ __launch_bounds__(256) void k_err_strip(DevicePlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
                                                    uint32_t *codes2, float *scales2, const float *__restrict__ Phat,
                                                    const float *__restrict__ Qn, uint32_t step_lo, uint32_t step_hi)
 {
     extern __shared__ __attribute__((aligned(16))) float X[];
-    err_strip<R, EXACT, TWO>(dp, blockIdx.x, X, grads, codes, scales, codes2, scales2, Phat, Qn, step_lo, step_hi);
+    err_strip<R, EXACT, TWO, GROUP>(dp, blockIdx.x, X, grads, codes, scales, codes2, scales2, Phat, Qn, step_lo, step_hi);
 }
 
 template <int SRC>
@@ -110,14 +110,15 @@ void pass_q_flat(const DevicePlan &dp, const Source &src, const float *Phat, flo
         });
 }
 
-template <bool TWO>
+template <bool TWO, bool GROUP>
 void pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, uint32_t *codes2, float *scales2,
               const float *Phat, const float *Qn, uint64_t step, hipStream_t st)
 {
-    if (dp.n_err_s <= 0) return;
+    const int n = GROUP ? dp.n_err_g : dp.n_err_s;
+    if (n <= 0) return;
     const uint32_t lo = (uint32_t)step, hi = (uint32_t)(step >> 32);
     by_rank(dp.rank, [&](auto rank, auto exact) {
-        hipLaunchKernelGGL((k_err_strip<decltype(rank)::value, decltype(exact)::value, TWO>), dim3(dp.n_err_s), dim3(256),
+        hipLaunchKernelGGL((k_err_strip<decltype(rank)::value, decltype(exact)::value, TWO, GROUP>), dim3(n), dim3(256),
                            (size_t)dp.es_lds * 4, st, dp, grads, codes, scales, codes2, scales2, Phat, Qn, lo, hi);
     });
 }
@@ -152,13 +153,15 @@ void strip_pass_q_flat(const DevicePlan &dp, const void *grads, const uint32_t *
 void strip_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, const float *Phat, const float *Qn,
                     uint64_t step, hipStream_t st)
 {
-    pass_err<false>(dp, grads, codes, scales, nullptr, nullptr, Phat, Qn, step, st);
+    pass_err<false, false>(dp, grads, codes, scales, nullptr, nullptr, Phat, Qn, step, st);
+    pass_err<false, true>(dp, grads, codes, scales, nullptr, nullptr, Phat, Qn, step, st);
 }
 
 void strip_pass_err_two(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, uint32_t *codes2, float *scales2,
                         const float *Phat, const float *Qn, uint64_t step, hipStream_t st)
 {
-    pass_err<true>(dp, grads, codes, scales, codes2, scales2, Phat, Qn, step, st);
+    pass_err<true, false>(dp, grads, codes, scales, codes2, scales2, Phat, Qn, step, st);
+    pass_err<true, true>(dp, grads, codes, scales, codes2, scales2, Phat, Qn, step, st);
 }
 
 void strip_cs_pass_p(const DevicePlan &dp, const void *grads, const void *table, const float *Q, float *P, double *ws, hipStream_t st)

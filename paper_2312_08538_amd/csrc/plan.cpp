@@ -463,7 +463,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         // against its share of the elements.
         const int64_t strip_chunk = std::min<int64_t>(2048, std::max<int64_t>(256, round_up(strip_elems / (kStripRows * 1536), 256)));
         const int64_t strip_q_rows = std::min<int64_t>(512, std::max<int64_t>(32, round_up(strip_elems / (64 * 1536), 32)));
-        const int64_t strip_err = strip_elems / 8192 >= 1024 ? 8192 : strip_elems / 4096 >= 768 ? 4096 : 2048;
+        const int64_t strip_err = strip_elems / 8192 >= 1024 ? 8192 : strip_elems / 4096 >= 768 ? 4096 : strip_elems / 2048 >= 64 ? 2048 : 1024;
         auto lay_out = [&](int64_t chunk_cols, int64_t tile_rows) {
             wd = 0;
             plan.any_p_chunks = false;
@@ -533,10 +533,17 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         }
         // The strip err pass: runs of the flat index of strip_err elements where that is at least eight rows (a wave's row of
         // Q+ per lane serves all rows of a run), else eight rows of a column segment.
+        // Matrices of up to 32 columns are walked in groups of rows, by a launch of their own.  With 16 columns or more they do
+        // not pay for one beside other matrices (64 x 27 in a small convolutional network: 10 - 17 us for the pass without
+        // groups, 15 - 21 with; the launches of 600 x 27 alone 9.0 and 7.7).
+        bool all_narrow = true;
+        for (const MatDesc &d : plan.mats) all_narrow = all_narrow && d.m <= 32;
         for (int l = 0; l < n_mats && !sketch && octet_blocks; ++l) {
             MatDesc &d = plan.mats[l];
             if (d.path != kPathGeneric) continue;
+            d.es_rows = 1;
             if (d.m <= 1024) {
+                if (d.m < 16 || (all_narrow && d.m <= 32)) d.es_rows = (int32_t)(64 / d.m);
                 int64_t tile = strip_err;
                 while (tile < 8192 && tile < 8 * d.m && strip_elems / tile >= 512) tile *= 2;      // (shorter runs rather than an empty chip)
                 d.es_tile = (int32_t)round_up(tile, block);
@@ -616,8 +623,9 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                     for (int64_t e0 = 0; e0 < d.n * rank; e0 += 256) plan.pred_items.push_back({l, (int32_t)e0, 0, 0});
                 if (!mf_e && !sketch && d.es_tile > 0)
                     for (int64_t t = 0; t * d.es_tile < d.N; ++t) {
-                        const int64_t i0 = t * d.es_tile / d.m, i1 = (std::min<int64_t>((t + 1) * d.es_tile, d.N) - 1) / d.m;
-                        plan.err_s_items.push_back({l, (int32_t)t, (int32_t)i0, (int32_t)(i1 - i0 + 1)});
+                        const int64_t row = d.m * d.es_rows;
+                        const int64_t i0 = t * d.es_tile / row, i1 = (std::min<int64_t>((t + 1) * d.es_tile, d.N) - 1) / row;
+                        (d.es_rows > 1 ? plan.err_g_items : plan.err_s_items).push_back({l, (int32_t)t, (int32_t)i0, (int32_t)(i1 - i0 + 1)});
                     }
                 const int64_t erow = std::min<int64_t>(8, std::max<int64_t>(1, kStripSpan / d.m));
                 if (!mf_e && !sketch && d.es_seg > 0)
@@ -945,6 +953,7 @@ bool check_plan(const Plan &plan)
         for (const WorkItem &it : plan.err_items) c.add_elems(plan, it, (int64_t)it.a * plan.block, (int64_t)4 * it.b * plan.block);
         for (const WorkItem &it : plan.err_s_items) {
             const MatDesc &d = plan.mats[it.mat];
+            if (d.es_rows != 1) return false;
             if (d.es_seg > 0) {
                 // the blocks that start in this rectangle: up to es_over columns more per row, inside the pitch
                 if (d.es_pitch < d.es_seg + d.es_over || (d.m % plan.block != 0 && d.es_over < plan.block) ||
@@ -957,6 +966,14 @@ bool check_plan(const Plan &plan)
                     return false;
                 c.add_elems(plan, it, j0, d.es_tile);
             }
+        }
+        for (const WorkItem &it : plan.err_g_items) {
+            const MatDesc &d = plan.mats[it.mat];
+            const int64_t j0 = (int64_t)it.a * d.es_tile, j1 = std::min<int64_t>(j0 + d.es_tile, d.N), group = d.m * d.es_rows;
+            if (d.es_rows < 2 || group > 64 || d.es_seg != 0 || d.es_tile % plan.block != 0 || d.es_tile > plan.es_lds ||
+                it.b != j0 / group || it.b + it.c - 1 != (j1 - 1) / group)
+                return false;
+            c.add_elems(plan, it, j0, d.es_tile);
         }
         for (const WorkItem &it : plan.err_f_items) {
             const int64_t strip = (int64_t)8 << plan.mats[it.mat].lr_shift;

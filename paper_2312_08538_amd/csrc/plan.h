@@ -48,8 +48,9 @@ struct MatDesc {
     int32_t p_chunk_cols;           // columns per partial of P
     int32_t path;                   // kernel family chosen for this matrix
     // strip err pass: a run of es_tile elements of the flat index per item, or (es_seg > 0) rows of a column segment of es_seg
-    // columns, es_over columns past it that the segment's last blocks may reach, es_pitch floats of LDS per row
-    int32_t es_tile, es_seg, es_over, es_pitch;
+    // columns, es_over columns past it that the segment's last blocks may reach, es_pitch floats of LDS per row;
+    // es_rows: rows of a narrow matrix that a wave takes as one (64 / columns), else 1
+    int32_t es_tile, es_seg, es_over, es_pitch, es_rows;
     // octet family: a lane owns 8 consecutive elements of a row; lr lanes share a row
     int32_t lr_shift;               // log2(lanes per row segment), 3..6
     int32_t lb_shift;               // log2(lanes per scale block) = log2(block/8)
@@ -124,6 +125,7 @@ struct Plan {
     std::vector<WorkItem> q_items;      // pass 2: (mat, strip of 64 columns, row tile)
     std::vector<WorkItem> q_flat_items; // pass 2, few rows: (mat, four strips)
     std::vector<WorkItem> err_s_items;  // pass 3: (mat, tile, its first row, rows it spans), or with segments (mat, first row, segment, rows)
+    std::vector<WorkItem> err_g_items;  // pass 3, es_rows > 1: (mat, tile, its first group of rows, groups it spans)
     std::vector<WorkItem> err_items;    // pass 3, blocks that are not 8 * 2^j elements (j <= 6): (mat, first block, blocks per wave)
     int es_lds = 0;                     // floats of LDS of the strip err pass
     int wshift = 0, lb_shift = 0;       // log2(code fields per word); log2(block / 8) for power-of-two blocks of 8 elements or more

@@ -420,6 +420,10 @@ __device__ __forceinline__ void q_flat(const DevicePlan &dp, int block, const So
 // each of it.c rows from row it.a the blocks that START in the columns of segment it.b; these may reach past the segment
 // by less than a block, into the next row after the last segment ("virtual" columns m, m + 1, ...).  Either way a row
 // has a window [lo, hi) of (virtual) columns and its residuals lie in LDS in the order of the flat index.
+// A matrix of up to 32 columns (GROUP) is walked in groups of es_rows rows that fill a wave, as if a group were a row; a lane
+// then has a row of P^ of its own.  One row per access left the lanes empty: 4096 x 9 at rank 4 21 us, 100000 x 1 140; 7.6 and
+// 7.6 in groups (7.5 and 7.3 with the kernel for any block, a lane per element, which needs 84 for 200000 x 12 where groups
+// take 11).  Launched apart from the other strips: both in one kernel cost those 5 - 10 %.
 //
 // First half: units of four rows x one strip, each wave a contiguous quarter of the units in strip-major order, so that
 // a strip's rows of Q+ are loaded once per wave; the next unit's loads are issued ahead of the current one's arithmetic.
@@ -488,7 +492,8 @@ __device__ __forceinline__ void quantise_run(const DevicePlan &dp, const MatDesc
 // codes / scales: the error vector that is replaced (TWO: the first one, also in the plan); codes2 / scales2: TWO only,
 // the second
 // X: LDS, dp.es_lds floats
-template <int R, bool EXACT, bool TWO>
+// GROUP: the matrix is walked in groups of rows (it has no segments)
+template <int R, bool EXACT, bool TWO, bool GROUP>
 __device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float *X, const void *__restrict__ grads, uint32_t *codes,
                                           float *scales, uint32_t *codes2, float *scales2, const float *__restrict__ Phat,
                                           const float *__restrict__ Qn, uint32_t step_lo, uint32_t step_hi)
@@ -496,17 +501,19 @@ __device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float
     constexpr int U = 4, SRC = TWO ? kSrcTwo : kSrcOne;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const WorkItem it = dp.err_s_items[block];
+    const WorkItem it = GROUP ? dp.err_g_items[block] : dp.err_s_items[block];
     const MatDesc d = dp.mats[it.mat];
     const int r = EXACT ? R : dp.rank;
     const int64_t B = dp.block;
-    const bool seg = d.es_seg != 0;
+    const bool seg = !GROUP && d.es_seg != 0;
     const int64_t j0 = seg ? 0 : (int64_t)it.a * d.es_tile;
     const int64_t j1 = seg ? 0 : (j0 + d.es_tile < d.N ? j0 + d.es_tile : d.N);
     const int64_t i_first = seg ? it.a : it.b;
     const int n_rows = it.c;
+    const int64_t M = GROUP ? d.m * d.es_rows : d.m;            // GROUP: below, a row is a group of them
+    const int lane_row = GROUP ? lane / (int)d.m : 0, lane_col = GROUP ? lane - lane_row * (int)d.m : lane;
     const int64_t c0 = seg ? (int64_t)it.b * d.es_seg : 0;
-    const int64_t c1 = seg ? (c0 + d.es_seg < d.m ? c0 + d.es_seg : d.m) : d.m;
+    const int64_t c1 = seg ? (c0 + d.es_seg < d.m ? c0 + d.es_seg : d.m) : M;
     // (virtual) columns: [c0, c0 + width)
     const int width = (int)(c1 - c0) + (seg ? d.es_over : 0);
     Source src;
@@ -514,10 +521,10 @@ __device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float
 
     // All indices are relative to the first owned block of the run (its first element: jb); row rl of the run owns the
     // elements [ws, we) and its (virtual) column 64 st + lane is element rel_row(rl) + 64 st + lane.
-    const int64_t f0 = i_first * d.m + c0;
+    const int64_t f0 = i_first * M + c0;
     const int64_t jb = seg ? ((f0 + B - 1) & ~(B - 1)) : j0;
     const int rel_f0 = (int)(f0 - jb);                          // (negative: the run's first row starts before its first block)
-    auto rel_row = [&](int rl) { return rel_f0 + rl * (int)d.m; };
+    auto rel_row = [&](int rl) { return rel_f0 + rl * (int)M; };
     const int last = (int)(seg ? (d.N - jb < INT32_MAX ? d.N - jb : INT32_MAX) : j1 - jb);
     auto window = [&](int rl, int &ws, int &we) {
         const int f = rel_row(rl);
@@ -526,7 +533,7 @@ __device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float
             we = (f + (int)(c1 - c0) + (int)B - 1) & ~((int)B - 1);
         } else {
             ws = f > 0 ? f : 0;
-            we = f + (int)d.m;
+            we = f + (int)M;
         }
         we = we < last ? we : last;
     };
@@ -573,7 +580,7 @@ __device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float
         const int64_t kk = c0 + 64 * strip + lane;             // the lane's (virtual) column
         if (strip != q_strip) {                                 // uniform
             q_strip = strip;
-            int64_t k = kk < d.m ? kk : kk - d.m;
+            int64_t k = GROUP ? lane_col : kk < d.m ? kk : kk - d.m;
             k = k < d.m ? k : d.m - 1;
             const float *qrow = Qn + d.q_off + k * r;
             if (EXACT && R >= 4) {
@@ -592,6 +599,20 @@ __device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float
         if (n_group == n_groups) { n_group = 0; ++n_strip; }
         if (un + 1 < u_end) load_unit(nxt, n_strip, n_group);
         const bool wraps = seg && c0 + 64 * strip + 63 >= d.m;  // uniform: some lanes may belong to the next row
+        constexpr int RL = GROUP && R <= 8 ? R : 1;
+        float pl[U][RL];                                        // GROUP: the lanes' rows of P^, of all four groups at once
+        auto lane_p = [&](int u) {
+            const int64_t i = (i_first + row_of(group, u)) * d.es_rows + lane_row;
+            return Phat + d.p_off + (i < d.n ? i : d.n - 1) * r;
+        };
+        if (GROUP && R <= 8) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float *prow = lane_p(u);
+#pragma unroll
+                for (int c = 0; c < RL; ++c) pl[u][c] = prow[EXACT ? c : (c < r ? c : r - 1)];
+            }
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (group * U + u < n_rows) {                       // uniform
@@ -602,14 +623,20 @@ __device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float
                 const int e = rel_row(rl) + 64 * strip + lane;
                 // (lanes outside the window work on another element's inputs and store nothing)
                 const float p = form_p<SRC>(dp, cur.o[u], (uint32_t)e, 1.0f);
-                float ph[R];
-                uniform_row<R, EXACT>(Phat + d.p_off + i * r, r, ph);
                 float acc = 0.0f;
-                if (!wraps) {
+                if (GROUP) {
+                    const float *prow = lane_p(u);
+#pragma unroll
+                    for (int c = 0; c < R; ++c)
+                        if (EXACT || c < r) acc = __builtin_fmaf(R <= 8 ? pl[u][R <= 8 && GROUP ? c : 0] : prow[c], q[c], acc);
+                } else if (!wraps) {
+                    float ph[R];
+                    uniform_row<R, EXACT>(Phat + d.p_off + i * r, r, ph);
 #pragma unroll
                     for (int c = 0; c < R; ++c) acc = __builtin_fmaf(ph[c], q[c], acc);
                 } else {
-                    float pn[R];
+                    float ph[R], pn[R];
+                    uniform_row<R, EXACT>(Phat + d.p_off + i * r, r, ph);
                     uniform_row<R, EXACT>(Phat + d.p_off + (i + 1 < d.n ? i + 1 : i) * r, r, pn);
 #pragma unroll
                     for (int c = 0; c < R; ++c) acc = __builtin_fmaf(kk < d.m ? ph[c] : pn[c], q[c], acc);
