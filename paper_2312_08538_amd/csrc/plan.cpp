@@ -461,7 +461,13 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         // The strip kernels: about 1536 workgroups per launch (six per CU) where the model is large enough, with limits that
         // keep a workgroup's fixed part (operand set-up, the sum over its waves, partial sums to be added later) small
         // against its share of the elements.
-        const int64_t strip_chunk = std::min<int64_t>(2048, std::max<int64_t>(256, round_up(strip_elems / (kStripRows * 1536), 256)));
+        // Where no matrix has more than 512 columns they stay in one chunk: a wave has two strips then, and the launch that adds
+        // the chunks, which nothing else needs, costs more (600 x 300 at rank 4: 9.3 us for the pass in two chunks, 7.8 in one;
+        // not so with the sketch, whose gathered rows are the longer chain: 10.3 and 11.6).
+        int64_t widest = 0;
+        for (const MatDesc &d : plan.mats) widest = std::max(widest, d.m);
+        const int64_t strip_chunk = !sketch && widest <= 512 ? 512
+            : std::min<int64_t>(2048, std::max<int64_t>(256, round_up(strip_elems / (kStripRows * 1536), 256)));
         const int64_t strip_q_rows = std::min<int64_t>(512, std::max<int64_t>(32, round_up(strip_elems / (64 * 1536), 32)));
         const int64_t strip_err = strip_elems / 8192 >= 1024 ? 8192 : strip_elems / 4096 >= 768 ? 4096 : strip_elems / 2048 >= 64 ? 2048 : 1024;
         auto lay_out = [&](int64_t chunk_cols, int64_t tile_rows) {
@@ -488,10 +494,8 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 d.p_chunk_cols = (int32_t)d.m;
                 const bool strip = d.path == kPathGeneric;
                 if ((d.path == kPathOctet && !d.cs_lin && !d.pack) || strip) {
-                    // strip kernels: chunks of one size, a multiple of a strip.  Up to 512 columns stay together: a wave has
-                    // two strips then, and the launch that adds the chunks costs more (600 x 300 at rank 4: 9.3 us in two
-                    // chunks, 7.8 in one)
-                    d.p_chunk_cols = strip ? (int32_t)std::min<int64_t>(round_up(ceil_div(d.m, d.m <= 512 ? 1 : ceil_div(d.m, chunk_cols)), 64), INT32_MAX / 64 * 64) : p_cols;
+                    // strip kernels: chunks of one size, a multiple of a strip
+                    d.p_chunk_cols = strip ? (int32_t)std::min<int64_t>(round_up(ceil_div(d.m, ceil_div(d.m, chunk_cols)), 64), INT32_MAX / 64 * 64) : p_cols;
                     d.n_p_chunks = (int32_t)ceil_div(d.m, d.p_chunk_cols);
                     if (d.n_p_chunks > 1) {
                         d.ppart_off = wd; wd += round_up((int64_t)d.n_p_chunks * d.n * rank, 32);
