@@ -103,6 +103,7 @@ int ensure_uploaded(conef_ctx *ctx)
     d.n_cs_lin = (int)pl.cs_lin_items.size();
     d.cs_cols_mode = pl.sketch_cols ? 1 : 0;
     d.csc_lds = 0;
+    d.csc_threads = pl.csc_threads;
     for (const MatDesc &m : pl.mats)
         if (pl.sketch_cols) d.csc_lds = std::max<int>(d.csc_lds, (int)(m.cs_cols * (m.m + m.w)));
     d.n_cs_err_f_old = 0;

@@ -80,10 +80,12 @@ __global__ __launch_bounds__(kCsCols) void k_cs_update_generic(DevicePlan dp, co
 
 // Column form (Section 5.3, "row or column"): the table is n x w, column k has bucket h(k) and sign s(k),
 //   S[i, b] <- fma(beta, S[i, b], sum over the columns k of bucket b, ascending, of s(k) (p - P^ Q+^T)[i, k]).
-// One workgroup per R rows of the matrix, R as many (at most 8) as have room in LDS: the rows of the table, then the rows of the
-// residual are staged there, the R values of a bucket or column side by side; a column's row of Q+, its hash and a bucket's
-// column list are then read once for R rows (with one row per workgroup these reads, r + 1 words per element, and not the
-// gradient were most of the traffic: 80 us for the 18-layer residual network, 11.7 M elements).
+// One workgroup per R rows of the matrix, R as many (at most 8) as have room in LDS and leave the chip enough workgroups (the
+// planner): the rows of the table, then the rows of the residual are staged there, the R values of a bucket or column side by
+// side; a column's row of Q+, its hash and a bucket's column list are then read once for R rows (with one row per workgroup
+// these reads, r + 1 words per element, and not the gradient were most of the traffic: 77 us for the 18-layer residual
+// network, 11.7 M elements, and 37 now).  The LDS of the launch is the largest matrix's: one matrix of 16384 columns and as
+// many buckets (128 KB, one workgroup per CU) beside ten of 512 x 4608 takes 227 us (398 with one row per workgroup).
 template <int R>
 __device__ __forceinline__ void csc_store(float *dst, const float (&v)[R])
 {
@@ -115,7 +117,7 @@ template <int RP, int R>
 __device__ __forceinline__ void csc_rows(const DevicePlan &dp, const MatDesc &d, const WorkItem &it, float *lds, const void *__restrict__ grads,
                                          void *table, const float *__restrict__ Phat, const float *__restrict__ Qn)
 {
-    const int r = dp.rank, m = (int)d.m, w = (int)d.w;
+    const int r = dp.rank, m = (int)d.m, w = (int)d.w, threads = (int)blockDim.x;
     float *s_t = lds, *s_x = lds + (size_t)R * w;
     const int64_t trow = d.table_off + (int64_t)it.a * d.w, grow = d.grad_off + (int64_t)it.a * d.m;
     const float *prow = Phat + d.p_off + (int64_t)it.a * r;
@@ -124,15 +126,15 @@ __device__ __forceinline__ void csc_rows(const DevicePlan &dp, const MatDesc &d,
     // rows of P^: uniform (scalar registers) for small ranks, else through LDS, read by all lanes at once
     __shared__ __attribute__((aligned(16))) float s_p[RP >= 16 ? 8 * RP : 4];
     if (RP >= 16)
-        for (int e = threadIdx.x; e < R * RP; e += kCscThreads) s_p[e] = prow[(int64_t)row_of(e / RP) * r + (e % RP < r ? e % RP : r - 1)];
-    for (int b = threadIdx.x; b < w; b += kCscThreads) {
+        for (int e = threadIdx.x; e < R * RP; e += threads) s_p[e] = prow[(int64_t)row_of(e / RP) * r + (e % RP < r ? e % RP : r - 1)];
+    for (int b = threadIdx.x; b < w; b += threads) {
         float t[R];
 #pragma unroll
         for (int i = 0; i < R; ++i) t[i] = table_load(table, dp.table_dtype, trow + (int64_t)row_of(i) * w + b);
         csc_store<R>(s_t + (size_t)b * R, t);
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < m; k += kCscThreads) {
+    for (int k = threadIdx.x; k < m; k += threads) {
         const int32_t hv = dp.row_hash[d.hash_off + k];
         float x[R], q[RP], t[R];
 #pragma unroll
@@ -156,7 +158,7 @@ __device__ __forceinline__ void csc_rows(const DevicePlan &dp, const MatDesc &d,
     __syncthreads();
     const int32_t *ptr = dp.bucket_ptr + d.bptr_off;
     const int32_t *cols = dp.bucket_rows + d.hash_off;
-    for (int b = threadIdx.x; b < w; b += kCscThreads) {
+    for (int b = threadIdx.x; b < w; b += threads) {
         float acc[R], x[R], s_old[R];
 #pragma unroll
         for (int i = 0; i < R; ++i) acc[i] = 0.0f;
@@ -1163,10 +1165,10 @@ hipError_t launch_cs_pass_err(const DevicePlan &dp, const void *grads, void *tab
     if (dp.n_cs_err > 0 && dp.cs_cols_mode) {
         const size_t lds = (size_t)dp.csc_lds * sizeof(float);
         switch (dp.rpad) {
-        case 4: hipLaunchKernelGGL(k_csc_update<4>, dim3(dp.n_cs_err), dim3(kCscThreads), lds, st, dp, grads, table, Phat, Qn); break;
-        case 8: hipLaunchKernelGGL(k_csc_update<8>, dim3(dp.n_cs_err), dim3(kCscThreads), lds, st, dp, grads, table, Phat, Qn); break;
-        case 16: hipLaunchKernelGGL(k_csc_update<16>, dim3(dp.n_cs_err), dim3(kCscThreads), lds, st, dp, grads, table, Phat, Qn); break;
-        default: hipLaunchKernelGGL(k_csc_update<32>, dim3(dp.n_cs_err), dim3(kCscThreads), lds, st, dp, grads, table, Phat, Qn); break;
+        case 4: hipLaunchKernelGGL(k_csc_update<4>, dim3(dp.n_cs_err), dim3(dp.csc_threads), lds, st, dp, grads, table, Phat, Qn); break;
+        case 8: hipLaunchKernelGGL(k_csc_update<8>, dim3(dp.n_cs_err), dim3(dp.csc_threads), lds, st, dp, grads, table, Phat, Qn); break;
+        case 16: hipLaunchKernelGGL(k_csc_update<16>, dim3(dp.n_cs_err), dim3(dp.csc_threads), lds, st, dp, grads, table, Phat, Qn); break;
+        default: hipLaunchKernelGGL(k_csc_update<32>, dim3(dp.n_cs_err), dim3(dp.csc_threads), lds, st, dp, grads, table, Phat, Qn); break;
         }
     }
     else if (dp.n_cs_err > 0)

@@ -234,6 +234,14 @@ int make_sketch_plan_columns(Plan &plan, const int64_t *rows, const int64_t *col
         plan.row_hash.assign((size_t)h, 0);
         plan.bucket_rows.assign((size_t)h, 0);
         plan.bucket_ptr.assign((size_t)bp, 0);
+        // Update: eight rows per workgroup, fewer where that would leave less than 256 workgroups (960 rows of convolutions, rank
+        // 4: 7.5 us in groups of two, 11.1 of eight, 9.4 one by one), and no more threads than the widest matrix has columns
+        // (100000 x 33, rank 32: 142 us with 64 threads, 504 with 512).
+        int64_t all_rows = 0, widest = 0;
+        for (const MatDesc &d : plan.mats) { all_rows += d.n; widest = std::max(widest, d.m); }
+        int32_t most_rows = 8;
+        while (most_rows > 1 && all_rows / most_rows < 256) most_rows /= 2;
+        plan.csc_threads = (int)std::min<int64_t>(kCscThreads, round_up(widest, 64));
         for (int l = 0; l < n_mats; ++l) {
             MatDesc &d = plan.mats[l];
             int32_t *ptr = plan.bucket_ptr.data() + d.bptr_off;
@@ -249,7 +257,7 @@ int make_sketch_plan_columns(Plan &plan, const int64_t *rows, const int64_t *col
                 const int32_t hv = plan.row_hash[(size_t)(d.hash_off + k)];
                 plan.bucket_rows[(size_t)(d.hash_off + fill[hv & INT32_MAX]++)] = (int32_t)k | (hv & INT32_MIN);
             }
-            d.cs_cols = 8;
+            d.cs_cols = most_rows;
             while (d.cs_cols > 1 && d.cs_cols * (d.m + d.w) > kCscLds) d.cs_cols /= 2;
             d.st_first = (int32_t)plan.cs_err_items.size();
             for (int64_t i = 0; i < d.n; i += d.cs_cols)

@@ -154,6 +154,7 @@ struct Plan {
     std::vector<WorkItem> qred_items;   // reduce partial Q+: (mat, first entry of m*r)
     std::vector<WorkItem> elem_items;   // element-wise helpers: (mat, first element / 1024)
     std::vector<WorkItem> upd_items;    // decompress / update: (mat, row tile of 64, column tile of 128, row tiles)
+    int csc_threads = 0;                // column form of the sketch: threads per workgroup of the update
     int upd_many = 0;                   // 1: the kernel that walks several row tiles takes them (else all are of one tile)
     // element-wise gradient compressors with the quantiser: stream tables (made with the plan)
     size_t sign_words = 0;
@@ -184,7 +185,7 @@ int make_plan(Plan &plan, const int64_t *rows, const int64_t *cols, int n_mats, 
 int make_sketch_plan(Plan &plan, const int64_t *rows, const int64_t *cols, const int64_t *sketch_rows, int n_mats,
                      int rank, float beta, int table_dtype, int dtype, uint64_t seed, bool columns = false);
 constexpr int kCscMaxCols = 16384;  // column form: a row of the residual and one of the table are staged in LDS
-constexpr int kCscThreads = 512;
+constexpr int kCscThreads = 512;   // most threads per workgroup
 constexpr int kCscLds = 20 * 1024;  // LDS floats that several rows of a workgroup may take: two workgroups per CU
 
 // Random-block gradient compressor: keep[l] coordinates of matrix l per step (1 .. rows * cols).  Sets the

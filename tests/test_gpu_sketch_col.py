@@ -203,3 +203,25 @@ def test_column_form_refuses_what_it_cannot_serve(env):
             call()
         assert e.value.code == B.ESTATE
     sk.close()
+
+
+ROWS_PER_WORKGROUP = [
+    # (layout, buckets, rank): rows per workgroup by the number of the model's rows, then by columns + buckets (10240 floats for two)
+    ([(2044, 33), (7, 64)], [6, 64], 4),                               # 2051 rows: eight, the last workgroups of each matrix ragged
+    ([(1027, 130)], [26], 3),                                          # four
+    ([(513, 200), (9, 31)], [40, 31], 8),                              # two
+    ([(511, 65)], [64], 16),                                           # one
+    ([(2100, 20), (3, 2000), (5, 2200)], [4, 560, 400], 2),            # eight, LDS for eight and for four only
+    ([(2100, 20), (3, 9000), (3, 9001)], [4, 1240, 1240], 1),          # LDS for two, for one
+    ([(5, 16384), (4, 100)], [16384, 20], 4),                          # the most columns and buckets: 128 KB of LDS
+    ([(300, 24)], [5], 12),                                            # 64 threads per workgroup
+]
+
+
+@pytest.mark.parametrize("case", range(len(ROWS_PER_WORKGROUP)))
+@pytest.mark.parametrize("gdt,fp16", [(wl.F32, False), (wl.BF16, True)])
+def test_update_with_every_number_of_rows_per_workgroup(env, case, gdt, fp16, monkeypatch):
+    import test_gpu_sketch_col as me
+
+    monkeypatch.setattr(me, "LAYOUTS", ROWS_PER_WORKGROUP)
+    me.test_update_stage_and_estimate_are_bit_exact(env, case, gdt, fp16, 0.9)
