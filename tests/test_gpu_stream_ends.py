@@ -83,3 +83,95 @@ def test_scaled_sign_at_the_end_of_a_matrix(env, bits, block, gdt, vectors):
             assert np.array_equal(got, words), f"{tag}: sign words"
             _compare_vectors(dev, o, states[l], tag)
     model.close()
+
+
+RAGGED = [(2, 16, 3), (2, 256, 10), (4, 8, 10), (4, 128, 2), (4, 512, 33), (8, 8, 7), (8, 64, 10)]      # bits, block, stratum length
+
+
+@pytest.mark.parametrize("bits,block,group", RAGGED)
+@pytest.mark.parametrize("kind", ["block", "strata", "uniform"])
+@pytest.mark.parametrize("vectors", [1, 2])
+def test_kept_coordinates_at_the_end_of_a_matrix(env, bits, block, group, kind, vectors):
+    R, B, S, torch = env
+    gdt = wl.BF16 if (bits + group) % 2 else wl.F32
+    beta = 0.0 if vectors == 2 else 0.75
+    seed = 4100 + bits + block
+    keep = [max(1, n * m // group) for n, m in LAYOUT]
+    model = B.Model(LAYOUT, 1, bits, block, gdt, seed)
+    B.conef_set_beta(model.ctx, beta)
+    if kind == "block":
+        B.conef_rb_configure(model.ctx, keep)
+        n_delta, offsets = B.conef_rb_sizes(model.ctx)["delta_elems"], B.conef_rb_offsets
+        arg, plain, two, call = keep, R.rb_step_matrix, R.i_rb_step_matrix, (B.conef_rb_step, B.conef_i_rb_step)
+    else:
+        if kind == "strata":
+            B.conef_rk_configure(model.ctx, [group] * len(LAYOUT))
+        else:
+            B.conef_rk_configure_uniform(model.ctx, keep)
+        n_delta, offsets = B.conef_rk_sizes(model.ctx)["delta_elems"], B.conef_rk_offsets
+        arg = [group] * len(LAYOUT) if kind == "strata" else [-k for k in keep]
+        plain, two, call = R.rk_step_matrix, R.i_rk_step_matrix, (B.conef_rk_step, B.conef_i_rk_step)
+    buf = model.alloc()
+    dev = [buf["codes"], buf["scales"]] + ([torch.zeros_like(buf["codes"]), torch.zeros_like(buf["scales"])] if vectors == 2 else [])
+    delta = torch.zeros(n_delta, dtype=torch.float32, device="cuda:0")
+    rng = np.random.default_rng([bits, block, vectors, 41])
+    states = _fresh(R, bits, block, vectors)
+    for t in range(STEPS):
+        grads = [S._grad(rng, n, m, gdt) for n, m in LAYOUT]
+        S._to_dev_grads(torch, model, buf, grads)
+        delta.fill_(float("nan"))
+        print(f"[{kind} ends bits {bits} block {block} vectors {vectors}] step {t}: launching", flush=True)
+        call[vectors - 1](model.ctx, buf["grads"], *dev, delta, t, model.stream_handle())
+        torch.cuda.synchronize()
+        for l, (n, m) in enumerate(LAYOUT):
+            tag = f"{n} x {m} (N mod 32 = {n * m % 32}) step {t}"
+            want = (two(grads[l], *states[l], arg[l], bits, block, seed, l, t) if vectors == 2 else
+                    plain(grads[l], *states[l], arg[l], bits, block, beta, seed, l, t))
+            o = offsets(model.ctx, l)
+            got = delta[o["delta_off"]:o["delta_off"] + want.size].cpu().numpy()
+            assert np.array_equal(got.view(np.uint32), want.view(np.uint32)), f"{tag}: kept values"
+            _compare_vectors(dev, model.offsets[l], states[l], tag)
+    model.close()
+
+
+@pytest.mark.parametrize("bits,block,group", RAGGED)
+@pytest.mark.parametrize("strata", [False, True])
+def test_the_first_vector_as_a_random_block_at_the_end_of_a_matrix(env, bits, block, group, strata):
+    R, B, S, torch = env
+    gdt = wl.F32 if (bits + group) % 2 else wl.BF16
+    seed = 4200 + bits + block
+    keep = [max(1, n * m // group) for n, m in LAYOUT]
+    keep_e = [n * m // 3 for n, m in LAYOUT]
+    model = B.Model(LAYOUT, 1, bits, block, gdt, seed)
+    if strata:
+        B.conef_rk_configure(model.ctx, [group] * len(LAYOUT))
+    else:
+        B.conef_rb_configure(model.ctx, keep)
+    B.conef_i2_configure(model.ctx, keep_e)
+    buf = model.alloc()
+    e_bufs = [torch.zeros(B.conef_i2_sizes(model.ctx)["e_elems"], dtype=torch.float32, device="cuda:0") for _ in range(2)]
+    delta = torch.zeros((B.conef_rk_sizes if strata else B.conef_rb_sizes)(model.ctx)["delta_elems"], dtype=torch.float32, device="cuda:0")
+    rng = np.random.default_rng([bits, block, int(strata), 42])
+    states = [[np.zeros(k, np.float32)] + s for k, s in zip(keep_e, _fresh(R, bits, block, 1))]
+    for t in range(STEPS):
+        grads = [S._grad(rng, n, m, gdt) for n, m in LAYOUT]
+        S._to_dev_grads(torch, model, buf, grads)
+        delta.fill_(float("nan"))
+        e_in, e_out = e_bufs[t % 2], e_bufs[(t + 1) % 2]
+        e_out.fill_(float("nan"))
+        print(f"[first vector block ends bits {bits} block {block} strata {strata}] step {t}: launching", flush=True)
+        (B.conef_i2_rk_step if strata else B.conef_i2_rb_step)(model.ctx, buf["grads"], e_in, e_out, buf["codes"], buf["scales"], delta, t,
+                                                               model.stream_handle())
+        torch.cuda.synchronize()
+        for l, (n, m) in enumerate(LAYOUT):
+            e, codes, scales = states[l]
+            tag = f"{n} x {m} (N mod 32 = {n * m % 32}) step {t}"
+            want = (R.i2_rk_step_matrix(grads[l], e, codes, scales, group, bits, block, seed, l, t) if strata else
+                    R.i2_rb_step_matrix(grads[l], e, codes, scales, keep[l], bits, block, seed, l, t))
+            o = (B.conef_rk_offsets if strata else B.conef_rb_offsets)(model.ctx, l)
+            got = delta[o["delta_off"]:o["delta_off"] + want.size].cpu().numpy()
+            assert np.array_equal(got.view(np.uint32), want.view(np.uint32)), f"{tag}: kept values"
+            eo = B.conef_i2_offsets(model.ctx, l)["e_off"]
+            assert np.array_equal(e_out[eo:eo + e.size].cpu().numpy().view(np.uint32), e.view(np.uint32)), f"{tag}: first vector"
+            _compare_vectors([buf["codes"], buf["scales"]], model.offsets[l], [codes, scales], tag)
+    model.close()
