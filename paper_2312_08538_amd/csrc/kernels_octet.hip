@@ -230,7 +230,7 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
             reinterpret_cast<float4 *>(sp + lane * 8)[0] = make_float4(p[0], p[1], p[2], p[3]);
             reinterpret_cast<float4 *>(sp + lane * 8)[1] = make_float4(p[4], p[5], p[6], p[7]);
             sk[lane] = 0;
-            wave_lds_sync();
+            wave_memory_sync();
             const uint32_t N = (uint32_t)d.N, j0 = (uint32_t)(((int64_t)it.a + rr) << 9);
             const uint32_t s0 = stratum_of(j0, d.rk_g, d.rk_magic), s1 = stratum_of(N - 1u - j0 < 511u ? N - 1u : j0 + 511u, d.rk_g, d.rk_magic);
             auto take = [&](uint32_t s, uint32_t u) {
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                         if (q * 4 + w >= s0 && q * 4 + w <= s1) take(q * 4 + w, out[w]);
                 }
             }
-            wave_lds_sync();
+            wave_memory_sync();
             // (an octet beyond the end is marked nowhere: it must not bring the last octet's kept coordinates to the maximum)
             const uint32_t left = valid ? ~sk[lane] : 0u;
             const float back = valid ? dp.beta : 0.0f;
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                 if (TWO || V2) x[e] = __uint_as_float(__float_as_uint(x[e]) & keep);
                 else x[e] = keep ? x[e] : back * (dstep * qf[e]);
             }
-            wave_lds_sync();                // the next run's values may not overtake these reads
+            wave_memory_sync();                // the next run's values may not overtake these reads
         } else if (SPARSE && kbits != 0) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
