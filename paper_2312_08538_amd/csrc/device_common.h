@@ -60,11 +60,14 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
 
 // The eight fields of an octet (8-bit codes: c0 elements 0..3, c1 elements 4..7; else all in c0) as fp32.  4-bit fields come
 // over 16 and are multiplied back, two instructions each; the factor is not moved into the step size, which would overflow
-// for scales above 1.5e38.
-template <int BITS>
+// for scales above 1.5e38.  PLAIN: extracted and converted as the other widths are, two instructions each as well, without
+// the shifted copy of the word: faster where the code has two vectors to decode (124 M elements, two vectors, rank 4: 497 us
+// a step, 500 by nibbles), not where it has one (381, 380) or where decode and rounding of a stream are all there is
+// (random-k, 1.3 G elements: 1831, 1818).
+template <int BITS, bool PLAIN = false>
 __device__ __forceinline__ void code_values(uint32_t c0, uint32_t c1, float q[8])
 {
-    if constexpr (BITS == 4) {
+    if constexpr (BITS == 4 && !PLAIN) {
         fields_over_16(c0, q);
 #pragma unroll
         for (int e = 0; e < 8; ++e) q[e] *= 16.0f;

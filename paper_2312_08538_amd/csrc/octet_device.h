@@ -77,13 +77,13 @@ __device__ __forceinline__ void add_codes(const RawCodes<BITS> &r, float p[8])
 {
     const float step = r.scale * inv_levels(BITS);
     float q[8];
-    code_values<BITS>(r.c0, r.c1, q);
+    code_values<BITS, true>(r.c0, r.c1, q);
 #pragma unroll
     for (int e = 0; e < 8; ++e) p[e] = __builtin_fmaf(step, q[e], p[e]);
 }
 
 // omb: 1 - beta of the partial update in the P and Q+ passes (Algorithm 4 line 5), 1 in the err pass
-template <bool BF16, int BITS>
+template <bool BF16, int BITS, bool TWO>
 __device__ __forceinline__ void decode_octet(const RawOctet<BF16, BITS> &r, float omb, float p[8])
 {
     float g[8];
@@ -101,7 +101,7 @@ __device__ __forceinline__ void decode_octet(const RawOctet<BF16, BITS> &r, floa
     }
     const float step = r.scale * inv_levels(BITS) * omb;
     float q[8];
-    code_values<BITS>(r.c0, r.c1, q);
+    code_values<BITS, TWO>(r.c0, r.c1, q);
 #pragma unroll
     for (int e = 0; e < 8; ++e) p[e] = __builtin_fmaf(step, q[e], g[e]);
 }
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(256) void k_err_octet(DevicePlan dp, const void *__
     // One row of this lane: decode, residual, block max-norm, rounding, store.
     auto process = [&](const RawOctet<BF16, BITS> &oct, const RawCodes<BITS> &oct2, const float (&ph)[RP], int row, bool valid) {
         float x[8];
-        decode_octet<BF16, BITS>(oct, 1.0f, x);
+        decode_octet<BF16, BITS, TWO>(oct, 1.0f, x);
         if (TWO) add_codes<BITS>(oct2, x);
         float a = 0.0f;
 #pragma unroll
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(256) void k_err_octet(DevicePlan dp, const void *__
         if (TWO) {
             const float dnew = a * inv_levels(BITS);
             float a2 = 0.0f, qn[8];
-            code_values<BITS>(w[0], w[1], qn);
+            code_values<BITS, true>(w[0], w[1], qn);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 x[e] = x[e] - dnew * qn[e];
@@ -378,7 +378,7 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
             float a = 0.0f;
 #pragma unroll
             for (int h = 0; h < NT; ++h) {
-                decode_octet<BF16, BITS>(in.o[h][v], 1.0f, x[h]);
+                decode_octet<BF16, BITS, TWO>(in.o[h][v], 1.0f, x[h]);
                 if (TWO) add_codes<BITS>(in.o2[TWO ? h : 0][TWO ? v : 0], x[h]);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
@@ -403,7 +403,7 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
                 }
                 if (TWO) {
                     float qn[8];
-                    code_values<BITS>(w[h][0], w[h][1], qn);
+                    code_values<BITS, true>(w[h][0], w[h][1], qn);
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
                         x[h][e] = x[h][e] - dnew * qn[e];
@@ -524,7 +524,7 @@ __device__ __forceinline__ void q_octet(const DevicePlan &dp, int block, float *
 #pragma unroll
         for (int s = 0; s < kLoads; ++s) {
             float p[8];
-            decode_octet<BF16, BITS>(cur.o[s], dp.omb, p);
+            decode_octet<BF16, BITS, TWO>(cur.o[s], dp.omb, p);
             if (TWO) add_codes<BITS>(cur.o2[s], p);
             float4 *dst = reinterpret_cast<float4 *>(T + (lrow + 8 * s) * kQTilePitch + loct * 8);
             dst[0] = make_float4(p[0], p[1], p[2], p[3]);
@@ -756,7 +756,7 @@ __device__ __forceinline__ void p_octet(const DevicePlan &dp, int block, float *
             RawOctet<BF16, BITS> o;
             o.g0 = cur[s].g0; o.g1 = cur[s].g1; o.c0 = k0.c0; o.c1 = k0.c1; o.scale = k0.scale;
             float p[8];
-            decode_octet<BF16, BITS>(o, dp.omb, p);
+            decode_octet<BF16, BITS, TWO>(o, dp.omb, p);
             if (TWO) add_codes<BITS>(staged(cstage, sstage), p);
             float4 *dst = reinterpret_cast<float4 *>(T + rr * kTileStride + loct * 8);
             dst[0] = make_float4(p[0], p[1], p[2], p[3]);
