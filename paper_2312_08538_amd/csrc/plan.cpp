@@ -596,6 +596,10 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         plan.ws_doubles = (size_t)round_up(wd, 32);
         plan.workspace_bytes = (size_t)round_up((int64_t)plan.ws_doubles * 8, 256);
 
+        // the longest table, an entry per 1024 elements
+        int64_t n_elem = 0;
+        for (const MatDesc &d : plan.mats) n_elem += ceil_div(d.N, 1024);
+        plan.elem_items.reserve((size_t)n_elem);
         for (int l = 0; l < n_mats; ++l) {
             const MatDesc &d = plan.mats[l];
             // passes of the MFMA family that exist; the others fall back to the generic kernels
