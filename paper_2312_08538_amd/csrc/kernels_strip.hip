@@ -1,8 +1,9 @@
 // Strip kernel family: the three passes for any layout (any number of columns, any rank up to 32, blocks that straddle
 // rows).  A wave works on strips of 64 neighbouring columns, a lane owns a column of the strip and the row is uniform over
 // the wave: a row of the strip is one coalesced access of the gradient (one element per lane, whatever the alignment of
-// the row), and everything that depends on the row alone (64-bit addresses, the division of the flat index by the block,
-// the row of a factor) is computed and loaded once per wave on the scalar side.
+// the row).  The 64-bit addresses of a workgroup's first block are formed once, on the scalar side; an element is a 32-bit
+// distance from there, from which each lane takes its code word and block by shifts (a division where the block is not a
+// power of two).  The row of a factor is a scalar operand.
 //
 // The element source is a template parameter: the quantiser's codes and scales (one or two error vectors) or the count
 // sketch's table in its row or column form.
@@ -11,11 +12,11 @@
 //             wave-private LDS tile into the operand layout of the fp64 matrix cores; the four waves' sums are added in
 //             wave order.  Products of fp32 values are exact in fp64, the sum stays in fp64, one rounding.
 //   Q+ pass   a workgroup per (strip, row tile), a quarter of the rows per wave; a lane adds up its column's r sums in
-//             fp64 registers, the row of P^ being a scalar operand.
+//             fp64 registers, the row of P^ being a scalar operand.  Matrices of a few rows: a strip per wave (k_q_flat).
 //   err pass  a workgroup per run of whole scale blocks: the residual (the fp32 fma chain over c = 0..r-1, a lane's row of
 //             Q+ in registers, the row of P^ on the scalar side) goes to LDS in the order of the flat index, then the
 //             workgroup walks the run in octets as the octet family does: block max-norm by DPP, one Philox call per
-//             eight elements, rounding, pack, in place.
+//             eight elements, rounding, pack, in place.  Matrices of a few columns: groups of rows that fill a wave.
 //
 // All sums are combined in a fixed order: results do not depend on scheduling.
 #include <type_traits>
