@@ -27,10 +27,11 @@ __global__ __launch_bounds__(256) CONEF_P_OCTET_WAVES(false)
 void k_p_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Q, float *P, double *ws)
 {
-    __shared__ __attribute__((aligned(16))) float lds[larger(p_octet_lds<false>(), kPStripLds)];
+    __shared__ __attribute__((aligned(16))) float lds[larger(kPOctetLds, kPStripLds)];
     const int b = blockIdx.x;
     if (b >= lead) {
-        p_octet<BF16, BITS, RH, false>(dp, b - lead, lds, grads, codes, scales, Q, P, ws);
+        const POctetLds o = {lds, reinterpret_cast<uint32_t *>(lds + kPOctetTiles), lds + kPOctetTiles + kPOctetCodes, nullptr, nullptr};
+        p_octet<BF16, BITS, RH, false>(dp, b - lead, o, grads, codes, scales, Q, P, ws);
     } else if (b < dp.n_p) {
         const Source src = {grads, codes, scales, nullptr};
         p_strip<kSrcOne, RH>(dp, b, lds, src, Q, P, ws);

@@ -34,7 +34,12 @@ __global__ __launch_bounds__(256) CONEF_P_OCTET_WAVES(TWO)
 void k_p_octet(DevicePlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Q, float *P, double *ws)
 {
-    __shared__ __attribute__((aligned(16))) float lds[p_octet_lds<TWO>()];
+    __shared__ __attribute__((aligned(16))) float tiles[kPOctetTiles];
+    __shared__ __attribute__((aligned(16))) uint32_t code[kPOctetCodes];
+    __shared__ float scale[kPOctetScales];
+    __shared__ __attribute__((aligned(16))) uint32_t code1[TWO ? kPOctetCodes : 4];
+    __shared__ float scale1[TWO ? kPOctetScales : 1];
+    const POctetLds lds = {tiles, code, scale, code1, scale1};
     p_octet<BF16, BITS, RH, TWO>(dp, blockIdx.x, lds, grads, codes, scales, Q, P, ws);
 }
 

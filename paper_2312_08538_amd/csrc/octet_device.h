@@ -592,28 +592,36 @@ constexpr int kCodePitch = 34;      // words per row of the code stage: 128 byte
 constexpr int kScalePitch = 9;      // floats per row of the scale stage: up to 8 blocks per group + 1
 
 constexpr int kPOctetTiles = 4 * kPTileRows * kTileStride, kPOctetCodes = kPTileRows * kCodePitch, kPOctetScales = kPTileRows * kScalePitch;
-template <bool TWO>
-constexpr int p_octet_lds() { return kPOctetTiles + (TWO ? 2 : 1) * (kPOctetCodes + kPOctetScales); }       // 4-byte words
+constexpr int kPOctetLds = kPOctetTiles + kPOctetCodes + kPOctetScales;         // 4-byte words, one vector
+
+// LDS of the P pass: kPOctetTiles, kPOctetCodes and kPOctetScales words (TWO: code1 and scale1 as many for the first vector).
+// The pass's own kernel has an array for each: the compiler then knows them apart (two vectors, 124 M elements: 1 % of the
+// pass).
+struct POctetLds {
+    float *tiles;
+    uint32_t *code;
+    float *scale;
+    uint32_t *code1;
+    float *scale1;
+};
 
 // TWO: p = g + e~ + q; the plan's first error vector (dp.i_codes) is staged beside the codes / scales arguments.
 // (the second stage costs LDS: two workgroups per CU instead of three)
-// lds: p_octet_lds<TWO>() words; `block` of `n_blocks`: index of the workgroup among those of this pass
+// `block`: index of the workgroup among those of this pass
 #define CONEF_P_OCTET_WAVES(TWO) __attribute__((amdgpu_waves_per_eu(TWO ? 2 : 3, TWO ? 2 : 3)))
 template <bool BF16, int BITS, int RH, bool TWO>
-__device__ __forceinline__ void p_octet(const DevicePlan &dp, int block, float *lds, const void *__restrict__ grads,
+__device__ __forceinline__ void p_octet(const DevicePlan &dp, int block, const POctetLds &lds, const void *__restrict__ grads,
                                         const uint32_t *__restrict__ codes, const float *__restrict__ scales,
                                         const float *__restrict__ Q, float *P, double *ws)
 {
     constexpr int kGroupCols = 1024 / BITS;                 // 512, 256, 128
     constexpr int kGroupSteps = kGroupCols / kStepCols;     // 4, 2, 1
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    uint32_t *cstage = reinterpret_cast<uint32_t *>(lds + kPOctetTiles);
-    float *sstage = lds + kPOctetTiles + kPOctetCodes;
-    uint32_t *cstage1 = reinterpret_cast<uint32_t *>(sstage + kPOctetScales);      // TWO: the first vector
-    float *sstage1 = sstage + kPOctetScales + kPOctetCodes;
+    uint32_t *cstage = lds.code, *cstage1 = lds.code1;
+    float *sstage = lds.scale, *sstage1 = lds.scale1;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    float *T = lds + wave * (kPTileRows * kTileStride);
+    float *T = lds.tiles + wave * (kPTileRows * kTileStride);
     const WorkItem it = dp.p_f_items[xcd_contiguous_item(block, dp.n_p_f)];
     const MatDesc d = dp.mats[it.mat];
     const int r = dp.rank;
@@ -787,7 +795,7 @@ __device__ __forceinline__ void p_octet(const DevicePlan &dp, int block, float *
     // ---- the four waves' sums, added in wave order.  D of block (lane % 16) / 4, entry [lane / 16][lane % 4]:
     // row 16 t + 4 ((lane % 16) / 4) + lane / 16 of the tile, factor column lane % 4 + 4 h
     __syncthreads();
-    double *red = reinterpret_cast<double *>(lds);      // [wave][row][8], 16 KB of the 36 KB of tiles
+    double *red = reinterpret_cast<double *>(lds.tiles);      // [wave][row][8], 16 KB of the 36 KB of tiles
     const int drow = 4 * (mi >> 2) + mk;
 #pragma unroll
     for (int t = 0; t < 4; ++t)
