@@ -85,6 +85,8 @@ int ensure_uploaded(conef_ctx *ctx)
     if ((rc = upload(ctx, pl.pred_items, &d.pred_items))) return rc;
     if ((rc = upload(ctx, pl.gram_items, &d.gram_items))) return rc;
     if ((rc = upload(ctx, pl.apply_items, &d.apply_items))) return rc;
+    if ((rc = upload(ctx, pl.gram_s_items, &d.gram_s_items))) return rc;
+    if ((rc = upload(ctx, pl.apply_s_items, &d.apply_s_items))) return rc;
     if ((rc = upload(ctx, pl.qred_items, &d.qred_items))) return rc;
     if ((rc = upload(ctx, pl.elem_items, &d.elem_items))) return rc;
     if ((rc = upload(ctx, pl.rb_items, &d.rb_items))) return rc;
@@ -142,6 +144,8 @@ int ensure_uploaded(conef_ctx *ctx)
     d.n_pred = (int)pl.pred_items.size();
     d.n_gram = (int)pl.gram_items.size();
     d.n_apply = (int)pl.apply_items.size();
+    d.n_gram_s = (int)pl.gram_s_items.size();
+    d.n_apply_s = (int)pl.apply_s_items.size();
     d.n_qred = (int)pl.qred_items.size();
     d.n_elem = (int)pl.elem_items.size();
     d.q_elems = (long long)pl.q_elems;
@@ -330,8 +334,10 @@ int conef_offsets(const conef_ctx *ctx, int mat, size_t *grad_off, size_t *word_
     return CONEF_OK;
 }
 
-int conef_step_p(conef_ctx *ctx, const void *grads, const uint32_t *err_codes, const float *err_scales,
-                 const float *Q_state, float *P_raw_out, void *workspace, void *hip_stream)
+namespace {
+// add_chunks (here and in the other P stages): false in a full step whose orthonormalisation adds the column chunks of P up
+int step_p_impl(conef_ctx *ctx, const void *grads, const uint32_t *err_codes, const float *err_scales,
+                const float *Q_state, float *P_raw_out, void *workspace, void *hip_stream, bool add_chunks)
 {
     if (!ctx || !grads || !err_codes || !err_scales || !Q_state || !P_raw_out || !workspace) return CONEF_EINVAL;
     if (ctx->plan.sketch) return CONEF_ESTATE;
@@ -341,22 +347,31 @@ int conef_step_p(conef_ctx *ctx, const void *grads, const uint32_t *err_codes, c
     int rc = ensure_uploaded(ctx);
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    return hip_rc(launch_pass_p(ctx->dev, grads, err_codes, err_scales, Q_state, P_raw_out, ws_doubles(ctx, workspace), st,
-                                stage_span(ctx, 0)));
+    return hip_rc(launch_pass_p(ctx->dev, grads, err_codes, err_scales, Q_state, P_raw_out, ws_doubles(ctx, workspace),
+                                add_chunks || !orth_adds_chunks(ctx->dev), st, stage_span(ctx, 0)));
+}
+}  // namespace
+
+int conef_step_p(conef_ctx *ctx, const void *grads, const uint32_t *err_codes, const float *err_scales,
+                 const float *Q_state, float *P_raw_out, void *workspace, void *hip_stream)
+{
+    return step_p_impl(ctx, grads, err_codes, err_scales, Q_state, P_raw_out, workspace, hip_stream, true);
 }
 
 namespace {
+// p_chunks: the workspace holds the column chunks of P that the P stage of the same step has not added up
 // tr_a / tr_b: block scales of the error vector(s) of a full step, copied column block by column block for the rank-32
 // family's Q+ and err passes inside this stage's launches (null in the stage call)
-int orthonormalise_impl(conef_ctx *ctx, float *P_inout, void *workspace, void *hip_stream, const float *tr_a = nullptr,
-                        const float *tr_b = nullptr)
+int orthonormalise_impl(conef_ctx *ctx, float *P_inout, void *workspace, void *hip_stream, bool p_chunks,
+                        const float *tr_a = nullptr, const float *tr_b = nullptr)
 {
     if (!ctx || !P_inout || !workspace) return CONEF_EINVAL;
     if (misaligned(P_inout, 16) || misaligned(workspace, 256)) return CONEF_EINVAL;
     int rc = ensure_uploaded(ctx);
     if (rc) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    return hip_rc(launch_orthonormalise(ctx->dev, P_inout, ws_doubles(ctx, workspace), st, stage_span(ctx, 1), tr_a, tr_b));
+    return hip_rc(launch_orthonormalise(ctx->dev, P_inout, ws_doubles(ctx, workspace), p_chunks && orth_adds_chunks(ctx->dev), st,
+                                        stage_span(ctx, 1), tr_a, tr_b));
 }
 
 int step_q_impl(conef_ctx *ctx, const void *grads, const uint32_t *err_codes, const float *err_scales,
@@ -365,7 +380,7 @@ int step_q_impl(conef_ctx *ctx, const void *grads, const uint32_t *err_codes, co
 
 int conef_orthonormalise(conef_ctx *ctx, float *P_inout, void *workspace, void *hip_stream)
 {
-    return orthonormalise_impl(ctx, P_inout, workspace, hip_stream);
+    return orthonormalise_impl(ctx, P_inout, workspace, hip_stream, false);
 }
 
 int conef_step_q(conef_ctx *ctx, const void *grads, const uint32_t *err_codes, const float *err_scales,
@@ -418,10 +433,10 @@ int conef_step(conef_ctx *ctx, const void *grads, uint32_t *err_codes, float *er
 {
     int rc;
     if (ctx && ctx->timing) { ctx->slot = (int)(ctx->steps_timed % kTimingSlots); ++ctx->steps_timed; }
-    if ((rc = conef_step_p(ctx, grads, err_codes, err_scales, Q_state, P_out, workspace, hip_stream))) return rc;
+    if ((rc = step_p_impl(ctx, grads, err_codes, err_scales, Q_state, P_out, workspace, hip_stream, false))) return rc;
     /* exchange point 1: mean of P over the workers -- identity for one worker */
     if (!err_scales) return CONEF_EINVAL;
-    if ((rc = orthonormalise_impl(ctx, P_out, workspace, hip_stream, err_scales))) return rc;
+    if ((rc = orthonormalise_impl(ctx, P_out, workspace, hip_stream, true, err_scales))) return rc;
     if ((rc = step_q_impl(ctx, grads, err_codes, err_scales, P_out, Q_out, workspace, hip_stream, true))) return rc;
     /* exchange point 2: mean of Q over the workers -- identity for one worker; the operand splits
        of P^ and Q+ made by the Q+ stage are therefore still valid for the err stage */
@@ -498,7 +513,7 @@ struct PlanWithFirst {
 };
 
 int i_step_p_impl(conef_ctx *ctx, const void *grads, const uint32_t *c1, const float *s1, const uint32_t *c2, const float *s2,
-                  const float *Q_state, float *P_raw_out, void *workspace, void *hip_stream)
+                  const float *Q_state, float *P_raw_out, void *workspace, void *hip_stream, bool add_chunks)
 {
     if (!ctx || !grads || !c1 || !s1 || !c2 || !s2 || !Q_state || !P_raw_out || !workspace) return CONEF_EINVAL;
     int rc = i_lowrank_state(ctx);
@@ -508,7 +523,7 @@ int i_step_p_impl(conef_ctx *ctx, const void *grads, const uint32_t *c1, const f
         return CONEF_EINVAL;
     if ((rc = ensure_uploaded(ctx))) return rc;
     return hip_rc(launch_pass_p(PlanWithFirst(ctx, c1, s1).dp, grads, c2, s2, Q_state, P_raw_out, ws_doubles(ctx, workspace),
-                                static_cast<hipStream_t>(hip_stream), stage_span(ctx, 0)));
+                                add_chunks || !orth_adds_chunks(ctx->dev), static_cast<hipStream_t>(hip_stream), stage_span(ctx, 0)));
 }
 
 int i_step_q_impl(conef_ctx *ctx, const void *grads, const uint32_t *c1, const float *s1, const uint32_t *c2, const float *s2,
@@ -529,7 +544,7 @@ int conef_i_step_p(conef_ctx *ctx, const void *grads, const uint32_t *err_codes,
                    const uint32_t *err2_codes, const float *err2_scales, const float *Q_state, float *P_raw_out,
                    void *workspace, void *hip_stream)
 {
-    return i_step_p_impl(ctx, grads, err_codes, err_scales, err2_codes, err2_scales, Q_state, P_raw_out, workspace, hip_stream);
+    return i_step_p_impl(ctx, grads, err_codes, err_scales, err2_codes, err2_scales, Q_state, P_raw_out, workspace, hip_stream, true);
 }
 
 int conef_i_step_q(conef_ctx *ctx, const void *grads, const uint32_t *err_codes, const float *err_scales,
@@ -571,10 +586,10 @@ int conef_i_step(conef_ctx *ctx, const void *grads, uint32_t *err_codes, float *
 {
     int rc;
     if (ctx && ctx->timing) { ctx->slot = (int)(ctx->steps_timed % kTimingSlots); ++ctx->steps_timed; }
-    if ((rc = i_step_p_impl(ctx, grads, err_codes, err_scales, err2_codes, err2_scales, Q_state, P_out, workspace, hip_stream)))
+    if ((rc = i_step_p_impl(ctx, grads, err_codes, err_scales, err2_codes, err2_scales, Q_state, P_out, workspace, hip_stream, false)))
         return rc;
     // the second vector's scales go to the first workspace region, the first vector's to the second (as launch_pass_q does)
-    if ((rc = orthonormalise_impl(ctx, P_out, workspace, hip_stream, err2_scales, err_scales))) return rc;
+    if ((rc = orthonormalise_impl(ctx, P_out, workspace, hip_stream, true, err2_scales, err_scales))) return rc;
     if ((rc = i_step_q_impl(ctx, grads, err_codes, err_scales, err2_codes, err2_scales, P_out, Q_out, workspace, hip_stream, true)))
         return rc;
     return i_step_err_impl(ctx, grads, err_codes, err_scales, err2_codes, err2_scales, P_out, Q_out, workspace, step, hip_stream,
@@ -906,8 +921,9 @@ int conef_cs_ss_step(conef_ctx *ctx, const void *grads, void *table, uint32_t *s
 }
 
 // ---------------------------------------------------------------- count-sketch mode
-int conef_cs_step_p(conef_ctx *ctx, const void *grads, const void *table, const float *Q_state, float *P_raw_out,
-                    void *workspace, void *hip_stream)
+namespace {
+int cs_step_p_impl(conef_ctx *ctx, const void *grads, const void *table, const float *Q_state, float *P_raw_out,
+                   void *workspace, void *hip_stream, bool add_chunks)
 {
     if (!ctx || !grads || !table || !Q_state || !P_raw_out || !workspace) return CONEF_EINVAL;
     if (!ctx->plan.sketch) return CONEF_ESTATE;
@@ -917,7 +933,14 @@ int conef_cs_step_p(conef_ctx *ctx, const void *grads, const void *table, const 
     int rc = ensure_uploaded(ctx);
     if (rc) return rc;
     return hip_rc(launch_cs_pass_p(ctx->dev, grads, table, Q_state, P_raw_out, ws_doubles(ctx, workspace),
-                                   static_cast<hipStream_t>(hip_stream), stage_span(ctx, 0)));
+                                   add_chunks || !orth_adds_chunks(ctx->dev), static_cast<hipStream_t>(hip_stream), stage_span(ctx, 0)));
+}
+}  // namespace
+
+int conef_cs_step_p(conef_ctx *ctx, const void *grads, const void *table, const float *Q_state, float *P_raw_out,
+                    void *workspace, void *hip_stream)
+{
+    return cs_step_p_impl(ctx, grads, table, Q_state, P_raw_out, workspace, hip_stream, true);
 }
 
 int conef_cs_step_q(conef_ctx *ctx, const void *grads, const void *table, const float *P_hat, float *Q_out,
@@ -953,9 +976,9 @@ int conef_cs_step(conef_ctx *ctx, const void *grads, void *table, const float *Q
 {
     int rc;
     if (ctx && ctx->timing) { ctx->slot = (int)(ctx->steps_timed % kTimingSlots); ++ctx->steps_timed; }
-    if ((rc = conef_cs_step_p(ctx, grads, table, Q_state, P_out, workspace, hip_stream))) return rc;
+    if ((rc = cs_step_p_impl(ctx, grads, table, Q_state, P_out, workspace, hip_stream, false))) return rc;
     /* exchange point 1: mean of P over the workers -- identity for one worker */
-    if ((rc = orthonormalise_impl(ctx, P_out, workspace, hip_stream))) return rc;
+    if ((rc = orthonormalise_impl(ctx, P_out, workspace, hip_stream, true))) return rc;
     if ((rc = conef_cs_step_q(ctx, grads, table, P_out, Q_out, workspace, hip_stream))) return rc;
     /* exchange point 2: mean of Q over the workers -- identity for one worker */
     return conef_cs_step_err(ctx, grads, table, P_out, Q_out, workspace, hip_stream);

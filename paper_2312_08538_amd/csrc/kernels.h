@@ -34,6 +34,8 @@ struct DevicePlan {
     float beta = 0.0f, omb = 1.0f;  // beta and fl32(1 - beta)
     const WorkItem *pred_items = nullptr, *gram_items = nullptr, *apply_items = nullptr, *qred_items = nullptr,
                    *elem_items = nullptr;
+    const OrthItem *gram_s_items = nullptr, *apply_s_items = nullptr;      // orthonormalisation, ranks up to 8
+    int n_gram_s = 0, n_apply_s = 0;
     int n_mats = 0;
     int n_p = 0, n_q = 0, n_err = 0, n_p_f = 0, n_q_f = 0, n_err_f = 0, n_err_t = 0;
     int n_p_m = 0, n_q_m = 0, n_err_m = 0, n_split_p = 0, n_split_qn = 0;
@@ -66,12 +68,15 @@ struct Span {
 };
 
 // Each launcher enqueues on `st` and returns hipGetLastError().  `ws` is the caller's workspace.
+// add_chunks: the partial sums of column chunks are added up into P; a full step leaves that to launch_orthonormalise's first
+// launch (p_chunks there) where orth_adds_chunks says so
 hipError_t launch_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
-                         const float *Q, float *P, double *ws, hipStream_t st, Span span = Span());
+                         const float *Q, float *P, double *ws, bool add_chunks, hipStream_t st, Span span = Span());
+inline bool orth_adds_chunks(const DevicePlan &dp) { return dp.rpad <= 8; }
 // tr_a / tr_b (the full step only): block scales of the error vector(s) whose column-block-major copies are made for
 // the rank-32 family alongside the factorisations (into the first / the second workspace region); launch_pass_q is then
 // called with scales_ready
-hipError_t launch_orthonormalise(const DevicePlan &dp, float *P, double *ws, hipStream_t st,
+hipError_t launch_orthonormalise(const DevicePlan &dp, float *P, double *ws, bool p_chunks, hipStream_t st,
                                  Span span = Span(), const float *tr_a = nullptr, const float *tr_b = nullptr);
 hipError_t launch_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
                          const float *Phat, float *Qout, double *ws, bool scales_ready, hipStream_t st,
@@ -112,7 +117,7 @@ void launch_ss_clear(const DevicePlan &dp, uint32_t *sign_words, hipStream_t st)
 
 // Count-sketch mode: the same three passes with a table as the error state.
 hipError_t launch_cs_pass_p(const DevicePlan &dp, const void *grads, const void *table, const float *Q, float *P,
-                            double *ws, hipStream_t st, Span span = Span());
+                            double *ws, bool add_chunks, hipStream_t st, Span span = Span());
 hipError_t launch_cs_pass_q(const DevicePlan &dp, const void *grads, const void *table, const float *Phat, float *Qout,
                             double *ws, hipStream_t st, Span span = Span());
 hipError_t launch_cs_pass_err(const DevicePlan &dp, const void *grads, void *table, const float *Phat, const float *Qn,

@@ -549,7 +549,7 @@ hipError_t launch_pass_err_two(const DevicePlan &dp, const void *grads, uint32_t
 
 // A stage's span brackets its main pass kernels (both families), not the small reductions after them.
 hipError_t launch_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
-                         const float *Q, float *P, double *ws, hipStream_t st, Span span)
+                         const float *Q, float *P, double *ws, bool add_chunks, hipStream_t st, Span span)
 {
     if (span.begin) (void)hipEventRecord(span.begin, st);
     mfma_pass_p(dp, grads, codes, scales, Q, P, st);
@@ -559,7 +559,7 @@ hipError_t launch_pass_p(const DevicePlan &dp, const void *grads, const uint32_t
         strip_pass_p(dp, grads, codes, scales, Q, P, ws, st);
     }
     if (span.end) (void)hipEventRecord(span.end, st);
-    generic_p_reduce(dp, ws, P, st);
+    if (add_chunks) generic_p_reduce(dp, ws, P, st);
     return hipGetLastError();
 }
 

@@ -1,15 +1,13 @@
 // Orthonormalisation of all left factors of a model: P^ = thin-QR factor of P with positive
 // diagonal of R, by Cholesky-QR in fp64:  G = P^T P,  G = R^T R,  P^ = P R^-1.  In exact arithmetic
-// this is the matrix Gram-Schmidt produces.  Four grouped launches (three for ranks up to 8, where
-// k_gram_sum_cholesky does the work of the second and the third):
+// this is the matrix Gram-Schmidt produces.  Ranks up to 8 take two grouped launches (k_gram_small, k_cholesky_apply), higher
+// ones four:
 //   k_gram_partial      fp64 Gram matrices of row tiles (4 x 4 register blocks per thread); at rank 32
 //                       k_gram_mfma32 does the same on the fp64 matrix cores, straight from global memory,
 //   k_gram_reduce       the tiles of a matrix added up: 16 interleaved partial sums per entry, each
 //                       in tile order, then those in order,
-//   k_cholesky_inverse  per matrix: factorisation and inversion of the triangle inside one wave (a
-//                       lane owns a column; rows are broadcast with v_readlane, no LDS traffic and
-//                       no barriers in the O(r^3) part).  This launch leaves the chip almost empty, so
-//                       the full step hands it the copy of the block scales that the rank-32 family's
+//   k_cholesky_inverse  per matrix: factorisation and inversion of the triangle, a workgroup each.  This launch leaves the
+//                       chip almost empty, so the full step hands it the copy of the block scales that the rank-32 family's
 //                       Q+ and err passes read (extra workgroups behind the matrices'),
 //   k_apply_rinv        P^ = P R^-1 on 64-row tiles staged through LDS; at rank 32 k_apply_mfma32 on the fp64
 //                       matrix cores, a wave per 64 rows, straight from and to global memory.
@@ -21,13 +19,6 @@
 namespace conef {
 
 namespace {
-
-__device__ __forceinline__ double bcast(double v, int src_lane)
-{
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src_lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src_lane);
-    return __hiloint2double(hi, lo);
-}
 
 // ---------------------------------------------------------------- partial Gram matrices
 // One workgroup per row tile (d.gram_tile_rows rows, walked in pieces of kGramRows).  The RP x RP
@@ -209,61 +200,66 @@ __device__ __forceinline__ double rsqrt_f64(double x)
     return y;
 }
 
-// One wave factors G = R^T R of one matrix and inverts R with lane j holding column j in registers (G: the r x r Gram
-// matrix in LDS with row pitch RP).  A column whose squared norm after projection is not above 1e-12 of its squared
-// norm is linearly dependent on the earlier ones: its column of R^-1 (and so of P^) is zero.  Divisions and square
-// roots are replaced by one reciprocal square root per column.
+// Factors G = R^T R (r x r, in LDS with row pitch RP) and writes R^-1 (row-major, r x r).  THREADS threads of the workgroup,
+// t = 0 .. THREADS - 1, take part: one wave, or all.  Forward elimination of the rows of [G | I], a row per trip: row c times
+// 1 / R[c][c] is row c of R and of (R^T)^-1, and a thread has its entries of both halves in registers.  A column whose squared
+// norm after projection is not above 1e-12 of its squared norm is linearly dependent on the earlier ones: its column of R^-1
+// (and so of P^) is zero.
+// The loop is not unrolled: a launch that runs its code once fetches every line of it from memory, and with all trips and lane
+// indices written out (61 KB at rank 32) that was most of its time (the stage's four launches for three matrices of 64 x 64
+// at rank 32: 40.0 -> 28.9 us).
 template <int RP>
-__device__ __forceinline__ void cholesky_inverse_wave(const double *G, int r, double *rinv)
+struct CholeskyLds {
+    double G[RP * RP];
+    double row_g[2][RP], row_y[2][RP];
+};
+
+template <int RP, int THREADS>
+__device__ __forceinline__ void cholesky_inverse(CholeskyLds<RP> &lds, int t, int r, double *rinv)
 {
-    const int j = threadIdx.x;                         // this lane's column (lanes >= r idle along)
-    double col[RP];
+    constexpr int V = RP * RP > THREADS ? RP * RP / THREADS : 1, kRows = THREADS / RP;
+    const int j = t % RP, i0 = t / RP;
+    double g[V], y[V];
 #pragma unroll
-    for (int i = 0; i < RP; ++i) col[i] = (i < r && j < r) ? G[i * RP + j] : 0.0;
-    double dg = 0.0;                                   // G[j][j] before any update (selected without dynamic indexing)
+    for (int v = 0; v < V; ++v) {
+        const int i = i0 + v * kRows;
+        g[v] = i < r && j < r ? lds.G[i * RP + j] : 0.0;
+        y[v] = i == j ? 1.0 : 0.0;
+    }
+#pragma unroll 1
+    for (int c = 0; c < r; ++c) {
+        double *row_g = lds.row_g[c & 1], *row_y = lds.row_y[c & 1];
 #pragma unroll
-    for (int i = 0; i < RP; ++i) dg = (i == j) ? col[i] : dg;
-    bool dead_j = false;
-    double dinv = 0.0;                                 // 1 / R[j][j]
-    // right-looking Cholesky: after step c, col[c] holds R[c][j]
+        for (int v = 0; v < V; ++v) {
+            if (i0 + v * kRows == c) {
+                row_g[j] = g[v];
+                row_y[j] = y[v];
+            }
+        }
+        if (THREADS > 64) __syncthreads();
+        else wave_lds_sync();
+        const double dcc = row_g[c], gcc = lds.G[c * RP + c];
+        const double ri = dcc > 1e-12 * gcc ? rsqrt_f64(dcc) : 0.0;        // 1 / R[c][c]
+        const double rj = row_g[j] * ri, yj = row_y[j] * ri;
 #pragma unroll
-    for (int c = 0; c < RP; ++c) {
-        if (c < r) {                                   // uniform
-            const double dcc = bcast(col[c], c), gcc = bcast(dg, c);
-            const bool dead = !(dcc > 1e-12 * gcc);
-            const double ri = dead ? 1.0 : rsqrt_f64(dcc);     // 1 / R[c][c]
-            double rcj = 0.0;
-            if (j == c) { rcj = dead ? 1.0 : dcc * ri; dead_j = dead; dinv = ri; }
-            else if (j > c && !dead) rcj = col[c] * ri;
-            col[c] = rcj;
-#pragma unroll
-            for (int i = c + 1; i < RP; ++i)
-                if (i < r) col[i] = __builtin_fma(-bcast(rcj, i), rcj, col[i]);
+        for (int v = 0; v < V; ++v) {
+            const int i = i0 + v * kRows;
+            if (i == c) y[v] = yj;
+            if (i > c && i < RP) {
+                const double rci = row_g[i] * ri;
+                g[v] = __builtin_fma(-rci, rj, g[v]);
+                y[v] = __builtin_fma(-rci, yj, y[v]);
+            }
         }
     }
-    // inverse of the upper triangle: x[i] = (R^-1)[i][j]
-    double x[RP];
 #pragma unroll
-    for (int i = 0; i < RP; ++i) x[i] = (i == j && !dead_j) ? dinv : 0.0;
-#pragma unroll
-    for (int i = RP - 2; i >= 0; --i) {
-        if (i < r) {
-            double s = 0.0;
-#pragma unroll
-            for (int k = i + 1; k < RP; ++k)
-                if (k < r) s = __builtin_fma(bcast(col[i], k), x[k], s);      // R[i][k] * x[k]; x[k] = 0 for k > j
-            const double di = bcast(dinv, i);
-            if (i < j && !dead_j) x[i] = -s * di;
-        }
-    }
-    if (j < r) {
-#pragma unroll
-        for (int i = 0; i < RP; ++i)
-            if (i < r) rinv[i * r + j] = x[i];
+    for (int v = 0; v < V; ++v) {
+        const int i = i0 + v * kRows;
+        if (i < r && j < r) rinv[j * r + i] = y[v];
     }
 }
 
-// Workgroups 0 .. n_mats - 1: the factorisation of one matrix each (first wave).  Workgroups behind those (the full
+// Workgroups 0 .. n_mats - 1: the factorisation of one matrix each.  Workgroups behind those (the full
 // step only): the column-block-major copy of the block scales for the rank-32 family (n_tr tiles of tr_a into the
 // first region, then n_tr tiles of tr_b into the second if tr_b is given), which fills the chip while the
 // factorisations run.
@@ -271,7 +267,7 @@ template <int RP>
 __global__ __launch_bounds__(256) void k_cholesky_inverse(DevicePlan dp, double *ws, const float *__restrict__ tr_a,
                                                           const float *__restrict__ tr_b, int n_tr)
 {
-    __shared__ double G[RP * RP];
+    __shared__ CholeskyLds<RP> lds;
     __shared__ float tile[64 * 33];
     if ((int)blockIdx.x >= dp.n_mats) {
         const int item = (int)blockIdx.x - dp.n_mats;
@@ -282,48 +278,9 @@ __global__ __launch_bounds__(256) void k_cholesky_inverse(DevicePlan dp, double 
     const MatDesc d = dp.mats[blockIdx.x];
     const int r = dp.rank;
     const int t = threadIdx.x;
-    for (int e = t; e < r * r; e += 256) G[(e / r) * RP + (e % r)] = ws[d.gsum_off + e];
+    for (int e = t; e < r * r; e += 256) lds.G[(e / r) * RP + (e % r)] = ws[d.gsum_off + e];
     __syncthreads();
-    if (t >= 64) return;
-    cholesky_inverse_wave<RP>(G, r, ws + d.rinv_off);
-}
-
-// Ranks up to 8: the sum of a matrix's partial Gram matrices (as k_gram_reduce adds them: thread (entry, part) adds
-// the tiles part, part + 16, ... in that order, then the 16 parts are added in order) and the factorisation in one
-// launch, one workgroup of 16 threads per entry per matrix.
-template <int RP>
-__global__ __launch_bounds__(16 * RP * RP) void k_gram_sum_cholesky(DevicePlan dp, double *ws)
-{
-    __shared__ double red[16][RP * RP];
-    __shared__ double G[RP * RP];
-    const MatDesc d = dp.mats[blockIdx.x];
-    const int r = dp.rank, t = threadIdx.x;
-    // thread = (slice of 16 entries, part, entry of the slice), the roles of k_gram_reduce's workgroups and threads
-    const int e = (t >> 8) * 16 + (t & 15), part = (t >> 4) & 15;
-    const bool live = e < r * r;
-    const int64_t stride = (int64_t)r * r;
-    const double *src = ws + d.gram_off + (live ? e : 0);
-    const int T = d.n_gram_tiles;
-    double s = 0.0;
-    int k = part;
-    for (; k + 48 < T; k += 64) {
-        const double v0 = src[(int64_t)k * stride], v1 = src[(int64_t)(k + 16) * stride];
-        const double v2 = src[(int64_t)(k + 32) * stride], v3 = src[(int64_t)(k + 48) * stride];
-        s = ((s + v0) + v1) + v2;
-        s += v3;
-    }
-    for (; k < T; k += 16) s += src[(int64_t)k * stride];
-    red[part][e < RP * RP ? e : 0] = (e < RP * RP) ? s : 0.0;
-    __syncthreads();
-    if (part == 0 && live) {
-        double a = red[0][e];
-#pragma unroll
-        for (int q = 1; q < 16; ++q) a += red[q][e];
-        G[(e / r) * RP + (e % r)] = a;
-    }
-    __syncthreads();
-    if (t >= 64) return;
-    cholesky_inverse_wave<RP>(G, r, ws + d.rinv_off);
+    cholesky_inverse<RP, 256>(lds, t, r, ws + d.rinv_off);
 }
 
 // ---------------------------------------------------------------- P^ = P R^-1
@@ -455,43 +412,227 @@ __global__ __launch_bounds__(256) void k_apply_mfma32(DevicePlan dp, float *P, c
     }
 }
 
+// ---------------------------------------------------------------- ranks up to 8
+// Two launches.  The first reads P (or, in a full step, adds up the column chunks of P that the P pass has left, and writes P)
+// and forms the partial Gram matrices; in the second every workgroup adds up its matrix's partial ones and factors the sum
+// for itself, one wave, while the rows it will multiply are on their way.  Bound by the round trips to memory of a launch that
+// has next to no work: with the addition of the chunks, the sum and factorisation, and the product in launches of their own
+// these were four of 3.4 - 5.3 us (18-layer residual network, rank 4: 16.2 -> 8.3 us; one matrix of 32768 x 1024 at rank 8, P in
+// one chunk: 14.8 -> 11.1).
+//
+// k_gram_small: v_mfma_f64_4x4x4_4b_f64 (operand layout at the octet family's P pass).  Lane l holds P[row l / 4 of 16][l % 4
+// (+ 4)], which is both its A and its B entry, so a load is coalesced and there is no staging; the instruction's four blocks
+// are four groups of four rows.  Wave w takes the 16-row groups w, w + 4, ... of the tile.
+template <int RP, bool CHUNKS>
+__global__ __launch_bounds__(256) void k_gram_small(DevicePlan dp, float *P, double *ws)
+{
+    constexpr int H = RP / 4, NG = H * (H + 1) / 2, U = 4;
+    __shared__ double red[4][NG][16];
+    const OrthItem it = dp.gram_s_items[blockIdx.x];
+    const int r = dp.rank;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int sub = lane >> 2, col = lane & 3;
+    const int64_t row1 = it.row1;
+    float *p = P + it.p_off;
+    double acc[NG];
+#pragma unroll
+    for (int q = 0; q < NG; ++q) acc[q] = 0.0;
+    for (int64_t g0 = it.row0 + 16 * wave; g0 < row1; g0 += 64 * U) {
+        int64_t e[U][H];
+        bool live[U][H];
+        float v[U][H];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                const int64_t row = g0 + 64 * u + sub;
+                live[u][h] = row < row1 && col + 4 * h < r;
+                e[u][h] = live[u][h] ? row * r + col + 4 * h : 0;
+            }
+        if (CHUNKS && it.chunks > 1) {               // uniform
+            const double *src = ws + it.ppart_off;
+            const int64_t len = it.n * r;
+            double s[U][H];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int h = 0; h < H; ++h) s[u][h] = 0.0;
+            for (int k0 = 0; k0 < it.chunks; k0 += 4) {      // (chunks beyond the last add 0.0)
+                double w[4][U][H];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int h = 0; h < H; ++h)
+                            w[k][u][h] = g0 + 64 * u < row1 && k0 + k < it.chunks ? src[(k0 + k) * len + e[u][h]] : 0.0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int h = 0; h < H; ++h) s[u][h] += w[k][u][h];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    v[u][h] = (float)s[u][h];
+                    if (live[u][h]) p[e[u][h]] = v[u][h];
+                }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int h = 0; h < H; ++h) v[u][h] = g0 + 64 * u < row1 ? p[e[u][h]] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (g0 + 64 * u < row1) {                   // uniform
+                double a[H];
+#pragma unroll
+                for (int h = 0; h < H; ++h) a[h] = live[u][h] ? (double)v[u][h] : 0.0;
+                acc[0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[0], a[0], acc[0], 0, 0, 0);
+                if (H == 2) {
+                    acc[NG == 3 ? 1 : 0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[0], a[H - 1], acc[NG == 3 ? 1 : 0], 0, 0, 0);
+                    acc[NG - 1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[H - 1], a[H - 1], acc[NG - 1], 0, 0, 0);
+                }
+            }
+        }
+    }
+    // D[l / 16][l % 4] of block (l / 4) % 4
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+        acc[q] += __shfl_xor(acc[q], 4, 64);
+        acc[q] += __shfl_xor(acc[q], 8, 64);
+        if ((lane & 12) == 0) red[wave][q][(lane >> 4) * 4 + col] = acc[q];
+    }
+    __syncthreads();
+    if (t < r * r) {
+        const int a = t / r, b = t - a * r;
+        const int lo = a < b ? a : b, hi = a < b ? b : a;
+        const int q = (lo >> 2) + (hi >> 2);            // blocks 00, 01, 11
+        const int idx = (lo & 3) * 4 + (hi & 3);
+        ws[it.gram_off + t] = ((red[0][q][idx] + red[1][q][idx]) + red[2][q][idx]) + red[3][q][idx];
+    }
+}
+
+// The sum of the partial Gram matrices (thread (part, entry): tiles part, part + PARTS, ... in that order, then the parts in
+// order), its factorisation, and P^ = P R^-1 for a row per thread, the products of a column in ascending k.
+template <int RP>
+__global__ __launch_bounds__(orth_threads(RP)) void k_cholesky_apply(DevicePlan dp, float *P, const double *ws)
+{
+    constexpr int E = RP * RP, THREADS = orth_threads(RP), PARTS = THREADS / E, U = 8;
+    __shared__ double red[PARTS][E], rinv[E];
+    __shared__ CholeskyLds<RP> lds;
+    const OrthItem it = dp.apply_s_items[blockIdx.x];
+    const int r = dp.rank, t = threadIdx.x;
+    float in[RP];
+    auto load_row = [&](int64_t row) {
+        const float *prow = P + it.p_off + (row < it.row1 ? row : it.row1 - 1) * r;
+        if (r == RP) {
+#pragma unroll
+            for (int c4 = 0; c4 < RP / 4; ++c4) {
+                const float4 v = reinterpret_cast<const float4 *>(prow)[c4];
+                in[4 * c4] = v.x; in[4 * c4 + 1] = v.y; in[4 * c4 + 2] = v.z; in[4 * c4 + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < RP; ++c) in[c] = prow[c < r ? c : r - 1];
+        }
+    };
+    int64_t row = it.row0 + t;
+    load_row(row);
+    {
+        const int e = t % E, part = t / E, T = it.tiles;
+        const int64_t stride = (int64_t)r * r;
+        const double *src = ws + it.gram_off + (e < r * r ? e : 0);
+        double s = 0.0;
+        for (int k = part; k < T; k += U * PARTS) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = src[(int64_t)(k + u * PARTS < T ? k + u * PARTS : k) * stride];
+#pragma unroll
+            for (int u = 0; u < U; ++u) s += k + u * PARTS < T ? v[u] : 0.0;
+        }
+        red[part][e] = s;
+    }
+    __syncthreads();
+    if (t < r * r) {
+        double a = red[0][t];
+#pragma unroll
+        for (int q = 1; q < PARTS; ++q) a += red[q][t];
+        lds.G[(t / r) * RP + (t % r)] = a;
+    }
+    __syncthreads();
+    if (t < 64) cholesky_inverse<RP, 64>(lds, t, r, rinv);
+    __syncthreads();
+    for (; row < it.row1; row += THREADS) {
+        if (row >= it.row0 + THREADS) load_row(row);
+        float out[RP];
+#pragma unroll
+        for (int c = 0; c < RP; ++c) {
+            double a = 0.0;
+            if (c < r) {                                // uniform
+#pragma unroll
+                for (int k = 0; k <= c; ++k) a = __builtin_fma((double)in[k], rinv[k * r + c], a);
+            }
+            out[c] = (float)a;
+        }
+        float *prow = P + it.p_off + row * r;
+        if (r == RP) {
+#pragma unroll
+            for (int c4 = 0; c4 < RP / 4; ++c4)
+                reinterpret_cast<float4 *>(prow)[c4] = make_float4(out[4 * c4], out[4 * c4 + 1], out[4 * c4 + 2], out[4 * c4 + 3]);
+        } else {
+#pragma unroll
+            for (int c = 0; c < RP; ++c)
+                if (c < r) prow[c] = out[c];
+        }
+    }
+}
+
 }  // namespace
 
+// ranks above 8
 #define CONEF_ORTH_DISPATCH(KERNEL, GRID, THREADS, ST, ...)                                       \
     do {                                                                                          \
-        switch (dp.rpad) {                                                                        \
-        case 4: hipLaunchKernelGGL(KERNEL<4>, GRID, dim3(THREADS), 0, ST, __VA_ARGS__); break;    \
-        case 8: hipLaunchKernelGGL(KERNEL<8>, GRID, dim3(THREADS), 0, ST, __VA_ARGS__); break;    \
-        case 16: hipLaunchKernelGGL(KERNEL<16>, GRID, dim3(THREADS), 0, ST, __VA_ARGS__); break;  \
-        default: hipLaunchKernelGGL(KERNEL<32>, GRID, dim3(THREADS), 0, ST, __VA_ARGS__); break;  \
-        }                                                                                         \
+        if (dp.rpad == 16) hipLaunchKernelGGL(KERNEL<16>, GRID, dim3(THREADS), 0, ST, __VA_ARGS__); \
+        else hipLaunchKernelGGL(KERNEL<32>, GRID, dim3(THREADS), 0, ST, __VA_ARGS__);             \
     } while (0)
 
-hipError_t launch_orthonormalise(const DevicePlan &dp, float *P, double *ws, hipStream_t st, Span span, const float *tr_a,
-                                 const float *tr_b)
+namespace {
+template <int RP>
+void orth_small(const DevicePlan &dp, float *P, double *ws, bool p_chunks, hipStream_t st)
+{
+    if (p_chunks) hipLaunchKernelGGL((k_gram_small<RP, true>), dim3(dp.n_gram_s), dim3(256), 0, st, dp, P, ws);
+    else hipLaunchKernelGGL((k_gram_small<RP, false>), dim3(dp.n_gram_s), dim3(256), 0, st, dp, P, ws);
+    hipLaunchKernelGGL(k_cholesky_apply<RP>, dim3(dp.n_apply_s), dim3(orth_threads(RP)), 0, st, dp, P, (const double *)ws);
+}
+}  // namespace
+
+hipError_t launch_orthonormalise(const DevicePlan &dp, float *P, double *ws, bool p_chunks, hipStream_t st, Span span,
+                                 const float *tr_a, const float *tr_b)
 {
     // the span covers all kernels of this stage
     if (span.begin) (void)hipEventRecord(span.begin, st);
-    if (dp.rpad == 32 && dp.rank == 32)
+    if (dp.rpad <= 8) {
+        if (dp.rpad == 4) orth_small<4>(dp, P, ws, p_chunks && dp.n_pred > 0, st);
+        else orth_small<8>(dp, P, ws, p_chunks && dp.n_pred > 0, st);
+        if (span.end) (void)hipEventRecord(span.end, st);
+        return hipGetLastError();
+    }
+    if (dp.rank == 32)
         hipLaunchKernelGGL(k_gram_mfma32, dim3(dp.n_gram), dim3(256), 0, st, dp, (const float *)P, ws);
     else
         CONEF_ORTH_DISPATCH(k_gram_partial, dim3(dp.n_gram), 256, st, dp, (const float *)P, ws);
     // tr_a / tr_b: block scales whose column-block-major copies the rank-32 family's later passes read
     const int n_tr = tr_a ? dp.n_split_p : 0;
     const int n_extra = n_tr * (tr_b ? 2 : 1);
-    if (dp.rpad <= 8 && n_extra == 0) {
-        if (dp.rpad == 4) hipLaunchKernelGGL(k_gram_sum_cholesky<4>, dim3(dp.n_mats), dim3(256), 0, st, dp, ws);
-        else hipLaunchKernelGGL(k_gram_sum_cholesky<8>, dim3(dp.n_mats), dim3(1024), 0, st, dp, ws);
-    } else {
-        switch (dp.rpad) {
-        case 4: hipLaunchKernelGGL(k_gram_reduce<4>, dim3(dp.n_mats), dim3(256), 0, st, dp, ws); break;
-        case 8: hipLaunchKernelGGL(k_gram_reduce<8>, dim3(dp.n_mats * 4), dim3(256), 0, st, dp, ws); break;
-        case 16: hipLaunchKernelGGL(k_gram_reduce<16>, dim3(dp.n_mats * 16), dim3(256), 0, st, dp, ws); break;
-        default: hipLaunchKernelGGL(k_gram_reduce<32>, dim3(dp.n_mats * 64), dim3(256), 0, st, dp, ws); break;
-        }
-        CONEF_ORTH_DISPATCH(k_cholesky_inverse, dim3(dp.n_mats + n_extra), 256, st, dp, ws, tr_a, tr_b, n_tr);
-    }
-    if (dp.rpad == 32 && dp.rank == 32)
+    if (dp.rpad == 16) hipLaunchKernelGGL(k_gram_reduce<16>, dim3(dp.n_mats * 16), dim3(256), 0, st, dp, ws);
+    else hipLaunchKernelGGL(k_gram_reduce<32>, dim3(dp.n_mats * 64), dim3(256), 0, st, dp, ws);
+    CONEF_ORTH_DISPATCH(k_cholesky_inverse, dim3(dp.n_mats + n_extra), 256, st, dp, ws, tr_a, tr_b, n_tr);
+    if (dp.rank == 32)
         hipLaunchKernelGGL(k_apply_mfma32, dim3((dp.n_apply + 3) / 4), dim3(256), 0, st, dp, P, (const double *)ws);
     else
         CONEF_ORTH_DISPATCH(k_apply_rinv, dim3(dp.n_apply), 256, st, dp, P, (const double *)ws);

@@ -1121,14 +1121,14 @@ __global__ __launch_bounds__(kCsCols) void k_cs_rb_generic(DevicePlan dp, const 
     } while (0)
 
 hipError_t launch_cs_pass_p(const DevicePlan &dp, const void *grads, const void *table, const float *Q, float *P,
-                            double *ws, hipStream_t st, Span span)
+                            double *ws, bool add_chunks, hipStream_t st, Span span)
 {
     if (span.begin) (void)hipEventRecord(span.begin, st);
     mfma_cs_pass_p(dp, grads, table, Q, P, ws, st);
     if (dp.n_p_f > 0) CONEF_CS_OCTET_DISPATCH(k_cs_p_octet, dim3(dp.n_p_f), st, dp, grads, table, Q, P, ws);
     strip_cs_pass_p(dp, grads, table, Q, P, ws, st);
     if (span.end) (void)hipEventRecord(span.end, st);
-    generic_p_reduce(dp, ws, P, st);
+    if (add_chunks) generic_p_reduce(dp, ws, P, st);
     return hipGetLastError();
 }
 

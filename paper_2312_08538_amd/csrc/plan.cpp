@@ -489,7 +489,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                     d.qs_off = wd;  wd += round_up(3 * 32 * d.m * 2 / 8, 32);
                 }
 
-                d.gram_tile_rows = d.n > 8192 ? 2 * kGramRows : kGramRows;
+                d.gram_tile_rows = rank <= 8 ? (int32_t)gram_rows_small(d.n) : d.n > 8192 ? 2 * kGramRows : kGramRows;
                 d.n_gram_tiles = (int32_t)ceil_div(d.n, d.gram_tile_rows);
                 d.gram_off = wd; wd += (int64_t)d.n_gram_tiles * rank * rank;
                 d.gsum_off = wd; wd += rank * rank;
@@ -686,8 +686,17 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 if (d.n_p_chunks > 1)
                     for (int64_t e0 = 0; e0 < d.n * rank; e0 += 256) plan.pred_items.push_back({l, (int32_t)e0, 0, 0});
             }
-            for (int32_t t = 0; t < d.n_gram_tiles; ++t) plan.gram_items.push_back({l, t, 0, 0});
-            for (int64_t r0 = 0; r0 < d.n; r0 += 64) plan.apply_items.push_back({l, (int32_t)r0, 0, 0});
+            if (rank <= 8) {
+                for (int64_t t = 0; t < d.n_gram_tiles; ++t)
+                    plan.gram_s_items.push_back({d.p_off, t * d.gram_tile_rows, std::min<int64_t>((t + 1) * d.gram_tile_rows, d.n), d.n,
+                                                 d.gram_off + t * rank * rank, d.ppart_off, d.n_gram_tiles, d.n_p_chunks, 0});
+                const int64_t per = apply_rows(rank, d.n);
+                for (int64_t r0 = 0; r0 < d.n; r0 += per)
+                    plan.apply_s_items.push_back({d.p_off, r0, std::min<int64_t>(r0 + per, d.n), d.n, d.gram_off, 0, d.n_gram_tiles, 0, 0});
+            } else {
+                for (int32_t t = 0; t < d.n_gram_tiles; ++t) plan.gram_items.push_back({l, t, 0, 0});
+                for (int64_t r0 = 0; r0 < d.n; r0 += 64) plan.apply_items.push_back({l, (int32_t)r0, 0, 0});
+            }
             // a matrix-core matrix with a single row tile gets its Q+ straight from the Q+ pass
             if (!((mf_q || d.pack || d.path == kPathGeneric) && d.n_q_tiles == 1) || d.cs_lin)
             {
@@ -1017,11 +1026,30 @@ bool check_plan(const Plan &plan)
     std::vector<int64_t> gram(nm, 0), apply(nm, 0), qred(nm, 0), pred(nm, 0);
     for (const WorkItem &it : plan.gram_items) gram[it.mat] += 1;
     for (const WorkItem &it : plan.apply_items) apply[it.mat] += 1;
+    if (plan.rank <= 8) {                                        // in the order of the matrices, each row once
+        auto rows_once = [&](const std::vector<OrthItem> &items, std::vector<int64_t> &count, bool partial) {
+            size_t l = 0;
+            int64_t next = 0;
+            for (const OrthItem &it : items) {
+                while (l < nm && next == plan.mats[l].n) { ++l; next = 0; }
+                if (l == nm) return false;
+                const MatDesc &d = plan.mats[l];
+                if (it.p_off != d.p_off || it.n != d.n || it.row0 != next || it.row1 <= it.row0 || it.row1 > d.n || it.tiles != d.n_gram_tiles)
+                    return false;
+                if (it.gram_off != d.gram_off + (partial ? count[l] * plan.rank * plan.rank : 0)) return false;
+                if (partial && (it.chunks != d.n_p_chunks || it.ppart_off != d.ppart_off)) return false;
+                next = it.row1;
+                count[l] += 1;
+            }
+            return l + 1 == nm && next == plan.mats[l].n;
+        };
+        if (!rows_once(plan.gram_s_items, gram, true) || !rows_once(plan.apply_s_items, apply, false)) return false;
+    }
     for (const WorkItem &it : plan.qred_items) qred[it.mat] += 1;
     for (const WorkItem &it : plan.pred_items) pred[it.mat] += 1;
     for (size_t l = 0; l < nm; ++l) {
         const MatDesc &d = plan.mats[l];
-        if (gram[l] != d.n_gram_tiles || apply[l] != (d.n + 63) / 64) return false;
+        if (gram[l] != d.n_gram_tiles || apply[l] != ceil_div(d.n, plan.rank <= 8 ? apply_rows(plan.rank, d.n) : 64)) return false;
         const bool direct_q = (d.path == kPathMfma || d.path == kPathGeneric || d.pack) && d.n_q_tiles == 1;
         if (d.pack && (d.path != kPathOctet || d.n_p_chunks != 1 || (d.m & 127) != 0 || plan.block < 128 || plan.dtype != 1 ||
                        (plan.bits != 2 && plan.bits != 4)))

@@ -10,6 +10,22 @@ namespace conef {
 constexpr int kAlign = 64;          // every per-matrix offset is a multiple of 64 elements
 constexpr int kMaxRank = 32;
 constexpr int kGramRows = 256;      // rows per LDS piece of the Gram kernel
+// Ranks up to 8: threads and rows per workgroup of the second orthonormalisation launch, and rows per partial Gram matrix (64
+// are one trip of a workgroup).  Every workgroup of the second launch adds the partial ones up for itself, one or two
+// rounds of eight loads per thread: at most 128 of them; a very tall matrix has up to four times as many, and 512 workgroups
+// (1000000 x 16, rank 8: 76 us for the stage with a workgroup per 256 rows, 53 so).
+constexpr int64_t kTallRows = 131072;
+constexpr int orth_threads(int rank) { return rank <= 4 ? 256 : 512; }
+constexpr int64_t gram_rows_small(int64_t n)
+{
+    const int64_t most = n > kTallRows ? 512 : 128;
+    return ((n + most - 1) / most + 63) / 64 * 64;
+}
+constexpr int64_t apply_rows(int rank, int64_t n)
+{
+    const int64_t t = orth_threads(rank);
+    return n > kTallRows ? ((n + 511) / 512 + t - 1) / t * t : t;
+}
 constexpr int kQredManyTiles = 32;  // partial sums of Q+ per entry from which 16 threads share an entry's sum
 constexpr int kStripRows = 32;      // rows per workgroup item of the strip P pass
 constexpr int64_t kStripSpan = (int64_t)1 << 29;    // elements a strip workgroup's rows may span (32-bit byte offsets)
@@ -43,7 +59,7 @@ struct MatDesc {
     int64_t qpart_off;              // partial sums of Q+, [n_q_tiles][m*r]
     int64_t ppart_off;              // partial sums of P, [n_p_chunks][n*r] (only if n_p_chunks > 1)
     int32_t n_gram_tiles, n_q_tiles, n_p_chunks;
-    int32_t gram_tile_rows;         // rows per partial Gram matrix (a multiple of kGramRows)
+    int32_t gram_tile_rows;         // rows per partial Gram matrix (a multiple of kGramRows, or of 64 up to rank 8)
     int32_t q_tile_rows;            // rows per partial of Q+
     int32_t p_chunk_cols;           // columns per partial of P
     int32_t path;                   // kernel family chosen for this matrix
@@ -99,6 +115,18 @@ struct WorkItem {
     int32_t mat, a, b, c;
 };
 
+// A unit of the two orthonormalisation launches for ranks up to 8, with all that a workgroup needs of its matrix: the
+// descriptor's own line is one more round trip to memory, of the five or six that such a launch consists of.
+struct OrthItem {
+    int64_t p_off;                  // element offset of the matrix in P
+    int64_t row0, row1;             // rows of this item
+    int64_t n;                      // rows of the matrix
+    int64_t gram_off;               // workspace offset: first launch, of this item's partial Gram matrix; second, of the matrix's first one
+    int64_t ppart_off;              // column chunks of P (first launch)
+    int32_t tiles, chunks;          // partial Gram matrices of the matrix, column chunks of P
+    int64_t pad;
+};
+
 struct Plan {
     int rank = 0, bits = 0, block = 0, dtype = 0, rpad = 0;
     uint64_t seed = 0;
@@ -151,6 +179,7 @@ struct Plan {
     std::vector<WorkItem> pred_items;   // reduce partial P: (mat, first entry of n*r)
     std::vector<WorkItem> gram_items;   // (mat, gram tile)
     std::vector<WorkItem> apply_items;  // (mat, first row)                    64 rows per workgroup
+    std::vector<OrthItem> gram_s_items, apply_s_items;      // the same for ranks up to 8
     std::vector<WorkItem> qred_items;   // reduce partial Q+: (mat, first entry of m*r)
     std::vector<WorkItem> elem_items;   // element-wise helpers: (mat, first element / 1024)
     std::vector<WorkItem> upd_items;    // decompress / update: (mat, row tile of 64, column tile of 128, row tiles)
