@@ -128,6 +128,7 @@ int ensure_uploaded(conef_ctx *ctx)
     d.n_q_flat = (int)pl.q_flat_items.size();
     d.es_lds = pl.es_lds; d.wshift = pl.wshift; d.lb_shift = pl.lb_shift; d.inv_s = pl.inv_s; d.bmagic = pl.bmagic;
     d.block_shift = pl.block_shift;
+    d.ragged = pl.ragged;
     d.n_upd = (int)pl.upd_items.size();
     d.upd_many = pl.upd_many;
     d.n_p_f = (int)pl.p_f_items.size();

@@ -44,6 +44,7 @@ struct DevicePlan {
     int n_pred = 0, n_gram = 0, n_apply = 0, n_qred = 0, n_elem = 0;
     int rank = 0, rpad = 0, bits = 0, block = 0, dtype = 0;
     int n_q_flat = 0, n_err_g = 0;
+    int ragged = 0;                 // strip family: P and Q+ passes on octets
     int n_err_s = 0, es_lds = 0;    // strip err pass: items, floats of LDS per workgroup
     int wshift = 0, lb_shift = 0;   // log2(code fields per word), log2(block / 8)
     int block_shift = -1;           // log2(block), -1 if it is not a power of two
@@ -148,6 +149,11 @@ void strip_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, fl
                     uint64_t step, hipStream_t st);
 void strip_pass_err_two(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, uint32_t *codes2, float *scales2,
                         const float *Phat, const float *Qn, uint64_t step, hipStream_t st);
+// the same for blocks of whole octets (kernels_ragged.hip): where dp.ragged
+void ragged_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Q, float *P,
+                   double *ws, hipStream_t st);
+void ragged_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Phat, double *ws,
+                   float *Qout, hipStream_t st);
 void strip_cs_pass_p(const DevicePlan &dp, const void *grads, const void *table, const float *Q, float *P, double *ws, hipStream_t st);
 void strip_cs_pass_q(const DevicePlan &dp, const void *grads, const void *table, const float *Phat, double *ws, float *Qout,
                      hipStream_t st);

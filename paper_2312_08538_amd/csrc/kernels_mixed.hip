@@ -14,6 +14,7 @@
 #include "device_common.h"
 #include "kernels.h"
 #include "octet_device.h"
+#include "ragged_device.h"
 #include "strip_device.h"
 
 namespace conef {
@@ -27,14 +28,13 @@ __global__ __launch_bounds__(256) CONEF_P_OCTET_WAVES(false)
 void k_p_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Q, float *P, double *ws)
 {
-    __shared__ __attribute__((aligned(16))) float lds[larger(kPOctetLds, kPStripLds)];
+    __shared__ __attribute__((aligned(16))) float lds[larger(kPOctetLds, kRagLds)];
     const int b = blockIdx.x;
     if (b >= lead) {
         const POctetLds o = {lds, reinterpret_cast<uint32_t *>(lds + kPOctetTiles), lds + kPOctetTiles + kPOctetCodes, nullptr, nullptr};
         p_octet<BF16, BITS, RH, false>(dp, b - lead, o, grads, codes, scales, Q, P, ws);
     } else if (b < dp.n_p) {
-        const Source src = {grads, codes, scales, nullptr};
-        p_strip<kSrcOne, RH>(dp, b, lds, src, Q, P, ws);
+        p_ragged<BF16, BITS, RH, false>(dp, b, lds, grads, codes, scales, Q, P, ws);
     }
 }
 
@@ -43,13 +43,12 @@ __global__ __launch_bounds__(256) CONEF_Q_OCTET_WAVES(BF16, false)
 void k_q_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Phat, double *ws, float *Qout)
 {
-    __shared__ __attribute__((aligned(16))) float lds[larger(kQOctetLds, 2 * 2 * R * 64)];
+    __shared__ __attribute__((aligned(16))) float lds[larger(kQOctetLds, kRagLds)];
     const int b = blockIdx.x;
     if (b >= lead) {
         q_octet<BF16, BITS, (R > 4 ? 2 : 1), false>(dp, b - lead, lds, grads, codes, scales, Phat, ws);
     } else if (b < dp.n_q) {
-        const Source src = {grads, codes, scales, nullptr};
-        q_strip<kSrcOne, R, true>(dp, b, reinterpret_cast<double *>(lds), src, Phat, ws, Qout);
+        q_ragged<BF16, BITS, (R > 4 ? 2 : 1), false>(dp, b, lds, grads, codes, scales, Phat, ws, Qout);
     }
 }
 
@@ -90,7 +89,7 @@ void by_type(const DevicePlan &dp, F &&go)
 bool mixed_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Q, float *P,
                   double *ws, hipStream_t st)
 {
-    if (dp.n_p <= 0 || dp.n_p_f <= 0 || dp.i_codes || dp.n_p > kMixedStrips) return false;
+    if (dp.n_p <= 0 || dp.n_p_f <= 0 || !dp.ragged || dp.i_codes || dp.n_p > kMixedStrips) return false;
     const int lead = lead_of(dp.n_p);
     by_type(dp, [&](auto bf, auto bits) {
         constexpr bool BF = decltype(bf)::value;
@@ -105,7 +104,7 @@ bool mixed_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes
 bool mixed_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Phat, double *ws,
                   float *Qout, hipStream_t st)
 {
-    if (dp.n_q <= 0 || dp.n_q_f <= 0 || dp.i_codes || dp.n_q > kMixedStrips) return false;
+    if (dp.n_q <= 0 || dp.n_q_f <= 0 || !dp.ragged || dp.i_codes || dp.n_q > kMixedStrips) return false;
     const int lead = lead_of(dp.n_q);
     by_type(dp, [&](auto bf, auto bits) {
         constexpr bool BF = decltype(bf)::value;

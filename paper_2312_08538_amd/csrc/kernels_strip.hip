@@ -1,5 +1,6 @@
 // Strip kernel family: the three passes for any layout (any number of columns, any rank up to 32, blocks that straddle
-// rows).  A wave works on strips of 64 neighbouring columns, a lane owns a column of the strip and the row is uniform over
+// rows).  The quantiser's P and Q+ passes for blocks of whole octets are in kernels_ragged.hip; here are the others and the err
+// pass.  A wave works on strips of 64 neighbouring columns, a lane owns a column of the strip and the row is uniform over
 // the wave: a row of the strip is one coalesced access of the gradient (one element per lane, whatever the alignment of
 // the row).  The 64-bit addresses of a workgroup's first block are formed once, on the scalar side; an element is a 32-bit
 // distance from there, from which each lane takes its code word and block by shifts (a division where the block is not a
@@ -13,10 +14,13 @@
 //             wave order.  Products of fp32 values are exact in fp64, the sum stays in fp64, one rounding.
 //   Q+ pass   a workgroup per (strip, row tile), a quarter of the rows per wave; a lane adds up its column's r sums in
 //             fp64 registers, the row of P^ being a scalar operand.  Matrices of a few rows: a strip per wave (k_q_flat).
-//   err pass  a workgroup per run of whole scale blocks: the residual (the fp32 fma chain over c = 0..r-1, a lane's row of
-//             Q+ in registers, the row of P^ on the scalar side) goes to LDS in the order of the flat index, then the
-//             workgroup walks the run in octets as the octet family does: block max-norm by DPP, one Philox call per
-//             eight elements, rounding, pack, in place.  Matrices of a few columns: groups of rows that fill a wave.
+//   err pass  a workgroup per run of whole scale blocks: p is loaded and decoded in octets and goes to LDS in the order of
+//             the flat index; there the reconstruction (the fp32 fma chain over c = 0..r-1, a lane's row of Q+ in registers,
+//             the row of P^ on the scalar side) is subtracted a row of a strip at a time; then the workgroup walks the run in
+//             octets as the octet family does: block max-norm by DPP, one Philox call per eight elements, rounding, pack, in
+//             place.  Matrices of a few columns: groups of rows that fill a wave.  28.4 M elements in matrices of 650 columns,
+//             rank 4: 46 us (76 with a load of gradient, code word and scale, and a decode, per element).  What is left is
+//             issue: 34 vector and 32 scalar instructions per 64 elements (65 and 65 then).
 //
 // All sums are combined in a fixed order: results do not depend on scheduling.
 #include <type_traits>

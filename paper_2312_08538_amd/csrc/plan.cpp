@@ -476,7 +476,12 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         for (const MatDesc &d : plan.mats) widest = std::max(widest, d.m);
         const int64_t strip_chunk = !sketch && widest <= 512 ? 512
             : std::min<int64_t>(2048, std::max<int64_t>(256, round_up(strip_elems / (kStripRows * 1536), 256)));
-        const int64_t strip_q_rows = std::min<int64_t>(512, std::max<int64_t>(32, round_up(strip_elems / (64 * 1536), 32)));
+        plan.ragged = !sketch && octet_blocks ? 1 : 0;
+        for (const MatDesc &d : plan.mats)
+            if (d.path == kPathGeneric && d.m > kRaggedMaxCols) plan.ragged = 0;
+        // (on octets a wave works in steps of 32 rows, and a workgroup's four waves have one each)
+        const int64_t strip_q_rows = plan.ragged ? std::min<int64_t>(512, std::max<int64_t>(128, round_up(strip_elems / (64 * 1024), 128)))
+                                                 : std::min<int64_t>(512, std::max<int64_t>(32, round_up(strip_elems / (64 * 1536), 32)));
         const int64_t strip_err = strip_elems / 8192 >= 1024 ? 8192 : strip_elems / 4096 >= 768 ? 4096 : strip_elems / 2048 >= 64 ? 2048 : 1024;
         auto lay_out = [&](int64_t chunk_cols, int64_t tile_rows) {
             wd = 0;

@@ -29,6 +29,7 @@ constexpr int64_t apply_rows(int rank, int64_t n)
 constexpr int kQredManyTiles = 32;  // partial sums of Q+ per entry from which 16 threads share an entry's sum
 constexpr int kStripRows = 32;      // rows per workgroup item of the strip P pass
 constexpr int64_t kStripSpan = (int64_t)1 << 29;    // elements a strip workgroup's rows may span (32-bit byte offsets)
+constexpr int64_t kRaggedMaxCols = kStripSpan / kStripRows;
 constexpr int kFlatRows = 8;        // matrices of at most so many rows: a wave of the strip Q+ pass takes all of them
 constexpr int kFastMaxRank = 8;     // the octet family holds rank <= 8 in registers
 constexpr int kPTileRows = 64;      // rows per workgroup item of the octet P pass
@@ -155,6 +156,7 @@ struct Plan {
     std::vector<WorkItem> err_s_items;  // pass 3: (mat, tile, its first row, rows it spans), or with segments (mat, first row, segment, rows)
     std::vector<WorkItem> err_g_items;  // pass 3, es_rows > 1: (mat, tile, its first group of rows, groups it spans)
     std::vector<WorkItem> err_items;    // pass 3, blocks that are not 8 * 2^j elements (j <= 6): (mat, first block, blocks per wave)
+    int ragged = 0;                     // 1: their P and Q+ passes take the quantiser's elements in octets (kernels_ragged.hip)
     int es_lds = 0;                     // floats of LDS of the strip err pass
     int wshift = 0, lb_shift = 0;       // log2(code fields per word); log2(block / 8) for power-of-two blocks of 8 elements or more
     int block_shift = -1;               // log2(block), -1 if it is not a power of two

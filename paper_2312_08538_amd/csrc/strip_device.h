@@ -5,6 +5,7 @@
 
 #include "device_common.h"
 #include "kernels.h"
+#include "ragged_device.h"
 
 namespace conef {
 
@@ -425,9 +426,8 @@ __device__ __forceinline__ void q_flat(const DevicePlan &dp, int block, const So
 // 7.6 in groups (7.5 and 7.3 with the kernel for any block, a lane per element, which needs 84 for 200000 x 12 where groups
 // take 11).  Launched apart from the other strips: both in one kernel cost those 5 - 10 %.
 //
-// First half: units of four rows x one strip, each wave a contiguous quarter of the units in strip-major order, so that
-// a strip's rows of Q+ are loaded once per wave; the next unit's loads are issued ahead of the current one's arithmetic.
-// Second half (after a barrier: every code of the run has been read): octets.
+// Three parts with barriers between them: p into LDS in octets; the reconstruction subtracted there; octets rounded and packed
+// (every code of the run has been read by then).
 template <int BITS, bool TWO>
 __device__ __forceinline__ void quantise_run(const DevicePlan &dp, const MatDesc &d, int mat, uint32_t step_lo, uint32_t step_hi,
                                              const float *X, int64_t flat0, int count, int slots, int first, int stride,
@@ -498,7 +498,7 @@ __device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float
                                           float *scales, uint32_t *codes2, float *scales2, const float *__restrict__ Phat,
                                           const float *__restrict__ Qn, uint32_t step_lo, uint32_t step_hi)
 {
-    constexpr int U = 4, SRC = TWO ? kSrcTwo : kSrcOne;
+    constexpr int U = 4;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const WorkItem it = GROUP ? dp.err_g_items[block] : dp.err_s_items[block];
@@ -516,8 +516,6 @@ __device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float
     const int64_t c1 = seg ? (c0 + d.es_seg < d.m ? c0 + d.es_seg : d.m) : M;
     // (virtual) columns: [c0, c0 + width)
     const int width = (int)(c1 - c0) + (seg ? d.es_over : 0);
-    Source src;
-    src.grads = grads; src.codes = TWO ? codes2 : codes; src.scales = TWO ? scales2 : scales; src.table = nullptr;
 
     // All indices are relative to the first owned block of the run (its first element: jb); row rl of the run owns the
     // elements [ws, we) and its (virtual) column 64 st + lane is element rel_row(rl) + 64 st + lane.
@@ -537,117 +535,198 @@ __device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float
         }
         we = we < last ? we : last;
     };
-    uint32_t rel_unused;
-    const Base<SRC> base = make_base<SRC>(dp, d, src, jb < d.N ? jb : d.N - 1, &rel_unused);
+    // First part: p of the run, octet by octet (the run's pieces start at scale blocks, so these are aligned and whole, up to
+    // the last one of the matrix).
+    auto fill = [&](auto bf_tag, auto bits_tag) {
+        constexpr bool BF16 = decltype(bf_tag)::value;
+        constexpr int BITS = decltype(bits_tag)::value, NB = 4;
+        const OctetBase<BF16, BITS, TWO> base = octet_base<BF16, BITS, TWO>(dp, d, grads, TWO ? codes2 : codes, TWO ? scales2 : scales, jb >> 3);
+        // octets first, first + stride, ... below n_oct of the piece that starts at the base's octet o0 and goes to `to`
+        auto piece = [&](int o0, int n_oct, float *to, int first, int stride) {
+            for (int at = first; at < n_oct; at += NB * stride) {
+                OctetRegs<BF16, BITS, TWO> o[NB];
+                int id[NB];
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {                  // (beyond the piece: its last one again, with what it holds)
+                    id[u] = at + u * stride < n_oct ? at + u * stride : n_oct - 1;
+                    load_octet_at<BF16, BITS, TWO>(base, (uint32_t)(o0 + id[u]), o[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    float x[8];
+                    decode_octet_at<BF16, BITS, TWO>(o[u], 1.0f, x);
+                    float4 *dst = reinterpret_cast<float4 *>(to + 8 * id[u]);
+                    dst[0] = make_float4(x[0], x[1], x[2], x[3]);
+                    dst[1] = make_float4(x[4], x[5], x[6], x[7]);
+                }
+            }
+        };
+        if (!seg) {
+            piece(0, ((int)(j1 - j0) + 7) >> 3, X, tid, 256);
+        } else {
+            for (int rl = wave; rl < n_rows; rl += 4) {
+                int ws, we;
+                window(rl, ws, we);
+                piece(ws >> 3, (we - ws + 7) >> 3, X + rl * d.es_pitch, lane, 64);
+            }
+        }
+    };
+    auto fill_bits = [&](auto bf_tag) {
+        if (dp.bits == 4) fill(bf_tag, std::integral_constant<int, 4>{});
+        else if (dp.bits == 2) fill(bf_tag, std::integral_constant<int, 2>{});
+        else fill(bf_tag, std::integral_constant<int, 8>{});
+    };
+    if (dp.dtype == 0) fill_bits(std::false_type{});
+    else fill_bits(std::true_type{});
+    __syncthreads();
 
+    // Second part: the reconstruction is subtracted, in units of four rows x one strip, each wave a contiguous quarter of the
+    // units in strip-major order.  Per row of the run: own are the lanes lo <= 64 st + lane < hi, and that lane's residual lies
+    // at X[base + 64 st + lane].
+    struct Row {
+        int lo, hi, base;
+    };
     const int n_strips = (width + 63) >> 6, n_groups = (n_rows + U - 1) / U;
     const int n_units = n_strips * n_groups;
     const int u_begin = (int)((int64_t)n_units * wave / 4), u_end = (int)((int64_t)n_units * (wave + 1) / 4);
-    int strip = n_groups > 0 ? u_begin / n_groups : 0, group = u_begin - strip * n_groups;
-    struct Unit {
-        Raw<SRC> o[U];
-    };
-    // the lane's element of a row, kept inside the row's window (an empty window: inside the matrix)
-    auto clamped = [&](int rl, int st) {
-        int ws, we;
-        window(rl, ws, we);
-        int e = rel_row(rl) + 64 * st + lane;
-        e = e > ws ? e : ws;
-        e = e < we ? e : we - 1;
-        return (uint32_t)(e > 0 ? e : 0);
-    };
-    auto row_of = [&](int g, int u) {
-        const int rl = g * U + u;
-        return rl < n_rows ? rl : n_rows - 1;
-    };
-    auto load_unit = [&](Unit &un, int st, int g) {
-        uint32_t rel[U];
-        int64_t row[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            rel[u] = clamped(row_of(g, u), st);
-            row[u] = 0;
-        }
-        load_rows<SRC, U>(dp, d, src, base, rel, row, 0, 0, 0, un.o);
-    };
-    float q[R];
-#pragma unroll
-    for (int c = 0; c < R; ++c) q[c] = 0.0f;
-    int q_strip = -1;
-    Unit cur, nxt;
-    if (u_begin < u_end) load_unit(cur, strip, group);
-    for (int un = u_begin; un < u_end; ++un) {
-        const int64_t kk = c0 + 64 * strip + lane;             // the lane's (virtual) column
-        if (strip != q_strip) {                                 // uniform
-            q_strip = strip;
-            int64_t k = GROUP ? lane_col : kk < d.m ? kk : kk - d.m;
-            k = k < d.m ? k : d.m - 1;
-            const float *qrow = Qn + d.q_off + k * r;
-            if (EXACT && R >= 4) {
-#pragma unroll
-                for (int c4 = 0; c4 < R / 4; ++c4) {
-                    const float4 v = reinterpret_cast<const float4 *>(qrow)[c4];
-                    q[4 * c4] = v.x; q[4 * c4 + 1] = v.y; q[4 * c4 + 2] = v.z; q[4 * c4 + 3] = v.w;
-                }
+    const float *prun = Phat + d.p_off + (GROUP ? 0 : i_first * r);
+    auto subtract = [&](auto seg_tag) {
+        constexpr bool SEG = decltype(seg_tag)::value;
+        auto row_at = [&](int rl) {
+            Row w;
+            const int f = rel_row(rl);
+            if (SEG) {
+                const int ws = (f + (int)B - 1) & ~((int)B - 1), we = (f + (int)(c1 - c0) + (int)B - 1) & ~((int)B - 1);
+                w.lo = ws - f;
+                w.hi = (we < last ? we : last) - f;
+                w.base = rl * d.es_pitch - w.lo;
             } else {
-#pragma unroll
-                for (int c = 0; c < R; ++c)
-                    if (EXACT || c < r) q[c] = qrow[c];
+                w.lo = f < 0 ? -f : 0;
+                w.hi = last - f < (int)M ? last - f : (int)M;
+                w.base = f;
             }
-        }
-        int n_strip = strip, n_group = group + 1;
-        if (n_group == n_groups) { n_group = 0; ++n_strip; }
-        if (un + 1 < u_end) load_unit(nxt, n_strip, n_group);
-        const bool wraps = seg && c0 + 64 * strip + 63 >= d.m;  // uniform: some lanes may belong to the next row
-        constexpr int RL = GROUP && R <= 8 ? R : 1;
-        float pl[U][RL];                                        // GROUP: the lanes' rows of P^, of all four groups at once
-        auto lane_p = [&](int u) {
-            const int64_t i = (i_first + row_of(group, u)) * d.es_rows + lane_row;
-            return Phat + d.p_off + (i < d.n ? i : d.n - 1) * r;
+            return w;
         };
-        if (GROUP && R <= 8) {
+        int strip = n_groups > 0 ? u_begin / n_groups : 0, group = u_begin - strip * n_groups;
+        float q[R];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const float *prow = lane_p(u);
+        for (int c = 0; c < R; ++c) q[c] = 0.0f;
+        int q_strip = -1;
+        for (int un = u_begin; un < u_end; ++un) {
+            const int v0 = 64 * strip, v = v0 + lane;               // the lane's column in the run (SEG: from c0 on)
+            if (strip != q_strip) {                                 // uniform
+                q_strip = strip;
+                const int m = (int)d.m;
+                int k = GROUP ? lane_col : (int)c0 + v;
+                k = k < m ? k : k - m;
+                k = k < m ? k : m - 1;
+                const float *qrow = Qn + d.q_off + (int64_t)k * r;
+                if (EXACT && R >= 4) {
 #pragma unroll
-                for (int c = 0; c < RL; ++c) pl[u][c] = prow[EXACT ? c : (c < r ? c : r - 1)];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (group * U + u < n_rows) {                       // uniform
-                const int rl = group * U + u;
-                const int64_t i = i_first + rl;
-                int ws, we;
-                window(rl, ws, we);
-                const int e = rel_row(rl) + 64 * strip + lane;
-                // (lanes outside the window work on another element's inputs and store nothing)
-                const float p = form_p<SRC>(dp, cur.o[u], (uint32_t)e, 1.0f);
-                float acc = 0.0f;
-                if (GROUP) {
-                    const float *prow = lane_p(u);
+                    for (int c4 = 0; c4 < R / 4; ++c4) {
+                        const float4 w = reinterpret_cast<const float4 *>(qrow)[c4];
+                        q[4 * c4] = w.x; q[4 * c4 + 1] = w.y; q[4 * c4 + 2] = w.z; q[4 * c4 + 3] = w.w;
+                    }
+                } else {
 #pragma unroll
                     for (int c = 0; c < R; ++c)
-                        if (EXACT || c < r) acc = __builtin_fmaf(R <= 8 ? pl[u][R <= 8 && GROUP ? c : 0] : prow[c], q[c], acc);
-                } else if (!wraps) {
-                    float ph[R];
-                    uniform_row<R, EXACT>(Phat + d.p_off + i * r, r, ph);
-#pragma unroll
-                    for (int c = 0; c < R; ++c) acc = __builtin_fmaf(ph[c], q[c], acc);
-                } else {
-                    float ph[R], pn[R];
-                    uniform_row<R, EXACT>(Phat + d.p_off + i * r, r, ph);
-                    uniform_row<R, EXACT>(Phat + d.p_off + (i + 1 < d.n ? i + 1 : i) * r, r, pn);
-#pragma unroll
-                    for (int c = 0; c < R; ++c) acc = __builtin_fmaf(kk < d.m ? ph[c] : pn[c], q[c], acc);
+                        if (EXACT || c < r) q[c] = qrow[c];
                 }
-                if (e >= ws && e < we) X[seg ? rl * d.es_pitch + (e - ws) : e] = p - acc;
             }
+            const int rl0 = group * U;
+            // UB rows at a time: their rows of P^ and their p are asked for together, so that a group costs one round trip to
+            // LDS and the scalar cache
+            constexpr int UB = R <= 8 ? U : R <= 16 ? 2 : 1;
+#pragma unroll
+            for (int u0 = 0; u0 < U; u0 += UB) {
+                if (rl0 + u0 >= n_rows) break;                      // uniform
+                const bool wraps = SEG && c0 + v0 + 63 >= d.m;      // uniform: some lanes may belong to the next row
+                const int f0 = rel_row(rl0 + u0);
+                Row w[UB];
+                bool whole = !GROUP && !wraps && rl0 + u0 + UB <= n_rows;      // uniform: every lane of every row is its owner
+                if (SEG) {
+#pragma unroll
+                    for (int u = 0; u < UB; ++u) {
+                        w[u] = row_at(rl0 + u0 + u);
+                        whole = whole && w[u].lo <= v0 && v0 + 64 <= w[u].hi;
+                    }
+                } else {
+                    whole = whole && f0 >= 0 && f0 + UB * (int)M <= last && v0 + 64 <= (int)M;
+                }
+                float x[UB], acc[UB];
+                if (whole) {
+                    int at[UB];
+#pragma unroll
+                    for (int u = 0; u < UB; ++u) at[u] = (SEG ? w[u].base : f0 + u * (int)M) + v;
+                    float ph[UB][R];
+                    const float *prow = prun + (uint32_t)((rl0 + u0) * r);
+#pragma unroll
+                    for (int u = 0; u < UB; ++u) uniform_row<R, EXACT>(prow + u * r, r, ph[u]);
+#pragma unroll
+                    for (int u = 0; u < UB; ++u) {
+                        x[u] = X[(uint32_t)at[u]];
+                        acc[u] = 0.0f;
+                    }
+#pragma unroll
+                    for (int c = 0; c < R; ++c)
+#pragma unroll
+                        for (int u = 0; u < UB; ++u) acc[u] = __builtin_fmaf(ph[u][c], q[c], acc[u]);
+#pragma unroll
+                    for (int u = 0; u < UB; ++u) X[(uint32_t)at[u]] = x[u] - acc[u];
+                    continue;
+                }
+                // rows beyond the run repeat its last one and store nothing
+                constexpr int RL = GROUP && R <= 8 ? R : 1;
+                float pl[UB][RL];                                   // GROUP: the lanes' rows of P^
+                bool own[UB];
+                auto lane_p = [&](int u) {
+                    const int rl = rl0 + u0 + u < n_rows ? rl0 + u0 + u : n_rows - 1;
+                    const int64_t i = (i_first + rl) * d.es_rows + lane_row;
+                    return prun + (i < d.n ? i : d.n - 1) * r;
+                };
+#pragma unroll
+                for (int u = 0; u < UB; ++u) {
+                    if (!SEG) w[u] = row_at(rl0 + u0 + u);
+                    own[u] = rl0 + u0 + u < n_rows && v >= w[u].lo && v < w[u].hi;
+                    x[u] = X[own[u] ? (uint32_t)(w[u].base + v) : 0u];
+                    acc[u] = 0.0f;
+                    if (GROUP && R <= 8) {
+                        const float *prow = lane_p(u);
+#pragma unroll
+                        for (int c = 0; c < RL; ++c) pl[u][c] = prow[EXACT ? c : (c < r ? c : r - 1)];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < UB; ++u) {
+                    if (GROUP) {
+                        const float *prow = lane_p(u);
+#pragma unroll
+                        for (int c = 0; c < R; ++c)
+                            if (EXACT || c < r) acc[u] = __builtin_fmaf(R <= 8 ? pl[u][R <= 8 && GROUP ? c : 0] : prow[c], q[c], acc[u]);
+                    } else {
+                        const int rl = rl0 + u0 + u < n_rows ? rl0 + u0 + u : n_rows - 1;
+                        float ph[R];
+                        uniform_row<R, EXACT>(prun + (uint32_t)(rl * r), r, ph);
+                        if (!wraps) {
+#pragma unroll
+                            for (int c = 0; c < R; ++c) acc[u] = __builtin_fmaf(ph[c], q[c], acc[u]);
+                        } else {
+                            float pn[R];
+                            uniform_row<R, EXACT>(prun + (uint32_t)((i_first + rl + 1 < d.n ? rl + 1 : rl) * r), r, pn);
+#pragma unroll
+                            for (int c = 0; c < R; ++c) acc[u] = __builtin_fmaf(c0 + v < d.m ? ph[c] : pn[c], q[c], acc[u]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < UB; ++u)
+                    if (own[u]) X[(uint32_t)(w[u].base + v)] = x[u] - acc[u];
+            }
+            if (++group == n_groups) { group = 0; ++strip; }
         }
-        cur = nxt;
-        strip = n_strip;
-        group = n_group;
-    }
+    };
+    if (!GROUP && seg) subtract(std::integral_constant<bool, !GROUP>{});
+    else subtract(std::false_type{});
     __syncthreads();
     auto quantise = [&](auto bits_tag) {
         constexpr int BITS = decltype(bits_tag)::value;

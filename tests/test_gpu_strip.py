@@ -172,3 +172,15 @@ def test_scales_near_the_largest_value_decode_finite(env):
     torch.cuda.synchronize()
     assert 0 < float(scales2.max()) <= float(buf["scales"].max()) / 7 * 1.0001
     model.close()
+
+
+@pytest.mark.parametrize("rank,bits,block,dtype", [(4, 4, 64, wl.F32), (8, 2, 8, wl.BF16), (3, 8, 128, wl.F32), (16, 4, 512, wl.BF16),
+                                                   (32, 8, 64, wl.F32)])
+def test_rows_that_start_anywhere_in_an_octet(env, rank, bits, block, dtype):
+    """The P and Q+ passes on octets: row lengths of every remainder by 8, below, at and above a strip and three strips; rows
+    one below, at and above a wave's step (32) and a workgroup's (128)."""
+    layout = [(n, m) for i, m in enumerate([57, 58, 59, 60, 61, 62, 63, 64, 65, 71, 193, 198, 1027])
+              for n in ((31, 33, 97, 127, 128, 129, 161)[i % 7],)] + [(40, 7), (33, 1), (50, 17)]
+    layout = [(max(n, rank), max(m, rank)) for n, m in layout]
+    w = wl.Workload("ragged", 13, tuple(layout), rank, bits, block, dtype, "normal", 1.0, 0x8A66)
+    _run_model(env, w, layout, 2, f"ragged-r{rank}-b{bits}-B{block}-dt{dtype}")
