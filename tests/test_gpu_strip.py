@@ -174,7 +174,7 @@ def test_scales_near_the_largest_value_decode_finite(env):
     model.close()
 
 
-@pytest.mark.parametrize("rank,bits,block,dtype", [(4, 4, 64, wl.F32), (8, 2, 8, wl.BF16), (3, 8, 128, wl.F32), (16, 4, 512, wl.BF16),
+@pytest.mark.parametrize("rank,bits,block,dtype", [(4, 4, 64, wl.F32), (8, 2, 16, wl.BF16), (3, 8, 128, wl.F32), (16, 4, 512, wl.BF16),
                                                    (32, 8, 64, wl.F32)])
 def test_rows_that_start_anywhere_in_an_octet(env, rank, bits, block, dtype):
     """The P and Q+ passes on octets: row lengths of every remainder by 8, below, at and above a strip and three strips; rows
