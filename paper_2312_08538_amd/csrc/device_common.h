@@ -58,22 +58,37 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
 }
 
-// The eight fields of an octet (8-bit codes: c0 elements 0..3, c1 elements 4..7; else all in c0) as fp32.  4-bit fields come
-// over 16 and are multiplied back, two instructions each; the factor is not moved into the step size, which would overflow
-// for scales above 1.5e38.  PLAIN: extracted and converted as the other widths are, two instructions each as well, without
-// the shifted copy of the word: faster where the code has two vectors to decode (124 M elements, two vectors, rank 4: 497 us
-// a step, 500 by nibbles), not where it has one (381, 380) or where decode and rounding of a stream are all there is
-// (random-k, 1.3 G elements: 1831, 1818).
-template <int BITS, bool PLAIN = false>
+// signed byte `byte` of w as fp32: one conversion, which reads the byte through its selector
+template <int byte>
+__device__ __forceinline__ float signed_byte(uint32_t w)
+{
+    return (float)(int)(int8_t)(w >> (8 * byte));
+}
+
+// What code_values leaves in a field's value: the caller's step size takes its inverse.  (inv_levels * field_unit is a
+// constant, and scaling by a power of two is exact as long as step * field_unit is a normal number, that is for scales of
+// 7e-36 and more.  Blocks below 1e-33 have no codes worth the name, see quantise_octet: their fields are zero.)
+__device__ __forceinline__ constexpr float field_unit(int bits) { return bits == 8 ? 1.0f : (bits == 4 ? 1.0f / 16.0f : 1.0f / 64.0f); }
+
+// The eight fields of an octet (8-bit codes: c0 elements 0..3, c1 elements 4..7; else all in c0, bits beyond the octet zero) as fp32, over field_unit.
+// Narrow fields are moved to the top of a byte, four at a time, and converted as signed bytes: 11 instructions for 4-bit
+// fields and 14 for 2-bit ones (16 to extract and convert each; 17 through the conversion of nibbles, whose sixteenths would
+// have to be multiplied back, since the factor 16 in the step size overflows for scales above 1.5e38).
+template <int BITS>
 __device__ __forceinline__ void code_values(uint32_t c0, uint32_t c1, float q[8])
 {
-    if constexpr (BITS == 4 && !PLAIN) {
-        fields_over_16(c0, q);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) q[e] *= 16.0f;
+    auto bytes = [](uint32_t v, float &a, float &b, float &c, float &d) {
+        a = signed_byte<0>(v); b = signed_byte<1>(v); c = signed_byte<2>(v); d = signed_byte<3>(v);
+    };
+    if constexpr (BITS == 8) {
+        bytes(c0, q[0], q[1], q[2], q[3]);
+        bytes(c1, q[4], q[5], q[6], q[7]);
+    } else if constexpr (BITS == 4) {
+        bytes((c0 << 4) & 0xF0F0F0F0u, q[0], q[2], q[4], q[6]);
+        bytes(c0 & 0xF0F0F0F0u, q[1], q[3], q[5], q[7]);
     } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) q[e] = (float)(BITS == 8 ? code_field(e < 4 ? c0 : c1, e & 3, 8) : code_field(c0, e, BITS));
+        bytes(((c0 << 6) | (c0 << 20)) & 0xC0C0C0C0u, q[0], q[4], q[1], q[5]);
+        bytes(((c0 << 2) | (c0 << 16)) & 0xC0C0C0C0u, q[2], q[6], q[3], q[7]);
     }
 }
 
@@ -241,45 +256,53 @@ __device__ __forceinline__ uint32_t quantise_field(float x, float inv16, uint32_
 
 // Fixed-point stochastic rounding of an octet (quantise_field on each of its 8 values) straight into packed
 // BITS-wide two's-complement fields: 8-bit codes give two words (elements 0..3, 4..7), 4- and 2-bit codes the low
-// 32 / 16 bits of w[0].  Byte 2 of U + draw is the magnitude, and byte permutes gather the magnitudes of an octet (8 - 13
-// instructions; a shift and an insertion per element were 16).  U + draw stays below 2^23, unless the block is so small that
-// inv16 is infinite: then a byte may be 0xFF, and a field keeps its own bits of it, as in quantise_field.  Sign bits are gathered field by field
-// and the negation is done on the whole word: with s the sign bit of a field,
-// ((mag ^ (s - (s >> (BITS-1)))) + (s >> (BITS-1))) ^ s is 2^BITS - mag for a negative field with mag >= 1 and 0 for mag = 0;
-// no carry leaves a field.
+// 32 / 16 bits of w[0].  With U the truncated |x| inv16 and d the 16-bit draw, -floor((U + d) / 2^16) is
+// floor((-U + 65535 - d) / 2^16): the signed product is truncated, the draws of a negative element are complemented (one
+// permute makes the sign masks of two elements, one exclusive or applies them), and bits 16 and up of the sum are the code
+// with its sign.  (Magnitudes, gathered sign bits and a negation of the whole word took 6 instructions more per octet with 2-
+// and 4-bit codes and 10 with 8-bit ones.)  Byte 2 of the sum is the code as a signed byte, which byte permutes gather.
+// t (if asked for): the sums, for rounded_values.  The product stays below 2^23, unless the block is so small that inv16 is
+// infinite: then byte 2 is 0 or 0xFF, and a field keeps its own bits of it, as in quantise_field.
+template <int BITS>
+__device__ __forceinline__ void quantise_octet(const float x[8], float inv16, const uint32_t rnd[4], uint32_t w[2], int32_t t[8])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        // selectors 9 and 11: the sign of the second operand's and of the first operand's top byte, in all bits
+        uint32_t d = rnd[i] ^ __builtin_amdgcn_perm(__float_as_uint(x[2 * i + 1]), __float_as_uint(x[2 * i]), 0x0B0B0909u);
+        asm("" : "+v"(d));          // one exclusive or for both halves, which the additions select
+        t[2 * i] = (int32_t)(x[2 * i] * inv16) + (int32_t)(d & 0xFFFFu);
+        t[2 * i + 1] = (int32_t)(x[2 * i + 1] * inv16) + (int32_t)(d >> 16);
+    }
+    // __builtin_amdgcn_perm(hi, lo, sel): result byte i is byte sel_i of {hi, lo} (0..3 lo, 4..7 hi, 12: zero)
+    auto low2 = [](int32_t a, int32_t b) { return __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0C0C0602u); };     // byte 0: a's, byte 1: b's
+    auto high2 = [](int32_t a, int32_t b) { return __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x06020C0Cu); };    // bytes 2 and 3
+    auto fields = [](uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); };                          // one v_bfi
+    if (BITS == 8) {
+        w[0] = low2(t[0], t[1]) | high2(t[2], t[3]);
+        w[1] = low2(t[4], t[5]) | high2(t[6], t[7]);
+    } else if (BITS == 4) {
+        w[0] = fields(0x0F0F0F0Fu, low2(t[0], t[2]) | high2(t[4], t[6]), (low2(t[1], t[3]) | high2(t[5], t[7])) << 4);
+    } else {
+        w[0] = fields(0x0303u, low2(t[0], t[4]), low2(t[1], t[5]) << 2);
+        w[0] = fields(0x0F0Fu, w[0], low2(t[2], t[6]) << 4);
+        w[0] = fields(0x3F3Fu, w[0], low2(t[3], t[7]) << 6) & 0xFFFFu;
+    }
+    if (BITS != 8) w[1] = 0;
+}
+
 template <int BITS>
 __device__ __forceinline__ void quantise_octet(const float x[8], float inv16, const uint32_t rnd[4], uint32_t w[2])
 {
-    constexpr uint32_t kSignBits = BITS == 8 ? 0x80808080u : (BITS == 4 ? 0x88888888u : 0x0000AAAAu);
-    uint32_t t[8], sg[2] = {0, 0}, mags[2] = {0, 0};
+    int32_t t[8];
+    quantise_octet<BITS>(x, inv16, rnd, w, t);
+}
+
+// The codes that quantise_octet has just packed, as fp32 (code_values of them, without unpacking; not over field_unit)
+__device__ __forceinline__ void rounded_values(const int32_t t[8], float q[8])
+{
 #pragma unroll
-    for (int e = 7; e >= 0; --e) {
-        const uint32_t U = (uint32_t)(fabsf(x[e]) * inv16);
-        t[e] = U + draw16(rnd, e);
-        uint32_t &s = sg[BITS == 8 ? e >> 2 : 0];
-        s = __builtin_amdgcn_alignbit(s, __float_as_uint(x[e]), 32 - BITS);       // (s << BITS) | top BITS bits of x
-    }
-    // __builtin_amdgcn_perm(hi, lo, sel): result byte i is byte sel_i of {hi, lo} (0..3 lo, 4..7 hi, 12: zero)
-    auto low2 = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x0C0C0602u); };     // byte 0: a's, byte 1: b's
-    auto high2 = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x06020C0Cu); };    // bytes 2 and 3
-    auto fields = [](uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); };                          // one v_bfi
-    if (BITS == 8) {
-        mags[0] = low2(t[0], t[1]) | high2(t[2], t[3]);
-        mags[1] = low2(t[4], t[5]) | high2(t[6], t[7]);
-    } else if (BITS == 4) {
-        mags[0] = fields(0x0F0F0F0Fu, low2(t[0], t[2]) | high2(t[4], t[6]), (low2(t[1], t[3]) | high2(t[5], t[7])) << 4);
-    } else {
-        mags[0] = fields(0x0303u, low2(t[0], t[4]), low2(t[1], t[5]) << 2);
-        mags[0] = fields(0x0F0Fu, mags[0], low2(t[2], t[6]) << 4);
-        mags[0] = fields(0x3F3Fu, mags[0], low2(t[3], t[7]) << 6) & 0xFFFFu;
-    }
-#pragma unroll
-    for (int h = 0; h < (BITS == 8 ? 2 : 1); ++h) {
-        const uint32_t s = sg[h] & kSignBits;
-        const uint32_t s1 = s >> (BITS - 1), sm = s - s1;
-        w[h] = ((mags[h] ^ sm) + s1) ^ s;
-    }
-    if (BITS != 8) w[1] = 0;
+    for (int e = 0; e < 8; ++e) q[e] = signed_byte<2>((uint32_t)t[e]);
 }
 
 // LDS of a wave's own: its instructions are executed in order, so what is needed between one lane's write and another lane's
@@ -301,17 +324,36 @@ __device__ __forceinline__ void wave_memory_sync()
     asm volatile("" ::: "memory");
 }
 
-// max over the 2^lb_shift lanes of a scale block (aligned group of lanes)
+// max(a, |x[0]|, .. |x[7]|) for a >= 0; a value that is not a number does not count.  Written out because the compiler puts
+// an instruction per value in front to quiet signalling ones, which none of the callers has, where it does not see x computed.
+__device__ __forceinline__ float abs_max_octet(float a, const float x[8])
+{
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(a) : "v"(x[e]), "v"(x[e + 1]));
+    return a;
+}
+
+// max over the 2^lb_shift lanes of a scale block (aligned group of lanes), of values that are neither negative nor NaN: their
+// bit patterns order as they do, and an integer maximum takes the lane permutation into the instruction, where the
+// floating-point one needs a move and a quieting of its own.  Across rows of 16 lanes: the row swaps, without the LDS.
 __device__ __forceinline__ float block_max(float a, int lb_shift)
 {
+    auto larger = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
+    uint32_t m = __float_as_uint(a);
     // quad_perm [1,0,3,2] = 0xB1, [2,3,0,1] = 0x4E, row_half_mirror = 0x141, row_mirror = 0x140
-    if (lb_shift >= 1) a = fmaxf(a, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(a), 0xB1, 0xF, 0xF, true)));
-    if (lb_shift >= 2) a = fmaxf(a, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(a), 0x4E, 0xF, 0xF, true)));
-    if (lb_shift >= 3) a = fmaxf(a, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(a), 0x141, 0xF, 0xF, true)));
-    if (lb_shift >= 4) a = fmaxf(a, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(a), 0x140, 0xF, 0xF, true)));
-    if (lb_shift >= 5) a = fmaxf(a, __shfl_xor(a, 16, 64));
-    if (lb_shift >= 6) a = fmaxf(a, __shfl_xor(a, 32, 64));
-    return a;
+    if (lb_shift >= 1) m = larger(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0xB1, 0xF, 0xF, true));
+    if (lb_shift >= 2) m = larger(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x4E, 0xF, 0xF, true));
+    if (lb_shift >= 3) m = larger(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x141, 0xF, 0xF, true));
+    if (lb_shift >= 4) m = larger(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x140, 0xF, 0xF, true));
+    if (lb_shift >= 5) {
+        const auto p = __builtin_amdgcn_permlane16_swap(m, m, false, false);       // {rows 0 0 2 2, rows 1 1 3 3}
+        m = larger(p[0], p[1]);
+    }
+    if (lb_shift >= 6) {
+        const auto p = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+        m = larger(p[0], p[1]);
+    }
+    return __uint_as_float(m);
 }
 
 // Workgroups are dealt to the eight XCDs (each with its own L2) in turn: workgroup b runs on XCD

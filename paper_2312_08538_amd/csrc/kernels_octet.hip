@@ -159,9 +159,9 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                 for (int e = 1; e < 8; ++e) g[e] = e < tail ? g[e] : 0.0f;
             }
         }
-        const float dstep1 = r.scale * inv_levels(BITS), dstep = dstep1;
-        const float dpart = TWO ? dstep : dstep1 * dp.omb;
-        const float dstep2 = r2.scale * inv_levels(BITS);
+        const float dstep = r.scale * (inv_levels(BITS) * field_unit(BITS));
+        const float dpart = TWO ? dstep : dstep * dp.omb;
+        const float dstep2 = r2.scale * (inv_levels(BITS) * field_unit(BITS));
         float qf[8], qf2[8];
         code_values<BITS>(r.c0, r.c1, qf);
         if (TWO) code_values<BITS>(r2.c0, r2.c1, qf2);
@@ -308,14 +308,12 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
             if (TAIL && o == n_oct - 1)
                 for (int64_t b = o + 1; (b & 3) != 0; ++b) sb[b] = 0;          // the rest of the last word
         }
-        float a = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) a = fmaxf(a, fabsf(x[e]));
-        a = block_max(a, d.lb_shift);
+        const float a = block_max(abs_max_octet(0.0f, x), d.lb_shift);
         const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
         uint32_t rnd[4], w[2];
+        int32_t t[8];
         philox4x32_10((uint32_t)o, (uint32_t)it.mat, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
-        quantise_octet<BITS>(x, inv16, rnd, w);
+        quantise_octet<BITS>(x, inv16, rnd, w, t);
         if (valid) {
             if (cut) store_code_words_end<BITS>(d, codes, o, tail, w);
             else store_code_words<BITS>(d, codes, o, w);
@@ -324,14 +322,11 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
         if (TWO) {
             // q+ = C(x - e~+): what the first rounding left, one level finer
             const float dnew = a * inv_levels(BITS);
-            float a2 = 0.0f, qn[8];
-            code_values<BITS>(w[0], w[1], qn);
+            float qn[8];
+            rounded_values(t, qn);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                x[e] = x[e] - dnew * qn[e];
-                a2 = fmaxf(a2, fabsf(x[e]));
-            }
-            a2 = block_max(a2, d.lb_shift);
+            for (int e = 0; e < 8; ++e) x[e] = x[e] - dnew * qn[e];
+            const float a2 = block_max(abs_max_octet(0.0f, x), d.lb_shift);
             const float inv16_2 = (a2 > 0.0f) ? (s_f / a2) * 65536.0f : 0.0f;
             philox4x32_10((uint32_t)o, (uint32_t)it.mat | 0x80000000u, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
             quantise_octet<BITS>(x, inv16_2, rnd, w);

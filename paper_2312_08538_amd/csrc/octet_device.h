@@ -14,7 +14,7 @@ namespace {
 template <bool BF16, int BITS>
 struct RawOctet {
     uint4 g0, g1;        // gradient bits (g1 only for fp32)
-    uint32_t c0, c1;     // code bits: 8-bit: two words; 4-bit: c0; 2-bit: low 16 bits of c0
+    uint32_t c0, c1;     // code bits: 8-bit: two words; 4-bit: c0; 2-bit: low 16 bits of c0, the others zero
     float scale;
 };
 
@@ -75,15 +75,15 @@ __device__ __forceinline__ RawCodes<BITS> load_codes_always(const MatDesc &d, co
 template <int BITS>
 __device__ __forceinline__ void add_codes(const RawCodes<BITS> &r, float p[8])
 {
-    const float step = r.scale * inv_levels(BITS);
+    const float step = r.scale * (inv_levels(BITS) * field_unit(BITS));
     float q[8];
-    code_values<BITS, true>(r.c0, r.c1, q);
+    code_values<BITS>(r.c0, r.c1, q);
 #pragma unroll
     for (int e = 0; e < 8; ++e) p[e] = __builtin_fmaf(step, q[e], p[e]);
 }
 
 // omb: 1 - beta of the partial update in the P and Q+ passes (Algorithm 4 line 5), 1 in the err pass
-template <bool BF16, int BITS, bool TWO>
+template <bool BF16, int BITS>
 __device__ __forceinline__ void decode_octet(const RawOctet<BF16, BITS> &r, float omb, float p[8])
 {
     float g[8];
@@ -99,9 +99,9 @@ __device__ __forceinline__ void decode_octet(const RawOctet<BF16, BITS> &r, floa
         g[3] = __uint_as_float(r.g0.w); g[4] = __uint_as_float(r.g1.x); g[5] = __uint_as_float(r.g1.y);
         g[6] = __uint_as_float(r.g1.z); g[7] = __uint_as_float(r.g1.w);
     }
-    const float step = r.scale * inv_levels(BITS) * omb;
+    const float step = r.scale * (inv_levels(BITS) * field_unit(BITS)) * omb;
     float q[8];
-    code_values<BITS, TWO>(r.c0, r.c1, q);
+    code_values<BITS>(r.c0, r.c1, q);
 #pragma unroll
     for (int e = 0; e < 8; ++e) p[e] = __builtin_fmaf(step, q[e], g[e]);
 }
@@ -188,38 +188,34 @@ __global__ __launch_bounds__(256) void k_err_octet(DevicePlan dp, const void *__
     // One row of this lane: decode, residual, block max-norm, rounding, store.
     auto process = [&](const RawOctet<BF16, BITS> &oct, const RawCodes<BITS> &oct2, const float (&ph)[RP], int row, bool valid) {
         float x[8];
-        decode_octet<BF16, BITS, TWO>(oct, 1.0f, x);
+        decode_octet<BF16, BITS>(oct, 1.0f, x);
         if (TWO) add_codes<BITS>(oct2, x);
-        float a = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             float acc = 0.0f;
 #pragma unroll
             for (int c = 0; c < RP; ++c) acc = __builtin_fmaf(ph[c], q[e][c], acc);
             x[e] = x[e] - acc;
-            a = fmaxf(a, fabsf(x[e]));
         }
-        a = block_max(a, d.lb_shift);
+        const float a = block_max(abs_max_octet(0.0f, x), d.lb_shift);
         const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
         const int64_t o = (int64_t)row * d.m8 + oc;
         uint32_t rnd[4];
         philox4x32_10((uint32_t)o, (uint32_t)it.mat, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
         uint32_t w[2];
-        quantise_octet<BITS>(x, inv16, rnd, w);
+        int32_t t[8];
+        quantise_octet<BITS>(x, inv16, rnd, w, t);
         if (valid) {
             store_code_words<BITS>(d, TWO ? codes_first : codes, o, w);
             if ((lc & ((1 << d.lb_shift) - 1)) == 0) (TWO ? scales_first : scales)[d.scale_off + (o >> d.lb_shift)] = a;
         }
         if (TWO) {
             const float dnew = a * inv_levels(BITS);
-            float a2 = 0.0f, qn[8];
-            code_values<BITS, true>(w[0], w[1], qn);
+            float qn[8];
+            rounded_values(t, qn);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                x[e] = x[e] - dnew * qn[e];
-                a2 = fmaxf(a2, fabsf(x[e]));
-            }
-            a2 = block_max(a2, d.lb_shift);
+            for (int e = 0; e < 8; ++e) x[e] = x[e] - dnew * qn[e];
+            const float a2 = block_max(abs_max_octet(0.0f, x), d.lb_shift);
             const float inv16_2 = (a2 > 0.0f) ? (s_f / a2) * 65536.0f : 0.0f;
             philox4x32_10((uint32_t)o, (uint32_t)it.mat | 0x80000000u, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
             quantise_octet<BITS>(x, inv16_2, rnd, w);
@@ -343,7 +339,7 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
                     a0.c0 = c.x; a1.c0 = c.y;
                 } else {
                     const uint32_t c = cw[o >> 1];          // the fields of the first octet are the low half
-                    a0.c0 = c; a1.c0 = c >> 16;
+                    a0.c0 = c & 0xFFFFu; a1.c0 = c >> 16;
                 }
                 a0.scale = a1.scale = (TWO ? scales_first : scales)[d.scale_off + (o >> d.lb_shift)];
                 if (TWO) {
@@ -378,13 +374,11 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
             float a = 0.0f;
 #pragma unroll
             for (int h = 0; h < NT; ++h) {
-                decode_octet<BF16, BITS, TWO>(in.o[h][v], 1.0f, x[h]);
+                decode_octet<BF16, BITS>(in.o[h][v], 1.0f, x[h]);
                 if (TWO) add_codes<BITS>(in.o2[TWO ? h : 0][TWO ? v : 0], x[h]);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    x[h][e] = x[h][e] - acc[h][e][v];
-                    a = fmaxf(a, fabsf(x[h][e]));
-                }
+                for (int e = 0; e < 8; ++e) x[h][e] = x[h][e] - acc[h][e][v];
+                a = abs_max_octet(a, x[h]);
             }
             a = block_max(a, lb);
             const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
@@ -396,19 +390,18 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
                 const int64_t o = (int64_t)rowc * d.m8 + oct_col(h);
                 uint32_t rnd[4];
                 philox4x32_10((uint32_t)o, (uint32_t)it.mat, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
-                quantise_octet<BITS>(x[h], inv16, rnd, w[h]);
+                int32_t tq[8];
+                quantise_octet<BITS>(x[h], inv16, rnd, w[h], tq);
                 if (valid) {
                     if (!WIDE) store_code_words<BITS>(d, TWO ? codes_first : codes, o, w[h]);
                     if (h == 0 && (cc & ((1 << lb) - 1)) == 0) (TWO ? scales_first : scales)[d.scale_off + (o >> d.lb_shift)] = a;
                 }
                 if (TWO) {
                     float qn[8];
-                    code_values<BITS, true>(w[h][0], w[h][1], qn);
+                    rounded_values(tq, qn);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        x[h][e] = x[h][e] - dnew * qn[e];
-                        a2 = fmaxf(a2, fabsf(x[h][e]));
-                    }
+                    for (int e = 0; e < 8; ++e) x[h][e] = x[h][e] - dnew * qn[e];
+                    a2 = abs_max_octet(a2, x[h]);
                 }
             }
             if (WIDE && valid) store_code_pair<BITS>(d, TWO ? codes_first : codes, (int64_t)rowc * d.m8 + oc0, w[0], w[NT - 1]);
@@ -524,7 +517,7 @@ __device__ __forceinline__ void q_octet(const DevicePlan &dp, int block, float *
 #pragma unroll
         for (int s = 0; s < kLoads; ++s) {
             float p[8];
-            decode_octet<BF16, BITS, TWO>(cur.o[s], dp.omb, p);
+            decode_octet<BF16, BITS>(cur.o[s], dp.omb, p);
             if (TWO) add_codes<BITS>(cur.o2[s], p);
             float4 *dst = reinterpret_cast<float4 *>(T + (lrow + 8 * s) * kQTilePitch + loct * 8);
             dst[0] = make_float4(p[0], p[1], p[2], p[3]);
@@ -764,7 +757,7 @@ __device__ __forceinline__ void p_octet(const DevicePlan &dp, int block, const P
             RawOctet<BF16, BITS> o;
             o.g0 = cur[s].g0; o.g1 = cur[s].g1; o.c0 = k0.c0; o.c1 = k0.c1; o.scale = k0.scale;
             float p[8];
-            decode_octet<BF16, BITS, TWO>(o, dp.omb, p);
+            decode_octet<BF16, BITS>(o, dp.omb, p);
             if (TWO) add_codes<BITS>(staged(cstage, sstage), p);
             float4 *dst = reinterpret_cast<float4 *>(T + rr * kTileStride + loct * 8);
             dst[0] = make_float4(p[0], p[1], p[2], p[3]);

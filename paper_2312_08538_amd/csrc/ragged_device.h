@@ -77,7 +77,7 @@ __device__ __forceinline__ void load_octet_at(const OctetBase<BF16, BITS, TWO> &
 template <bool BF16, int BITS, bool TWO>
 __device__ __forceinline__ void decode_octet_at(const OctetRegs<BF16, BITS, TWO> &r, float omb, float p[8])
 {
-    decode_octet<BF16, BITS, TWO>(r.o, omb, p);
+    decode_octet<BF16, BITS>(r.o, omb, p);
     if (TWO) add_codes<BITS>(r.o2, p);
 }
 

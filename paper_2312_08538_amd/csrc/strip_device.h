@@ -451,15 +451,13 @@ __device__ __forceinline__ void quantise_run(const DevicePlan &dp, const MatDesc
             for (int e = 0; e < 8; ++e) x[e] = pos + e < count ? x[e] : 0.0f;
         }
         const int64_t o = (flat0 >> 3) + id;
-        auto round_octet = [&](uint32_t mat_word, uint32_t *cw, float *sc, uint32_t (&w)[2]) {
-            float a = 0.0f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) a = fmaxf(a, fabsf(x[e]));
-            a = block_max(a, lb);
+        auto round_octet = [&](uint32_t mat_word, uint32_t *cw, float *sc, int32_t (&t)[8]) {
+            const float a = block_max(abs_max_octet(0.0f, x), lb);
             const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
             uint32_t rnd[4];
             philox4x32_10((uint32_t)o, mat_word, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
-            quantise_octet<BITS>(x, inv16, rnd, w);
+            uint32_t w[2];
+            quantise_octet<BITS>(x, inv16, rnd, w, t);
             if (any) {
                 uint32_t *wp = cw + d.word_off;
                 if (BITS == 8) {
@@ -475,16 +473,15 @@ __device__ __forceinline__ void quantise_run(const DevicePlan &dp, const MatDesc
             }
             return a;
         };
-        uint32_t w[2];
-        const float a = round_octet((uint32_t)mat, codes, scales, w);
+        int32_t t[8];
+        const float a = round_octet((uint32_t)mat, codes, scales, t);
         if (TWO) {
             const float dnew = a * inv_levels(BITS);
+            float qn[8];
+            rounded_values(t, qn);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int qn = BITS == 8 ? code_field(w[e >> 2], e & 3, 8) : code_field(w[0], e, BITS);
-                x[e] = x[e] - dnew * (float)qn;
-            }
-            round_octet((uint32_t)mat | 0x80000000u, codes2, scales2, w);
+            for (int e = 0; e < 8; ++e) x[e] = x[e] - dnew * qn[e];
+            round_octet((uint32_t)mat | 0x80000000u, codes2, scales2, t);
         }
     }
 }
