@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kCsCols) void k_cs_update_generic(DevicePlan dp, co
 // planner): the rows of the table, then the rows of the residual are staged there, the R values of a bucket or column side by
 // side; a column's row of Q+, its hash and a bucket's column list are then read once for R rows (with one row per workgroup
 // these reads, r + 1 words per element, and not the gradient were most of the traffic: 77 us for the 18-layer residual
-// network, 11.7 M elements, and 37 now).  The LDS of the launch is the largest matrix's: one matrix of 16384 columns and as
+// network, 11.7 M elements, 38 with eight; 34 with loads in groups and a column ahead, as below).  The LDS of the launch is the largest matrix's: one matrix of 16384 columns and as
 // many buckets (128 KB, one workgroup per CU) beside ten of 512 x 4608 takes 227 us (398 with one row per workgroup).
 template <int R>
 __device__ __forceinline__ void csc_store(float *dst, const float (&v)[R])
@@ -127,47 +127,78 @@ __device__ __forceinline__ void csc_rows(const DevicePlan &dp, const MatDesc &d,
     __shared__ __attribute__((aligned(16))) float s_p[RP >= 16 ? 8 * RP : 4];
     if (RP >= 16)
         for (int e = threadIdx.x; e < R * RP; e += threads) s_p[e] = prow[(int64_t)row_of(e / RP) * r + (e % RP < r ? e % RP : r - 1)];
-    for (int b = threadIdx.x; b < w; b += threads) {
-        float t[R];
+    // a column's hash, gradient and row of Q+ are requested while the one before is worked on (beyond the end: the last one
+    // again, not used), the first ones before the table is staged
+    struct Column { int32_t hv; float x[R], q[RP]; } nx;
+    auto load_column = [&](Column &o, int k) {
+        k = k < m ? k : m - 1;
+        o.hv = dp.row_hash[d.hash_off + k];
+        if (dp.dtype == 0) {
 #pragma unroll
-        for (int i = 0; i < R; ++i) t[i] = table_load(table, dp.table_dtype, trow + (int64_t)row_of(i) * w + b);
+            for (int i = 0; i < R; ++i) o.x[i] = load_grad(grads, 0, grow + (int64_t)row_of(i) * m + k);
+        } else {
+#pragma unroll
+            for (int i = 0; i < R; ++i) o.x[i] = load_grad(grads, 1, grow + (int64_t)row_of(i) * m + k);
+        }
+        const float *qrow = Qn + d.q_off + (int64_t)k * r;
+#pragma unroll
+        for (int c = 0; c < RP; ++c) o.q[c] = qrow[c < r ? c : r - 1];
+    };
+    constexpr bool AHEAD = RP <= 8;                // at higher ranks there are no registers for a second column
+    if (AHEAD) load_column(nx, threadIdx.x);
+    for (int b = threadIdx.x; b < w; b += threads) {
+        // one branch on the type around all R loads: a branch around each would wait for its value before the next
+        float t[R];
+        if (dp.table_dtype == 0) {
+#pragma unroll
+            for (int i = 0; i < R; ++i) t[i] = table_load(table, 0, trow + (int64_t)row_of(i) * w + b);
+        } else {
+#pragma unroll
+            for (int i = 0; i < R; ++i) t[i] = table_load(table, 1, trow + (int64_t)row_of(i) * w + b);
+        }
         csc_store<R>(s_t + (size_t)b * R, t);
     }
     __syncthreads();
     for (int k = threadIdx.x; k < m; k += threads) {
-        const int32_t hv = dp.row_hash[d.hash_off + k];
-        float x[R], q[RP], t[R];
-#pragma unroll
-        for (int i = 0; i < R; ++i) x[i] = load_grad(grads, dp.dtype, grow + (int64_t)row_of(i) * m + k);
-        const float *qrow = Qn + d.q_off + (int64_t)k * r;
-#pragma unroll
-        for (int c = 0; c < RP; ++c) q[c] = qrow[c < r ? c : r - 1];
-        csc_load<R>(s_t + (size_t)(hv & INT32_MAX) * R, t);
-        const float somb = signed_omb(dp, hv);
+        if (!AHEAD) load_column(nx, k);
+        Column cu = nx;
+        if (AHEAD) load_column(nx, k + threads);
+        float t[R];
+        csc_load<R>(s_t + (size_t)(cu.hv & INT32_MAX) * R, t);
+        const float somb = signed_omb(dp, cu.hv);
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             const float *ph = prow + (int64_t)row_of(i) * r;
             float rec = 0.0f;
 #pragma unroll
             for (int c = 0; c < RP; ++c)
-                if (c < r) rec = __builtin_fmaf(RP >= 16 ? s_p[i * RP + c] : ph[c], q[c], rec);
-            x[i] = __builtin_fmaf(somb, t[i], x[i]) - rec;
+                if (c < r) rec = __builtin_fmaf(RP >= 16 ? s_p[i * RP + c] : ph[c], cu.q[c], rec);
+            cu.x[i] = __builtin_fmaf(somb, t[i], cu.x[i]) - rec;
         }
-        csc_store<R>(s_x + (size_t)k * R, x);
+        csc_store<R>(s_x + (size_t)k * R, cu.x);
     }
     __syncthreads();
     const int32_t *ptr = dp.bucket_ptr + d.bptr_off;
     const int32_t *cols = dp.bucket_rows + d.hash_off;
     for (int b = threadIdx.x; b < w; b += threads) {
-        float acc[R], x[R], s_old[R];
+        float acc[R], s_old[R];
 #pragma unroll
         for (int i = 0; i < R; ++i) acc[i] = 0.0f;
         const int32_t e1 = ptr[b + 1];
-        for (int32_t e = ptr[b]; e < e1; ++e) {
-            const int32_t hv = cols[e];
-            csc_load<R>(s_x + (size_t)(hv & INT32_MAX) * R, x);
+        // the next four entries of the bucket are requested together: one by one, each waits for its index and then its x
+        for (int32_t e = ptr[b]; e < e1; e += 4) {
+            int32_t hv[4];
+            float x[4][R];
 #pragma unroll
-            for (int i = 0; i < R; ++i) acc[i] = hv < 0 ? acc[i] - x[i] : acc[i] + x[i];
+            for (int u = 0; u < 4; ++u) hv[u] = cols[e + u < e1 ? e + u : e1 - 1];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) csc_load<R>(s_x + (size_t)(hv[u] & INT32_MAX) * R, x[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (e + u >= e1) break;
+#pragma unroll
+                for (int i = 0; i < R; ++i) acc[i] = hv[u] < 0 ? acc[i] - x[u][i] : acc[i] + x[u][i];
+            }
         }
         csc_load<R>(s_t + (size_t)b * R, s_old);
 #pragma unroll
@@ -594,14 +625,18 @@ void k_cs_q_octet(DevicePlan dp, const void *__restrict__ grads, const void *__r
 // CPL = 512 / THREADS consecutive columns and keeps their rows of Q+ in registers (CPL * RP = 64 values,
 // zero beyond the rank).  The rows of the item's buckets form one list; it is walked 64 entries at a time: their row
 // indices and rows of P^ are staged in LDS by the whole workgroup (a thread then reads a row of P^ with
-// RP / 4 broadcast reads), and the gradient of the next entry is requested before the current one is
-// worked on, the table row of the next bucket before the current bucket is.
+// RP / 4 broadcast reads).  A chunk is one loop over its entries, the buckets opened and closed on the way, so that the
+// gradients of the next kCsAhead entries are in flight whatever the buckets hold; the table row of the next bucket is
+// requested before the current bucket is.  Four waves per SIMD hold the whole grid of a large model (3478 workgroups for
+// 209.7 M elements) in one round; the vector ALU (16 instructions per element) takes 85 us of the pass.  That model at
+// rank 8, bf16, fp16 table: 175 -> 158 us.
 constexpr int kCsChunk = 64;
 
 constexpr int kCsMaxBuckets = 256;
 
 template <bool BF16, bool F16, int CPL, int RP>
-__global__ __launch_bounds__(512 / CPL) void k_cs_update_octet(DevicePlan dp, const void *__restrict__ grads, void *table,
+__global__ __launch_bounds__(512 / CPL) __attribute__((amdgpu_waves_per_eu(F16 || CPL < 8 ? 4 : 3)))
+void k_cs_update_octet(DevicePlan dp, const void *__restrict__ grads, void *table,
                                                          const float *__restrict__ Phat, const float *__restrict__ Qn)
 {
     constexpr int THREADS = 512 / CPL;
@@ -673,47 +708,21 @@ __global__ __launch_bounds__(512 / CPL) void k_cs_update_octet(DevicePlan dp, co
         }
     };
 
-    int32_t e = e0;
+    constexpr int kCsAhead = GW == 8 ? 1 : 2;         // gradient rows in flight; more of them spill and gain nothing
+    // bucket `bi` of the item: its old entries, its sums so far and where its rows end
+    int bi = 0, e_stop = s_ptr[1];
+    float s_old[CPL], acc[CPL];
     Words tn = load_words(table, d.table_off + (int64_t)it.a * d.m + col, F16 ? 2 : 4, TW);
-    Words gn = tn;                                   // set when a chunk is staged
-    for (int bi = 0; bi < it.b; ++bi) {
-        const int b = it.a + bi;
-        float s_old[CPL], acc[CPL];
+    auto open = [&] {
         widen_t(tn, s_old);
-        const int bn = bi + 1 < it.b ? b + 1 : b;
+        const int bn = it.a + (bi + 1 < it.b ? bi + 1 : bi);
         tn = load_words(table, d.table_off + (int64_t)bn * d.m + col, F16 ? 2 : 4, TW);
 #pragma unroll
         for (int j = 0; j < CPL; ++j) acc[j] = 0.0f;
-        const int32_t e_stop = s_ptr[bi + 1];
-        for (; e < e_stop; ++e) {
-            const int j = (e - e0) & (kCsChunk - 1);          // uniform over the workgroup
-            if (j == 0) {
-                __syncthreads();                              // every thread is done with the previous chunk
-                stage(e);
-                __syncthreads();
-                gn = load_grad_row(s_row[0]);
-            }
-            const int32_t hv = s_row[j];
-            float g[CPL];
-            widen_g(gn, g);
-            gn = load_grad_row(s_row[j + 1 < kCsChunk ? j + 1 : j]);
-            const float somb = hv < 0 ? -dp.omb : dp.omb;
-            float ph[RP];
-#pragma unroll
-            for (int c4 = 0; c4 < RP / 4; ++c4) {
-                const float4 v = reinterpret_cast<const float4 *>(s_p + j * RP)[c4];
-                ph[4 * c4] = v.x; ph[4 * c4 + 1] = v.y; ph[4 * c4 + 2] = v.z; ph[4 * c4 + 3] = v.w;
-            }
-#pragma unroll
-            for (int jj = 0; jj < CPL; ++jj) {
-                const float pv = __builtin_fmaf(somb, s_old[jj], g[jj]);
-                float rec = 0.0f;
-#pragma unroll
-                for (int c = 0; c < RP; ++c) rec = __builtin_fmaf(ph[c], q[jj][c], rec);     // beyond the rank: + 0 * 0
-                const float x = pv - rec;
-                acc[jj] = hv < 0 ? acc[jj] - x : acc[jj] + x;
-            }
-        }
+        e_stop = s_ptr[bi + 1];
+    };
+    auto close = [&] {
+        const int b = it.a + bi;
         if (active) {
             float out[CPL];
 #pragma unroll
@@ -747,6 +756,49 @@ __global__ __launch_bounds__(512 / CPL) void k_cs_update_octet(DevicePlan dp, co
                 }
             }
         }
+    };
+    open();
+    for (int32_t c0 = e0; c0 < e1; c0 += kCsChunk) {
+        const int n = min(e1 - c0, kCsChunk);
+        if (c0 != e0) __syncthreads();                        // every thread is done with the previous chunk
+        stage(c0);
+        __syncthreads();
+        Words gn[kCsAhead];
+#pragma unroll
+        for (int u = 0; u < kCsAhead; ++u) gn[u] = load_grad_row(s_row[u]);
+        for (int j0 = 0; j0 < n; j0 += kCsAhead) {
+#pragma unroll
+            for (int u = 0; u < kCsAhead; ++u) {
+                const int j = j0 + u;                         // uniform over the workgroup
+                if (j >= n) break;
+                while (c0 + j == e_stop) { close(); ++bi; open(); }     // buckets without rows among them
+                const int32_t hv = s_row[j];
+                float g[CPL];
+                widen_g(gn[u], g);
+                gn[u] = load_grad_row(s_row[j + kCsAhead < n ? j + kCsAhead : n - 1]);
+                const float somb = hv < 0 ? -dp.omb : dp.omb;
+                float ph[RP];
+#pragma unroll
+                for (int c4 = 0; c4 < RP / 4; ++c4) {
+                    const float4 v = reinterpret_cast<const float4 *>(s_p + j * RP)[c4];
+                    ph[4 * c4] = v.x; ph[4 * c4 + 1] = v.y; ph[4 * c4 + 2] = v.z; ph[4 * c4 + 3] = v.w;
+                }
+#pragma unroll
+                for (int jj = 0; jj < CPL; ++jj) {
+                    const float pv = __builtin_fmaf(somb, s_old[jj], g[jj]);
+                    float rec = 0.0f;
+#pragma unroll
+                    for (int c = 0; c < RP; ++c) rec = __builtin_fmaf(ph[c], q[jj][c], rec);     // beyond the rank: + 0 * 0
+                    const float x = pv - rec;
+                    acc[jj] = hv < 0 ? acc[jj] - x : acc[jj] + x;
+                }
+            }
+        }
+    }
+    for (;;) {
+        close();
+        if (++bi >= it.b) break;
+        open();
     }
 }
 
