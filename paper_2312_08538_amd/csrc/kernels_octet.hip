@@ -53,7 +53,8 @@ void k_q_octet(DevicePlan dp, const void *__restrict__ grads, const uint32_t *__
 }
 
 template <bool BF16, int BITS, int RP, bool WIDE, bool TWO>
-__global__ __launch_bounds__(256, 2) void k_err_tile(DevicePlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
+__global__ __launch_bounds__(256) CONEF_ERR_TILE_WAVES(BF16, WIDE, TWO)
+void k_err_tile(DevicePlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
                                                   const float *__restrict__ Phat, const float *__restrict__ Qn,
                                                   uint32_t step_lo, uint32_t step_hi, uint32_t *codes_first, float *scales_first)
 {

@@ -264,6 +264,17 @@ __global__ __launch_bounds__(256) void k_err_octet(DevicePlan dp, const void *__
 // floats per lane).  A scale block is 2^lb_shift <= 16 lanes of one DPP row (WIDE: the row's 16 lanes, both tiles).
 // WIDE: lane cc takes the neighbouring octets 2 cc and 2 cc + 1 of the strip, one per tile, so that its two gradient
 // loads are adjacent, its code bits are one load and one store, and its block scale is loaded once.
+// A trip's inputs have one set of registers: as soon as a row is decoded, the same row of the next trip is requested into
+// its place.  (Two sets, the next trip's loads before the whole of the present one, took 40 - 60 registers more: one wave
+// per SIMD less, or 60 - 150 spilled ones with two vectors on wide strips.)
+// Waves per SIMD: three where three fit without spilling more than a few registers, else two; never more, which the pass
+// with one vector could do on narrow strips: it is bound by memory there, and more waves are slower.  Measured, us per step,
+// two sets -> one set at 2 / 3 waves: 124 M fp32 elements at rank 4, 4-bit codes: blocks of 128 368.3 -> 365.8 / 367.5
+// (370.4 at 4), of 256 403 -> 368 / 386; two vectors, of 128 477 -> 464.5 / 459.1, of 256 647 -> 459 / 765.  210 M bf16 at rank 8:
+// 2-bit codes, blocks of 256 390.8 -> 390.4 / 380.8; 4-bit, of 128 414.7 -> 427 / 410.9.
+#define CONEF_ERR_TILE_WAVES_N(BF16, WIDE, TWO) (((BF16) ? !((WIDE) && (TWO)) : (!(WIDE) && (TWO))) ? 3 : 2)
+#define CONEF_ERR_TILE_WAVES(BF16, WIDE, TWO) \
+    __attribute__((amdgpu_waves_per_eu(CONEF_ERR_TILE_WAVES_N(BF16, WIDE, TWO), CONEF_ERR_TILE_WAVES_N(BF16, WIDE, TWO))))
 typedef float tile_f32x4 __attribute__((ext_vector_type(4)));
 
 // s_bq: LDS, err_tile_lds<RP, WIDE>() floats; `block`: index of the workgroup among those of this pass
@@ -311,49 +322,49 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
         float a[NQ];
     };
     // Rows at or beyond the end of the item re-read its last row (nothing is stored for them): unconditional loads.
-    auto load_trip = [&](TripIn &in, int r0) {
+    TripIn in;
+    auto load_a = [&](int r0) {
         const int ar = r0 + cc < row_end ? r0 + cc : row_end - 1;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) in.a[q] = Phat[d.p_off + (int64_t)ar * RP + 4 * q + kg];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int row = r0 + 4 * kg + v < row_end ? r0 + 4 * kg + v : row_end - 1;
-            if (WIDE) {
-                // both octets at once: o is even
-                const int64_t o = (int64_t)row * d.m8 + oc0;
-                const uint32_t *cw = (TWO ? codes_first : codes) + d.word_off;
-                RawOctet<BF16, BITS> &a0 = in.o[0][v], &a1 = in.o[NT - 1][v];
-                a0.g1 = a1.g1 = make_uint4(0, 0, 0, 0); a0.c1 = a1.c1 = 0;
-                if (BF16) {
-                    const uint4 *gp = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(grads) + d.grad_off + o * 8);
-                    a0.g0 = gp[0]; a1.g0 = gp[1];
-                } else {
-                    const uint4 *gp = reinterpret_cast<const uint4 *>(reinterpret_cast<const float *>(grads) + d.grad_off + o * 8);
-                    a0.g0 = gp[0]; a0.g1 = gp[1]; a1.g0 = gp[2]; a1.g1 = gp[3];
-                }
-                if (BITS == 8) {
-                    const uint4 c = *reinterpret_cast<const uint4 *>(cw + o * 2);
-                    a0.c0 = c.x; a0.c1 = c.y; a1.c0 = c.z; a1.c1 = c.w;
-                } else if (BITS == 4) {
-                    const uint2 c = *reinterpret_cast<const uint2 *>(cw + o);
-                    a0.c0 = c.x; a1.c0 = c.y;
-                } else {
-                    const uint32_t c = cw[o >> 1];          // the fields of the first octet are the low half
-                    a0.c0 = c & 0xFFFFu; a1.c0 = c >> 16;
-                }
-                a0.scale = a1.scale = (TWO ? scales_first : scales)[d.scale_off + (o >> d.lb_shift)];
-                if (TWO) {
-#pragma unroll
-                    for (int h = 0; h < NT; ++h) in.o2[TWO ? h : 0][TWO ? v : 0] = load_codes_always<BITS>(d, codes, scales, o + h);
-                }
+    };
+    auto load_row = [&](int r0, int v) {
+        const int row = r0 + 4 * kg + v < row_end ? r0 + 4 * kg + v : row_end - 1;
+        if (WIDE) {
+            // both octets at once: o is even
+            const int64_t o = (int64_t)row * d.m8 + oc0;
+            const uint32_t *cw = (TWO ? codes_first : codes) + d.word_off;
+            RawOctet<BF16, BITS> &a0 = in.o[0][v], &a1 = in.o[NT - 1][v];
+            a0.g1 = a1.g1 = make_uint4(0, 0, 0, 0); a0.c1 = a1.c1 = 0;
+            if (BF16) {
+                const uint4 *gp = reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(grads) + d.grad_off + o * 8);
+                a0.g0 = gp[0]; a1.g0 = gp[1];
             } else {
-                const int64_t o = (int64_t)row * d.m8 + oc0;
-                in.o[0][v] = load_octet_always<BF16, BITS>(d, grads, TWO ? codes_first : codes, TWO ? scales_first : scales, o);
-                if (TWO) in.o2[0][TWO ? v : 0] = load_codes_always<BITS>(d, codes, scales, o);
+                const uint4 *gp = reinterpret_cast<const uint4 *>(reinterpret_cast<const float *>(grads) + d.grad_off + o * 8);
+                a0.g0 = gp[0]; a0.g1 = gp[1]; a1.g0 = gp[2]; a1.g1 = gp[3];
             }
+            if (BITS == 8) {
+                const uint4 c = *reinterpret_cast<const uint4 *>(cw + o * 2);
+                a0.c0 = c.x; a0.c1 = c.y; a1.c0 = c.z; a1.c1 = c.w;
+            } else if (BITS == 4) {
+                const uint2 c = *reinterpret_cast<const uint2 *>(cw + o);
+                a0.c0 = c.x; a1.c0 = c.y;
+            } else {
+                const uint32_t c = cw[o >> 1];          // the fields of the first octet are the low half
+                a0.c0 = c & 0xFFFFu; a1.c0 = c >> 16;
+            }
+            a0.scale = a1.scale = (TWO ? scales_first : scales)[d.scale_off + (o >> d.lb_shift)];
+            if (TWO) {
+#pragma unroll
+                for (int h = 0; h < NT; ++h) in.o2[TWO ? h : 0][TWO ? v : 0] = load_codes_always<BITS>(d, codes, scales, o + h);
+            }
+        } else {
+            const int64_t o = (int64_t)row * d.m8 + oc0;
+            in.o[0][v] = load_octet_always<BF16, BITS>(d, grads, TWO ? codes_first : codes, TWO ? scales_first : scales, o);
+            if (TWO) in.o2[0][TWO ? v : 0] = load_codes_always<BITS>(d, codes, scales, o);
         }
     };
-    auto process = [&](const TripIn &in, int r0) {
+    auto process = [&](int r0) {
         tile_f32x4 acc[NT][8];
 #pragma unroll
         for (int h = 0; h < NT; ++h)
@@ -365,6 +376,7 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
                     acc[h][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(in.a[q], WIDE ? my_bq[((h * 8 + t) * NQ + q) * 64] : bq[h][t][q],
                                                                      acc[h][t], 0, 0, 0);
             }
+        load_a(r0 + 16);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = r0 + 4 * kg + v;
@@ -380,6 +392,7 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
                 for (int e = 0; e < 8; ++e) x[h][e] = x[h][e] - acc[h][e][v];
                 a = abs_max_octet(a, x[h]);
             }
+            load_row(r0 + 16, v);
             a = block_max(a, lb);
             const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
             const float dnew = a * inv_levels(BITS);
@@ -422,16 +435,11 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
             }
         }
     };
-    // the next trip is loaded before the current one is worked on; two register sets take turns
-    TripIn ta, tb;
-    load_trip(ta, it.b);
-    for (int r0 = it.b; r0 < row_end; r0 += 32) {
-        load_trip(tb, r0 + 16);
-        process(ta, r0);
-        if (r0 + 16 >= row_end) break;              // uniform
-        load_trip(ta, r0 + 32);
-        process(tb, r0 + 16);
-    }
+    // as soon as a row of a trip is decoded, the same row of the next trip is requested into its registers
+    load_a(it.b);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) load_row(it.b, v);
+    for (int r0 = it.b; r0 < row_end; r0 += 16) process(r0);
 }
 
 // ------------------------------------------------------------------ Q+ pass
