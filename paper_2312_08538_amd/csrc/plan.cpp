@@ -483,6 +483,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         const int64_t strip_q_rows = plan.ragged ? std::min<int64_t>(512, std::max<int64_t>(128, round_up(strip_elems / (64 * 1024), 128)))
                                                  : std::min<int64_t>(512, std::max<int64_t>(32, round_up(strip_elems / (64 * 1536), 32)));
         const int64_t strip_err = strip_elems / 8192 >= 1024 ? 8192 : strip_elems / 4096 >= 768 ? 4096 : strip_elems / 2048 >= 64 ? 2048 : 1024;
+        bool coarse_gram = false;
         auto lay_out = [&](int64_t chunk_cols, int64_t tile_rows) {
             wd = 0;
             plan.any_p_chunks = false;
@@ -494,7 +495,8 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                     d.qs_off = wd;  wd += round_up(3 * 32 * d.m * 2 / 8, 32);
                 }
 
-                d.gram_tile_rows = rank <= 8 ? (int32_t)gram_rows_small(d.n) : d.n > 8192 ? 2 * kGramRows : kGramRows;
+                d.gram_tile_rows = d.n > 8192 ? 2 * kGramRows : kGramRows;
+                if (rank <= 8) d.gram_tile_rows = (int32_t)std::max<int64_t>(gram_rows_small(d.n), coarse_gram ? d.gram_tile_rows : 0);
                 d.n_gram_tiles = (int32_t)ceil_div(d.n, d.gram_tile_rows);
                 d.gram_off = wd; wd += (int64_t)d.n_gram_tiles * rank * rank;
                 d.gsum_off = wd; wd += rank * rank;
@@ -530,21 +532,26 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         };
         lay_out(strip_chunk, strip_q_rows);
         // Partial sums of small and middle-sized models at high ranks can take the workspace beyond the static one of
-        // conef_step_static (98304 wave-rows x 32 entries: 25 MB).  They are split more coarsely until it fits: whole rows of P
-        // and 512 rows per partial of Q+ are the least, then longer items of the stream kernels.  Where that does not fit
-        // either, nothing is gained by a coarser split.
+        // conef_step_static (98304 wave-rows x 32 entries: 25 MB), and so can the partial Gram matrices of 64 rows of models of
+        // hundreds of matrices at ranks up to 8 (350 of 8192 x 64 at rank 8: 44 MB, 28 with 256 rows).  They are split more
+        // coarsely until it fits: first the Gram matrices (256 rows, 512 of more than 8192), then whole rows of P and 512 rows
+        // per partial of Q+ are the least, then longer items of the stream kernels.  Where that does not fit either, nothing
+        // is gained by a coarser split.
         auto fits = [&]() {
             int64_t all = wd;
             for (const MatDesc &d : plan.mats) all += stream_slots(d);
             return all <= (int64_t)CONEF_STATIC_WORKSPACE_BYTES / 8;
         };
         if (!sketch && !fits()) {
+            coarse_gram = true;
+            lay_out(strip_chunk, strip_q_rows);
             for (int64_t k = 2; k <= 16 && strip_elems > 0 && !fits(); k *= 2)
                 lay_out(strip_chunk * k, std::min<int64_t>(512, strip_q_rows * k));
             if (strip_elems > 0 && !fits()) lay_out(INT32_MAX, 512);
             while (stream_ok && stream_runs < 64 && !fits()) stream_runs *= 2;
             if (!fits()) {
                 stream_runs = stream_runs_rule;
+                coarse_gram = false;
                 lay_out(strip_chunk, strip_q_rows);
             }
         }

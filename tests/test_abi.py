@@ -526,6 +526,16 @@ def test_high_rank_strip_models_keep_to_the_static_workspace(layout, rank):
     model.close()
 
 
+@pytest.mark.parametrize("layout,rank", [([(8192, 64)] * 350, 8), ([(512, 64)] * 1800, 8), ([(140000, 16)] * 75, 8), ([(4096, 60)] * 400, 7)])
+def test_models_of_many_matrices_keep_to_the_static_workspace(layout, rank):
+    """Partial Gram matrices of 64 rows alone take these models beyond the static workspace; in row tiles of 256 or more they
+    fit, and the tables still cover everything once."""
+    ctx = B.conef_init(layout, rank, 4, 64, B.F32, 0)
+    assert B.conef_sizes(ctx)["workspace_bytes"] <= B.STATIC_WORKSPACE_BYTES
+    B.conef_check_plan(ctx)
+    B.conef_destroy(ctx)
+
+
 @pytest.mark.parametrize("layout,rank,bits,block", [
     ([(593, 70), (2369, 26002)], 32, 8, 64), ([(403, 355), (10087, 162), (5939, 437), (59, 7138), (69, 26011), (660, 6651), (716, 23053), (8641, 1573)], 32, 2, 512)])
 def test_the_static_workspace_counts_the_stream_kernels_partial_sums(layout, rank, bits, block):

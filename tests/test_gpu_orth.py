@@ -78,3 +78,26 @@ def test_full_step_adds_the_chunks(env, rank):
     for k in ("P", "Q", "codes", "scales"):
         assert torch.equal(one[k], two[k]), k
     model.close()
+
+
+def test_coarse_gram_tiles(env):
+    """A model of so many matrices that its partial Gram matrices cover 256 rows and not 64 (they would exceed the static
+    workspace), against QR in float64 as above: tiles of one, two and a part of one."""
+    import torch
+
+    B = env[1]
+    rank, rows = 8, [16, 255, 256, 257, 512] + [512] * 1750
+    model = B.Model([(n, 64) for n in rows], rank, 4, 64, wl.F32, 5)
+    assert model.sizes["workspace_bytes"] <= B.STATIC_WORKSPACE_BYTES
+    buf = model.alloc()
+    buf["P"].normal_()
+    panels = _panels(rows[:5], rank, False)
+    for P, o in zip(panels, model.offsets):
+        buf["P"][o["p_off"]:o["p_off"] + P.size] = torch.from_numpy(P.ravel()).cuda()
+    B.conef_orthonormalise(model.ctx, buf["P"], buf["ws"], model.stream_handle())
+    torch.cuda.synchronize()
+    for n, P, o in zip(rows, panels, model.offsets):
+        got = buf["P"][o["p_off"]:o["p_off"] + P.size].cpu().numpy().reshape(n, rank).astype(np.float64)
+        q, r = np.linalg.qr(P.astype(np.float64))
+        assert np.abs(got - q * np.sign(np.diag(r))).max() <= 2e-7, n
+    model.close()
