@@ -996,6 +996,15 @@ bool check_plan(const Plan &plan)
                 if (d.es_pitch < d.es_seg + d.es_over || (d.m % plan.block != 0 && d.es_over < plan.block) ||
                     (d.m % plan.block == 0 && d.es_seg % plan.block != 0) || 8 * d.es_pitch > plan.es_lds || it.c > 8)
                     return false;
+                // every lane of the last segment's strips takes its row of Q+ from this matrix, the owners of an element from its column
+                const int64_t c0 = (int64_t)it.b * d.es_seg;
+                if (it.a == 0 && c0 + d.es_seg >= d.m) {
+                    const int64_t own = d.m - c0 + d.es_over;
+                    for (int64_t v = 0; v < round_up(own, 64); ++v) {
+                        const int64_t k = virtual_column((uint32_t)d.m, (uint32_t)c0, (uint32_t)v);
+                        if (k < 0 || k >= d.m || (v < own && k != std::min<int64_t>((c0 + v) % d.m, d.m - 1))) return false;
+                    }
+                }
                 c.add(plan, it, it.a, it.c, (int64_t)it.b * d.es_seg, d.es_seg);
             } else {
                 const int64_t j0 = (int64_t)it.a * d.es_tile, j1 = std::min<int64_t>(j0 + d.es_tile, d.N);

@@ -42,6 +42,13 @@ constexpr int kUpdCols = 128;
 constexpr bool update_on_cores(int rank) { return rank > 8 && (rank & 3) == 0; }
 // End of the chunk of columns that starts at c_begin (the last chunk may be short, and c_begin + chunk beyond 2^31).
 constexpr int chunk_end(int64_t m, int chunk, int c_begin) { return m - c_begin > chunk ? c_begin + chunk : (int)m; }
+// Strip err pass: the column whose row of Q+ belongs to virtual column c0 + v of a segment (those past the end belong to the next
+// row; a segment's last strip may reach further still: the last column).  Unsigned: m + v may pass 2^31.
+constexpr uint32_t virtual_column(uint32_t m, uint32_t c0, uint32_t v)
+{
+    const uint32_t k = c0 + v < m ? c0 + v : c0 + v - m;
+    return k < m ? k : m - 1;
+}
 // Widest matrix of the octet kernels, whose column indices run ahead of a row's end in 32 bits; the strip kernels take wider ones.
 constexpr int64_t kOctetMaxCols = ((int64_t)1 << 31) - 4096;
 constexpr int kErrRows = 128;       // rows per workgroup item of the MFMA err pass (8 waves x 16)

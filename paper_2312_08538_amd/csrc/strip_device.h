@@ -613,10 +613,7 @@ __device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float
             const int v0 = 64 * strip, v = v0 + lane;               // the lane's column in the run (SEG: from c0 on)
             if (strip != q_strip) {                                 // uniform
                 q_strip = strip;
-                const int m = (int)d.m;
-                int k = GROUP ? lane_col : (int)c0 + v;
-                k = k < m ? k : k - m;
-                k = k < m ? k : m - 1;
+                const uint32_t k = virtual_column((uint32_t)d.m, (uint32_t)c0, (uint32_t)(GROUP ? lane_col : v));
                 const float *qrow = Qn + d.q_off + (int64_t)k * r;
                 if (EXACT && R >= 4) {
 #pragma unroll

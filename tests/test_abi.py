@@ -266,6 +266,16 @@ def test_plans_of_the_widest_matrices_are_consistent(layout, rank):
     B.conef_destroy(ctx)
 
 
+@pytest.mark.parametrize("layout,rank,block", [([(1, 2 ** 31 - 1)], 1, 8), ([(1, 2 ** 31 - 1)], 1, 64), ([(2, 2 ** 31 - 65)], 2, 512),
+                                               ([(1, 2 ** 31 - 1100)], 1, 512)])
+def test_rows_of_q_behind_the_last_segment_of_the_widest_matrices(layout, rank, block):
+    """Strip err pass, columns that are not a whole number of blocks: the last segment reaches into the next row, its strips
+    further, and a lane's index passes 2^31.  The plan's self-check walks them with the function that the kernel calls."""
+    ctx = B.conef_init(layout, rank, 4, block, B.F32, 0)
+    B.conef_check_plan(ctx)
+    B.conef_destroy(ctx)
+
+
 def test_set_beta_validates_its_argument():
     ctx = B.conef_init([(64, 64)], 4, 4, 64, B.F32, 0)
     L = B.lib()
