@@ -204,7 +204,8 @@ __device__ __forceinline__ double rsqrt_f64(double x)
 // t = 0 .. THREADS - 1, take part: one wave, or all.  Forward elimination of the rows of [G | I], a row per trip: row c times
 // 1 / R[c][c] is row c of R and of (R^T)^-1, and a thread has its entries of both halves in registers.  A column whose squared
 // norm after projection is not above 1e-12 of its squared norm is linearly dependent on the earlier ones: its column of R^-1
-// (and so of P^) is zero.
+// (and so of P^) is zero.  So it is for a column with an entry that is not finite, and nothing of it reaches the others: P^ then
+// has NaN in that entry's row and nowhere else.
 // The loop is not unrolled: a launch that runs its code once fetches every line of it from memory, and with all trips and lane
 // indices written out (61 KB at rank 32) that was most of its time (the stage's four launches for three matrices of 64 x 64
 // at rank 32: 40.0 -> 28.9 us).
@@ -239,7 +240,14 @@ __device__ __forceinline__ void cholesky_inverse(CholeskyLds<RP> &lds, int t, in
         if (THREADS > 64) __syncthreads();
         else wave_lds_sync();
         const double dcc = row_g[c], gcc = lds.G[c * RP + c];
-        const double ri = dcc > 1e-12 * gcc ? rsqrt_f64(dcc) : 0.0;        // 1 / R[c][c]
+        if (!(dcc > 1e-12 * gcc)) {                     // uniform
+            // not 0 times the row: a column of P that is not finite comes here, and its row of G is not finite either
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (i0 + v * kRows == c) y[v] = 0.0;
+            continue;
+        }
+        const double ri = rsqrt_f64(dcc);               // 1 / R[c][c]
         const double rj = row_g[j] * ri, yj = row_y[j] * ri;
 #pragma unroll
         for (int v = 0; v < V; ++v) {

@@ -101,3 +101,33 @@ def test_coarse_gram_tiles(env):
         q, r = np.linalg.qr(P.astype(np.float64))
         assert np.abs(got - q * np.sign(np.diag(r))).max() <= 2e-7, n
     model.close()
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), -float("inf")])
+@pytest.mark.parametrize("rank", [1, 2, 4, 7, 8, 12, 16, 32])
+def test_an_entry_that_is_not_finite_stays_in_its_row(env, rank, value):
+    """One entry of P that is not finite, in the first, a middle or the last column: in every other row P^ is the factor of the
+    other columns, its own column zero (QR in float64 as above)."""
+    import torch
+
+    B = env[1]
+    bad = sorted({0, rank // 2, rank - 1})
+    n, row = 300, 130
+    panels = _panels([n] * len(bad), rank, False)
+    model = B.Model([(n, 64)] * len(bad), rank, 4, 64, wl.F32, 5)
+    buf = model.alloc()
+    for P, c, o in zip(panels, bad, model.offsets):
+        P[row, c] = value
+        buf["P"][o["p_off"]:o["p_off"] + P.size] = torch.from_numpy(P.ravel()).cuda()
+    B.conef_orthonormalise(model.ctx, buf["P"], buf["ws"], model.stream_handle())
+    torch.cuda.synchronize()
+    rest = np.arange(n) != row
+    for P, c, o in zip(panels, bad, model.offsets):
+        got = buf["P"][o["p_off"]:o["p_off"] + P.size].cpu().numpy().reshape(n, rank).astype(np.float64)
+        keep = [k for k in range(rank) if k != c]
+        assert not got[rest, c].any(), (rank, c)
+        if keep:
+            q, r = np.linalg.qr(P[:, keep].astype(np.float64))
+            q *= np.sign(np.diag(r))
+            assert np.abs(got[np.ix_(rest, keep)] - q[rest]).max() <= 2e-7, (rank, c)
+    model.close()
