@@ -295,6 +295,7 @@ void ref_quantise(const float *x, int64_t N, int bits, int block,
          * (U mod 2^16) / 2^16.  For finite input U <= s * 2^16 (the product exceeds it by less
          * than 1/2), so the magnitude never exceeds s.  Non-finite input is outside the contract. */
         float inv16 = ((float)s / a) * 65536.0f;           /* IEEE fp32 division, exact scaling */
+        if (isinf(inv16)) continue;                        /* a <= s * 2^-112, too small to divide by: codes 0, scale a */
         for (int64_t j = j0; j < j1; ++j) {
             uint32_t U = (uint32_t)(fabsf(x[j]) * inv16);
             uint32_t r16 = draw ? draw[j] : ref_rand16(seed, mat, step, (uint64_t)j);

@@ -67,7 +67,8 @@ __device__ __forceinline__ float signed_byte(uint32_t w)
 
 // What code_values leaves in a field's value: the caller's step size takes its inverse.  (inv_levels * field_unit is a
 // constant, and scaling by a power of two is exact as long as step * field_unit is a normal number, that is for scales of
-// 7e-36 and more.  Blocks below 1e-33 have no codes worth the name, see quantise_octet: their fields are zero.)
+// 7.6e-37 (2-bit codes), 1.4e-36 (4-bit) and 1.5e-36 (8-bit) and more.  The fields of blocks below 1.9e-34 are zero, see
+// levels_over.)
 __device__ __forceinline__ constexpr float field_unit(int bits) { return bits == 8 ? 1.0f : (bits == 4 ? 1.0f / 16.0f : 1.0f / 64.0f); }
 
 // The eight fields of an octet (8-bit codes: c0 elements 0..3, c1 elements 4..7; else all in c0, bits beyond the octet zero) as fp32, over field_unit.
@@ -243,6 +244,14 @@ __device__ __forceinline__ uint32_t draw16(const uint32_t out[4], int j_low3)
     return (j_low3 & 1) ? (w >> 16) : (w & 0xFFFFu);
 }
 
+// The factor (s / a) * 2^16 of the rounding of a block of max-norm a, and 0 where a is 0 or so small that the factor would be
+// infinite (s * 2^-112: 1.9e-34 for 2-bit codes, 1.3e-33 for 4-bit, 2.4e-32 for 8-bit): the codes of such a block are zero in
+// every kernel, and its scale is a.  s / a is rounded to at least 2^112 exactly for a <= s * 2^-112.
+__device__ __forceinline__ float levels_over(float a, float s)
+{
+    return a > s * 0x1p-112f ? (s / a) * 65536.0f : 0.0f;
+}
+
 // Stochastic rounding of one value (eq. (3) with max-norm a; inv16 = (s/a) * 2^16) in 16.16
 // fixed point: the truncated product plus a uniform 16-bit draw, integer part kept.  Returns
 // the b-bit two's-complement field (not yet shifted into place).
@@ -261,8 +270,8 @@ __device__ __forceinline__ uint32_t quantise_field(float x, float inv16, uint32_
 // permute makes the sign masks of two elements, one exclusive or applies them), and bits 16 and up of the sum are the code
 // with its sign.  (Magnitudes, gathered sign bits and a negation of the whole word took 6 instructions more per octet with 2-
 // and 4-bit codes and 10 with 8-bit ones.)  Byte 2 of the sum is the code as a signed byte, which byte permutes gather.
-// t (if asked for): the sums, for rounded_values.  The product stays below 2^23, unless the block is so small that inv16 is
-// infinite: then byte 2 is 0 or 0xFF, and a field keeps its own bits of it, as in quantise_field.
+// t (if asked for): the sums, for rounded_values.  They are below 2^23: |x| inv16 exceeds s * 2^16 by less than 1/2.  (A value
+// that is not a number converts to zero, as does one times the 0 that the factor is for an infinite block.)
 template <int BITS>
 __device__ __forceinline__ void quantise_octet(const float x[8], float inv16, const uint32_t rnd[4], uint32_t w[2], int32_t t[8])
 {

@@ -146,7 +146,7 @@ __global__ __launch_bounds__(256) void k_pass_err_generic(DevicePlan dp, const v
             a = fmaxf(a, fabsf(residual_at<RP>(dp, d, grads, codes, scales, Phat, Qn, j0 + e)));
         a = wave_max(a);
         // the old scale of this block is read by nobody else; codes are overwritten word by word below
-        const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
+        const float inv16 = levels_over(a, s_f);
         const int sweeps = (cnt + 63) / 64;
         if (TWO) {
             const uint32_t mask = (1u << bits) - 1u;
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(256) void k_pass_err_generic(DevicePlan dp, const v
                 a2 = fmaxf(a2, fabsf(second_argument(j0 + e, f1)));
             }
             a2 = wave_max(a2);
-            const float inv16_2 = (a2 > 0.0f) ? (s_f / a2) * 65536.0f : 0.0f;
+            const float inv16_2 = levels_over(a2, s_f);
             for (int sw = 0; sw < sweeps; ++sw) {
                 const int e = sw * 64 + lane;
                 uint32_t field = 0, field2 = 0;
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(256) void k_rb_generic(DevicePlan dp, const void *g
         }
         if (MODE == kModeNorm) continue;
         a = wave_max(a);
-        const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
+        const float inv16 = levels_over(a, s_f);
         const int sweeps = (cnt + 63) / 64;
         if (TWO) {
             const uint32_t mask = (1u << bits) - 1u;
@@ -374,7 +374,7 @@ __global__ __launch_bounds__(256) void k_rb_generic(DevicePlan dp, const void *g
                 a2 = fmaxf(a2, fabsf(second_argument(j0 + e, f1)));
             }
             a2 = wave_max(a2);
-            const float inv16_2 = (a2 > 0.0f) ? (s_f / a2) * 65536.0f : 0.0f;
+            const float inv16_2 = levels_over(a2, s_f);
             for (int sw = 0; sw < sweeps; ++sw) {
                 const int e = sw * 64 + lane;
                 uint32_t field = 0, field2 = 0;

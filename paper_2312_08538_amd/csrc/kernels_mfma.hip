@@ -981,7 +981,7 @@ __global__ __launch_bounds__(512, TWO ? 2 : 4) void k_err_mfma(DevicePlan dp, co
         // steps are integer maxima (one instruction each with the lane permutation folded in)
         const float amax = block_max(acc);            // max-norm of block cb of row 4 kg + vq
         // ... then the reciprocal step size s / a of the lane's row, exchanged inside the quad
-        const float isel = (amax > 0.0f) ? (7.0f / amax) * 65536.0f : 0.0f;
+        const float isel = levels_over(amax, 7.0f);
         float inv16v[4];
         quad_rows(isel, inv16v);
         if (TWO) {
@@ -1010,7 +1010,7 @@ __global__ __launch_bounds__(512, TWO ? 2 : 4) void k_err_mfma(DevicePlan dp, co
             }
             const float amax2 = block_max(acc);
             keep_scale(keep, amax2, b);
-            const float isel2 = (amax2 > 0.0f) ? (7.0f / amax2) * 65536.0f : 0.0f;
+            const float isel2 = levels_over(amax2, 7.0f);
             quad_rows(isel2, inv16v);
         } else {
             keep_scale(keep, amax, b);

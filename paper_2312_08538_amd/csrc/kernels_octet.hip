@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                 for (int64_t b = o + 1; (b & 3) != 0; ++b) sb[b] = 0;          // the rest of the last word
         }
         const float a = block_max(abs_max_octet(0.0f, x), d.lb_shift);
-        const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
+        const float inv16 = levels_over(a, s_f);
         uint32_t rnd[4], w[2];
         int32_t t[8];
         philox4x32_10((uint32_t)o, (uint32_t)it.mat, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
 #pragma unroll
             for (int e = 0; e < 8; ++e) x[e] = x[e] - dnew * qn[e];
             const float a2 = block_max(abs_max_octet(0.0f, x), d.lb_shift);
-            const float inv16_2 = (a2 > 0.0f) ? (s_f / a2) * 65536.0f : 0.0f;
+            const float inv16_2 = levels_over(a2, s_f);
             philox4x32_10((uint32_t)o, (uint32_t)it.mat | 0x80000000u, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
             quantise_octet<BITS>(x, inv16_2, rnd, w);
             if (valid) {

@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) void k_err_octet(DevicePlan dp, const void *__
             x[e] = x[e] - acc;
         }
         const float a = block_max(abs_max_octet(0.0f, x), d.lb_shift);
-        const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
+        const float inv16 = levels_over(a, s_f);
         const int64_t o = (int64_t)row * d.m8 + oc;
         uint32_t rnd[4];
         philox4x32_10((uint32_t)o, (uint32_t)it.mat, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256) void k_err_octet(DevicePlan dp, const void *__
 #pragma unroll
             for (int e = 0; e < 8; ++e) x[e] = x[e] - dnew * qn[e];
             const float a2 = block_max(abs_max_octet(0.0f, x), d.lb_shift);
-            const float inv16_2 = (a2 > 0.0f) ? (s_f / a2) * 65536.0f : 0.0f;
+            const float inv16_2 = levels_over(a2, s_f);
             philox4x32_10((uint32_t)o, (uint32_t)it.mat | 0x80000000u, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
             quantise_octet<BITS>(x, inv16_2, rnd, w);
             if (valid) {
@@ -394,7 +394,7 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
             }
             load_row(r0 + 16, v);
             a = block_max(a, lb);
-            const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
+            const float inv16 = levels_over(a, s_f);
             const float dnew = a * inv_levels(BITS);
             float a2 = 0.0f;
             uint32_t w[NT][2];
@@ -420,7 +420,7 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
             if (WIDE && valid) store_code_pair<BITS>(d, TWO ? codes_first : codes, (int64_t)rowc * d.m8 + oc0, w[0], w[NT - 1]);
             if (TWO) {
                 a2 = block_max(a2, lb);
-                const float inv16_2 = (a2 > 0.0f) ? (s_f / a2) * 65536.0f : 0.0f;
+                const float inv16_2 = levels_over(a2, s_f);
 #pragma unroll
                 for (int h = 0; h < NT; ++h) {
                     const int64_t o = (int64_t)rowc * d.m8 + oct_col(h);

@@ -453,7 +453,7 @@ __device__ __forceinline__ void quantise_run(const DevicePlan &dp, const MatDesc
         const int64_t o = (flat0 >> 3) + id;
         auto round_octet = [&](uint32_t mat_word, uint32_t *cw, float *sc, int32_t (&t)[8]) {
             const float a = block_max(abs_max_octet(0.0f, x), lb);
-            const float inv16 = (a > 0.0f) ? (s_f / a) * 65536.0f : 0.0f;
+            const float inv16 = levels_over(a, s_f);
             uint32_t rnd[4];
             philox4x32_10((uint32_t)o, mat_word, step_lo, step_hi, dp.seed_lo, dp.seed_hi, rnd);
             uint32_t w[2];

@@ -126,9 +126,8 @@ def test_an_infinite_factor_entry_stays_in_its_products(env):
 @pytest.mark.parametrize("rank", [3, 4])
 @pytest.mark.parametrize("bits,block", [(2, 64), (4, 128), (8, 64)])
 def test_blocks_too_small_to_divide_by_keep_their_codes_apart(env, rank, bits, block):
-    """Residuals of 1e-41: levels / max-norm is infinite, so the fixed-point product saturates and the draw wraps it.  What
-    comes out for such a value is of no use, but the field of its neighbour (here zero) stays zero.  Strip and octet
-    matrices; one value in 65536 draws the zero that gives an all-ones magnitude."""
+    """Residuals of 1e-41: levels / max-norm is infinite (a fixed-point product would saturate and the draw wrap it).  The field
+    of such a value's neighbour (here zero) stays zero.  Strip and octet matrices; enough values for every draw."""
     R, B, U = env
     import torch
 
@@ -146,6 +145,66 @@ def test_blocks_too_small_to_divide_by_keep_their_codes_apart(env, rank, bits, b
     for (n, m), o in zip(layout, model.offsets):
         words = buf["codes"][o["word_off"]:o["word_off"] + R.n_words(n * m, bits)].cpu().numpy().view(np.uint32)
         assert not U.unpack(words, n * m, bits).reshape(n, m)[:, 1::2].any()
+    model.close()
+
+
+@pytest.mark.parametrize("rank,bits,block,dtype", [(3, 2, 64, wl.F32), (4, 4, 128, wl.F32), (8, 8, 64, wl.F32), (4, 2, 256, wl.BF16),
+                                                   (2, 4, 24, wl.F32), (32, 4, 128, wl.BF16)])
+def test_blocks_too_small_to_divide_by_have_zero_codes(env, rank, bits, block, dtype):
+    """Blocks whose largest value is at most levels * 2^-112, half of them negative: codes zero, scale kept, in the err pass of
+    every family and in the streams (random-k, one and two vectors: of the second the first's argument, unchanged).  A million
+    values and more, as one in 65536 draws the zero that made a code of such a value.  Just above, the codes are the oracle's."""
+    R, B, U = env
+    import torch
+
+    s = (1 << (bits - 1)) - 1
+    edge = np.float32(s * 2.0 ** -112)
+    layout = [(1100, 1032), (1100, 1024)]
+    model = B.Model(layout, rank, bits, block, dtype, 5)
+    buf = model.alloc("cuda:0")
+    B.conef_rk_configure(model.ctx, [10, 10])
+    st, P, Q = model.stream_handle(), torch.zeros_like(buf["P"]), torch.zeros_like(buf["Q"])
+    delta = torch.zeros(B.conef_rk_sizes(model.ctx)["delta_elems"], device="cuda:0")
+    codes2, scales2 = torch.zeros_like(buf["codes"]), torch.zeros_like(buf["scales"])
+
+    def steps():
+        yield "err", lambda: B.conef_step_err(model.ctx, buf["grads"], buf["codes"], buf["scales"], P, Q, buf["ws"], 3, st)
+        yield "two vectors", lambda: B.conef_i_step_err(model.ctx, buf["grads"], buf["codes"], buf["scales"], codes2, scales2, P, Q,
+                                                        buf["ws"], 3, st)
+        yield "random-k", lambda: B.conef_i_rk_step(model.ctx, buf["grads"], buf["codes"], buf["scales"], codes2, scales2, delta, 3, st)
+
+    for value in (edge, np.float32(1e-39)):
+        for name, step in steps():
+            g = torch.full((model.sizes["grad_elems"],), float(value))
+            g[::2] *= -1
+            buf["grads"].copy_(g.to(buf["grads"].dtype).cuda())
+            for x in (buf["codes"], buf["scales"], codes2, scales2):
+                x.zero_()
+            step()
+            torch.cuda.synchronize()
+            assert not buf["codes"].any() and not codes2.any(), (name, value)
+            for (n, m), o in zip(layout, model.offsets):
+                blocks = R.n_blocks(n * m, block)
+                want = buf["grads"][0].abs().float()
+                if name != "random-k":          # (there the kept coordinates leave)
+                    assert bool((buf["scales"][o["scale_off"]:o["scale_off"] + blocks] == want).all()), (name, value)
+    if dtype == wl.F32:
+        rng = np.random.default_rng(9)
+        x = [(rng.uniform(-1, 1, n * m) * float(edge) * 4).astype(np.float32) for n, m in layout]
+        for y in x:
+            y[::2 * block] = np.nextafter(edge, np.float32(1))
+            for b in range(1, block):
+                y[b::2 * block] = np.clip(y[b::2 * block], -edge, edge)
+        for y, o in zip(x, model.offsets):
+            buf["grads"][o["grad_off"]:o["grad_off"] + y.size] = torch.from_numpy(y).cuda()
+        B.conef_reset_error(model.ctx, buf["codes"], buf["scales"], st)
+        B.conef_step_err(model.ctx, buf["grads"], buf["codes"], buf["scales"], P, Q, buf["ws"], 3, st)
+        torch.cuda.synchronize()
+        for l, (y, o) in enumerate(zip(x, model.offsets)):
+            words, scales = R.quantise(y, bits, block, 5, l, 3)
+            got = buf["codes"][o["word_off"]:o["word_off"] + words.size].cpu().numpy().view(np.uint32)
+            assert words.any() and np.array_equal(got, words)
+            assert np.array_equal(buf["scales"][o["scale_off"]:o["scale_off"] + scales.size].cpu().numpy(), scales)
     model.close()
 
 
