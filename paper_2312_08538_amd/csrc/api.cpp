@@ -142,6 +142,7 @@ int ensure_uploaded(conef_ctx *ctx)
     d.n_err_m = (int)pl.err_m_items.size();
     d.n_split_p = (int)pl.split_p_items.size();
     d.n_split_qn = (int)pl.split_qn_items.size();
+    for (const MatDesc &m : pl.mats) d.most_p_chunks = std::max(d.most_p_chunks, (int)m.n_p_chunks);
     d.n_pred = (int)pl.pred_items.size();
     d.n_gram = (int)pl.gram_items.size();
     d.n_apply = (int)pl.apply_items.size();

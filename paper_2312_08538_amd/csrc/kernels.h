@@ -41,6 +41,7 @@ struct DevicePlan {
     int n_p_m = 0, n_q_m = 0, n_err_m = 0, n_split_p = 0, n_split_qn = 0;
     int n_p_k = 0, n_q_k = 0;
     int n_upd = 0, upd_many = 0;    // upd_many: its items may be of several row tiles
+    int most_p_chunks = 1;          // column chunks of P of the matrix that has the most
     int n_pred = 0, n_gram = 0, n_apply = 0, n_qred = 0, n_elem = 0;
     int rank = 0, rpad = 0, bits = 0, block = 0, dtype = 0;
     int n_q_flat = 0, n_err_g = 0;
@@ -73,7 +74,11 @@ struct Span {
 // launch (p_chunks there) where orth_adds_chunks says so
 hipError_t launch_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
                          const float *Q, float *P, double *ws, bool add_chunks, hipStream_t st, Span span = Span());
-inline bool orth_adds_chunks(const DevicePlan &dp) { return dp.rpad <= 8; }
+// Ranks up to 4: up to 16 chunks, 5 to 8: up to 8.  A workgroup of that launch adds the chunks of its 64 rows one group of loads
+// after another, 0.13 us a chunk (0.25), where the launch for the sums has a thread per entry of P and costs 2 us.  A step of 64
+// rows in 2 / 8 / 16 / 24 / 64 chunks: rank 4 1.2 / 0.8 / 0.4 us faster, 0.3 / 4.4 slower than with that launch; rank 8 1.4 /
+// 0.5 faster, 0.6 / 2.5 / 10 slower (512 rows: 1.7 / 1.8 / 0.9, 0.1 / 5.3; 1.7 / 1.3, 1.8 / 1.4 / 9.8).
+inline bool orth_adds_chunks(const DevicePlan &dp) { return dp.rpad <= 8 && dp.most_p_chunks <= (dp.rpad == 4 ? 16 : 8); }
 // tr_a / tr_b (the full step only): block scales of the error vector(s) whose column-block-major copies are made for
 // the rank-32 family alongside the factorisations (into the first / the second workspace region); launch_pass_q is then
 // called with scales_ready

@@ -80,6 +80,30 @@ def test_full_step_adds_the_chunks(env, rank):
     model.close()
 
 
+@pytest.mark.parametrize("rank,layout", [(rank, [(70, cols), (130, 512)]) for rank, step in ((3, 257), (4, 512), (6, 257), (8, 512))
+                                         for cols in (8 * step - 1, 8 * step, 9 * step, 16 * step, 17 * step)])
+def test_chunks_on_either_side_of_the_rule(env, rank, layout):
+    """Column chunks of P up to and beyond what the orthonormalisation adds up itself (8 and 16 of them): the bits of the stage
+    calls."""
+    import torch
+
+    B = env[1]
+    model = B.Model(layout, rank, 4, 64, wl.F32, 5)
+    one, two = model.alloc(), model.alloc()
+    torch.manual_seed(4)
+    one["grads"].normal_()
+    one["Q"].normal_()
+    for k in ("grads", "Q"):
+        two[k].copy_(one[k])
+    st = model.stream_handle()
+    model.step(one, 0)
+    B.conef_step_p(model.ctx, two["grads"], two["codes"], two["scales"], two["Q"], two["P"], two["ws"], st)
+    B.conef_orthonormalise(model.ctx, two["P"], two["ws"], st)
+    torch.cuda.synchronize()
+    assert torch.equal(one["P"], two["P"])
+    model.close()
+
+
 def test_coarse_gram_tiles(env):
     """A model of so many matrices that its partial Gram matrices cover 256 rows and not 64 (they would exceed the static
     workspace), against QR in float64 as above: tiles of one, two and a part of one."""
