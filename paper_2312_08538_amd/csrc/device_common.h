@@ -75,13 +75,20 @@ __device__ __forceinline__ constexpr float field_unit(int bits) { return bits ==
 // Narrow fields are moved to the top of a byte, four at a time, and converted as signed bytes: 11 instructions for 4-bit
 // fields and 14 for 2-bit ones (16 to extract and convert each; 17 through the conversion of nibbles, whose sixteenths would
 // have to be multiplied back, since the factor 16 in the step size overflows for scales above 1.5e38).
-template <int BITS>
+// NIBBLES: 4-bit fields through that conversion, the same values: for kernels at their limit of registers, where the two
+// shifted and masked copies of the word cost more than the instructions (octet_device.h, Q+ pass).
+template <int BITS, bool NIBBLES = false>
 __device__ __forceinline__ void code_values(uint32_t c0, uint32_t c1, float q[8])
 {
+    static_assert(!NIBBLES || BITS == 4, "4-bit fields only");
     auto bytes = [](uint32_t v, float &a, float &b, float &c, float &d) {
         a = signed_byte<0>(v); b = signed_byte<1>(v); c = signed_byte<2>(v); d = signed_byte<3>(v);
     };
-    if constexpr (BITS == 8) {
+    if constexpr (NIBBLES) {
+        fields_over_16(c0, q);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) q[e] *= 256.0f;
+    } else if constexpr (BITS == 8) {
         bytes(c0, q[0], q[1], q[2], q[3]);
         bytes(c1, q[4], q[5], q[6], q[7]);
     } else if constexpr (BITS == 4) {

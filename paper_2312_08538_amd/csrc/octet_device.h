@@ -83,7 +83,7 @@ __device__ __forceinline__ void add_codes(const RawCodes<BITS> &r, float p[8])
 }
 
 // omb: 1 - beta of the partial update in the P and Q+ passes (Algorithm 4 line 5), 1 in the err pass
-template <bool BF16, int BITS>
+template <bool BF16, int BITS, bool NIBBLES = false>
 __device__ __forceinline__ void decode_octet(const RawOctet<BF16, BITS> &r, float omb, float p[8])
 {
     float g[8];
@@ -101,7 +101,7 @@ __device__ __forceinline__ void decode_octet(const RawOctet<BF16, BITS> &r, floa
     }
     const float step = r.scale * (inv_levels(BITS) * field_unit(BITS)) * omb;
     float q[8];
-    code_values<BITS>(r.c0, r.c1, q);
+    code_values<BITS, NIBBLES>(r.c0, r.c1, q);
 #pragma unroll
     for (int e = 0; e < 8; ++e) p[e] = __builtin_fmaf(step, q[e], g[e]);
 }
@@ -450,6 +450,9 @@ __device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float 
 // time: octets are decoded in the coalesced load layout (8 lanes per row) into a wave-private LDS
 // tile (32 rows x 64 columns of p), read back one value per lane and instruction; the rows of P^
 // are converted from fp32.  Loads run one step ahead.  Partial sums per row tile go to the workspace.
+// 4-bit codes of one vector are decoded by nibbles, except with bf16 gradients at rank 8: by bytes, these forms of the kernel
+// spill up to 19 registers (41 M elements, bytes / nibbles: fp32 at rank 8 74 / 57 us, rank 4 39 / 39, bf16 at ranks 2 and 4
+// 35 / 30 and 36 / 31; at rank 8 41 / 44).
 // Occupancy target (measured): four waves per SIMD with bf16 gradients (a few spilled registers cost less
 // than the fourth wave brings), three with fp32 gradients, whose octets take twice the registers.
 constexpr int kQTileCols = 64;
@@ -525,7 +528,7 @@ __device__ __forceinline__ void q_octet(const DevicePlan &dp, int block, float *
 #pragma unroll
         for (int s = 0; s < kLoads; ++s) {
             float p[8];
-            decode_octet<BF16, BITS>(cur.o[s], dp.omb, p);
+            decode_octet<BF16, BITS, BITS == 4 && !TWO && !(BF16 && RH == 2)>(cur.o[s], dp.omb, p);
             if (TWO) add_codes<BITS>(cur.o2[s], p);
             float4 *dst = reinterpret_cast<float4 *>(T + (lrow + 8 * s) * kQTilePitch + loct * 8);
             dst[0] = make_float4(p[0], p[1], p[2], p[3]);
