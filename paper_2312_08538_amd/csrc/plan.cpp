@@ -468,14 +468,17 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         }
         // The strip kernels: about 1536 workgroups per launch (six per CU) where the model is large enough, with limits that
         // keep a workgroup's fixed part (operand set-up, the sum over its waves, partial sums to be added later) small
-        // against its share of the elements.
+        // against its share of the elements.  The P pass on octets: 512, since fewer of them fit on a CU (three at rank 4, two at rank
+        // 32) and a wave with several strips has the next one's loads in flight (us for the pass, chunks for 1536 / 512 workgroups:
+        // 600 x 20001 fp32 at rank 1 23.5 / 17.8, at 16 29.8 / 23.1, six of 2600 x 650 at rank 4 18.6 / 11.5, at 32 32.4 / 22.7, 4000 x
+        // 5001 at 8 27.8 / 25.7, smaller models the same).
         // Where no matrix has more than 512 columns they stay in one chunk: a wave has two strips then, and the launch that adds
         // the chunks, which nothing else needs, costs more (600 x 300 at rank 4: 9.3 us for the pass in two chunks, 7.8 in one;
         // not so with the sketch, whose gathered rows are the longer chain: 10.3 and 11.6).
         int64_t widest = 0;
         for (const MatDesc &d : plan.mats) widest = std::max(widest, d.m);
         const int64_t strip_chunk = !sketch && widest <= 512 ? 512
-            : std::min<int64_t>(2048, std::max<int64_t>(256, round_up(strip_elems / (kStripRows * 1536), 256)));
+            : std::min<int64_t>(2048, std::max<int64_t>(256, round_up(strip_elems / (kStripRows * (!sketch && octet_blocks ? 512 : 1536)), 256)));
         plan.ragged = !sketch && octet_blocks ? 1 : 0;
         for (const MatDesc &d : plan.mats)
             if (d.path == kPathGeneric && d.m > kRaggedMaxCols) plan.ragged = 0;
