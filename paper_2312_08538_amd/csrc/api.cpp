@@ -66,6 +66,8 @@ int ensure_uploaded(conef_ctx *ctx)
     if ((rc = upload(ctx, pl.mats, &d.mats))) return rc;
     if ((rc = upload(ctx, pl.p_items, &d.p_items))) return rc;
     if ((rc = upload(ctx, pl.q_items, &d.q_items))) return rc;
+    if ((rc = upload(ctx, pl.p_r_items, &d.p_r_items))) return rc;
+    if ((rc = upload(ctx, pl.q_r_items, &d.q_r_items))) return rc;
     if ((rc = upload(ctx, pl.err_items, &d.err_items))) return rc;
     if ((rc = upload(ctx, pl.err_s_items, &d.err_s_items))) return rc;
     if ((rc = upload(ctx, pl.err_g_items, &d.err_g_items))) return rc;
@@ -122,13 +124,14 @@ int ensure_uploaded(conef_ctx *ctx)
     d.n_mats = (int)pl.mats.size();
     d.n_p = (int)pl.p_items.size();
     d.n_q = (int)pl.q_items.size();
+    d.n_p_r = (int)pl.p_r_items.size();
+    d.n_q_r = (int)pl.q_r_items.size();
     d.n_err = (int)pl.err_items.size();
     d.n_err_s = (int)pl.err_s_items.size();
     d.n_err_g = (int)pl.err_g_items.size();
     d.n_q_flat = (int)pl.q_flat_items.size();
     d.es_lds = pl.es_lds; d.wshift = pl.wshift; d.lb_shift = pl.lb_shift; d.inv_s = pl.inv_s; d.bmagic = pl.bmagic;
     d.block_shift = pl.block_shift;
-    d.ragged = pl.ragged;
     d.n_upd = (int)pl.upd_items.size();
     d.upd_many = pl.upd_many;
     d.n_p_f = (int)pl.p_f_items.size();

@@ -9,7 +9,7 @@ namespace conef {
 // Device-resident copy of a plan: descriptor array and work tables.
 struct DevicePlan {
     const MatDesc *mats = nullptr;
-    const WorkItem *p_items = nullptr, *q_items = nullptr, *err_s_items = nullptr;        // strip kernels (any shape)
+    const WorkItem *p_r_items = nullptr, *q_r_items = nullptr, *err_s_items = nullptr;    // strip kernels (any shape), on octets
     const WorkItem *q_flat_items = nullptr, *err_g_items = nullptr;     // few rows (Q+ pass), few columns (err pass)
     const WorkItem *err_items = nullptr;        // err pass of blocks the strip kernel does not take
     const WorkItem *p_f_items = nullptr, *q_f_items = nullptr, *err_f_items = nullptr;    // octet family
@@ -37,15 +37,14 @@ struct DevicePlan {
     const OrthItem *gram_s_items = nullptr, *apply_s_items = nullptr;      // orthonormalisation, ranks up to 8
     int n_gram_s = 0, n_apply_s = 0;
     int n_mats = 0;
-    int n_p = 0, n_q = 0, n_err = 0, n_p_f = 0, n_q_f = 0, n_err_f = 0, n_err_t = 0;
+    int n_p_r = 0, n_q_r = 0, n_err = 0, n_p_f = 0, n_q_f = 0, n_err_f = 0, n_err_t = 0;
     int n_p_m = 0, n_q_m = 0, n_err_m = 0, n_split_p = 0, n_split_qn = 0;
     int n_p_k = 0, n_q_k = 0;
     int n_upd = 0, upd_many = 0;    // upd_many: its items may be of several row tiles
-    int most_p_chunks = 1;          // column chunks of P of the matrix that has the most
     int n_pred = 0, n_gram = 0, n_apply = 0, n_qred = 0, n_elem = 0;
     int rank = 0, rpad = 0, bits = 0, block = 0, dtype = 0;
     int n_q_flat = 0, n_err_g = 0;
-    int ragged = 0;                 // strip family: P and Q+ passes on octets
+    int most_p_chunks = 1;          // column chunks of P of the matrix that has the most
     int n_err_s = 0, es_lds = 0;    // strip err pass: items, floats of LDS per workgroup
     int wshift = 0, lb_shift = 0;   // log2(code fields per word), log2(block / 8)
     int block_shift = -1;           // log2(block), -1 if it is not a power of two
@@ -62,6 +61,8 @@ struct DevicePlan {
     // every matrix, MatDesc::i2_k values at i2_off) as it comes in and where the new one goes (another buffer)
     const float *i2_in = nullptr;
     float *i2_out = nullptr;
+    const WorkItem *p_items = nullptr, *q_items = nullptr;      // strip kernels, P and Q+ passes element by element
+    int n_p = 0, n_q = 0;
 };
 
 // Optional pair of events recorded immediately before and after a stage's main kernel.
@@ -154,7 +155,7 @@ void strip_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, fl
                     uint64_t step, hipStream_t st);
 void strip_pass_err_two(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, uint32_t *codes2, float *scales2,
                         const float *Phat, const float *Qn, uint64_t step, hipStream_t st);
-// the same for blocks of whole octets (kernels_ragged.hip): where dp.ragged
+// the same for the matrices that the plan takes on octets (kernels_ragged.hip)
 void ragged_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Q, float *P,
                    double *ws, hipStream_t st);
 void ragged_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Phat, double *ws,

@@ -556,9 +556,9 @@ hipError_t launch_pass_p(const DevicePlan &dp, const void *grads, const uint32_t
     pack_pass_p(dp, grads, codes, scales, Q, P, st);
     if (!mixed_pass_p(dp, grads, codes, scales, Q, P, ws, st)) {
         octet_pass_p(dp, grads, codes, scales, Q, P, ws, st);
-        if (dp.ragged) ragged_pass_p(dp, grads, codes, scales, Q, P, ws, st);
-        else strip_pass_p(dp, grads, codes, scales, Q, P, ws, st);
+        ragged_pass_p(dp, grads, codes, scales, Q, P, ws, st);
     }
+    strip_pass_p(dp, grads, codes, scales, Q, P, ws, st);
     if (span.end) (void)hipEventRecord(span.end, st);
     if (add_chunks) generic_p_reduce(dp, ws, P, st);
     return hipGetLastError();
@@ -578,9 +578,9 @@ hipError_t launch_pass_q(const DevicePlan &dp, const void *grads, const uint32_t
     pack_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
     if (!mixed_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st)) {
         octet_pass_q(dp, grads, codes, scales, Phat, ws, st);
-        if (dp.ragged) ragged_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
-        else strip_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
+        ragged_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
     }
+    strip_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
     strip_pass_q_flat(dp, grads, codes, scales, Phat, Qout, st);
     if (span.end) (void)hipEventRecord(span.end, st);
     // the reduction also writes the matrix-core family's operand splits of Q+

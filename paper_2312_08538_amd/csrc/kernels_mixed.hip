@@ -33,7 +33,7 @@ void k_p_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const ui
     if (b >= lead) {
         const POctetLds o = {lds, reinterpret_cast<uint32_t *>(lds + kPOctetTiles), lds + kPOctetTiles + kPOctetCodes, nullptr, nullptr};
         p_octet<BF16, BITS, RH, false>(dp, b - lead, o, grads, codes, scales, Q, P, ws);
-    } else if (b < dp.n_p) {
+    } else if (b < dp.n_p_r) {
         p_ragged<BF16, BITS, RH, false>(dp, b, lds, grads, codes, scales, Q, P, ws);
     }
 }
@@ -47,7 +47,7 @@ void k_q_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const ui
     const int b = blockIdx.x;
     if (b >= lead) {
         q_octet<BF16, BITS, (R > 4 ? 2 : 1), false>(dp, b - lead, lds, grads, codes, scales, Phat, ws);
-    } else if (b < dp.n_q) {
+    } else if (b < dp.n_q_r) {
         q_ragged<BF16, BITS, (R > 4 ? 2 : 1), false>(dp, b, lds, grads, codes, scales, Phat, ws, Qout);
     }
 }
@@ -89,8 +89,8 @@ void by_type(const DevicePlan &dp, F &&go)
 bool mixed_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Q, float *P,
                   double *ws, hipStream_t st)
 {
-    if (dp.n_p <= 0 || dp.n_p_f <= 0 || !dp.ragged || dp.i_codes || dp.n_p > kMixedStrips) return false;
-    const int lead = lead_of(dp.n_p);
+    if (dp.n_p_r <= 0 || dp.n_p_f <= 0 || dp.i_codes || dp.n_p_r > kMixedStrips) return false;
+    const int lead = lead_of(dp.n_p_r);
     by_type(dp, [&](auto bf, auto bits) {
         constexpr bool BF = decltype(bf)::value;
         constexpr int B = decltype(bits)::value;
@@ -104,8 +104,8 @@ bool mixed_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes
 bool mixed_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Phat, double *ws,
                   float *Qout, hipStream_t st)
 {
-    if (dp.n_q <= 0 || dp.n_q_f <= 0 || !dp.ragged || dp.i_codes || dp.n_q > kMixedStrips) return false;
-    const int lead = lead_of(dp.n_q);
+    if (dp.n_q_r <= 0 || dp.n_q_f <= 0 || dp.i_codes || dp.n_q_r > kMixedStrips) return false;
+    const int lead = lead_of(dp.n_q_r);
     by_type(dp, [&](auto bf, auto bits) {
         constexpr bool BF = decltype(bf)::value;
         constexpr int B = decltype(bits)::value;

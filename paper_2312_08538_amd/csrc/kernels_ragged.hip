@@ -2,8 +2,9 @@
 // gradient, codes and scales are loaded and decoded in octets of the flat index, which are aligned whatever the row length
 // and never cross a scale block; a wave puts them into its LDS tile as they are, each row shifted by where it starts in its
 // first octet, and the operands of the fp64 matrix cores are read with that shift (ragged_device.h).  Blocks that no
-// power-of-two number of lanes holds in octets, the count sketch, and matrices of more than 2^24 columns take the kernels of
-// kernels_strip.hip, a lane per column and a load per element.
+// power-of-two number of lanes holds in octets, the count sketch, and a matrix of more than 2^24 columns take the kernels of
+// kernels_strip.hip, a lane per column and a load per element; so does the Q+ pass of a model whose matrices are too small or have
+// too few rows (ragged_q_pays in plan.h).
 //
 // Measured (28.4 M elements in five matrices of 650 columns, fp32, rank 4, 4-bit codes in blocks of 128), before and after: P
 // pass 35 -> 29 us (0.13 GB: 4.4 TB/s), Q+ pass 46 -> 28 us.  Of the latter 43 -> 28 came from giving every XCD a contiguous
@@ -61,9 +62,9 @@ void by_type(const DevicePlan &dp, F &&go)
 void ragged_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Q, float *P,
                    double *ws, hipStream_t st)
 {
-    if (dp.n_p <= 0) return;
+    if (dp.n_p_r <= 0) return;
     by_type(dp, [&](auto bf, auto bits, auto rh, auto two) {
-        hipLaunchKernelGGL((k_p_ragged<decltype(bf)::value, decltype(bits)::value, decltype(rh)::value, decltype(two)::value>), dim3(dp.n_p),
+        hipLaunchKernelGGL((k_p_ragged<decltype(bf)::value, decltype(bits)::value, decltype(rh)::value, decltype(two)::value>), dim3(dp.n_p_r),
                            dim3(256), 0, st, dp, grads, codes, scales, Q, P, ws);
     });
 }
@@ -71,9 +72,9 @@ void ragged_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *code
 void ragged_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Phat, double *ws,
                    float *Qout, hipStream_t st)
 {
-    if (dp.n_q <= 0) return;
+    if (dp.n_q_r <= 0) return;
     by_type(dp, [&](auto bf, auto bits, auto rh, auto two) {
-        hipLaunchKernelGGL((k_q_ragged<decltype(bf)::value, decltype(bits)::value, decltype(rh)::value, decltype(two)::value>), dim3(dp.n_q),
+        hipLaunchKernelGGL((k_q_ragged<decltype(bf)::value, decltype(bits)::value, decltype(rh)::value, decltype(two)::value>), dim3(dp.n_q_r),
                            dim3(256), 0, st, dp, grads, codes, scales, Phat, ws, Qout);
     });
 }

@@ -1,6 +1,6 @@
 // Strip kernel family: the three passes for any layout (any number of columns, any rank up to 32, blocks that straddle
-// rows).  The quantiser's P and Q+ passes for blocks of whole octets are in kernels_ragged.hip; here are the others and the err
-// pass.  A wave works on strips of 64 neighbouring columns, a lane owns a column of the strip and the row is uniform over
+// rows).  Most P and Q+ passes of the quantiser for blocks of whole octets are in kernels_ragged.hip; here are the others and the
+// err pass.  A wave works on strips of 64 neighbouring columns, a lane owns a column of the strip and the row is uniform over
 // the wave: a row of the strip is one coalesced access of the gradient (one element per lane, whatever the alignment of
 // the row).  The 64-bit addresses of a workgroup's first block are formed once, on the scalar side; an element is a 32-bit
 // distance from there, from which each lane takes its code word and block by shifts (a division where the block is not a

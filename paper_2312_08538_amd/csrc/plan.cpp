@@ -479,15 +479,28 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         for (const MatDesc &d : plan.mats) widest = std::max(widest, d.m);
         const int64_t strip_chunk = !sketch && widest <= 512 ? 512
             : std::min<int64_t>(2048, std::max<int64_t>(256, round_up(strip_elems / (kStripRows * (!sketch && octet_blocks ? 512 : 1536)), 256)));
-        plan.ragged = !sketch && octet_blocks ? 1 : 0;
-        for (const MatDesc &d : plan.mats)
-            if (d.path == kPathGeneric && d.m > kRaggedMaxCols) plan.ragged = 0;
-        // (on octets a wave works in steps of 32 rows, and a workgroup's four waves have one each)
-        const int64_t strip_q_rows = plan.ragged ? std::min<int64_t>(512, std::max<int64_t>(128, round_up(strip_elems / (64 * 1024), 128)))
-                                                 : std::min<int64_t>(512, std::max<int64_t>(32, round_up(strip_elems / (64 * 1536), 32)));
+        auto on_octets = [&](const MatDesc &d) { return !sketch && octet_blocks && d.path == kPathGeneric && d.m <= kRaggedMaxCols; };
+        // the Q+ pass of most of these matrices decides for all of them (two launches cost more than either form does), and where
+        // the octet family's kernels run too, the launch for both takes them on octets
+        int64_t pays = 0, of = 0;
+        bool joint = false;
+        for (const MatDesc &d : plan.mats) {
+            joint = joint || (d.path == kPathOctet && !d.pack);
+            if (!on_octets(d) || d.n <= kFlatRows) continue;
+            of += d.N;
+            if (ragged_q_pays(rank, d.n, strip_elems)) pays += d.N;
+        }
+        const bool q_octets = joint || 2 * pays >= of;
+        auto q_on_octets = [&](const MatDesc &d) { return q_octets && on_octets(d); };
+        // On octets a wave works in steps of 32 rows, and a workgroup's four waves have one each.  Above rank 16 a CU holds one
+        // workgroup or two: 256 of them with more steps each (rank 32, fp32, in tiles for 1024 / 256 workgroups: 10000 x 650 59 / 30
+        // us, 100000 x 65 95 / 50, 256 x 20001 47 / 35; element by element 52, 77 and 40).
+        const int64_t ragged_q_rows = std::min<int64_t>(512, std::max<int64_t>(128, round_up(strip_elems / (64 * (rank > 16 ? 256 : 1024)), 128)));
+        const int64_t strip_q_rows = std::min<int64_t>(512, std::max<int64_t>(32, round_up(strip_elems / (64 * 1536), 32)));
         const int64_t strip_err = strip_elems / 8192 >= 1024 ? 8192 : strip_elems / 4096 >= 768 ? 4096 : strip_elems / 2048 >= 64 ? 2048 : 1024;
         bool coarse_gram = false;
-        auto lay_out = [&](int64_t chunk_cols, int64_t tile_rows) {
+        // times: how much coarser the row tiles of the strip Q+ pass are than by the rules above
+        auto lay_out = [&](int64_t chunk_cols, int64_t times) {
             wd = 0;
             plan.any_p_chunks = false;
             for (int l = 0; l < n_mats; ++l) {
@@ -505,7 +518,8 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 d.gsum_off = wd; wd += rank * rank;
                 d.rinv_off = wd; wd += rank * rank;
                 d.q_tile_rows = d.cs_lin ? 2048 : d.pack ? kPackQRows : d.path == kPathOctet ? q_rows : (d.path == kPathMfma && (kMfmaPasses & 2)) ? 2048
-                                : (int32_t)std::min<int64_t>(tile_rows, 4 * std::max<int64_t>(1, kStripSpan / d.m));
+                                : (int32_t)std::min<int64_t>(std::min<int64_t>(512, times * (q_on_octets(d) ? ragged_q_rows : strip_q_rows)),
+                                                             4 * std::max<int64_t>(1, kStripSpan / d.m));
                 d.n_q_tiles = (int32_t)ceil_div(d.n, d.q_tile_rows);
                 d.qpart_off = wd; wd += round_up((int64_t)d.n_q_tiles * d.m * rank, 32);
                 d.n_p_chunks = 1;
@@ -533,7 +547,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         auto stream_slots = [&](const MatDesc &d) {
             return stream_ok ? ceil_div(ceil_div(d.N, 512), stream_runs) : 4 * ceil_div(d.nblk, 4 * blocks_per_wave(d));
         };
-        lay_out(strip_chunk, strip_q_rows);
+        lay_out(strip_chunk, 1);
         // Partial sums of small and middle-sized models at high ranks can take the workspace beyond the static one of
         // conef_step_static (98304 wave-rows x 32 entries: 25 MB), and so can the partial Gram matrices of 64 rows of models of
         // hundreds of matrices at ranks up to 8 (350 of 8192 x 64 at rank 8: 44 MB, 28 with 256 rows).  They are split more
@@ -547,15 +561,15 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         };
         if (!sketch && !fits()) {
             coarse_gram = true;
-            lay_out(strip_chunk, strip_q_rows);
+            lay_out(strip_chunk, 1);
             for (int64_t k = 2; k <= 16 && strip_elems > 0 && !fits(); k *= 2)
-                lay_out(strip_chunk * k, std::min<int64_t>(512, strip_q_rows * k));
-            if (strip_elems > 0 && !fits()) lay_out(INT32_MAX, 512);
+                lay_out(strip_chunk * k, k);
+            if (strip_elems > 0 && !fits()) lay_out(INT32_MAX, 16);
             while (stream_ok && stream_runs < 64 && !fits()) stream_runs *= 2;
             if (!fits()) {
                 stream_runs = stream_runs_rule;
                 coarse_gram = false;
-                lay_out(strip_chunk, strip_q_rows);
+                lay_out(strip_chunk, 1);
             }
         }
         // The strip err pass: runs of the flat index of strip_err elements where that is at least eight rows (a wave's row of
@@ -643,13 +657,13 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 if (!mf_p)
                     for (int64_t r0 = 0; r0 < d.n; r0 += prow)
                         for (int32_t cc = 0; cc < d.n_p_chunks; ++cc)
-                            plan.p_items.push_back({l, (int32_t)r0, cc, (int32_t)std::min<int64_t>(prow, d.n - r0)});
+                            (on_octets(d) ? plan.p_r_items : plan.p_items).push_back({l, (int32_t)r0, cc, (int32_t)std::min<int64_t>(prow, d.n - r0)});
                 const int32_t nct = (int32_t)ceil_div(d.m, 64);
                 if (!mf_q && d.n <= kFlatRows && d.n_q_tiles == 1 && d.N <= kStripSpan)
                     for (int32_t ct = 0; ct < nct; ct += 4) plan.q_flat_items.push_back({l, ct / 4, 0, 0});
                 else if (!mf_q)
                     for (int32_t rt = 0; rt < d.n_q_tiles; ++rt)
-                        for (int32_t ct = 0; ct < nct; ++ct) plan.q_items.push_back({l, ct, rt, 0});
+                        for (int32_t ct = 0; ct < nct; ++ct) (q_on_octets(d) ? plan.q_r_items : plan.q_items).push_back({l, ct, rt, 0});
                 if (!mf_p && d.n_p_chunks > 1)
                     for (int64_t e0 = 0; e0 < d.n * rank; e0 += 256) plan.pred_items.push_back({l, (int32_t)e0, 0, 0});
                 if (!mf_e && !sketch && d.es_tile > 0)
@@ -902,6 +916,11 @@ bool check_plan(const Plan &plan)
         for (const WorkItem &it : plan.p_items)
             c.add(plan, it, it.a, it.c <= kStripRows && it.c * plan.mats[it.mat].m < 2 * kStripSpan * 2 ? it.c : 0,
                   (int64_t)it.b * plan.mats[it.mat].p_chunk_cols, plan.mats[it.mat].p_chunk_cols);
+        for (const WorkItem &it : plan.p_r_items) {
+            const MatDesc &d = plan.mats[it.mat];
+            if (plan.sketch || d.m > kRaggedMaxCols || it.c > kStripRows) return false;
+            c.add(plan, it, it.a, it.c, (int64_t)it.b * d.p_chunk_cols, d.p_chunk_cols);
+        }
         for (const WorkItem &it : plan.p_f_items)
             c.add(plan, it, it.a, kPTileRows, (int64_t)it.b * plan.mats[it.mat].p_chunk_cols, plan.mats[it.mat].p_chunk_cols);
         if (plan.p_m_items.size() % 8 != 0) return false;                  // eight lists of one length
@@ -920,6 +939,11 @@ bool check_plan(const Plan &plan)
         Cover c(nm);
         for (const WorkItem &it : plan.q_items)
             c.add(plan, it, (int64_t)it.b * plan.mats[it.mat].q_tile_rows, plan.mats[it.mat].q_tile_rows, (int64_t)it.a * 64, 64);
+        for (const WorkItem &it : plan.q_r_items) {
+            const MatDesc &d = plan.mats[it.mat];
+            if (plan.sketch || d.m > kRaggedMaxCols || d.q_tile_rows % 128 != 0) return false;
+            c.add(plan, it, (int64_t)it.b * d.q_tile_rows, d.q_tile_rows, (int64_t)it.a * 64, 64);
+        }
         for (const WorkItem &it : plan.q_flat_items) {
             const MatDesc &d = plan.mats[it.mat];
             if (d.n > kFlatRows || plan.rank > kFlatRows || d.n_q_tiles != 1 || d.N > kStripSpan) return false;

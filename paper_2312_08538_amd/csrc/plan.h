@@ -29,7 +29,30 @@ constexpr int64_t apply_rows(int rank, int64_t n)
 constexpr int kQredManyTiles = 32;  // partial sums of Q+ per entry from which 16 threads share an entry's sum
 constexpr int kStripRows = 32;      // rows per workgroup item of the strip P pass
 constexpr int64_t kStripSpan = (int64_t)1 << 29;    // elements a strip workgroup's rows may span (32-bit byte offsets)
+// Strip family, quantiser, blocks of whole octets.  P pass: on octets unless 32 rows span more than kStripSpan elements (the
+// matrix then takes the kernels that load element by element, and only that matrix).
 constexpr int64_t kRaggedMaxCols = kStripSpan / kStripRows;
+// Q+ pass: also only where a matrix gives the kernel enough to do.  A wave takes 32 rows at a time, so that a matrix of few rows
+// leaves waves idle, which costs where the workgroups fill the chip, and a workgroup sets up more; element by element, a row tile
+// is 32 rows and not 128, and a matrix of more rows needs the launch that adds partial sums.  `total`: elements of the model's strip
+// matrices.  us for a step of one matrix with fp32 gradients, element by element / on octets:
+//   ranks to 4    32 x 5000 at rank 1 23.9 / 24.8, 16 x 100001 40 / 45, 256 x 1300 25.6 / 27.2, 600 x 650 24.0 / 25.3; 64 x 5000 needs no
+//                 launch for partial sums on octets (the pass 6.5 / 4.8), 10000 x 33 and 600 x 5000 have fewer of them (8.5 / 7.8, 10.6 / 9.3)
+//   8             the same for up to 32 rows (16 x 100001 49 / 55), from there on octets are as good or better
+//   16            600 x 300 44.1 / 44.9, 64 x 300 38.7 / 37.0, 38 of 64 x 2500 84 / 92, eight 82 / 82, 10000 x 65 51.2 / 48.8
+//   32            64 x 300 57.2 / 57.6, 42 of 40 x 300 66.9 / 63.7, 38 of 64 x 2500 125 / 165, 128 x 300 57.5 / 58.9, 19 of 128 x 2500
+//                 134 / 129, 128 x 100001 195 / 222, 600 x 300 61.6 / 64.5, 600 x 1300 70 / 73
+//   between       element by element the padding of the rank is multiplied too: the pass at rank 24 600 x 300 18.4 / 15.9, 32 x 20001
+//                 18.5 / 24.2, at 12 16.5 / 11.4
+constexpr bool ragged_q_pays(int rank, int64_t n, int64_t total)
+{
+    constexpr int64_t M = 1000000;
+    if (n <= 32) return rank > 8 && rank != 16 && rank != 32 && (rank < 16 || total < M / 2);
+    if (rank <= 4) return n <= 128 || n > 2048 || total >= M;
+    if (rank == 16) return n <= 64 ? total < 2 * M : n <= 128 || n > 4096 || total >= M;
+    if (rank == 32) return n <= 128 ? total > M / 4 && total < (n <= 64 ? 1 : 8) * M : n > 4096 || total >= M;
+    return true;
+}
 constexpr int kFlatRows = 8;        // matrices of at most so many rows: a wave of the strip Q+ pass takes all of them
 constexpr int kFastMaxRank = 8;     // the octet family holds rank <= 8 in registers
 constexpr int kPTileRows = 64;      // rows per workgroup item of the octet P pass
@@ -159,11 +182,11 @@ struct Plan {
     // strip kernels (any shape)
     std::vector<WorkItem> p_items;      // pass 1: (mat, first row, column chunk, rows: kStripRows or fewer)
     std::vector<WorkItem> q_items;      // pass 2: (mat, strip of 64 columns, row tile)
+    std::vector<WorkItem> p_r_items, q_r_items;     // the same of the quantiser on octets (kernels_ragged.hip)
     std::vector<WorkItem> q_flat_items; // pass 2, few rows: (mat, four strips)
     std::vector<WorkItem> err_s_items;  // pass 3: (mat, tile, its first row, rows it spans), or with segments (mat, first row, segment, rows)
     std::vector<WorkItem> err_g_items;  // pass 3, es_rows > 1: (mat, tile, its first group of rows, groups it spans)
     std::vector<WorkItem> err_items;    // pass 3, blocks that are not 8 * 2^j elements (j <= 6): (mat, first block, blocks per wave)
-    int ragged = 0;                     // 1: their P and Q+ passes take the quantiser's elements in octets (kernels_ragged.hip)
     int es_lds = 0;                     // floats of LDS of the strip err pass
     int wshift = 0, lb_shift = 0;       // log2(code fields per word); log2(block / 8) for power-of-two blocks of 8 elements or more
     int block_shift = -1;               // log2(block), -1 if it is not a power of two

@@ -39,6 +39,12 @@ CASES = [
     # bf16 gradients: the packed-split P and Q+ passes on the bf16 matrix cores, each vector's share in a launch of its own
     ([(300, 256), (77, 384), (1100, 128)], 4, 4, 128),         # an odd number of column blocks, partial sums of Q+
     ([(130, 1536), (520, 512)], 2, 2, 512),
+    # strip matrices at every padded rank, beside a tall one that takes the Q+ pass on octets: more than 1024 columns (the err
+    # pass in segments of a row, whose blocks reach into the next one, or whole), few, and an odd number
+    ([(40, 1025), (37, 1027), (33, 2560), (4300, 250)], 12, 4, 64),
+    ([(40, 1300), (64, 147), (4300, 251)], 16, 2, 128),
+    ([(70, 1027), (80, 2560), (4300, 250)], 32, 8, 64),
+    ([(20, 1025), (17, 2560), (2100, 650)], 3, 2, 256),
 ]
 
 

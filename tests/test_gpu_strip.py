@@ -233,14 +233,75 @@ def test_scales_near_the_largest_value_decode_finite(env):
     model.close()
 
 
+@pytest.mark.parametrize("tall", [False, True])
 @pytest.mark.parametrize("rank,bits,block,dtype", [(4, 4, 64, wl.F32), (8, 2, 16, wl.BF16), (3, 8, 128, wl.F32), (16, 4, 512, wl.BF16),
-                                                   (32, 8, 64, wl.F32)])
-def test_rows_that_start_anywhere_in_an_octet(env, rank, bits, block, dtype):
+                                                   (32, 8, 64, wl.F32), (9, 2, 128, wl.BF16), (17, 4, 64, wl.F32)])
+def test_rows_that_start_anywhere_in_an_octet(env, rank, bits, block, dtype, tall):
     """The P and Q+ passes on octets: row lengths of every remainder by 8, below, at and above a strip and three strips; rows
-    one below, at and above a wave's step (32) and a workgroup's (128).  (Twice the rank and more columns: what a full-rank
-    factorisation leaves is rounding error, whose codes are not determined.)"""
+    one below, at and above a wave's step (32) and a workgroup's (128), those of twice the rank and more columns (what a full-rank
+    factorisation leaves is rounding error, whose codes are not determined; ranks 9 and 17 are padded to 16 and 32 and leave the
+    small ones in, and the stages have a test without this limit).  Without the tall matrix the Q+ pass of most of these models goes
+    element by element."""
     layout = [(n, m) for i, m in enumerate([57, 58, 59, 60, 61, 62, 63, 64, 65, 71, 193, 198, 1027])
               for n in ((31, 33, 97, 127, 128, 129, 161)[i % 7],)] + [(40, 7), (33, 1), (50, 17)]
-    layout = [(max(n, 2 * rank), max(m, 2 * rank + 1)) for n, m in layout]
+    layout = [(max(n, 2 * rank), max(m, 2 * rank + 1)) for n, m in layout] + [(4500, 257)] * tall
     w = wl.Workload("ragged", 13, tuple(layout), rank, bits, block, dtype, "normal", 1.0, 0x8A66)
     _run_model(env, w, layout, 2, f"ragged-r{rank}-b{bits}-B{block}-dt{dtype}")
+
+
+def _stages(env, layout, rank, bits, block, dtype, two, seed):
+    """P and Q+ by stage calls on random gradients, codes and factors against float64 products of p: an fp32 rounding of p for
+    each vector and one of the result, 6e-8 of it each at most."""
+    R, B, U = env
+    import torch
+
+    model = B.Model(layout, rank, bits, block, dtype, 5)
+    buf = model.alloc("cuda:0")
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    s, per = (1 << (bits - 1)) - 1, 32 // bits
+    for k in ("grads", "Q", "P"):
+        buf[k].normal_(generator=gen)
+
+    def vector(size):
+        fields = torch.randint(-s, s + 1, (model.sizes["code_words"], per), device="cuda:0", generator=gen)
+        codes = ((fields & ((1 << bits) - 1)) << (torch.arange(per, device="cuda:0") * bits)).sum(1)
+        codes = torch.where(codes >= 1 << 31, codes - (1 << 32), codes).to(torch.int32)
+        scales = torch.rand(model.sizes["n_scales"], device="cuda:0", generator=gen) * size
+        e = torch.zeros(model.sizes["grad_elems"], device="cuda:0")
+        B.conef_decode_error(model.ctx, codes, scales, e, model.stream_handle())
+        return codes, scales, e
+
+    vectors = [vector(2.0)] + ([vector(0.3)] if two else [])
+    P, Q, st = torch.zeros_like(buf["P"]), torch.zeros_like(buf["Q"]), model.stream_handle()
+    args = [x for v in vectors for x in v[:2]]
+    print(f"[stages {layout[:3]} .. rank {rank} {bits} bits, blocks of {block}, two {two}]: launching", flush=True)
+    (B.conef_i_step_p if two else B.conef_step_p)(model.ctx, buf["grads"], *args, buf["Q"], P, buf["ws"], st)
+    (B.conef_i_step_q if two else B.conef_step_q)(model.ctx, buf["grads"], *args, buf["P"], Q, buf["ws"], st)
+    torch.cuda.synchronize()
+    for (n, m), o in zip(layout, model.offsets):
+        g = slice(o["grad_off"], o["grad_off"] + n * m)
+        p = (buf["grads"][g].double() + sum(v[2][g].double() for v in vectors)).view(n, m)
+        rows, cols = slice(o["p_off"], o["p_off"] + n * rank), slice(o["q_off"], o["q_off"] + m * rank)
+        for got, want in ((P[rows].view(n, rank), p @ buf["Q"][cols].double().view(m, rank)),
+                          (Q[cols].view(m, rank), p.T.contiguous() @ buf["P"][rows].double().view(n, rank))):
+            assert float((got.double() - want).norm() / want.norm()) <= 3e-7, (n, m, rank)
+    model.close()
+
+
+@pytest.mark.parametrize("rank,bits,block,dtype,two", [
+    (16, 4, 64, wl.F32, False), (32, 2, 64, wl.BF16, False), (32, 8, 512, wl.F32, True), (16, 2, 128, wl.BF16, True), (12, 4, 64, wl.F32, True),
+    (24, 4, 8, wl.F32, True), (31, 4, 128, wl.F32, False), (8, 2, 16, wl.BF16, True), (3, 8, 64, wl.F32, True), (1, 4, 64, wl.BF16, True)])
+@pytest.mark.parametrize("tall", [False, True])
+def test_stages_of_strip_matrices(env, rank, bits, block, dtype, two, tall):
+    """Every padded rank, one and two vectors: strips of part of 64 columns, whole ones and a few more, rows below, at and above a
+    wave's step; the Q+ pass element by element and (with a tall matrix) on octets."""
+    layout = [(33, m) for m in (57, 58, 59, 60, 61, 62, 63, 64, 65, 193)] + [(32, 40), (40, 33), (64, 71), (129, 1027), (161, 35)]
+    _stages(env, layout + [(4500, 257)] * tall, rank, bits, block, dtype, two, rank)
+
+
+@pytest.mark.parametrize("rank", [2, 3])
+def test_a_very_wide_matrix_beside_others(env, rank):
+    """More than 2^24 columns: that matrix goes element by element, the others on octets (at rank 2 beside an octet matrix, in
+    the launch for both)."""
+    _stages(env, [(3, 2 ** 24 + 72), (64, 147), (500, 77), (100, 512), (2500, 700)], rank, 4, 64, wl.F32, False, 7)
