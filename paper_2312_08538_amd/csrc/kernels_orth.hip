@@ -208,7 +208,9 @@ __device__ __forceinline__ double rsqrt_f64(double x)
 // has NaN in that entry's row and nowhere else.
 // The loop is not unrolled: a launch that runs its code once fetches every line of it from memory, and with all trips and lane
 // indices written out (61 KB at rank 32) that was most of its time (the stage's four launches for three matrices of 64 x 64
-// at rank 32: 40.0 -> 28.9 us).
+// at rank 32: 40.0 -> 28.9 us).  A trip is a chain of LDS reads, the reciprocal root and the products: with a branch around a
+// dead pivot's the reads wait for the comparison (600 x 300, the stage at ranks 8 / 16 / 32 9.4 / 18.4 / 28.5 us, so 9.1 / 17.5 /
+// 27.7).
 template <int RP>
 struct CholeskyLds {
     double G[RP * RP];
@@ -239,23 +241,23 @@ __device__ __forceinline__ void cholesky_inverse(CholeskyLds<RP> &lds, int t, in
         }
         if (THREADS > 64) __syncthreads();
         else wave_lds_sync();
+        // all that the trip reads is asked for at once
         const double dcc = row_g[c], gcc = lds.G[c * RP + c];
-        if (!(dcc > 1e-12 * gcc)) {                     // uniform
-            // not 0 times the row: a column of P that is not finite comes here, and its row of G is not finite either
+        double gj = row_g[j], yj = row_y[j], gi[V];
 #pragma unroll
-            for (int v = 0; v < V; ++v)
-                if (i0 + v * kRows == c) y[v] = 0.0;
-            continue;
-        }
-        const double ri = rsqrt_f64(dcc);               // 1 / R[c][c]
-        const double rj = row_g[j] * ri, yj = row_y[j] * ri;
+        for (int v = 0; v < V; ++v) gi[v] = row_g[i0 + v * kRows < RP ? i0 + v * kRows : 0];
+        // a dead pivot's row counts as zero before it is multiplied: that of a column of P that is not finite is not finite either
+        const bool live = dcc > 1e-12 * gcc;            // uniform
+        const double ri = rsqrt_f64(live ? dcc : 1.0);  // 1 / R[c][c]
+        gj = live ? gj * ri : 0.0;
+        yj = live ? yj * ri : 0.0;
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             const int i = i0 + v * kRows;
             if (i == c) y[v] = yj;
             if (i > c && i < RP) {
-                const double rci = row_g[i] * ri;
-                g[v] = __builtin_fma(-rci, rj, g[v]);
+                const double rci = live ? gi[v] * ri : 0.0;
+                g[v] = __builtin_fma(-rci, gj, g[v]);
                 y[v] = __builtin_fma(-rci, yj, y[v]);
             }
         }
