@@ -9,7 +9,7 @@ namespace conef {
 // Device-resident copy of a plan: descriptor array and work tables.
 struct DevicePlan {
     const MatDesc *mats = nullptr;
-    const WorkItem *p_r_items = nullptr, *q_r_items = nullptr, *err_s_items = nullptr;    // strip kernels (any shape), on octets
+    const WorkItem *p_items = nullptr, *q_items = nullptr, *err_s_items = nullptr;        // strip kernels (any shape)
     const WorkItem *q_flat_items = nullptr, *err_g_items = nullptr;     // few rows (Q+ pass), few columns (err pass)
     const WorkItem *err_items = nullptr;        // err pass of blocks the strip kernel does not take
     const WorkItem *p_f_items = nullptr, *q_f_items = nullptr, *err_f_items = nullptr;    // octet family
@@ -37,7 +37,7 @@ struct DevicePlan {
     const OrthItem *gram_s_items = nullptr, *apply_s_items = nullptr;      // orthonormalisation, ranks up to 8
     int n_gram_s = 0, n_apply_s = 0;
     int n_mats = 0;
-    int n_p_r = 0, n_q_r = 0, n_err = 0, n_p_f = 0, n_q_f = 0, n_err_f = 0, n_err_t = 0;
+    int n_p = 0, n_q = 0, n_err = 0, n_p_f = 0, n_q_f = 0, n_err_f = 0, n_err_t = 0;
     int n_p_m = 0, n_q_m = 0, n_err_m = 0, n_split_p = 0, n_split_qn = 0;
     int n_p_k = 0, n_q_k = 0;
     int n_upd = 0, upd_many = 0;    // upd_many: its items may be of several row tiles
@@ -61,9 +61,18 @@ struct DevicePlan {
     // every matrix, MatDesc::i2_k values at i2_off) as it comes in and where the new one goes (another buffer)
     const float *i2_in = nullptr;
     float *i2_out = nullptr;
-    const WorkItem *p_items = nullptr, *q_items = nullptr;      // strip kernels, P and Q+ passes element by element
-    int n_p = 0, n_q = 0;
+    // Strip kernels, P and Q+ passes on octets.  The launchers of those kernels put them in the place of p_items and the others
+    // (octet_items): what a kernel reads stands together in its arguments, and a line of them more costs 0.1 - 0.4 us a launch.
+    const WorkItem *p_r_items = nullptr, *q_r_items = nullptr;
+    int n_p_r = 0, n_q_r = 0;
 };
+
+inline DevicePlan octet_items(DevicePlan dp)
+{
+    dp.p_items = dp.p_r_items; dp.q_items = dp.q_r_items;
+    dp.n_p = dp.n_p_r; dp.n_q = dp.n_q_r;
+    return dp;
+}
 
 // Optional pair of events recorded immediately before and after a stage's main kernel.
 struct Span {

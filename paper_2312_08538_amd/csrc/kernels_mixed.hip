@@ -33,7 +33,7 @@ void k_p_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const ui
     if (b >= lead) {
         const POctetLds o = {lds, reinterpret_cast<uint32_t *>(lds + kPOctetTiles), lds + kPOctetTiles + kPOctetCodes, nullptr, nullptr};
         p_octet<BF16, BITS, RH, false>(dp, b - lead, o, grads, codes, scales, Q, P, ws);
-    } else if (b < dp.n_p_r) {
+    } else if (b < dp.n_p) {
         p_ragged<BF16, BITS, RH, false>(dp, b, lds, grads, codes, scales, Q, P, ws);
     }
 }
@@ -47,7 +47,7 @@ void k_q_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const ui
     const int b = blockIdx.x;
     if (b >= lead) {
         q_octet<BF16, BITS, (R > 4 ? 2 : 1), false>(dp, b - lead, lds, grads, codes, scales, Phat, ws);
-    } else if (b < dp.n_q_r) {
+    } else if (b < dp.n_q) {
         q_ragged<BF16, BITS, (R > 4 ? 2 : 1), false>(dp, b, lds, grads, codes, scales, Phat, ws, Qout);
     }
 }
@@ -95,8 +95,8 @@ bool mixed_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes
         constexpr bool BF = decltype(bf)::value;
         constexpr int B = decltype(bits)::value;
         const dim3 grid(lead + dp.n_p_f), block(256);
-        if (dp.rank > 4) hipLaunchKernelGGL((k_p_mixed<BF, B, 2>), grid, block, 0, st, dp, lead, grads, codes, scales, Q, P, ws);
-        else hipLaunchKernelGGL((k_p_mixed<BF, B, 1>), grid, block, 0, st, dp, lead, grads, codes, scales, Q, P, ws);
+        if (dp.rank > 4) hipLaunchKernelGGL((k_p_mixed<BF, B, 2>), grid, block, 0, st, octet_items(dp), lead, grads, codes, scales, Q, P, ws);
+        else hipLaunchKernelGGL((k_p_mixed<BF, B, 1>), grid, block, 0, st, octet_items(dp), lead, grads, codes, scales, Q, P, ws);
     });
     return true;
 }
@@ -110,9 +110,9 @@ bool mixed_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes
         constexpr bool BF = decltype(bf)::value;
         constexpr int B = decltype(bits)::value;
         const dim3 grid(lead + (dp.n_q_f + 3) / 4), block(256);
-        if (dp.rank == 8) hipLaunchKernelGGL((k_q_mixed<BF, B, 8>), grid, block, 0, st, dp, lead, grads, codes, scales, Phat, ws, Qout);
-        else if (dp.rank == 4) hipLaunchKernelGGL((k_q_mixed<BF, B, 4>), grid, block, 0, st, dp, lead, grads, codes, scales, Phat, ws, Qout);
-        else hipLaunchKernelGGL((k_q_mixed<BF, B, 2>), grid, block, 0, st, dp, lead, grads, codes, scales, Phat, ws, Qout);
+        if (dp.rank == 8) hipLaunchKernelGGL((k_q_mixed<BF, B, 8>), grid, block, 0, st, octet_items(dp), lead, grads, codes, scales, Phat, ws, Qout);
+        else if (dp.rank == 4) hipLaunchKernelGGL((k_q_mixed<BF, B, 4>), grid, block, 0, st, octet_items(dp), lead, grads, codes, scales, Phat, ws, Qout);
+        else hipLaunchKernelGGL((k_q_mixed<BF, B, 2>), grid, block, 0, st, octet_items(dp), lead, grads, codes, scales, Phat, ws, Qout);
     });
     return true;
 }

@@ -65,7 +65,7 @@ void ragged_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *code
     if (dp.n_p_r <= 0) return;
     by_type(dp, [&](auto bf, auto bits, auto rh, auto two) {
         hipLaunchKernelGGL((k_p_ragged<decltype(bf)::value, decltype(bits)::value, decltype(rh)::value, decltype(two)::value>), dim3(dp.n_p_r),
-                           dim3(256), 0, st, dp, grads, codes, scales, Q, P, ws);
+                           dim3(256), 0, st, octet_items(dp), grads, codes, scales, Q, P, ws);
     });
 }
 
@@ -75,7 +75,7 @@ void ragged_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *code
     if (dp.n_q_r <= 0) return;
     by_type(dp, [&](auto bf, auto bits, auto rh, auto two) {
         hipLaunchKernelGGL((k_q_ragged<decltype(bf)::value, decltype(bits)::value, decltype(rh)::value, decltype(two)::value>), dim3(dp.n_q_r),
-                           dim3(256), 0, st, dp, grads, codes, scales, Phat, ws, Qout);
+                           dim3(256), 0, st, octet_items(dp), grads, codes, scales, Phat, ws, Qout);
     });
 }
 

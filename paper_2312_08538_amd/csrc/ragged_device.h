@@ -131,7 +131,7 @@ __device__ __forceinline__ void p_ragged(const DevicePlan &dp, int block, float 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float *T = lds + wave * kRagTile;
-    const WorkItem it = dp.p_r_items[block];
+    const WorkItem it = dp.p_items[block];
     const MatDesc d = dp.mats[it.mat];
     const int r = dp.rank;
     const int64_t row0 = it.a;
@@ -285,7 +285,7 @@ __device__ __forceinline__ void q_ragged(const DevicePlan &dp, int block, float 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float *T = lds + wave * kRagTile;
-    const WorkItem it = dp.q_r_items[xcd_contiguous_item(block, dp.n_q_r)];
+    const WorkItem it = dp.q_items[xcd_contiguous_item(block, dp.n_q)];
     const MatDesc d = dp.mats[it.mat];
     const int r = dp.rank;
     const int64_t col0 = (int64_t)it.a * 64;
