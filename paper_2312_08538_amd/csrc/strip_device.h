@@ -266,14 +266,22 @@ __device__ __forceinline__ void p_strip(const DevicePlan &dp, int block, float *
     }
 }
 
-// A factor row at a wave-uniform address (scalar loads); entries at or beyond the rank are zero.
+// A factor row at a wave-uniform address (scalar loads); entries at or beyond the rank are zero.  A rank that is not R takes its
+// whole groups of four as one load each: entry by entry they were most of the err pass (10000 x 650 at rank 24: 102 -> 54 us, 600 x
+// 5000 at rank 12 36 -> 25).
 template <int R, bool EXACT>
 __device__ __forceinline__ void uniform_row(const float *__restrict__ F, int r, float (&out)[R])
 {
 #pragma unroll
-    for (int c = 0; c < R; ++c) {
-        const float v = F[EXACT ? c : (c < r ? c : r - 1)];
-        out[c] = (EXACT || c < r) ? v : 0.0f;
+    for (int c0 = 0; c0 < R; c0 += 4) {
+        constexpr int G = R < 4 ? R : 4;
+        if (EXACT || c0 + G <= r) {                     // uniform: four entries in one load
+#pragma unroll
+            for (int c = c0; c < c0 + G; ++c) out[c] = F[c];
+        } else {
+#pragma unroll
+            for (int c = c0; c < c0 + G; ++c) out[c] = c < r ? F[c < r ? c : r - 1] : 0.0f;
+        }
     }
 }
 
