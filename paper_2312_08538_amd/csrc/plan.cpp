@@ -515,8 +515,10 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 if (rank <= 8) d.gram_tile_rows = (int32_t)std::max<int64_t>(gram_rows_small(d.n), coarse_gram ? d.gram_tile_rows : 0);
                 d.n_gram_tiles = (int32_t)ceil_div(d.n, d.gram_tile_rows);
                 d.gram_off = wd; wd += (int64_t)d.n_gram_tiles * rank * rank;
-                d.gsum_off = wd; wd += rank * rank;
-                d.rinv_off = wd; wd += rank * rank;
+                if (rank > 8) {                     // up to 8 the sum and the factor stay in the second launch's workgroups
+                    d.gsum_off = wd; wd += rank * rank;
+                    d.rinv_off = wd; wd += rank * rank;
+                }
                 d.q_tile_rows = d.cs_lin ? 2048 : d.pack ? kPackQRows : d.path == kPathOctet ? q_rows : (d.path == kPathMfma && (kMfmaPasses & 2)) ? 2048
                                 : (int32_t)std::min<int64_t>(std::min<int64_t>(512, times * (q_on_octets(d) ? ragged_q_rows : strip_q_rows)),
                                                              4 * std::max<int64_t>(1, kStripSpan / d.m));
@@ -1106,8 +1108,10 @@ bool check_plan(const Plan &plan)
         if (qred[l] != (direct_q ? 0 : (d.m * plan.rank + qper - 1) / qper)) return false;
         if (pred[l] != (d.n_p_chunks > 1 ? (d.n * plan.rank + 255) / 256 : 0)) return false;
         regions.push_back({d.gram_off, d.gram_off + (int64_t)d.n_gram_tiles * plan.rank * plan.rank});
-        regions.push_back({d.gsum_off, d.gsum_off + (int64_t)plan.rank * plan.rank});
-        regions.push_back({d.rinv_off, d.rinv_off + (int64_t)plan.rank * plan.rank});
+        if (plan.rank > 8) {
+            regions.push_back({d.gsum_off, d.gsum_off + (int64_t)plan.rank * plan.rank});
+            regions.push_back({d.rinv_off, d.rinv_off + (int64_t)plan.rank * plan.rank});
+        }
         regions.push_back({d.qpart_off, d.qpart_off + (int64_t)d.n_q_tiles * d.m * plan.rank});
         if (d.st_slots > 0) regions.push_back({d.st_part_off, d.st_part_off + d.st_slots});
         if (d.n_p_chunks > 1) regions.push_back({d.ppart_off, d.ppart_off + (int64_t)d.n_p_chunks * d.n * plan.rank});

@@ -85,8 +85,8 @@ struct MatDesc {
     int64_t grad_off, word_off, scale_off, p_off, q_off;   // element offsets in the flat buffers
     int64_t nblk;                   // number of scale blocks
     int64_t gram_off;               // partial Gram matrices, [n_gram_tiles][r*r]
-    int64_t gsum_off;               // r*r Gram matrix (the partial ones added up in a fixed order)
-    int64_t rinv_off;               // r*r inverse triangular factor
+    int64_t gsum_off;               // r*r Gram matrix (the partial ones added up in a fixed order), ranks above 8
+    int64_t rinv_off;               // r*r inverse triangular factor, ranks above 8
     int64_t qpart_off;              // partial sums of Q+, [n_q_tiles][m*r]
     int64_t ppart_off;              // partial sums of P, [n_p_chunks][n*r] (only if n_p_chunks > 1)
     int32_t n_gram_tiles, n_q_tiles, n_p_chunks;

@@ -546,6 +546,15 @@ def test_models_of_many_matrices_keep_to_the_static_workspace(layout, rank):
     B.conef_destroy(ctx)
 
 
+def test_low_ranks_reserve_no_room_for_sums_of_gram_matrices():
+    """Up to rank 8 the workspace holds partial Gram matrices only: 24000 matrices of one each beside their partial sums of Q+
+    and streams fit the static workspace, with two more per matrix they would not."""
+    ctx = B.conef_init([(16, 8)] * 24000, 8, 4, 64, B.F32, 0)
+    assert B.conef_sizes(ctx)["workspace_bytes"] <= B.STATIC_WORKSPACE_BYTES
+    B.conef_check_plan(ctx)
+    B.conef_destroy(ctx)
+
+
 @pytest.mark.parametrize("layout,rank,bits,block", [
     ([(593, 70), (2369, 26002)], 32, 8, 64), ([(403, 355), (10087, 162), (5939, 437), (59, 7138), (69, 26011), (660, 6651), (716, 23053), (8641, 1573)], 32, 2, 512)])
 def test_the_static_workspace_counts_the_stream_kernels_partial_sums(layout, rank, bits, block):
