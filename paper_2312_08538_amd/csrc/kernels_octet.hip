@@ -112,6 +112,8 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
     if (MODE == kModeUniform) ku = rku_keys((uint32_t)it.mat, step_lo, step_hi, dp.seed_lo, dp.seed_hi);
     __shared__ __attribute__((aligned(16))) float s_val[MODE == kModeStrata ? 4 : 1][MODE == kModeStrata ? 512 : 4];
     __shared__ uint32_t s_kept[MODE == kModeStrata ? 4 : 1][64];
+    __shared__ __attribute__((aligned(16))) uint32_t s_pos[MODE == kModeStrata ? 4 : 1][MODE == kModeStrata ? 256 : 4];
+    uint32_t win = 0xFFFFFFFFu;        // MODE 3: first Philox call of the window of strata in s_pos (none yet)
     double l1 = 0.0;
     const float s_f = (float)((1 << (BITS - 1)) - 1);
     // The last run of a matrix may be short: octets beyond the end re-read the last octet and store nothing (where they share
@@ -225,42 +227,54 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
         }
         // ... then the kept coordinates: Delta = p there, and beta e (plain) or nothing (two vectors) is left
         if (MODE == kModeStrata) {
-            // The run's values of p go through LDS, and the lanes take the run's strata: each draws its stratum's coordinate,
+            // The run's values of p go through LDS, and the lanes take the run's strata: each looks up its stratum's coordinate,
             // passes the value on and marks it in its octet's word.  (An octet looking for its strata's coordinates evaluated
-            // two Philox calls and a branch per element: half of the pass.)  With short strata a lane takes the four of a call.
+            // two Philox calls and a branch per element: half of the pass.)
+            // Strata of 8 or more: the coordinates are drawn a window at a time, 64 calls, one per lane, all four words of
+            // each: 256 strata, that is four runs of the shortest.  (A call per lane and run used one word of its four: two vectors,
+            // 1.3 G elements in strata of ten 1702 us, so 1591.)  Of shorter ones a run has more than a window would serve: a lane takes
+            // the four of a call.
             float *sp = s_val[threadIdx.x >> 6];
             uint32_t *sk = s_kept[threadIdx.x >> 6];
+            uint32_t *su = s_pos[threadIdx.x >> 6];
             float p[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) p[e] = (TWO || V2) ? x[e] : __builtin_fmaf(dpart, qf[e], g[e]);
             reinterpret_cast<float4 *>(sp + lane * 8)[0] = make_float4(p[0], p[1], p[2], p[3]);
             reinterpret_cast<float4 *>(sp + lane * 8)[1] = make_float4(p[4], p[5], p[6], p[7]);
             sk[lane] = 0;
-            wave_memory_sync();
             const uint32_t N = (uint32_t)d.N, j0 = (uint32_t)(((int64_t)it.a + rr) << 9);
             const uint32_t s0 = stratum_of(j0, d.rk_g, d.rk_magic), s1 = stratum_of(N - 1u - j0 < 511u ? N - 1u : j0 + 511u, d.rk_g, d.rk_magic);
-            auto take = [&](uint32_t s, uint32_t u) {
+            uint32_t out[4];
+            auto position = [&](uint32_t s, uint32_t u) {
                 const uint32_t base = s * d.rk_g;
                 const uint32_t len = N - base < d.rk_g ? N - base : d.rk_g;
-                const uint32_t rel = base + __umulhi(u, len) - j0;            // wraps to a large value before the run
+                return base + __umulhi(u, len);
+            };
+            auto take = [&](uint32_t s, uint32_t pos) {
+                const uint32_t rel = pos - j0;                                // wraps to a large value before the run
                 if (rel < 512u) {
                     delta[d.rk_delta_off + s] = sp[rel];
                     __hip_atomic_fetch_or(sk + (rel >> 3), 1u << (rel & 7u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
             };
-            uint32_t out[4];
             if (d.rk_g >= 8) {
-                for (uint32_t s = s0 + lane; s <= s1; s += 64) {
-                    philox4x32_10(s >> 2, (uint32_t)it.mat + 0x40000000u, step_lo, step_hi, dp.seed_lo, dp.seed_hi, out);
-                    const uint32_t w = s & 3u;
-                    take(s, w == 0 ? out[0] : (w == 1 ? out[1] : (w == 2 ? out[2] : out[3])));
+                if (win == 0xFFFFFFFFu || (s1 >> 2) - win >= 64u) {          // uniform
+                    win = s0 >> 2;
+                    philox4x32_10(win + lane, (uint32_t)it.mat + 0x40000000u, step_lo, step_hi, dp.seed_lo, dp.seed_hi, out);
+                    const uint32_t s = (win + lane) * 4;                      // (strata behind the last one are never looked up)
+                    *reinterpret_cast<uint4 *>(su + lane * 4) =
+                        make_uint4(position(s, out[0]), position(s + 1, out[1]), position(s + 2, out[2]), position(s + 3, out[3]));
                 }
+                wave_memory_sync();
+                for (uint32_t s = s0 + lane; s <= s1; s += 64) take(s, su[s - win * 4]);
             } else {
+                wave_memory_sync();
                 for (uint32_t q = (s0 >> 2) + lane; q <= (s1 >> 2); q += 64) {
                     philox4x32_10(q, (uint32_t)it.mat + 0x40000000u, step_lo, step_hi, dp.seed_lo, dp.seed_hi, out);
 #pragma unroll
                     for (uint32_t w = 0; w < 4; ++w)
-                        if (q * 4 + w >= s0 && q * 4 + w <= s1) take(q * 4 + w, out[w]);
+                        if (q * 4 + w >= s0 && q * 4 + w <= s1) take(q * 4 + w, position(q * 4 + w, out[w]));
                 }
             }
             wave_memory_sync();
