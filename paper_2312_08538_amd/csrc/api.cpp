@@ -134,6 +134,7 @@ int ensure_uploaded(conef_ctx *ctx)
     d.block_shift = pl.block_shift;
     d.n_upd = (int)pl.upd_items.size();
     d.upd_many = pl.upd_many;
+    d.small_lds = (size_t)pl.small_lds;
     d.n_p_f = (int)pl.p_f_items.size();
     d.n_q_f = (int)pl.q_f_items.size();
     d.n_err_f = (int)pl.err_f_items.size();
@@ -437,6 +438,16 @@ int conef_step(conef_ctx *ctx, const void *grads, uint32_t *err_codes, float *er
                void *hip_stream)
 {
     int rc;
+    // a model of small matrices: one launch, except where the stages are timed
+    if (ctx && ctx->plan.small_lds > 0 && !ctx->timing) {
+        if (!grads || !err_codes || !err_scales || !Q_state || !P_out || !Q_out || !workspace) return CONEF_EINVAL;
+        if (misaligned(grads, 16) || misaligned(err_codes, 16) || misaligned(err_scales, 4) || misaligned(Q_state, 16) ||
+            misaligned(P_out, 16) || misaligned(Q_out, 16) || misaligned(workspace, 256))
+            return CONEF_EINVAL;
+        if ((rc = ensure_uploaded(ctx))) return rc;
+        return hip_rc(launch_step_small(ctx->dev, grads, err_codes, err_scales, Q_state, P_out, Q_out, step,
+                                        static_cast<hipStream_t>(hip_stream)));
+    }
     if (ctx && ctx->timing) { ctx->slot = (int)(ctx->steps_timed % kTimingSlots); ++ctx->steps_timed; }
     if ((rc = step_p_impl(ctx, grads, err_codes, err_scales, Q_state, P_out, workspace, hip_stream, false))) return rc;
     /* exchange point 1: mean of P over the workers -- identity for one worker */

@@ -65,6 +65,15 @@ struct DevicePlan {
     // (octet_items): what a kernel reads stands together in its arguments, and a line of them more costs 0.1 - 0.4 us a launch.
     const WorkItem *p_r_items = nullptr, *q_r_items = nullptr;
     int n_p_r = 0, n_q_r = 0;
+    size_t small_lds = 0;           // bytes of LDS of the step in one launch (0: the model does not take it)
+};
+
+// What the step in one launch reads of it
+struct SmallPlan {
+    const MatDesc *mats;
+    int rank;
+    float omb;
+    uint32_t seed_lo, seed_hi;
 };
 
 inline DevicePlan octet_items(DevicePlan dp)
@@ -100,6 +109,9 @@ hipError_t launch_pass_q(const DevicePlan &dp, const void *grads, const uint32_t
 hipError_t launch_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales,
                            const float *Phat, const float *Qn, uint64_t step, double *ws, bool splits_ready,
                            hipStream_t st, Span span = Span());
+// The whole step of a model of small matrices (dp.small_lds > 0; kernels_small.hip).  Q_out may be Q_in.
+hipError_t launch_step_small(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, const float *Q_in, float *P_out,
+                             float *Q_out, uint64_t step, hipStream_t st);
 hipError_t launch_update(const DevicePlan &dp, const float *Phat, const float *Qn, float *x, bool subtract,
                          hipStream_t st);
 // Random-block gradient compressor: one streaming pass (decode + add, keep the block, compress the rest).

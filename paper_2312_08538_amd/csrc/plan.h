@@ -54,6 +54,22 @@ constexpr bool ragged_q_pays(int rank, int64_t n, int64_t total)
     return true;
 }
 constexpr int kFlatRows = 8;        // matrices of at most so many rows: a wave of the strip Q+ pass takes all of them
+// The step in one launch, a workgroup per matrix (kernels_small.hip): matrices whose p = g + e and factors fit into the LDS of a
+// CU, rows of whole octets, blocks of 8 * 2^j elements, ranks up to 8, no matrix of the packed-split family (whose stages add up in
+// fp32, and the step keeps the bits of its stages).  Up to 256 matrices, a CU each; more, which take turns, only if they are worth
+// a CU.  us a step, in one launch / in the stages' six: 8 x 8 at rank 4, bf16 7.9 / 19.6, at rank 8 10.3 / 19.6, 300 of them 15.3 /
+// 19.6 and 20.1 / 19.6, 1000 29 / 19 and 39 / 25; 64 x 64 at rank 8 11.1 / 21.1, 300 of them 22.0 / 25.8, 1000 42.6 / 47, 4000 167 / 134;
+// 16 x 1024 at rank 8 17.0 / 30.1, 300 of them 38.6 / 66.6, 4000 346 / 648; 256 x 128 at rank 2 14.6 / 23.1, at rank 4, bf16 16.6 / 22.5, 256
+// of them 18.6 / 45.8, 4000 272 / 401.
+constexpr int64_t kSmallMaxElems = 32768, kSmallMaxRows = 1024;
+constexpr bool small_pays(int64_t n_mats, int64_t total) { return n_mats <= 256 || total >= 8192 * n_mats; }
+constexpr int kSmallPad = 4;        // floats between the rows of p in LDS: 16 rows of a matrix-core operand fall on distinct banks
+constexpr int64_t kSmallLds = 160 * 1024 - 2048;      // (2 KB: the factorisation's own)
+constexpr int64_t small_lds_bytes(int64_t n, int64_t m, int rpad)
+{
+    const int64_t n16 = (n + 15) / 16 * 16, m16 = (m + 15) / 16 * 16;
+    return 8 * (16 * 16 + m16 + n16) * rpad + 4 * n16 * (rpad + m16 + kSmallPad);
+}
 constexpr int kFastMaxRank = 8;     // the octet family holds rank <= 8 in registers
 constexpr int kPTileRows = 64;      // rows per workgroup item of the octet P pass
 
@@ -216,6 +232,7 @@ struct Plan {
     std::vector<WorkItem> elem_items;   // element-wise helpers: (mat, first element / 1024)
     std::vector<WorkItem> upd_items;    // decompress / update: (mat, row tile of 64, column tile of 128, row tiles)
     int csc_threads = 0;                // column form of the sketch: threads per workgroup of the update
+    int64_t small_lds = 0;              // bytes of LDS of the step in one launch; 0: not for this model
     int upd_many = 0;                   // 1: the kernel that walks several row tiles takes them (else all are of one tile)
     // element-wise gradient compressors with the quantiser: stream tables (made with the plan)
     size_t sign_words = 0;
