@@ -321,6 +321,21 @@ __device__ __forceinline__ void rounded_values(const int32_t t[8], float q[8])
     for (int e = 0; e < 8; ++e) q[e] = signed_byte<2>((uint32_t)t[e]);
 }
 
+// Bit e: the sign bit of x[e].  Byte permutes make the signs of four values the bytes of a word, all ones or zero, each keeps its
+// own bit, and the bytes are added up: 8 instructions for the octet (20 with a shift, a mask and an or per value).
+__device__ __forceinline__ uint32_t octet_signs(const float x[8])
+{
+    uint32_t bits = 0;
+#pragma unroll
+    for (int i = 0; i < 8; i += 4) {
+        // selectors 9 and 11: the sign of the second operand's and of the first operand's top byte, 12: zero
+        const uint32_t lo = __builtin_amdgcn_perm(__float_as_uint(x[i + 1]), __float_as_uint(x[i]), 0x0C0C0B09u);
+        const uint32_t hi = __builtin_amdgcn_perm(__float_as_uint(x[i + 3]), __float_as_uint(x[i + 2]), 0x0B090C0Cu);
+        bits = __builtin_amdgcn_sad_u8((lo | hi) & (0x08040201u << i), 0u, bits);
+    }
+    return bits;
+}
+
 // LDS of a wave's own: its instructions are executed in order, so what is needed between one lane's write and another lane's
 // read is that the compiler keeps their order.  The fences name LDS alone: a fence of all memory (an asm statement's memory
 // clobber) also kept the loads of the next rows behind it, and the strip P pass on the sketch took twice as long (200000 x

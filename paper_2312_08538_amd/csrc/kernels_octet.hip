@@ -93,6 +93,7 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                                                   uint32_t *__restrict__ sign_words, const float *__restrict__ c_scale, double *ws,
                                                   uint32_t *codes2, float *scales2)
 {
+    constexpr bool BACK = TWO || V2;
     constexpr bool SPARSE = MODE == kModeBlock || MODE == kModeStrata || MODE == kModeUniform;      // Delta keeps a few coordinates as they are
     const int lane = threadIdx.x & 63;
     const int item = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
     RkuKeys ku = {};
     if (MODE == kModeUniform) ku = rku_keys((uint32_t)it.mat, step_lo, step_hi, dp.seed_lo, dp.seed_hi);
     __shared__ __attribute__((aligned(16))) float s_val[MODE == kModeStrata ? 4 : 1][MODE == kModeStrata ? 512 : 4];
-    __shared__ uint32_t s_kept[MODE == kModeStrata ? 4 : 1][64];
+    __shared__ uint32_t s_kept[MODE == kModeStrata && !BACK ? 4 : 1][64];
     __shared__ __attribute__((aligned(16))) uint32_t s_pos[MODE == kModeStrata ? 4 : 1][MODE == kModeStrata ? 256 : 4];
     uint32_t win = 0xFFFFFFFFu;        // MODE 3: first Philox call of the window of strata in s_pos (none yet)
     double l1 = 0.0;
@@ -123,22 +124,32 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
     const int tail = (int)(d.N - ((n_oct - 1) << 3));
     // does the last octet end its code word and (sign mode) its sign word?
     const bool ends = tail != 8 || (BITS == 2 && (n_oct & 1) != 0) || (MODE == kModeSign && (n_oct & 3) != 0);
-    auto clamp = [&](int64_t o) { return o < n_oct ? o : n_oct - 1; };
-    RawOctet<BF16, BITS> cur = load_octet_always<BF16, BITS>(d, grads, codes, scales, clamp((int64_t)it.a * 64 + lane));
+    // An octet of the item is a 32-bit distance from its first one, and an address a scalar base and such a distance (in 64 bits per
+    // lane: 12 to 15 instructions more per octet).  The passes that round are bound by their vector instructions: random-k with two
+    // vectors, 1.3 G elements, 1591 -> 1460 us with this and the kept coordinates' zeros read back below; the scaled sign, 210 M
+    // elements of 2-bit codes, 227 -> 218 us for both passes with this, the signs of an octet at once, and p formed beside g + e only
+    // where beta is not 0.
+    const int64_t o_first = (int64_t)it.a * 64;             // (whole blocks)
+    const uint32_t n_rel = (uint32_t)((n_oct - o_first < (int64_t)it.b * 64) ? n_oct - o_first : (int64_t)it.b * 64);
+    const FlatOctets<BF16, BITS> base = flat_octets<BF16, BITS>(d, grads, codes, scales, o_first);
+    const FlatCodes<BITS> base2 = TWO ? flat_codes<BITS>(d, codes2, scales2, o_first) : base.c;
+    auto clamp = [&](uint32_t o) { return o < n_rel ? o : n_rel - 1; };
+    RawOctet<BF16, BITS> cur = load_octet_rel<BF16, BITS>(base, d.lb_shift, clamp(lane));
     RawCodes<BITS> cur2 = {0u, 0u, 0.0f};
-    if (TWO) cur2 = load_codes_always<BITS>(d, codes2, scales2, clamp((int64_t)it.a * 64 + lane));
+    if (TWO) cur2 = load_codes_rel<BITS>(base2, d.lb_shift, clamp(lane));
     // TAIL: the run that holds the last octet of a matrix that ends inside that octet or inside its word
     auto run = [&](int rr, auto tail_tag) {
         constexpr bool TAIL = decltype(tail_tag)::value;
-        const int64_t o_raw = ((int64_t)it.a + rr) * 64 + lane;
-        const bool valid = o_raw < n_oct;
-        const int64_t o = clamp(o_raw);
+        const uint32_t rel_raw = (uint32_t)(rr * 64 + lane);
+        const bool valid = rel_raw < n_rel;
+        const uint32_t rel = clamp(rel_raw);
+        const int64_t o = o_first + rel;
         RawOctet<BF16, BITS> r = cur;
         RawCodes<BITS> r2 = cur2;
-        const bool cut = TAIL && o == n_oct - 1;
+        const bool cut = TAIL && rel == n_rel - 1;
         // the next run is requested before this one is worked on (the last one re-reads itself)
-        cur = load_octet_always<BF16, BITS>(d, grads, codes, scales, clamp(o_raw + (rr + 1 < it.b ? 64 : 0)));
-        if (TWO) cur2 = load_codes_always<BITS>(d, codes2, scales2, clamp(o_raw + (rr + 1 < it.b ? 64 : 0)));
+        cur = load_octet_rel<BF16, BITS>(base, d.lb_shift, clamp(rel_raw + 64));
+        if (TWO) cur2 = load_codes_rel<BITS>(base2, d.lb_shift, clamp(rel_raw + 64));
         float g[8];
         if (BF16) {
             const uint32_t w[4] = {r.g0.x, r.g0.y, r.g0.z, r.g0.w};
@@ -195,18 +206,32 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
         uint32_t neg_bits = 0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            float ge = __builtin_fmaf(dstep, qf[e], g[e]);
-            float pv = TWO ? ge : __builtin_fmaf(dpart, qf[e], g[e]);     // p = g + (1 - beta) e
-            if (TWO) pv = ge = __builtin_fmaf(dstep2, qf2[e], ge);
-            if (MODE == kModeNorm) {
-                l1 += valid ? (double)fabsf(pv) : 0.0;
-                x[e] = 0.0f;
-            } else if (MODE == kModeSign) {
-                const bool neg = (__float_as_uint(pv) >> 31) != 0;
-                neg_bits |= (neg ? 1u : 0u) << e;
-                x[e] = ge - (neg ? -c : c);
+            x[e] = __builtin_fmaf(dstep, qf[e], g[e]);
+            if (TWO) x[e] = __builtin_fmaf(dstep2, qf2[e], x[e]);
+        }
+        if (MODE == kModeNorm || MODE == kModeSign) {
+            // |p| and its sign, p = g + (1 - beta) e: x itself where beta is 0 (the empty statement keeps the compiler from forming
+            // both)
+            float v[8];
+            auto take = [&](int e, float pv) { v[e] = MODE == kModeNorm ? fabsf(pv) : __builtin_copysignf(c, pv); };
+            if (TWO || dp.omb == 1.0f) {                            // uniform
+#pragma unroll
+                for (int e = 0; e < 8; ++e) take(e, x[e]);
             } else {
-                x[e] = ge;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    float pv = __builtin_fmaf(dpart, qf[e], g[e]);
+                    asm volatile("" : "+v"(pv));
+                    take(e, pv);
+                }
+            }
+            if (MODE == kModeNorm) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) l1 += (double)(valid ? v[e] : 0.0f);
+            } else {
+                neg_bits = octet_signs(v);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] = x[e] - v[e];
             }
         }
         if (MODE == kModeNorm) return;
@@ -228,21 +253,22 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
         // ... then the kept coordinates: Delta = p there, and beta e (plain) or nothing (two vectors) is left
         if (MODE == kModeStrata) {
             // The run's values of p go through LDS, and the lanes take the run's strata: each looks up its stratum's coordinate,
-            // passes the value on and marks it in its octet's word.  (An octet looking for its strata's coordinates evaluated
+            // passes the value on and, where nothing stays behind (two vectors, version 2), leaves zero for the octet to read back,
+            // else marks it in the octet's word.  (An octet looking for its strata's coordinates evaluated
             // two Philox calls and a branch per element: half of the pass.)
             // Strata of 8 or more: the coordinates are drawn a window at a time, 64 calls, one per lane, all four words of
             // each: 256 strata, that is four runs of the shortest.  (A call per lane and run used one word of its four: two vectors,
             // 1.3 G elements in strata of ten 1702 us, so 1591.)  Of shorter ones a run has more than a window would serve: a lane takes
             // the four of a call.
             float *sp = s_val[threadIdx.x >> 6];
-            uint32_t *sk = s_kept[threadIdx.x >> 6];
+            uint32_t *sk = s_kept[BACK ? 0 : threadIdx.x >> 6];
             uint32_t *su = s_pos[threadIdx.x >> 6];
             float p[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) p[e] = (TWO || V2) ? x[e] : __builtin_fmaf(dpart, qf[e], g[e]);
             reinterpret_cast<float4 *>(sp + lane * 8)[0] = make_float4(p[0], p[1], p[2], p[3]);
             reinterpret_cast<float4 *>(sp + lane * 8)[1] = make_float4(p[4], p[5], p[6], p[7]);
-            sk[lane] = 0;
+            if (!BACK) sk[lane] = 0;
             const uint32_t N = (uint32_t)d.N, j0 = (uint32_t)(((int64_t)it.a + rr) << 9);
             const uint32_t s0 = stratum_of(j0, d.rk_g, d.rk_magic), s1 = stratum_of(N - 1u - j0 < 511u ? N - 1u : j0 + 511u, d.rk_g, d.rk_magic);
             uint32_t out[4];
@@ -255,7 +281,8 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                 const uint32_t rel = pos - j0;                                // wraps to a large value before the run
                 if (rel < 512u) {
                     delta[d.rk_delta_off + s] = sp[rel];
-                    __hip_atomic_fetch_or(sk + (rel >> 3), 1u << (rel & 7u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (BACK) sp[rel] = 0.0f;
+                    else __hip_atomic_fetch_or(sk + (rel >> 3), 1u << (rel & 7u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
             };
             if (d.rk_g >= 8) {
@@ -278,14 +305,22 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
                 }
             }
             wave_memory_sync();
-            // (an octet beyond the end is marked nowhere: it must not bring the last octet's kept coordinates to the maximum)
-            const uint32_t left = valid ? ~sk[lane] : 0u;
-            const float back = valid ? dp.beta : 0.0f;
+            // (an octet beyond the end must not bring the last octet's coordinates to the maximum)
+            if (BACK) {
+                const float4 lo = reinterpret_cast<const float4 *>(sp + lane * 8)[0], hi = reinterpret_cast<const float4 *>(sp + lane * 8)[1];
+                x[0] = lo.x; x[1] = lo.y; x[2] = lo.z; x[3] = lo.w; x[4] = hi.x; x[5] = hi.y; x[6] = hi.z; x[7] = hi.w;
+                if ((uint32_t)(rr * 64 + 64) > n_rel) {             // uniform
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint32_t keep = (uint32_t)((int32_t)(left << (31 - e)) >> 31);        // all ones where nothing was taken
-                if (TWO || V2) x[e] = __uint_as_float(__float_as_uint(x[e]) & keep);
-                else x[e] = keep ? x[e] : back * (dstep * qf[e]);
+                    for (int e = 0; e < 8; ++e) x[e] = valid ? x[e] : 0.0f;
+                }
+            } else {
+                const uint32_t left = valid ? ~sk[lane] : 0u;
+                const float back = valid ? dp.beta : 0.0f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const bool keep = (left >> e) & 1u;             // nothing was taken
+                    x[e] = keep ? x[e] : back * (dstep * qf[e]);
+                }
             }
             wave_memory_sync();                // the next run's values may not overtake these reads
         } else if (SPARSE && kbits != 0) {
@@ -318,10 +353,10 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
             }
         }
         if (MODE == kModeSign && valid) {
-            uint8_t *sb = reinterpret_cast<uint8_t *>(sign_words + d.sign_off);
-            sb[o] = (uint8_t)neg_bits;
-            if (TAIL && o == n_oct - 1)
-                for (int64_t b = o + 1; (b & 3) != 0; ++b) sb[b] = 0;          // the rest of the last word
+            uint8_t *sb = reinterpret_cast<uint8_t *>(sign_words + d.sign_off) + o_first;
+            sb[rel] = (uint8_t)neg_bits;
+            if (TAIL && cut)
+                for (uint32_t b = rel + 1; (b & 3) != 0; ++b) sb[b] = 0;       // the rest of the last word (o_first is a whole one)
         }
         const float a = block_max(abs_max_octet(0.0f, x), d.lb_shift);
         const float inv16 = levels_over(a, s_f);
@@ -331,8 +366,8 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
         quantise_octet<BITS>(x, inv16, rnd, w, t);
         if (valid) {
             if (cut) store_code_words_end<BITS>(d, codes, o, tail, w);
-            else store_code_words<BITS>(d, codes, o, w);
-            if ((lane & ((1 << d.lb_shift) - 1)) == 0) scales[d.scale_off + (o >> d.lb_shift)] = a;
+            else store_codes_rel<BITS>(base.c, rel, w);
+            if ((lane & ((1 << d.lb_shift) - 1)) == 0) store_scale_rel(base.c, rel >> d.lb_shift, a);
         }
         if (TWO) {
             // q+ = C(x - e~+): what the first rounding left, one level finer
@@ -347,8 +382,8 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
             quantise_octet<BITS>(x, inv16_2, rnd, w);
             if (valid) {
                 if (cut) store_code_words_end<BITS>(d, codes2, o, tail, w);
-                else store_code_words<BITS>(d, codes2, o, w);
-                if ((lane & ((1 << d.lb_shift) - 1)) == 0) scales2[d.scale_off + (o >> d.lb_shift)] = a2;
+                else store_codes_rel<BITS>(base2, rel, w);
+                if ((lane & ((1 << d.lb_shift) - 1)) == 0) store_scale_rel(base2, rel >> d.lb_shift, a2);
             }
         }
     };

@@ -71,6 +71,73 @@ __device__ __forceinline__ RawCodes<BITS> load_codes_always(const MatDesc &d, co
     return r;
 }
 
+// The same by a 32-bit distance `rel` from an octet that starts a scale block and a code word: the addresses are scalar bases and
+// 32-bit lane offsets, which the load instructions add.
+template <int BITS>
+struct FlatCodes {
+    uint8_t *codes, *scales;
+};
+
+template <bool BF16, int BITS>
+struct FlatOctets {
+    const uint8_t *grads;
+    FlatCodes<BITS> c;
+};
+
+template <int BITS>
+__device__ __forceinline__ FlatCodes<BITS> flat_codes(const MatDesc &d, uint32_t *codes, float *scales, int64_t o)
+{
+    return {reinterpret_cast<uint8_t *>(codes + d.word_off) + o * BITS, reinterpret_cast<uint8_t *>(scales + d.scale_off + (o >> d.lb_shift))};
+}
+
+template <bool BF16, int BITS>
+__device__ __forceinline__ FlatOctets<BF16, BITS> flat_octets(const MatDesc &d, const void *grads, uint32_t *codes, float *scales, int64_t o)
+{
+    return {reinterpret_cast<const uint8_t *>(grads) + (d.grad_off + o * 8) * (BF16 ? 2 : 4), flat_codes<BITS>(d, codes, scales, o)};
+}
+
+template <int BITS>
+__device__ __forceinline__ RawCodes<BITS> load_codes_rel(const FlatCodes<BITS> &b, int lb_shift, uint32_t rel)
+{
+    RawCodes<BITS> r;
+    r.c1 = 0;
+    if (BITS == 8) {
+        const uint2 c = *reinterpret_cast<const uint2 *>(b.codes + rel * 8);
+        r.c0 = c.x; r.c1 = c.y;
+    } else if (BITS == 4) {
+        r.c0 = *reinterpret_cast<const uint32_t *>(b.codes + rel * 4);
+    } else {
+        r.c0 = *reinterpret_cast<const uint16_t *>(b.codes + rel * 2);
+    }
+    r.scale = *reinterpret_cast<const float *>(b.scales + (rel >> lb_shift) * 4);
+    return r;
+}
+
+template <bool BF16, int BITS>
+__device__ __forceinline__ RawOctet<BF16, BITS> load_octet_rel(const FlatOctets<BF16, BITS> &b, int lb_shift, uint32_t rel)
+{
+    RawOctet<BF16, BITS> r;
+    r.g0 = *reinterpret_cast<const uint4 *>(b.grads + rel * (BF16 ? 16 : 32));
+    r.g1 = BF16 ? make_uint4(0, 0, 0, 0) : *reinterpret_cast<const uint4 *>(b.grads + rel * (BF16 ? 16 : 32) + 16);
+    const RawCodes<BITS> c = load_codes_rel<BITS>(b.c, lb_shift, rel);
+    r.c0 = c.c0; r.c1 = c.c1; r.scale = c.scale;
+    return r;
+}
+
+template <int BITS>
+__device__ __forceinline__ void store_codes_rel(const FlatCodes<BITS> &b, uint32_t rel, const uint32_t w[2])
+{
+    if (BITS == 8) *reinterpret_cast<uint2 *>(b.codes + rel * 8) = make_uint2(w[0], w[1]);
+    else if (BITS == 4) *reinterpret_cast<uint32_t *>(b.codes + rel * 4) = w[0];
+    else *reinterpret_cast<uint16_t *>(b.codes + rel * 2) = (uint16_t)w[0];
+}
+
+template <int BITS>
+__device__ __forceinline__ void store_scale_rel(const FlatCodes<BITS> &b, uint32_t blk, float a)
+{
+    *reinterpret_cast<float *>(b.scales + blk * 4) = a;
+}
+
 // p <- p + second vector (the outer fused multiply-add of Algorithm 3's accumulation)
 template <int BITS>
 __device__ __forceinline__ void add_codes(const RawCodes<BITS> &r, float p[8])
