@@ -71,6 +71,7 @@ int ensure_uploaded(conef_ctx *ctx)
     if ((rc = upload(ctx, pl.err_items, &d.err_items))) return rc;
     if ((rc = upload(ctx, pl.err_s_items, &d.err_s_items))) return rc;
     if ((rc = upload(ctx, pl.err_g_items, &d.err_g_items))) return rc;
+    if ((rc = upload(ctx, pl.err_w_items, &d.err_w_items))) return rc;
     if ((rc = upload(ctx, pl.q_flat_items, &d.q_flat_items))) return rc;
     if ((rc = upload(ctx, pl.upd_items, &d.upd_items))) return rc;
     if ((rc = upload(ctx, pl.p_f_items, &d.p_f_items))) return rc;
@@ -129,6 +130,8 @@ int ensure_uploaded(conef_ctx *ctx)
     d.n_err = (int)pl.err_items.size();
     d.n_err_s = (int)pl.err_s_items.size();
     d.n_err_g = (int)pl.err_g_items.size();
+    d.n_err_w = (int)pl.err_w_items.size();
+    d.ew_lds = pl.ew_lds;
     d.n_q_flat = (int)pl.q_flat_items.size();
     d.es_lds = pl.es_lds; d.wshift = pl.wshift; d.lb_shift = pl.lb_shift; d.inv_s = pl.inv_s; d.bmagic = pl.bmagic;
     d.block_shift = pl.block_shift;

@@ -45,6 +45,8 @@ struct DevicePlan {
     int rank = 0, rpad = 0, bits = 0, block = 0, dtype = 0;
     int n_q_flat = 0, n_err_g = 0;
     int most_p_chunks = 1;          // column chunks of P of the matrix that has the most
+    const WorkItem *err_w_items = nullptr;      // strip err pass with Q+ in LDS
+    int n_err_w = 0, ew_lds = 0;    // its items, floats of LDS per workgroup
     int n_err_s = 0, es_lds = 0;    // strip err pass: items, floats of LDS per workgroup
     int wshift = 0, lb_shift = 0;   // log2(code fields per word), log2(block / 8)
     int block_shift = -1;           // log2(block), -1 if it is not a power of two
@@ -176,6 +178,9 @@ void strip_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, fl
                     uint64_t step, hipStream_t st);
 void strip_pass_err_two(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, uint32_t *codes2, float *scales2,
                         const float *Phat, const float *Qn, uint64_t step, hipStream_t st);
+// err pass with Q+ in LDS (kernels_walk.hip); codes2 / scales2: the second error vector (codes / scales the first), or null
+void walk_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, uint32_t *codes2, float *scales2,
+                   const float *Phat, const float *Qn, uint64_t step, hipStream_t st);
 // the same for the matrices that the plan takes on octets (kernels_ragged.hip)
 void ragged_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Q, float *P,
                    double *ws, hipStream_t st);
@@ -189,7 +194,8 @@ void generic_q_reduce(const DevicePlan &dp, double *ws, float *Qout, hipStream_t
 void generic_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, const float *Phat,
                       const float *Qn, uint64_t step, hipStream_t st);
 // The octet family's and the strip family's workgroups in one launch (kernels_mixed.hip), where that is the faster way:
-// false if it is not, and then nothing has been enqueued.  The err pass takes the plan's err_t_items and err_s_items.
+// false if it is not, and then nothing has been enqueued.  The err pass takes the plan's err_t_items and err_w_items, or
+// err_s_items where it has none of those.
 bool mixed_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Q, float *P,
                   double *ws, hipStream_t st);
 bool mixed_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales, const float *Phat, double *ws,

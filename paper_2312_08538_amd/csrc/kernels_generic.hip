@@ -533,6 +533,7 @@ hipError_t launch_pass_err_two(const DevicePlan &dp, const void *grads, uint32_t
     if (span.begin) (void)hipEventRecord(span.begin, st);
     mfma_pass_err_two(dp, grads, codes, scales, codes2, scales2, Phat, ws, step, st);
     octet_pass_err_two(dp, grads, codes, scales, codes2, scales2, Phat, Qn, step, st);
+    walk_pass_err(dp, grads, codes, scales, codes2, scales2, Phat, Qn, step, st);
     strip_pass_err_two(dp, grads, codes, scales, codes2, scales2, Phat, Qn, step, st);
     if (dp.n_err > 0) {
         const uint32_t lo = (uint32_t)step, hi = (uint32_t)(step >> 32);
@@ -600,8 +601,13 @@ hipError_t launch_pass_err(const DevicePlan &dp, const void *grads, uint32_t *co
     if (span.begin) (void)hipEventRecord(span.begin, st);
     mfma_pass_err(dp, grads, codes, scales, Phat, ws, step, st);
     DevicePlan rest = dp;
-    if (mixed_pass_err(dp, grads, codes, scales, Phat, Qn, step, st)) rest.n_err_t = rest.n_err_s = 0;
+    if (mixed_pass_err(dp, grads, codes, scales, Phat, Qn, step, st)) {
+        rest.n_err_t = 0;
+        if (dp.n_err_w > 0) rest.n_err_w = 0;
+        else rest.n_err_s = 0;
+    }
     octet_pass_err(rest, grads, codes, scales, Phat, Qn, step, st);
+    walk_pass_err(rest, grads, codes, scales, nullptr, nullptr, Phat, Qn, step, st);
     strip_pass_err(rest, grads, codes, scales, Phat, Qn, step, st);
     generic_pass_err(dp, grads, codes, scales, Phat, Qn, step, st);
     if (span.end) (void)hipEventRecord(span.end, st);

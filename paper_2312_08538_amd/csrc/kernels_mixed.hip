@@ -16,6 +16,7 @@
 #include "octet_device.h"
 #include "ragged_device.h"
 #include "strip_device.h"
+#include "walk_device.h"
 
 namespace conef {
 
@@ -52,7 +53,8 @@ void k_q_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const ui
     }
 }
 
-template <bool BF16, int BITS, int R, bool WIDE>
+// WALK: the strip family's workgroups are those with Q+ in LDS
+template <bool BF16, int BITS, int R, bool WIDE, bool WALK>
 __global__ __launch_bounds__(256, 2) void k_err_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, uint32_t *codes,
                                                       float *scales, const float *__restrict__ Phat, const float *__restrict__ Qn,
                                                       uint32_t step_lo, uint32_t step_hi)
@@ -61,7 +63,9 @@ __global__ __launch_bounds__(256, 2) void k_err_mixed(DevicePlan dp, int lead, c
     const int b = blockIdx.x;
     if (b >= lead)
         err_tile<BF16, BITS, R, WIDE, false>(dp, b - lead, lds, grads, codes, scales, Phat, Qn, step_lo, step_hi, nullptr, nullptr);
-    else if (b < dp.n_err_s)
+    else if (WALK && b < dp.n_err_w)
+        err_walk<BF16, BITS, R, false>(dp, b, lds, grads, codes, scales, nullptr, nullptr, Phat, Qn, step_lo, step_hi);
+    else if (!WALK && b < dp.n_err_s)
         err_strip<R, true, false, false>(dp, b, lds, grads, codes, scales, nullptr, nullptr, Phat, Qn, step_lo, step_hi);
 }
 
@@ -120,8 +124,10 @@ bool mixed_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes
 bool mixed_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, const float *Phat, const float *Qn,
                     uint64_t step, hipStream_t st)
 {
-    if (dp.n_err_s <= 0 || dp.n_err_t <= 0 || dp.i_codes || dp.n_err_s > kMixedStrips || dp.es_lds > kMixedLds) return false;
-    const int lead = lead_of(dp.n_err_s);
+    const bool walk = dp.n_err_w > 0;
+    const int n_strip = walk ? dp.n_err_w : dp.n_err_s, strip_lds = walk ? dp.ew_lds : dp.es_lds;
+    if (n_strip <= 0 || dp.n_err_t <= 0 || dp.i_codes || n_strip > kMixedStrips || strip_lds > kMixedLds) return false;
+    const int lead = lead_of(n_strip);
     const uint32_t lo = (uint32_t)step, hi = (uint32_t)(step >> 32);
     by_type(dp, [&](auto bf, auto bits) {
         constexpr bool BF = decltype(bf)::value;
@@ -130,8 +136,9 @@ bool mixed_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, fl
         auto go = [&](auto rank, auto wide) {
             constexpr int R = decltype(rank)::value;
             constexpr bool W = decltype(wide)::value;
-            const size_t lds = 4 * (size_t)larger(dp.es_lds, err_tile_lds<R, W>());
-            hipLaunchKernelGGL((k_err_mixed<BF, B, R, W>), grid, block, lds, st, dp, lead, grads, codes, scales, Phat, Qn, lo, hi);
+            const size_t lds = 4 * (size_t)larger(strip_lds, err_tile_lds<R, W>());
+            if (walk) hipLaunchKernelGGL((k_err_mixed<BF, B, R, W, true>), grid, block, lds, st, dp, lead, grads, codes, scales, Phat, Qn, lo, hi);
+            else hipLaunchKernelGGL((k_err_mixed<BF, B, R, W, false>), grid, block, lds, st, dp, lead, grads, codes, scales, Phat, Qn, lo, hi);
         };
         auto width = [&](auto rank) {
             if (dp.block == 256) go(rank, std::true_type{});

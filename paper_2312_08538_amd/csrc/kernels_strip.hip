@@ -14,13 +14,12 @@
 //             wave order.  Products of fp32 values are exact in fp64, the sum stays in fp64, one rounding.
 //   Q+ pass   a workgroup per (strip, row tile), a quarter of the rows per wave; a lane adds up its column's r sums in
 //             fp64 registers, the row of P^ being a scalar operand.  Matrices of a few rows: a strip per wave (k_q_flat).
-//   err pass  a workgroup per run of whole scale blocks: p is loaded and decoded in octets and goes to LDS in the order of
+//   err pass  (ranks above 8 and matrices too wide for their Q+ to stand in LDS; the others: kernels_walk.hip)  a workgroup per run
+//             of whole scale blocks: p is loaded and decoded in octets and goes to LDS in the order of
 //             the flat index; there the reconstruction (the fp32 fma chain over c = 0..r-1, a lane's row of Q+ in registers,
 //             the row of P^ on the scalar side) is subtracted a row of a strip at a time; then the workgroup walks the run in
 //             octets as the octet family does: block max-norm by DPP, one Philox call per eight elements, rounding, pack, in
-//             place.  Matrices of a few columns: groups of rows that fill a wave.  28.4 M elements in matrices of 650 columns,
-//             rank 4: 46 us (76 with a load of gradient, code word and scale, and a decode, per element).  What is left is
-//             issue: 34 vector and 32 scalar instructions per 64 elements (65 and 65 then).
+//             place.  Matrices of a few columns: groups of rows that fill a wave.
 //
 // All sums are combined in a fixed order: results do not depend on scheduling.
 #include <type_traits>

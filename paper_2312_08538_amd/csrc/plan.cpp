@@ -576,15 +576,31 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         }
         // The strip err pass: runs of the flat index of strip_err elements where that is at least eight rows (a wave's row of
         // Q+ per lane serves all rows of a run), else eight rows of a column segment.
-        // Matrices of up to 32 columns are walked in groups of rows, by a launch of their own.  With 16 columns or more they do
-        // not pay for one beside other matrices (64 x 27 in a small convolutional network: 10 - 17 us for the pass without
-        // groups, 15 - 21 with; the launches of 600 x 27 alone 9.0 and 7.7).
+        // With Q+ in LDS: all of them or none, since two launches cost more than the others gain (400 x 650 beside 100 x 5000 29.7 us
+        // a step on strips, 34.1 in two launches, 16000 x 650 beside 2000 x 5000 94.5 and 97); matrices of less than eight columns,
+        // which have a launch of their own, aside.  About 2048 workgroups, eight per CU (512 - 4096 of them are within 6 %).
+        auto walks = [&](const MatDesc &d) { return rank <= 8 && d.path == kPathGeneric && d.m >= 8 && walk_lds(d.m, rank) <= kWalkLds; };
+        int64_t walk_elems = 0, thin_elems = 0;
+        for (const MatDesc &d : plan.mats) {
+            walk_elems += walks(d) ? d.N : 0;
+            thin_elems += rank <= 8 && d.path == kPathGeneric && d.m < 8 ? d.N : 0;
+        }
+        const bool walk = walk_elems + thin_elems == strip_elems;
+        const int64_t walk_runs = std::min<int64_t>(64, 4 * std::max<int64_t>(1, ceil_div(walk_elems / 512, 4 * 2048)));
+        // Matrices of up to 32 columns that are not among those (less than eight columns, ranks above 8) are walked in groups of rows,
+        // by a launch of their own.  With 16 columns or more they do not pay for one beside other matrices (64 x 27 in a small
+        // convolutional network: 10 - 17 us for the pass without groups, 15 - 21 with; the launches of 600 x 27 alone 9.0 and 7.7).
         bool all_narrow = true;
         for (const MatDesc &d : plan.mats) all_narrow = all_narrow && d.m <= 32;
         for (int l = 0; l < n_mats && !sketch && octet_blocks; ++l) {
             MatDesc &d = plan.mats[l];
             if (d.path != kPathGeneric) continue;
             d.es_rows = 1;
+            if (walk && walks(d)) {
+                d.es_walk = 1;
+                plan.ew_lds = std::max(plan.ew_lds, (int)walk_lds(d.m, rank));
+                continue;
+            }
             if (d.m <= 1024) {
                 if (d.m < 16 || (all_narrow && d.m <= 32)) d.es_rows = (int32_t)(64 / d.m);
                 int64_t tile = strip_err;
@@ -680,6 +696,11 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                         for (int32_t ct = 0; ct < nct; ++ct) (q_on_octets(d) ? plan.q_r_items : plan.q_items).push_back({l, ct, rt, 0});
                 if (!mf_p && d.n_p_chunks > 1)
                     for (int64_t e0 = 0; e0 < d.n * rank; e0 += 256) plan.pred_items.push_back({l, (int32_t)e0, 0, 0});
+                if (!mf_e && !sketch && d.es_walk) {
+                    const int64_t runs = ceil_div(d.N, 512);
+                    for (int64_t r0 = 0; r0 < runs; r0 += walk_runs)
+                        plan.err_w_items.push_back({l, (int32_t)r0, (int32_t)std::min<int64_t>(walk_runs, runs - r0), (int32_t)(r0 * 512 / d.m)});
+                }
                 if (!mf_e && !sketch && d.es_tile > 0)
                     for (int64_t t = 0; t * d.es_tile < d.N; ++t) {
                         const int64_t row = d.m * d.es_rows;
@@ -693,7 +714,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                             plan.err_s_items.push_back({l, (int32_t)r0, sg, (int32_t)std::min<int64_t>(erow, d.n - r0)});
                 // 4 waves per workgroup, each wave takes blocks b0+wave, b0+wave+4, ...: 16 per wave, or
                 // one per wave for small matrices (a: first block, b: blocks per wave)
-                if (!mf_e && !sketch && d.es_tile == 0 && d.es_seg == 0) {
+                if (!mf_e && !sketch && d.es_tile == 0 && d.es_seg == 0 && !d.es_walk) {
                     const int32_t per_wave = d.nblk <= 16384 ? 1 : 16;
                     for (int64_t b0 = 0; b0 < d.nblk; b0 += 4 * per_wave)
                         plan.err_items.push_back({l, (int32_t)b0, per_wave, 0});
@@ -1053,6 +1074,11 @@ bool check_plan(const Plan &plan)
                     return false;
                 c.add_elems(plan, it, j0, d.es_tile);
             }
+        }
+        for (const WorkItem &it : plan.err_w_items) {
+            const MatDesc &d = plan.mats[it.mat];
+            if (!d.es_walk || it.b < 1 || it.b > 64 || it.c != (int64_t)it.a * 512 / d.m || walk_lds(d.m, plan.rank) > plan.ew_lds) return false;
+            c.add_elems(plan, it, (int64_t)it.a * 512, (int64_t)it.b * 512);
         }
         for (const WorkItem &it : plan.err_g_items) {
             const MatDesc &d = plan.mats[it.mat];

@@ -53,6 +53,13 @@ constexpr bool ragged_q_pays(int rank, int64_t n, int64_t total)
     if (rank == 32) return n <= 128 ? total > M / 4 && total < (n <= 64 ? 1 : 8) * M : n > 4096 || total >= M;
     return true;
 }
+// Strip err pass of matrices whose Q+ fits into LDS (kernels_walk.hip): ranks up to 8, eight columns or more, 48 KB, three
+// workgroups per CU.  us a step, bf16 and fp32, the err pass on strips / with Q+ in LDS: rank 4 250 x 3300 (60 KB) 28.8 / 28.2, 250 x 4500
+// (81 KB) 31.4 / 34.9, 1000 x 6001 50.9 / 73; rank 8 1000 x 1300 (48 KB) 35.7 / 32.6, 1000 x 1700 37.2 / 37.9; rank 2 250 x 5001 (50 KB)
+// 30.7 / 30.4, 250 x 8001 32.4 / 38.3.
+constexpr int kWalkLds = 12288;     // floats
+constexpr int walk_rank(int rank) { return rank <= 2 ? rank : rank <= 4 ? 4 : 8; }
+constexpr int64_t walk_lds(int64_t m, int rank) { return (m + 8) * walk_rank(rank) + (m + 15) / 8 * 4; }
 constexpr int kFlatRows = 8;        // matrices of at most so many rows: a wave of the strip Q+ pass takes all of them
 // The step in one launch, a workgroup per matrix (kernels_small.hip): matrices whose p = g + e and factors fit into the LDS of a
 // CU, rows of whole octets, blocks of 8 * 2^j elements, ranks up to 8, no matrix of the packed-split family (whose stages add up in
@@ -114,6 +121,7 @@ struct MatDesc {
     // columns, es_over columns past it that the segment's last blocks may reach, es_pitch floats of LDS per row;
     // es_rows: rows of a narrow matrix that a wave takes as one (64 / columns), else 1
     int32_t es_tile, es_seg, es_over, es_pitch, es_rows;
+    int32_t es_walk;                // 1: the err pass walks octets with Q+ in LDS (err_w_items), the others are not set
     // octet family: a lane owns 8 consecutive elements of a row; lr lanes share a row
     int32_t lr_shift;               // log2(lanes per row segment), 3..6
     int32_t lb_shift;               // log2(lanes per scale block) = log2(block/8)
@@ -202,6 +210,8 @@ struct Plan {
     std::vector<WorkItem> q_flat_items; // pass 2, few rows: (mat, four strips)
     std::vector<WorkItem> err_s_items;  // pass 3: (mat, tile, its first row, rows it spans), or with segments (mat, first row, segment, rows)
     std::vector<WorkItem> err_g_items;  // pass 3, es_rows > 1: (mat, tile, its first group of rows, groups it spans)
+    std::vector<WorkItem> err_w_items;  // pass 3, Q+ in LDS: (mat, first run of 512 elements, runs, its first row)
+    int ew_lds = 0;                     // floats of LDS of that pass
     std::vector<WorkItem> err_items;    // pass 3, blocks that are not 8 * 2^j elements (j <= 6): (mat, first block, blocks per wave)
     int es_lds = 0;                     // floats of LDS of the strip err pass
     int wshift = 0, lb_shift = 0;       // log2(code fields per word); log2(block / 8) for power-of-two blocks of 8 elements or more
