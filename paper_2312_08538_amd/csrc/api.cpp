@@ -89,6 +89,7 @@ int ensure_uploaded(conef_ctx *ctx)
     if ((rc = upload(ctx, pl.gram_items, &d.gram_items))) return rc;
     if ((rc = upload(ctx, pl.apply_items, &d.apply_items))) return rc;
     if ((rc = upload(ctx, pl.gram_s_items, &d.gram_s_items))) return rc;
+    if ((rc = upload(ctx, pl.orth_first, &d.orth_first))) return rc;
     if ((rc = upload(ctx, pl.apply_s_items, &d.apply_s_items))) return rc;
     if ((rc = upload(ctx, pl.qred_items, &d.qred_items))) return rc;
     if ((rc = upload(ctx, pl.elem_items, &d.elem_items))) return rc;
@@ -140,6 +141,7 @@ int ensure_uploaded(conef_ctx *ctx)
     d.small_lds = (size_t)pl.small_lds;
     d.n_p_f = (int)pl.p_f_items.size();
     d.n_q_f = (int)pl.q_f_items.size();
+    d.q_joined = pl.q_joined ? 1 : 0;
     d.n_err_f = (int)pl.err_f_items.size();
     d.n_err_t = (int)pl.err_t_items.size();
     d.n_p_m = (int)pl.p_m_items.size();

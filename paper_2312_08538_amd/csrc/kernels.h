@@ -36,6 +36,7 @@ struct DevicePlan {
                    *elem_items = nullptr;
     const OrthItem *gram_s_items = nullptr, *apply_s_items = nullptr;      // orthonormalisation, ranks up to 8
     int n_gram_s = 0, n_apply_s = 0;
+    const int32_t *orth_first = nullptr;        // both in one launch: each matrix's first gram_s_items entry; null: two launches
     int n_mats = 0;
     int n_p = 0, n_q = 0, n_err = 0, n_p_f = 0, n_q_f = 0, n_err_f = 0, n_err_t = 0;
     int n_p_m = 0, n_q_m = 0, n_err_m = 0, n_split_p = 0, n_split_qn = 0;
@@ -54,6 +55,7 @@ struct DevicePlan {
     uint64_t bmagic = 0;            // j / block = mulhi64(j, bmagic) for j < 2^35
     uint32_t seed_lo = 0, seed_hi = 0;
     long long q_elems = 0;
+    int q_joined = 0;               // octet Q+ pass: a workgroup per strip, its waves the row tiles, Q+ straight from there
     // Improved contractive error feedback around the rank-r compressor: the FIRST error vector, laid out like the
     // codes / scales arguments of the pass kernels (which then hold the second one): p = g + first + second.  Null in
     // every other call; set in a copy of the plan by the launchers of the two-vector passes.
@@ -77,6 +79,9 @@ struct SmallPlan {
     float omb;
     uint32_t seed_lo, seed_hi;
 };
+
+// workgroups of the octet Q+ pass
+inline int q_octet_groups(const DevicePlan &dp) { return dp.q_joined ? dp.n_q_f : (dp.n_q_f + 3) / 4; }
 
 inline DevicePlan octet_items(DevicePlan dp)
 {
@@ -205,7 +210,7 @@ bool mixed_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, fl
 void octet_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
                   const float *Q, float *P, double *ws, hipStream_t st);
 void octet_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
-                  const float *Phat, double *ws, hipStream_t st);
+                  const float *Phat, double *ws, float *Qout, hipStream_t st);
 void octet_pass_err(const DevicePlan &dp, const void *grads, uint32_t *codes, float *scales, const float *Phat,
                     const float *Qn, uint64_t step, hipStream_t st);
 

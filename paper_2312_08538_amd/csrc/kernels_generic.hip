@@ -578,7 +578,7 @@ hipError_t launch_pass_q(const DevicePlan &dp, const void *grads, const uint32_t
     mfma_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
     pack_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
     if (!mixed_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st)) {
-        octet_pass_q(dp, grads, codes, scales, Phat, ws, st);
+        octet_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
         ragged_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);
     }
     strip_pass_q(dp, grads, codes, scales, Phat, ws, Qout, st);

@@ -47,7 +47,7 @@ void k_q_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const ui
     __shared__ __attribute__((aligned(16))) float lds[larger(kQOctetLds, kRagLds)];
     const int b = blockIdx.x;
     if (b >= lead) {
-        q_octet<BF16, BITS, (R > 4 ? 2 : 1), false>(dp, b - lead, lds, grads, codes, scales, Phat, ws);
+        q_octet<BF16, BITS, (R > 4 ? 2 : 1), false>(dp, b - lead, lds, grads, codes, scales, Phat, ws, Qout);
     } else if (b < dp.n_q) {
         q_ragged<BF16, BITS, (R > 4 ? 2 : 1), false>(dp, b, lds, grads, codes, scales, Phat, ws, Qout);
     }
@@ -113,7 +113,7 @@ bool mixed_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes
     by_type(dp, [&](auto bf, auto bits) {
         constexpr bool BF = decltype(bf)::value;
         constexpr int B = decltype(bits)::value;
-        const dim3 grid(lead + (dp.n_q_f + 3) / 4), block(256);
+        const dim3 grid(lead + q_octet_groups(dp)), block(256);
         if (dp.rank == 8) hipLaunchKernelGGL((k_q_mixed<BF, B, 8>), grid, block, 0, st, octet_items(dp), lead, grads, codes, scales, Phat, ws, Qout);
         else if (dp.rank == 4) hipLaunchKernelGGL((k_q_mixed<BF, B, 4>), grid, block, 0, st, octet_items(dp), lead, grads, codes, scales, Phat, ws, Qout);
         else hipLaunchKernelGGL((k_q_mixed<BF, B, 2>), grid, block, 0, st, octet_items(dp), lead, grads, codes, scales, Phat, ws, Qout);

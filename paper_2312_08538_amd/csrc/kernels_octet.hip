@@ -46,10 +46,10 @@ void k_p_octet(DevicePlan dp, const void *__restrict__ grads, const uint32_t *__
 template <bool BF16, int BITS, int RH, bool TWO = false>
 __global__ __launch_bounds__(256) CONEF_Q_OCTET_WAVES(BF16, TWO)
 void k_q_octet(DevicePlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
-               const float *__restrict__ scales, const float *__restrict__ Phat, double *ws)
+               const float *__restrict__ scales, const float *__restrict__ Phat, double *ws, float *Qout)
 {
     __shared__ __attribute__((aligned(16))) float lds[kQOctetLds];
-    q_octet<BF16, BITS, RH, TWO>(dp, blockIdx.x, lds, grads, codes, scales, Phat, ws);
+    q_octet<BF16, BITS, RH, TWO>(dp, blockIdx.x, lds, grads, codes, scales, Phat, ws, Qout);
 }
 
 template <bool BF16, int BITS, int RP, bool WIDE, bool TWO>
@@ -520,11 +520,12 @@ void octet_pass_p(const DevicePlan &dp, const void *grads, const uint32_t *codes
 }
 
 void octet_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes, const float *scales,
-                  const float *Phat, double *ws, hipStream_t st)
+                  const float *Phat, double *ws, float *Qout, hipStream_t st)
 {
     if (dp.n_q_f <= 0) return;
-    if (dp.i_codes) CONEF_OCTET2T_DISPATCH(k_q_octet, dim3((dp.n_q_f + 3) / 4), st, dp, grads, codes, scales, Phat, ws);
-    else CONEF_OCTET2_DISPATCH(k_q_octet, dim3((dp.n_q_f + 3) / 4), st, dp, grads, codes, scales, Phat, ws);
+    const dim3 grid(q_octet_groups(dp));
+    if (dp.i_codes) CONEF_OCTET2T_DISPATCH(k_q_octet, grid, st, dp, grads, codes, scales, Phat, ws, Qout);
+    else CONEF_OCTET2_DISPATCH(k_q_octet, grid, st, dp, grads, codes, scales, Phat, ws, Qout);
 }
 
 // The strip kernel for the plan's err_t_items (rank 4 or 8; `first`: the first vector of Algorithm 3, or null)

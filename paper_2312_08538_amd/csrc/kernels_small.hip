@@ -32,8 +32,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_step_small(SmallPlan sp, cons
                                                               const float *Q_in, float *P_out, float *Q_out, uint32_t step_lo,
                                                               uint32_t step_hi)
 {
-    constexpr int H = RP / 4, NG = H * (H + 1) / 2, E = RP * RP;
-    constexpr int PARTS = orth_threads(RP) / E;             // of k_cholesky_apply's sum of the partial Gram matrices
+    constexpr int H = RP / 4, E = RP * RP;
     extern __shared__ __attribute__((aligned(16))) double small_lds[];
     __shared__ CholeskyLds<RP> chol;
     __shared__ double rinv[E];
@@ -147,43 +146,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_step_small(SmallPlan sp, cons
 
     // ---- partial Gram matrices: 64 rows per wave, groups of 16 added in order
     const int tiles = (n + 63) >> 6;
-    if (wave < tiles) {
-        double sum[NG];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int row = 64 * wave + 16 * g + (lane >> 2);
-            double a[H];
-#pragma unroll
-            for (int h = 0; h < H; ++h) a[h] = row < n ? (double)fp[row * RP + mc + 4 * h] : 0.0;
-#pragma unroll
-            for (int q = 0; q < NG; ++q) {
-                double acc = __builtin_amdgcn_mfma_f64_4x4x4f64(a[q == 2 ? H - 1 : 0], a[q == 0 ? 0 : H - 1], 0.0, 0, 0, 0);
-                acc += __shfl_xor(acc, 4, 64);
-                acc += __shfl_xor(acc, 8, 64);
-                sum[q] = g == 0 ? acc : sum[q] + acc;
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < NG; ++q)
-            if ((lane & 12) == 0) part[(wave * NG + q) * 16 + mk * 4 + mc] = sum[q];
-    }
+    if (wave < tiles) gram_tile<RP>(fp, n, wave, lane, part);
     __syncthreads();
-    if (t < 64) {
-        if (t < r * r) {
-            const int i = t / r, j = t - i * r;
-            const int lo = i < j ? i : j, hi = i < j ? j : i;
-            const double *src = part + ((lo >> 2) + (hi >> 2)) * 16 + (lo & 3) * 4 + (hi & 3);
-            double v[16];                                   // (at most kSmallMaxRows / 64 tiles)
-#pragma unroll
-            for (int k = 0; k < 16; ++k) v[k] = k < tiles ? src[k * NG * 16] : 0.0;
-            double all = 0.0;
-#pragma unroll
-            for (int k = 0; k < PARTS; ++k) all += PARTS < 16 ? v[k] + v[(k + PARTS) & 15] : v[k];
-            chol.G[i * RP + j] = all;
-        }
-        wave_lds_sync();
-        cholesky_inverse<RP, 64>(chol, t, r, rinv);
-    }
+    if (t < 64) factor_tiles<RP>(chol, part, tiles, t, r, rinv);
     __syncthreads();
 
     // ---- P^ = P R^-1, a row per thread

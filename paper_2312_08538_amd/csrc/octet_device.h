@@ -534,18 +534,19 @@ constexpr int kQOctetLds = 4 * kQStepRows * kQTilePitch;       // floats
 template <bool BF16, int BITS, int RH, bool TWO>
 __device__ __forceinline__ void q_octet(const DevicePlan &dp, int block, float *lds, const void *__restrict__ grads,
                                         const uint32_t *__restrict__ codes, const float *__restrict__ scales,
-                                        const float *__restrict__ Phat, double *ws)
+                                        const float *__restrict__ Phat, double *ws, float *Qout)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int item = __builtin_amdgcn_readfirstlane(block * 4 + (int)(threadIdx.x >> 6));
+    const bool joined = dp.q_joined != 0;             // the workgroup's waves are the row tiles of one strip
+    const int item = __builtin_amdgcn_readfirstlane(joined ? block : block * 4 + (int)(threadIdx.x >> 6));
     if (item >= dp.n_q_f) return;
     float *T = lds + wave * (kQStepRows * kQTilePitch);
     const WorkItem it = dp.q_f_items[item];
     const MatDesc d = dp.mats[it.mat];
     const int r = dp.rank;
     const int col0 = it.a * kQTileCols;
-    const int64_t row0 = (int64_t)it.b * d.q_tile_rows;
+    const int64_t row0 = (int64_t)(joined ? wave : it.b) * d.q_tile_rows;
     const int64_t row1 = (row0 + d.q_tile_rows < d.n) ? row0 + d.q_tile_rows : d.n;
     const int lrow = lane >> 3, loct = lane & 7;      // load layout: 8 lanes per row, rows lrow + 8 s
     const int mi = lane & 15, mk = lane >> 4;         // matrix-core roles
@@ -589,7 +590,7 @@ __device__ __forceinline__ void q_octet(const DevicePlan &dp, int block, float *
     };
 
     Step cur;
-    load_step(cur, row0);
+    if (row0 < row1) load_step(cur, row0);            // uniform; (joined: a wave may have no rows)
     for (int64_t i0 = row0; i0 < row1; i0 += kQStepRows) {
         // decode into the tile
 #pragma unroll
@@ -622,6 +623,26 @@ __device__ __forceinline__ void q_octet(const DevicePlan &dp, int block, float *
     }
     // D of block (lane % 16) / 4, entry [lane / 16][lane % 4]: column 16 t + 4 ((lane % 16) / 4) + lane / 16 of the strip
     const int dcol = 4 * (mi >> 2) + mk;
+    if (joined) {
+        // the waves' sums, added in wave order
+        constexpr int RC = 4 * RH;
+        double *red = reinterpret_cast<double *>(lds);            // [wave][column][RC], 16 KB of the 40 KB of tiles
+        __syncthreads();                              // every wave is done with its tile
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int h = 0; h < RH; ++h) red[(wave * 64 + 16 * t + dcol) * RC + mc + 4 * h] = acc[t][h];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < RH; ++u) {
+            const int e = (int)threadIdx.x + 256 * u, col = col0 + e / RC, c = e % RC;
+            double sum = red[e];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) sum += red[w * 64 * RC + e];
+            if (col < d.m && c < r) Qout[d.q_off + (int64_t)col * r + c] = (float)sum;
+        }
+        return;
+    }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const int col = col0 + 16 * t + dcol;

@@ -86,6 +86,54 @@ __device__ __forceinline__ void cholesky_inverse(CholeskyLds<RP> &lds, int t, in
     }
 }
 
+// Partial Gram matrices of a factor that stands in LDS ([row][RP], n rows, zero beyond the rank): 64 rows per wave, groups of 16
+// (v_mfma_f64_4x4x4_4b_f64, see k_gram_small) added in order; tile w's blocks 00, 01, 11 to part[w][.][16].
+template <int RP>
+__device__ __forceinline__ void gram_tile(const float *rows, int n, int wave, int lane, double *part)
+{
+    constexpr int H = RP / 4, NG = H * (H + 1) / 2;
+    const int mc = lane & 3;
+    double sum[NG];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int row = 64 * wave + 16 * g + (lane >> 2);
+        double a[H];
+#pragma unroll
+        for (int h = 0; h < H; ++h) a[h] = row < n ? (double)rows[row * RP + mc + 4 * h] : 0.0;
+#pragma unroll
+        for (int q = 0; q < NG; ++q) {
+            double acc = __builtin_amdgcn_mfma_f64_4x4x4f64(a[q == 2 ? H - 1 : 0], a[q == 0 ? 0 : H - 1], 0.0, 0, 0, 0);
+            acc += __shfl_xor(acc, 4, 64);
+            acc += __shfl_xor(acc, 8, 64);
+            sum[q] = g == 0 ? acc : sum[q] + acc;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+        if ((lane & 12) == 0) part[(wave * NG + q) * 16 + (lane >> 4) * 4 + mc] = sum[q];
+}
+
+// The sum of up to 16 such tiles, in the order of k_cholesky_apply, and its factorisation, by one wave (t = 0 .. 63).
+template <int RP>
+__device__ __forceinline__ void factor_tiles(CholeskyLds<RP> &chol, const double *part, int tiles, int t, int r, double *rinv)
+{
+    constexpr int H = RP / 4, NG = H * (H + 1) / 2, PARTS = orth_threads(RP) / (RP * RP);
+    if (t < r * r) {
+        const int i = t / r, j = t - i * r;
+        const int lo = i < j ? i : j, hi = i < j ? j : i;
+        const double *src = part + ((lo >> 2) + (hi >> 2)) * 16 + (lo & 3) * 4 + (hi & 3);
+        double v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = k < tiles ? src[k * NG * 16] : 0.0;
+        double all = 0.0;
+#pragma unroll
+        for (int k = 0; k < PARTS; ++k) all += PARTS < 16 ? v[k] + v[(k + PARTS) & 15] : v[k];
+        chol.G[i * RP + j] = all;
+    }
+    wave_lds_sync();
+    cholesky_inverse<RP, 64>(chol, t, r, rinv);
+}
+
 }  // namespace
 
 }  // namespace conef

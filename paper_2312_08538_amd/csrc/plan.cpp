@@ -417,9 +417,12 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         // 210 M elements: half and twice as many rows per item are both slower)
         int err_rows = 128;
         while (err_rows > 8 && total_elems / ((int64_t)err_rows * 512) < 8192) err_rows >>= 1;
-        // rows per wave item of the Q+ pass (64 columns wide): aim at >= ~4096 wave items
+        // rows per wave item of the Q+ pass (64 columns wide): at least 4000 wave items, a matrix's rows in equal tiles (124 M fp32
+        // elements at rank 4, most of them in matrices of 768 rows: 128 / 256 / 384 / 512 rows 363.6 / 361.0 / 358.6 / 366.8 us a step,
+        // 365.5 with 256 and short last tiles)
         int q_rows = 512;
-        while (q_rows > 64 && total_elems / ((int64_t)q_rows * 64) < 4096) q_rows >>= 1;
+        for (int rows : {384, 256, 192, 128, 96, 64})
+            if (total_elems / ((int64_t)q_rows * 64) < 4000) q_rows = rows;
         // columns per workgroup item of the P pass (64 rows high): a multiple of every code group
         // (1024 / bits columns) and of every block size of the family
         const int p_cols = 512;
@@ -500,6 +503,13 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         const int64_t strip_err = strip_elems / 8192 >= 1024 ? 8192 : strip_elems / 4096 >= 768 ? 4096 : strip_elems / 2048 >= 64 ? 2048 : 1024;
         bool coarse_gram = false;
         // times: how much coarser the row tiles of the strip Q+ pass are than by the rules above
+        // Octet Q+ pass: where no matrix has more than 256 rows a workgroup takes a strip whole, a quarter of the rows per wave, and
+        // writes Q+; nothing is left for the launch that adds partial sums.  us a step without / so: fp32 at rank 4 64 x 2048 25.6 / 21.9,
+        // 256 x 8192 29.6 / 27.5, 600 x 2048 28.4 / 29.2, 1000 x 512 28.2 / 32.3; bf16, 8-bit codes, at rank 8 64 x 512 32.6 / 27.3, 256 x 2048
+        // 38.0 / 35.4, 600 x 512 39.4 / 49.2, 80 of 256 x 1024 93 / 90.
+        bool q_joined = !sketch;
+        for (const MatDesc &d : plan.mats) q_joined = q_joined && (d.path != kPathOctet || d.pack || d.n <= 256);
+        plan.q_joined = q_joined;
         auto lay_out = [&](int64_t chunk_cols, int64_t times) {
             wd = 0;
             plan.any_p_chunks = false;
@@ -519,10 +529,11 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                     d.gsum_off = wd; wd += rank * rank;
                     d.rinv_off = wd; wd += rank * rank;
                 }
-                d.q_tile_rows = d.cs_lin ? 2048 : d.pack ? kPackQRows : d.path == kPathOctet ? q_rows : (d.path == kPathMfma && (kMfmaPasses & 2)) ? 2048
+                d.q_tile_rows = d.cs_lin ? 2048 : d.pack ? kPackQRows : d.path == kPathOctet ? (int32_t)round_up(ceil_div(d.n, ceil_div(d.n, q_rows)), 32) : (d.path == kPathMfma && (kMfmaPasses & 2)) ? 2048
                                 : (int32_t)std::min<int64_t>(std::min<int64_t>(512, times * (q_on_octets(d) ? ragged_q_rows : strip_q_rows)),
                                                              4 * std::max<int64_t>(1, kStripSpan / d.m));
-                d.n_q_tiles = (int32_t)ceil_div(d.n, d.q_tile_rows);
+                if (q_joined && d.path == kPathOctet && !d.pack) d.q_tile_rows = (int32_t)round_up(ceil_div(d.n, 4), 32);
+                d.n_q_tiles = q_joined && d.path == kPathOctet && !d.pack ? 1 : (int32_t)ceil_div(d.n, d.q_tile_rows);
                 d.qpart_off = wd; wd += round_up((int64_t)d.n_q_tiles * d.m * rank, 32);
                 d.n_p_chunks = 1;
                 d.p_chunk_cols = (int32_t)d.m;
@@ -655,6 +666,18 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         plan.ws_doubles = (size_t)round_up(wd, 32);
         plan.workspace_bytes = (size_t)round_up((int64_t)plan.ws_doubles * 8, 256);
 
+        // The orthonormalisation in one launch (kOrthRows)
+        bool orth_rows = rank <= 8 && !coarse_gram && n_mats <= (rank <= 4 ? 512 : 128);
+        for (const MatDesc &d : plan.mats) orth_rows = orth_rows && d.n <= orth_most_rows(rank) && d.n * d.n_p_chunks <= 5000;
+        // Rows per item (wave) of the octet family's err pass on the matrix cores: 64, 128 at rank 8, whose rows of Q+ an item loads
+        // first are twice as many, and fewer where that would leave less than 800 items; at least a trip's 16.  us a step with 16 / 32 /
+        // 64 / 128 rows: 124 M fp32 elements at rank 4 387 / 367 / 362 / 366, at rank 8 491 / 453 / 434 / 427; 210 M bf16 at rank 8 480 / 425
+        // / 400 / 382; 2000 x 4096 at rank 4 44.5 / 43.5 / 42.6 / 48.8, 8000 x 2048 in blocks of 256 at rank 8 88 / 84 / 82 / 94; 256 x 2048
+        // 26.5 / 28.4 / 31.8 / 38.5.
+        const int64_t tile_cols = block == 256 ? 256 : 128;
+        int64_t err_t_elems = 0, err_t_rows = rank == 8 ? 128 : 64;
+        for (const MatDesc &d : plan.mats) err_t_elems += d.err_tile ? d.N : 0;
+        while (err_t_rows > 16 && err_t_elems / (err_t_rows * tile_cols) < 800) err_t_rows /= 2;
         // the longest table, an entry per 1024 elements
         int64_t n_elem = 0;
         for (const MatDesc &d : plan.mats) n_elem += ceil_div(d.N, 1024);
@@ -737,12 +760,10 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 }
                 const int64_t rows_item = (int64_t)std::max(err_rows, rw);
                 // the err pass with the residual on the fp32 matrix cores: strips of 128 columns (256 for blocks of 256)
-                const int64_t tile_cols = block == 256 ? 256 : 128;
                 if (d.err_tile) {
-                    const int64_t rows_t = d.n >= 1024 ? 128 : 64;
-                    for (int64_t r0 = 0; r0 < d.n; r0 += rows_t)
+                    for (int64_t r0 = 0; r0 < d.n; r0 += err_t_rows)
                         for (int32_t st = 0; st < (int32_t)(d.m / tile_cols); ++st)
-                            plan.err_t_items.push_back({l, st, (int32_t)r0, (int32_t)std::min<int64_t>(rows_t, d.n - r0)});
+                            plan.err_t_items.push_back({l, st, (int32_t)r0, (int32_t)std::min<int64_t>(err_t_rows, d.n - r0)});
                 }
                 for (int64_t r0 = 0; r0 < d.n && !sketch && !d.err_tile; r0 += rows_item)
                     for (int32_t st = 0; st < strips; ++st)
@@ -751,6 +772,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                     for (int64_t e0 = 0; e0 < d.n * rank; e0 += 256) plan.pred_items.push_back({l, (int32_t)e0, 0, 0});
             }
             if (rank <= 8) {
+                if (orth_rows) plan.orth_first.push_back((int32_t)plan.gram_s_items.size());
                 for (int64_t t = 0; t < d.n_gram_tiles; ++t)
                     plan.gram_s_items.push_back({d.p_off, t * d.gram_tile_rows, std::min<int64_t>((t + 1) * d.gram_tile_rows, d.n), d.n,
                                                  d.gram_off + t * rank * rank, d.ppart_off, d.n_gram_tiles, d.n_p_chunks, 0});
@@ -762,7 +784,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 for (int64_t r0 = 0; r0 < d.n; r0 += 64) plan.apply_items.push_back({l, (int32_t)r0, 0, 0});
             }
             // a matrix-core matrix with a single row tile gets its Q+ straight from the Q+ pass
-            if (!((mf_q || d.pack || d.path == kPathGeneric) && d.n_q_tiles == 1) || d.cs_lin)
+            if (!((mf_q || d.pack || d.path == kPathGeneric || q_joined) && d.n_q_tiles == 1) || d.cs_lin)
             {
                 // 256 entries per workgroup, a thread per entry; with kQredManyTiles partial sums or more per entry, 16
                 // entries per workgroup and 16 threads per entry (item.c = 1)
@@ -984,8 +1006,11 @@ bool check_plan(const Plan &plan)
             if (d.n > kFlatRows || plan.rank > kFlatRows || d.n_q_tiles != 1 || d.N > kStripSpan) return false;
             c.add(plan, it, 0, d.n, (int64_t)it.a * 256, 256);
         }
-        for (const WorkItem &it : plan.q_f_items)
-            c.add(plan, it, (int64_t)it.b * plan.mats[it.mat].q_tile_rows, plan.mats[it.mat].q_tile_rows, (int64_t)it.a * 64, 64);
+        for (const WorkItem &it : plan.q_f_items) {
+            const MatDesc &d = plan.mats[it.mat];
+            if (plan.q_joined && (plan.sketch || it.b != 0 || d.n_q_tiles != 1 || 4 * (int64_t)d.q_tile_rows < d.n)) return false;
+            c.add(plan, it, (int64_t)it.b * d.q_tile_rows, plan.q_joined ? d.n : d.q_tile_rows, (int64_t)it.a * 64, 64);
+        }
         for (const WorkItem &it : plan.q_m_items)
             c.add(plan, it, (int64_t)it.b * plan.mats[it.mat].q_tile_rows, plan.mats[it.mat].q_tile_rows, (int64_t)it.a * 256, 256);
         for (const WorkItem &it : plan.q_k_items)
@@ -1138,7 +1163,7 @@ bool check_plan(const Plan &plan)
     for (size_t l = 0; l < nm; ++l) {
         const MatDesc &d = plan.mats[l];
         if (gram[l] != d.n_gram_tiles || apply[l] != ceil_div(d.n, plan.rank <= 8 ? apply_rows(plan.rank, d.n) : 64)) return false;
-        const bool direct_q = (d.path == kPathMfma || d.path == kPathGeneric || d.pack) && d.n_q_tiles == 1;
+        const bool direct_q = (d.path == kPathMfma || d.path == kPathGeneric || d.pack || plan.q_joined) && d.n_q_tiles == 1;
         if (d.pack && (d.path != kPathOctet || d.n_p_chunks != 1 || (d.m & 127) != 0 || plan.block < 128 || plan.dtype != 1 ||
                        (plan.bits != 2 && plan.bits != 4)))
             return false;

@@ -26,6 +26,12 @@ constexpr int64_t apply_rows(int rank, int64_t n)
     const int64_t t = orth_threads(rank);
     return n > kTallRows ? ((n + 511) / 512 + t - 1) / t * t : t;
 }
+// Ranks up to 8: models of matrices of few rows are orthonormalised in one launch, a workgroup per matrix (k_orth_rows), which saves
+// the time of a launch where a workgroup has little to add up.  us a step, two launches / one: rank 4 64 x 500 20.6 / 19.6, 600 x
+// 2048 (4 chunks of P) 34.2 / 33.5, 1000 x 500 24.7 / 24.5, 600 x 8192 (16 chunks) 41.0 / 42.8, 500 of 1000 x 260 345 / 341; rank 8 256 x 2048
+// 41.1 / 40.0, 600 x 500 30.2 / 30.6, 1000 x 500 30.4 / 34.6, 100 and 300 of 64 x 260 27.8 / 26.2 and 43.4 / 45.3.
+constexpr int kOrthRows = 1024;
+constexpr int64_t orth_most_rows(int rank) { return rank <= 4 ? kOrthRows : 256; }
 constexpr int kQredManyTiles = 32;  // partial sums of Q+ per entry from which 16 threads share an entry's sum
 constexpr int kStripRows = 32;      // rows per workgroup item of the strip P pass
 constexpr int64_t kStripSpan = (int64_t)1 << 29;    // elements a strip workgroup's rows may span (32-bit byte offsets)
@@ -211,6 +217,7 @@ struct Plan {
     std::vector<WorkItem> err_s_items;  // pass 3: (mat, tile, its first row, rows it spans), or with segments (mat, first row, segment, rows)
     std::vector<WorkItem> err_g_items;  // pass 3, es_rows > 1: (mat, tile, its first group of rows, groups it spans)
     std::vector<WorkItem> err_w_items;  // pass 3, Q+ in LDS: (mat, first run of 512 elements, runs, its first row)
+    bool q_joined = false;              // q_f_items: (mat, strip, 0), a workgroup each, whose four waves are the row tiles
     int ew_lds = 0;                     // floats of LDS of that pass
     std::vector<WorkItem> err_items;    // pass 3, blocks that are not 8 * 2^j elements (j <= 6): (mat, first block, blocks per wave)
     int es_lds = 0;                     // floats of LDS of the strip err pass
@@ -238,6 +245,7 @@ struct Plan {
     std::vector<WorkItem> gram_items;   // (mat, gram tile)
     std::vector<WorkItem> apply_items;  // (mat, first row)                    64 rows per workgroup
     std::vector<OrthItem> gram_s_items, apply_s_items;      // the same for ranks up to 8
+    std::vector<int32_t> orth_first;    // one launch for both: each matrix's first gram_s_items entry; empty: two launches
     std::vector<WorkItem> qred_items;   // reduce partial Q+: (mat, first entry of m*r)
     std::vector<WorkItem> elem_items;   // element-wise helpers: (mat, first element / 1024)
     std::vector<WorkItem> upd_items;    // decompress / update: (mat, row tile of 64, column tile of 128, row tiles)
