@@ -118,6 +118,9 @@ int ensure_uploaded(conef_ctx *ctx)
     d.n_cs_err_f = (int)pl.cs_err_f_items.size();
     if ((rc = upload(ctx, pl.row_hash, &d.row_hash))) return rc;
     if ((rc = upload(ctx, pl.bucket_ptr, &d.bucket_ptr))) return rc;
+    const std::array<int32_t, 2> *order = nullptr;
+    if ((rc = upload(ctx, pl.row_order, &order))) return rc;
+    d.row_order = reinterpret_cast<const int2 *>(order);
     if ((rc = upload(ctx, pl.bucket_rows, &d.bucket_rows))) return rc;
     d.n_cs_err = (int)pl.cs_err_items.size();
     d.table_dtype = pl.table_dtype;

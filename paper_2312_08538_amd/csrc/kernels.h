@@ -28,6 +28,7 @@ struct DevicePlan {
     int csc_lds = 0, csc_threads = 0;   // column form: LDS floats and threads per workgroup of the update pass
     int cs_cols_mode = 0;       // count sketch in the column form: row_hash / bucket lists are over columns, tables rows x w
     int n_cs_err_f_old = 0;     // matrices of the octet path that are NOT in the linear form (0: skip their update launch)
+    const int2 *row_order = nullptr;        // row sketch: a matrix's rows bucket by bucket: (row, bit 31: sign -1; bucket)
     const int32_t *row_hash = nullptr, *bucket_ptr = nullptr, *bucket_rows = nullptr;
     int n_cs_err = 0, n_cs_err_f = 0;
     int table_dtype = 0;            // 0 fp32, 1 fp16

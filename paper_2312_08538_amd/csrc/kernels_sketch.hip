@@ -362,17 +362,17 @@ void k_cs_p_octet(DevicePlan dp, const void *__restrict__ grads, const void *__r
         for (int h = 0; h < (WIDE ? BN : 1); ++h) accw[t][h] = f64x4{0.0, 0.0, 0.0, 0.0};
     }
 
-    // the lane's four rows (rows at or beyond n re-read the last row: their rows of D are not stored)
+    // the lane's four rows, in bucket order (beyond the last one: that one again, whose rows of D are not stored)
     int64_t grow[4], trow[4];
     float somb[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-        int64_t row = row0 + s * 16 + lrow;
-        row = row < d.n ? row : d.n - 1;
-        const int32_t hv = dp.row_hash[d.hash_off + row];
-        grow[s] = d.grad_off + row * d.m;
-        trow[s] = d.table_off + (int64_t)(hv & INT32_MAX) * d.m;
-        somb[s] = hv < 0 ? -dp.omb : dp.omb;
+        int64_t at = row0 + s * 16 + lrow;
+        at = at < d.n ? at : d.n - 1;
+        const int2 e = dp.row_order[d.hash_off + at];
+        grow[s] = d.grad_off + (int64_t)(e.x & INT32_MAX) * d.m;
+        trow[s] = d.table_off + (int64_t)e.y * d.m;
+        somb[s] = e.x < 0 ? -dp.omb : dp.omb;
     }
     const int oct_end = c_end >> 3;
     auto load_tile = [&](SketchOctet<BF16, F16> (&o)[4], int col0) {
@@ -474,8 +474,8 @@ void k_cs_p_octet(DevicePlan dp, const void *__restrict__ grads, const void *__r
 #pragma unroll
     for (int u = 0; u < (kPTileRows * RC + 255) / 256; ++u) {
         const int idx = tid + 256 * u, rr = idx / RC, c = idx % RC;
-        const int64_t row = row0 + rr;
-        if (idx < kPTileRows * RC && c < r && row < d.n) {
+        if (idx < kPTileRows * RC && c < r && row0 + rr < d.n) {
+            const int64_t row = dp.row_order[d.hash_off + row0 + rr].x & INT32_MAX;
             if (d.n_p_chunks == 1) P[d.p_off + row * r + c] = (float)sum[u];
             else ws[d.ppart_off + ((int64_t)it.b * d.n + row) * r + c] = sum[u];
         }
@@ -531,40 +531,35 @@ void k_cs_q_octet(DevicePlan dp, const void *__restrict__ grads, const void *__r
         float somb[kLoads];
         float ph[kGroups][BN];    // P^[i0 + 4 g + mk][mc + 4 h] (wide: [mi + 16 h])
     };
-    int32_t hvn[kLoads];          // hash of the rows of the step after the one being loaded
-    auto load_hash = [&](int64_t i0) {
-#pragma unroll
-        for (int s = 0; s < kLoads; ++s) {
-            int64_t row = i0 + lrow + 8 * s;
-            row = row < row1 ? row : row1 - 1;
-            hvn[s] = dp.row_hash[d.hash_off + row];
-        }
+    int2 order;                   // lane l: row l % 32 (in bucket order) of the step after the one being loaded
+    auto load_order = [&](int64_t i0) {
+        const int64_t at = i0 + (lane & (kCsQStepRows - 1));
+        order = dp.row_order[d.hash_off + (at < row1 ? at : row1 - 1)];      // beyond the tile: its last row, with a zero row of P^
     };
     auto load_step = [&](Step &st, int64_t i0) {
 #pragma unroll
         for (int s = 0; s < kLoads; ++s) {
-            int64_t row = i0 + lrow + 8 * s;
-            row = row < row1 ? row : row1 - 1;         // rows at or beyond row1 re-read the last row; their P^ operand is zero
-            const int32_t hv = hvn[s];
+            const int hv = __shfl(order.x, lrow + 8 * s, 64), bucket = __shfl(order.y, lrow + 8 * s, 64);
             st.somb[s] = hv < 0 ? -dp.omb : dp.omb;
-            st.o[s] = load_sketch_octet<BF16, F16>(grads, table, d.grad_off + (row * d.m8 + oct0) * 8,
-                                                   d.table_off + ((int64_t)(hv & INT32_MAX) * d.m8 + oct0) * 8);
+            st.o[s] = load_sketch_octet<BF16, F16>(grads, table, d.grad_off + ((int64_t)(hv & INT32_MAX) * d.m8 + oct0) * 8,
+                                                   d.table_off + ((int64_t)bucket * d.m8 + oct0) * 8);
         }
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
-            const int64_t row = i0 + 4 * g + mk;
+            const int64_t row = __shfl(order.x, 4 * g + mk, 64) & INT32_MAX;
+            const bool live = i0 + 4 * g + mk < row1;
 #pragma unroll
             for (int h = 0; h < BN; ++h) {
                 const int c = WIDE ? mi + 16 * h : mc + 4 * h;
-                const float v = Phat[d.p_off + (row < row1 ? row : row1 - 1) * r + (c < r ? c : r - 1)];
-                st.ph[g][h] = v * ((row < row1 && c < r) ? 1.0f : 0.0f);
+                const float v = Phat[d.p_off + row * r + (c < r ? c : r - 1)];
+                st.ph[g][h] = v * ((live && c < r) ? 1.0f : 0.0f);
             }
         }
-        load_hash(i0 + kCsQStepRows);
+        load_order(i0 + kCsQStepRows);
     };
 
     Step cur;
-    load_hash(row0);
+    load_order(row0);
     load_step(cur, row0);
     for (int64_t i0 = row0; i0 < row1; i0 += kCsQStepRows) {
 #pragma unroll

@@ -308,6 +308,7 @@ int make_sketch_plan(Plan &plan, const int64_t *rows, const int64_t *cols, const
         while (cs_rows < 256 && total_elems / (cs_rows * 2 * 512) >= min_items) cs_rows *= 2;
         plan.row_hash.assign((size_t)h, 0);
         plan.bucket_rows.assign((size_t)h, 0);
+        plan.row_order.reserve((size_t)h);
         plan.bucket_ptr.assign((size_t)bp, 0);
         for (int l = 0; l < n_mats; ++l) {
             const MatDesc &d = plan.mats[l];
@@ -326,6 +327,8 @@ int make_sketch_plan(Plan &plan, const int64_t *rows, const int64_t *cols, const
                 const int32_t b = hv & INT32_MAX;
                 plan.bucket_rows[(size_t)(d.hash_off + fill[b]++)] = (int32_t)i | (hv & INT32_MIN);
             }
+            for (int64_t b = 0; b < d.w; ++b)
+                for (int32_t k = ptr[b]; k < ptr[b + 1]; ++k) plan.row_order.push_back({plan.bucket_rows[(size_t)(d.hash_off + k)], (int32_t)b});
             // buckets per item: about 16 rows of the matrix each (at most 64 buckets); on the octet path, where
             // a workgroup first loads 512 rows of Q+, `cs_rows` rows (at most 256 buckets)
             const bool fast = d.path == kPathOctet;

@@ -1,6 +1,7 @@
 // Host-side plan of a model: per-matrix descriptors, buffer offsets and the work tables
 // the grouped kernels index with blockIdx.  Plain C++, no device code.
 #pragma once
+#include <array>
 #include <cstddef>
 #include <cstdint>
 #include <vector>
@@ -198,6 +199,7 @@ struct Plan {
     size_t table_elems = 0;
     std::vector<int32_t> row_hash;      // per row: bucket, bit 31 set for sign -1
     std::vector<int32_t> bucket_ptr;    // per matrix w + 1 entries: rows of bucket b are bucket_rows[ptr[b] .. ptr[b+1])
+    std::vector<std::array<int32_t, 2>> row_order;  // row sketch, per matrix n entries: bucket_rows' entry, its bucket
     std::vector<int32_t> bucket_rows;   // per matrix n entries: row index (bit 31: sign -1), ascending within a bucket
     std::vector<WorkItem> cs_err_items; // sketch update: (mat, first bucket, buckets, column tile of cs_cols); column form: (mat, first row, rows, 0)
     std::vector<WorkItem> cs_err_f_items;  // the same for matrices of the octet path (wider tiles)
