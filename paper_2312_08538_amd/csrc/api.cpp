@@ -108,6 +108,10 @@ int ensure_uploaded(conef_ctx *ctx)
     d.n_cs_u = (int)pl.cs_u_items.size();
     d.n_cs_lin = (int)pl.cs_lin_items.size();
     d.cs_cols_mode = pl.sketch_cols ? 1 : 0;
+    if ((rc = upload(ctx, pl.csc_p_items, &d.csc_p_items))) return rc;
+    d.n_csc_p = (int)pl.csc_p_items.size();
+    d.csc_p_lds = pl.csc_p_lds;
+    d.csc_p_threads = pl.csc_p_threads;
     d.csc_lds = 0;
     d.csc_threads = pl.csc_threads;
     for (const MatDesc &m : pl.mats)

@@ -25,6 +25,8 @@ struct DevicePlan {
     const WorkItem *cs_err_items = nullptr, *cs_err_f_items = nullptr;
     const WorkItem *cs_t_items = nullptr, *cs_qt_items = nullptr, *cs_u_items = nullptr, *cs_lin_items = nullptr;   // linear form
     int n_cs_t = 0, n_cs_qt = 0, n_cs_u = 0, n_cs_lin = 0;
+    const WorkItem *csc_p_items = nullptr;      // column form, P pass by rows
+    int n_csc_p = 0, csc_p_lds = 0, csc_p_threads = 0;
     int csc_lds = 0, csc_threads = 0;   // column form: LDS floats and threads per workgroup of the update pass
     int cs_cols_mode = 0;       // count sketch in the column form: row_hash / bucket lists are over columns, tables rows x w
     int n_cs_err_f_old = 0;     // matrices of the octet path that are NOT in the linear form (0: skip their update launch)

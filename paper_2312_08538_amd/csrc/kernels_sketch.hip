@@ -222,6 +222,100 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_update(DevicePlan dp, const
     }
 }
 
+// P = p Q for the column form, ranks up to 4: a workgroup per R rows (as in the update, but the table's rows alone are staged), a
+// thread per column and trip, R x 4 sums per thread in fp64, added up over the lanes and then over the waves in a fixed order.  About
+// as fast as the strip kernels' P pass (18-layer residual network, 20 us: the loads of a trip are one behind the sums), but a row is
+// in one workgroup: no partial sums of column chunks, and the launch that adds them and one of the orthonormalisation's fall away.
+template <int R>
+__device__ __forceinline__ void csc_p_rows(const DevicePlan &dp, const MatDesc &d, const WorkItem &it, float *s_t, double *red,
+                                           const void *__restrict__ grads, const void *__restrict__ table, const float *__restrict__ Q, float *P)
+{
+    constexpr int RP = 4, V = R * RP;
+    const int r = dp.rank, m = (int)d.m, w = (int)d.w, threads = (int)blockDim.x, lane = threadIdx.x & 63;
+    const int64_t trow = d.table_off + (int64_t)it.a * d.w, grow = d.grad_off + (int64_t)it.a * d.m;
+    auto row_of = [&](int i) { return i < it.b ? i : it.b - 1; };       // (fewer than R rows: the last one again, not stored)
+    struct Column { int32_t hv; float g[R], q[RP]; } nx;
+    auto load_column = [&](Column &o, int k) {
+        k = k < m ? k : m - 1;
+        o.hv = dp.row_hash[d.hash_off + k];
+        if (dp.dtype == 0) {
+#pragma unroll
+            for (int i = 0; i < R; ++i) o.g[i] = load_grad(grads, 0, grow + (int64_t)row_of(i) * m + k);
+        } else {
+#pragma unroll
+            for (int i = 0; i < R; ++i) o.g[i] = load_grad(grads, 1, grow + (int64_t)row_of(i) * m + k);
+        }
+        const float *qrow = Q + d.q_off + (int64_t)k * r;
+#pragma unroll
+        for (int c = 0; c < RP; ++c) o.q[c] = qrow[c < r ? c : r - 1];
+    };
+    load_column(nx, threadIdx.x);
+    for (int b = threadIdx.x; b < w; b += threads) {
+        float t[R];
+        if (dp.table_dtype == 0) {
+#pragma unroll
+            for (int i = 0; i < R; ++i) t[i] = table_load(table, 0, trow + (int64_t)row_of(i) * w + b);
+        } else {
+#pragma unroll
+            for (int i = 0; i < R; ++i) t[i] = table_load(table, 1, trow + (int64_t)row_of(i) * w + b);
+        }
+        csc_store<R>(s_t + (size_t)b * R, t);
+    }
+    __syncthreads();
+    double x[V];                                    // [row][column of the factor]
+#pragma unroll
+    for (int v = 0; v < V; ++v) x[v] = 0.0;
+    for (int k = threadIdx.x; k < m; k += threads) {
+        const Column cu = nx;
+        load_column(nx, k + threads);
+        float t[R];
+        csc_load<R>(s_t + (size_t)(cu.hv & INT32_MAX) * R, t);
+        const float somb = signed_omb(dp, cu.hv);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const double p = (double)__builtin_fmaf(somb, t[i], cu.g[i]);
+#pragma unroll
+            for (int c = 0; c < RP; ++c) x[i * RP + c] = __builtin_fma(p, (double)cu.q[c], x[i * RP + c]);
+        }
+    }
+    // each exchange halves the sums a lane holds: it keeps the half that its lane's bit names and adds the partner's
+    int s = 32;
+#pragma unroll
+    for (int n = V / 2; n >= 1; n /= 2, s /= 2) {
+        const bool upper = (lane & s) != 0;
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            const double keep = upper ? x[j + n] : x[j], send = upper ? x[j] : x[j + n];
+            x[j] = keep + __shfl_xor(send, s, 64);
+        }
+    }
+    for (; s >= 1; s /= 2) x[0] += __shfl_xor(x[0], s, 64);
+    constexpr int kLanes = 64 / V;                  // that hold the same sum
+    if (lane % kLanes == 0) red[(threadIdx.x >> 6) * V + lane / kLanes] = x[0];
+    __syncthreads();
+    if (threadIdx.x < V) {
+        double sum = red[threadIdx.x];
+        for (int wv = 1; wv < threads >> 6; ++wv) sum += red[wv * V + threadIdx.x];
+        const int i = threadIdx.x / RP, c = threadIdx.x % RP;
+        if (i < it.b && c < r) P[d.p_off + (int64_t)(it.a + i) * r + c] = (float)sum;
+    }
+}
+
+__global__ __launch_bounds__(kCscThreads) void k_csc_p(DevicePlan dp, const void *__restrict__ grads, const void *__restrict__ table,
+                                                       const float *__restrict__ Q, float *P)
+{
+    extern __shared__ __attribute__((aligned(16))) float csc_p_lds[];     // R w floats of the largest table
+    __shared__ double red[kCscThreads / 64 * 32];
+    const WorkItem it = dp.csc_p_items[blockIdx.x];
+    const MatDesc &d = dp.mats[it.mat];
+    switch (it.c) {                     // rows per workgroup
+    case 8: csc_p_rows<8>(dp, d, it, csc_p_lds, red, grads, table, Q, P); break;
+    case 4: csc_p_rows<4>(dp, d, it, csc_p_lds, red, grads, table, Q, P); break;
+    case 2: csc_p_rows<2>(dp, d, it, csc_p_lds, red, grads, table, Q, P); break;
+    default: csc_p_rows<1>(dp, d, it, csc_p_lds, red, grads, table, Q, P); break;
+    }
+}
+
 // e[i, :] = s(i) S[h(i), :] in fp32, for tests and export
 __global__ __launch_bounds__(256) void k_cs_decode(DevicePlan dp, const void *table, float *e_out)
 {
@@ -1174,6 +1268,8 @@ hipError_t launch_cs_pass_p(const DevicePlan &dp, const void *grads, const void 
     mfma_cs_pass_p(dp, grads, table, Q, P, ws, st);
     if (dp.n_p_f > 0) CONEF_CS_OCTET_DISPATCH(k_cs_p_octet, dim3(dp.n_p_f), st, dp, grads, table, Q, P, ws);
     strip_cs_pass_p(dp, grads, table, Q, P, ws, st);
+    if (dp.n_csc_p > 0)
+        hipLaunchKernelGGL(k_csc_p, dim3(dp.n_csc_p), dim3(dp.csc_p_threads), (size_t)dp.csc_p_lds * sizeof(float), st, dp, grads, table, Q, P);
     if (span.end) (void)hipEventRecord(span.end, st);
     if (add_chunks) generic_p_reduce(dp, ws, P, st);
     return hipGetLastError();

@@ -251,6 +251,9 @@ struct Plan {
     std::vector<WorkItem> qred_items;   // reduce partial Q+: (mat, first entry of m*r)
     std::vector<WorkItem> elem_items;   // element-wise helpers: (mat, first element / 1024)
     std::vector<WorkItem> upd_items;    // decompress / update: (mat, row tile of 64, column tile of 128, row tiles)
+    bool csc_rows_p = false;            // column form: the P pass takes whole rows (csc_p_items), not the strip kernels'
+    std::vector<WorkItem> csc_p_items;  // (mat, first row, rows, rows per workgroup)
+    int csc_p_lds = 0, csc_p_threads = 0;
     int csc_threads = 0;                // column form of the sketch: threads per workgroup of the update
     int64_t small_lds = 0;              // bytes of LDS of the step in one launch; 0: not for this model
     int upd_many = 0;                   // 1: the kernel that walks several row tiles takes them (else all are of one tile)
