@@ -391,7 +391,8 @@ int conef_i_step(conef_ctx *ctx, const void *grads, uint32_t *err_codes, float *
  * kernels; q: the Q+ pass without its final reduction; err: the residual + quantise pass).  Up to
  * 64 conef_step calls are kept (a ring); stage calls made on their own share one slot.
  * conef_get_timing waits for the recorded events and returns the mean duration per stage in
- * milliseconds over the kept calls: ms[4] = {p, orthonormalise, q, err}.  Switching timing on
+ * milliseconds over the kept calls: ms[4] = {p, orthonormalise, q, err}.  While timing is on, models of
+ * small matrices take the stages one by one, too (the same results).  Switching timing on
  * again clears the ring.  Errors: CONEF_ESTATE if timing is off, CONEF_EHIP. */
 int conef_set_timing(conef_ctx *ctx, int on);
 int conef_get_timing(conef_ctx *ctx, float ms[4]);

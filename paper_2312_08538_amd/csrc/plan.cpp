@@ -650,9 +650,8 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
                 plan.es_lds = std::max(plan.es_lds, 8 * d.es_pitch + 8);
             }
         }
-        // The step in one launch.  CONEF_SMALL=0 in the environment keeps the stages' own launches (the same results).
-        const char *small_env = std::getenv("CONEF_SMALL");
-        if (!sketch && octet_blocks && rank <= 8 && !coarse_gram && small_pays(n_mats, total_elems) && !(small_env && small_env[0] == '0')) {
+        // The step in one launch
+        if (!sketch && octet_blocks && rank <= 8 && !coarse_gram && small_pays(n_mats, total_elems)) {
             for (const MatDesc &d : plan.mats) {
                 const int64_t lds = small_lds_bytes(d.n, d.m, plan.rpad);
                 if (d.pack || d.m % 8 != 0 || d.n > kSmallMaxRows || d.N > kSmallMaxElems || lds > kSmallLds) {

@@ -43,7 +43,6 @@ def test_few_rows(env, case, monkeypatch):
     import test_gpu_parity as G
 
     R, B, U, torch = env
-    monkeypatch.setenv("CONEF_SMALL", "0")
     monkeypatch.setenv("CONEF_PACK", "0")
     rank, bits, block, dtype, layout = CASES[case]
     w = wl.Workload("few-rows", 23, tuple(layout), rank, bits, block, dtype, "normal", 1.0, 0x7A46)

@@ -1,4 +1,4 @@
-"""The step of models of small matrices in one launch against the stages' own launches (CONEF_SMALL=0), which the other tests
+"""The step of models of small matrices in one launch against the stages' own launches (which timed stages take), that the other tests
 hold to the oracle: the same bits in P, Q, codes and scales, and nothing written beside them.  Sums are fp64 in both; only the
 order of P's and Q+'s differs, which a rounding to fp32 shows for about one entry in 10^8."""
 import numpy as np
@@ -21,12 +21,13 @@ CASES = [
 ]
 
 
-def _run(layout, rank, bits, block, gdt, beta, kind):
+def _run(layout, rank, bits, block, gdt, beta, kind, stages):
     import torch
 
     from paper_2312_08538_amd import binding as B
 
     model = B.Model(layout, rank, bits, block, gdt, 991)
+    B.conef_set_timing(model.ctx, stages)
     if beta:
         B.conef_set_beta(model.ctx, beta)
     buf = model.alloc()
@@ -62,13 +63,12 @@ def _run(layout, rank, bits, block, gdt, beta, kind):
 @pytest.mark.parametrize("case", range(len(CASES)))
 @pytest.mark.parametrize("gdt", [wl.F32, wl.BF16])
 @pytest.mark.parametrize("beta,kind", [(0.0, "normal"), (0.5, "normal"), (0.0, "zero"), (0.0, "not finite"), (0.0, "low rank")])
-def test_small_step_has_the_bits_of_the_stages(case, gdt, beta, kind, monkeypatch):
+def test_small_step_has_the_bits_of_the_stages(case, gdt, beta, kind):
     layout, rank, bits, block = CASES[case]
     if kind == "low rank" and rank > 1:
         rank = 1                            # (a second column would be rounding noise, normalised)
-    got = _run(layout, rank, bits, block, gdt, beta, kind)
-    monkeypatch.setenv("CONEF_SMALL", "0")
-    want = _run(layout, rank, bits, block, gdt, beta, kind)
+    got = _run(layout, rank, bits, block, gdt, beta, kind, stages=False)
+    want = _run(layout, rank, bits, block, gdt, beta, kind, stages=True)
     for t, (g, w) in enumerate(zip(got, want)):
         for k in g:
             same = np.array_equal(g[k].view(np.uint32), w[k].view(np.uint32))
