@@ -96,7 +96,10 @@ __global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__r
     constexpr bool BACK = TWO || V2;
     constexpr bool SPARSE = MODE == kModeBlock || MODE == kModeStrata || MODE == kModeUniform;      // Delta keeps a few coordinates as they are
     const int lane = threadIdx.x & 63;
-    const int item = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    // the norm pass goes backwards: the pass behind it begins with what the 256 MB last-level cache still holds of it (the scaled sign
+    // of 210 M bf16 elements 216.8 -> 207.8 us)
+    const int block = MODE == kModeNorm ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
+    const int item = __builtin_amdgcn_readfirstlane(block * 4 + (int)(threadIdx.x >> 6));
     if (item >= dp.n_rb) return;
     const WorkItem it = dp.rb_items[item];
     const MatDesc d = dp.mats[it.mat];

@@ -816,6 +816,14 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
             }
             for (int64_t e0 = 0; e0 < d.N; e0 += 1024) plan.elem_items.push_back({l, (int32_t)(e0 >> 10), 0, 0});
         }
+        // The Q+ pass of a model of more than 256 MB goes backwards: it begins with what the P pass has just read, and the err pass,
+        // forwards again, with what it ends on, of which the 256 MB last-level cache still holds a part.  us a step, forwards / so: 124 M
+        // fp32 elements at rank 4 369.0 / 359.7, two vectors 462.8 / 457.7; 210 M bf16 at rank 8 391.3 / 389.7, the row sketch 460.3 /
+        // 457.8; models many times as large the same; 28 M fp32, which fit into the cache whole, 106.5 / 107.3.  (The
+        // matrix-core tables dealt to the XCDs in the P pass's order, shape by shape: 388.8, not worth its code.)
+        if (total_elems * (dtype == 0 ? 32 + bits : 16 + bits) > ((int64_t)8 << 28))
+            for (auto *items : {&plan.q_items, &plan.q_r_items, &plan.q_f_items, &plan.q_m_items, &plan.q_k_items})
+                std::reverse(items->begin(), items->end());
         // Decompress / update: row tiles per workgroup.  On the matrix cores a workgroup keeps its strip of Q+ for several of
         // them (a matrix's tiles in equal shares), where that leaves enough workgroups.  Measured, rank 32, a tile / 4 / 8 tiles
         // per workgroup: 4096 x 8192 (4096 tiles) 64 / 54 / 52 us, 4096 x 4096 35 / 32 / 28, 15.7 M elements in ten matrices
