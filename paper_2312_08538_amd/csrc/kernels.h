@@ -6,59 +6,43 @@
 
 namespace conef {
 
-// Device-resident copy of a plan: descriptor array and work tables.
-struct DevicePlan {
+// Device-resident copy of a plan: descriptor array and work tables.  What kernels read of it, and so what every launch carries: a
+// line of 64 bytes more costs 0.1 - 0.4 us a launch, in the copy and, if the kernel reads it, in the fetch.  The scalars that most
+// kernels read are one line, a table and the counts read beside it neighbours.  us a step of six launches, 664 bytes / so: 4482 x 147 at
+// rank 4 30.1 / 28.4, 600 x 200 at rank 32 56.2 / 55.6, scaled sign of 4 M elements 16.0 / 15.5, 28.4 M elements in matrices of 650 columns
+// 109.4 / 108.1.
+struct KernelPlan {
     const MatDesc *mats = nullptr;
-    const WorkItem *p_items = nullptr, *q_items = nullptr, *err_s_items = nullptr;        // strip kernels (any shape)
-    const WorkItem *q_flat_items = nullptr, *err_g_items = nullptr;     // few rows (Q+ pass), few columns (err pass)
-    const WorkItem *err_items = nullptr;        // err pass of blocks the strip kernel does not take
-    const WorkItem *p_f_items = nullptr, *q_f_items = nullptr, *err_f_items = nullptr;    // octet family
-    const WorkItem *err_t_items = nullptr;      // octet family, err pass with the residual on the fp32 matrix cores
-    const WorkItem *p_m_items = nullptr, *q_m_items = nullptr, *err_m_items = nullptr;    // MFMA family
-    const WorkItem *p_k_items = nullptr, *q_k_items = nullptr;                            // packed-split passes
-    const WorkItem *split_p_items = nullptr, *split_qn_items = nullptr;
-    const WorkItem *upd_items = nullptr;                                                   // decompress / update
-    // random-block gradient compressor
-    const WorkItem *rb_items = nullptr, *rb_g_items = nullptr;
-    int n_rb = 0, n_rb_g = 0;
-    // count-sketch mode
-    const WorkItem *cs_err_items = nullptr, *cs_err_f_items = nullptr;
-    const WorkItem *cs_t_items = nullptr, *cs_qt_items = nullptr, *cs_u_items = nullptr, *cs_lin_items = nullptr;   // linear form
-    int n_cs_t = 0, n_cs_qt = 0, n_cs_u = 0, n_cs_lin = 0;
-    const WorkItem *csc_p_items = nullptr;      // column form, P pass by rows
-    int n_csc_p = 0, csc_p_lds = 0, csc_p_threads = 0;
-    int csc_lds = 0, csc_threads = 0;   // column form: LDS floats and threads per workgroup of the update pass
-    int cs_cols_mode = 0;       // count sketch in the column form: row_hash / bucket lists are over columns, tables rows x w
-    int n_cs_err_f_old = 0;     // matrices of the octet path that are NOT in the linear form (0: skip their update launch)
-    const int2 *row_order = nullptr;        // row sketch: a matrix's rows bucket by bucket: (row, bit 31: sign -1; bucket)
-    const int32_t *row_hash = nullptr, *bucket_ptr = nullptr, *bucket_rows = nullptr;
-    int n_cs_err = 0, n_cs_err_f = 0;
-    int table_dtype = 0;            // 0 fp32, 1 fp16
-    float beta = 0.0f, omb = 1.0f;  // beta and fl32(1 - beta)
-    const WorkItem *pred_items = nullptr, *gram_items = nullptr, *apply_items = nullptr, *qred_items = nullptr,
-                   *elem_items = nullptr;
-    const OrthItem *gram_s_items = nullptr, *apply_s_items = nullptr;      // orthonormalisation, ranks up to 8
-    int n_gram_s = 0, n_apply_s = 0;
-    const int32_t *orth_first = nullptr;        // both in one launch: each matrix's first gram_s_items entry; null: two launches
-    int n_mats = 0;
-    int n_p = 0, n_q = 0, n_err = 0, n_p_f = 0, n_q_f = 0, n_err_f = 0, n_err_t = 0;
-    int n_p_m = 0, n_q_m = 0, n_err_m = 0, n_split_p = 0, n_split_qn = 0;
-    int n_p_k = 0, n_q_k = 0;
-    int n_upd = 0, upd_many = 0;    // upd_many: its items may be of several row tiles
-    int n_pred = 0, n_gram = 0, n_apply = 0, n_qred = 0, n_elem = 0;
-    int rank = 0, rpad = 0, bits = 0, block = 0, dtype = 0;
-    int n_q_flat = 0, n_err_g = 0;
-    int most_p_chunks = 1;          // column chunks of P of the matrix that has the most
-    const WorkItem *err_w_items = nullptr;      // strip err pass with Q+ in LDS
-    int n_err_w = 0, ew_lds = 0;    // its items, floats of LDS per workgroup
-    int n_err_s = 0, es_lds = 0;    // strip err pass: items, floats of LDS per workgroup
+    int rank = 0, bits = 0, block = 0, dtype = 0;
     int wshift = 0, lb_shift = 0;   // log2(code fields per word), log2(block / 8)
     int block_shift = -1;           // log2(block), -1 if it is not a power of two
     float inv_s = 0.0f;             // fl32(1 / s)
     uint64_t bmagic = 0;            // j / block = mulhi64(j, bmagic) for j < 2^35
     uint32_t seed_lo = 0, seed_hi = 0;
-    long long q_elems = 0;
+    float beta = 0.0f, omb = 1.0f;  // beta and fl32(1 - beta)
+    const WorkItem *p_items = nullptr, *q_items = nullptr, *err_s_items = nullptr;        // strip kernels (any shape)
+    const WorkItem *err_w_items = nullptr;      // strip err pass with Q+ in LDS
+    int n_p = 0, n_q = 0, n_err_s = 0, n_err_w = 0;
+    // count-sketch mode
+    const int32_t *row_hash = nullptr;
+    int table_dtype = 0;            // 0 fp32, 1 fp16
+    int cs_cols_mode = 0;       // count sketch in the column form: row_hash / bucket lists are over columns, tables rows x w
+    const WorkItem *upd_items = nullptr;                                                   // decompress / update
+    const int32_t *bucket_ptr = nullptr, *bucket_rows = nullptr;
+    const int2 *row_order = nullptr;        // row sketch: a matrix's rows bucket by bucket: (row, bit 31: sign -1; bucket)
+    const WorkItem *cs_err_items = nullptr, *cs_err_f_items = nullptr;
+    const WorkItem *csc_p_items = nullptr;      // column form, P pass by rows
+    const WorkItem *q_flat_items = nullptr, *err_g_items = nullptr;     // few rows (Q+ pass), few columns (err pass)
+    const WorkItem *p_f_items = nullptr, *q_f_items = nullptr, *err_f_items = nullptr;    // octet family
+    const WorkItem *err_t_items = nullptr;      // octet family, err pass with the residual on the fp32 matrix cores
+    int n_p_f = 0, n_q_f = 0, n_err_f = 0, n_err_t = 0;
     int q_joined = 0;               // octet Q+ pass: a workgroup per strip, its waves the row tiles, Q+ straight from there
+    int n_mats = 0;
+    const WorkItem *p_m_items = nullptr, *q_m_items = nullptr, *err_m_items = nullptr;    // MFMA family
+    const WorkItem *split_p_items = nullptr, *split_qn_items = nullptr;
+    int n_p_m = 0, n_q_m = 0, n_err_m = 0, n_apply = 0;
+    const WorkItem *p_k_items = nullptr, *q_k_items = nullptr;                            // packed-split passes
+    int n_p_k = 0, n_q_k = 0;
     // Improved contractive error feedback around the rank-r compressor: the FIRST error vector, laid out like the
     // codes / scales arguments of the pass kernels (which then hold the second one): p = g + first + second.  Null in
     // every other call; set in a copy of the plan by the launchers of the two-vector passes.
@@ -68,8 +52,35 @@ struct DevicePlan {
     // every matrix, MatDesc::i2_k values at i2_off) as it comes in and where the new one goes (another buffer)
     const float *i2_in = nullptr;
     float *i2_out = nullptr;
+    // element-wise gradient compressors
+    const WorkItem *rb_items = nullptr, *rb_g_items = nullptr;
+    int n_rb = 0;
+    int n_cs_lin = 0;
+    const WorkItem *cs_t_items = nullptr, *cs_qt_items = nullptr, *cs_u_items = nullptr, *cs_lin_items = nullptr;   // count sketch, linear form
+    const WorkItem *err_items = nullptr;        // err pass of blocks the strip kernel does not take
+    const WorkItem *pred_items = nullptr, *gram_items = nullptr, *apply_items = nullptr, *qred_items = nullptr,
+                   *elem_items = nullptr;
+    const OrthItem *gram_s_items = nullptr, *apply_s_items = nullptr;      // orthonormalisation, ranks up to 8
+    const int32_t *orth_first = nullptr;        // both in one launch: each matrix's first gram_s_items entry; null: two launches
+};
+static_assert(sizeof(KernelPlan) <= 8 * 64, "a line of arguments more for every launch");
+
+// ... and what only their launchers read
+struct DevicePlan : KernelPlan {
+    int n_rb_g = 0;
+    int n_cs_t = 0, n_cs_qt = 0, n_cs_u = 0, n_cs_err = 0, n_cs_err_f = 0;
+    int n_cs_err_f_old = 0;     // matrices of the octet path that are NOT in the linear form (0: skip their update launch)
+    int n_csc_p = 0, csc_p_lds = 0, csc_p_threads = 0;      // column form, P pass by rows
+    int csc_lds = 0, csc_threads = 0;   // column form: LDS floats and threads per workgroup of the update pass
+    int n_gram_s = 0, n_apply_s = 0, n_err = 0, n_split_p = 0, n_split_qn = 0;
+    int n_upd = 0, upd_many = 0;    // upd_many: its items may be of several row tiles
+    int n_pred = 0, n_gram = 0, n_qred = 0, n_elem = 0;
+    int rpad = 0, n_q_flat = 0, n_err_g = 0;
+    int most_p_chunks = 1;          // column chunks of P of the matrix that has the most
+    int ew_lds = 0, es_lds = 0;     // floats of LDS per workgroup of the strip err passes
+    long long q_elems = 0;
     // Strip kernels, P and Q+ passes on octets.  The launchers of those kernels put them in the place of p_items and the others
-    // (octet_items): what a kernel reads stands together in its arguments, and a line of them more costs 0.1 - 0.4 us a launch.
+    // (octet_items).
     const WorkItem *p_r_items = nullptr, *q_r_items = nullptr;
     int n_p_r = 0, n_q_r = 0;
     size_t small_lds = 0;           // bytes of LDS of the step in one launch (0: the model does not take it)

@@ -28,7 +28,7 @@ __device__ __forceinline__ float form_p(const MatDesc &d, const void *grads, con
 
 // The same with the plan's first error vector, if there is one (Algorithm 3: p = g + e~ + q, the first vector in the
 // inner fused multiply-add, the codes / scales arguments in the outer one; no partial update there).
-__device__ __forceinline__ float form_p(const DevicePlan &dp, const MatDesc &d, const void *grads, const uint32_t *codes,
+__device__ __forceinline__ float form_p(const KernelPlan &dp, const MatDesc &d, const void *grads, const uint32_t *codes,
                                         const float *scales, int64_t j, float omb)
 {
     if (!dp.i_codes) return form_p(d, grads, codes, scales, dp.dtype, dp.bits, dp.block, j, omb);
@@ -64,7 +64,7 @@ __device__ __forceinline__ double ordered_sum(const double *src, int T, int64_t 
 // Adds the row-tile partial sums of Q+ and rounds once to fp32.  item.c = 0: 256 entries, a thread per entry, the tiles
 // in order.  item.c = 1 (a tall matrix: kQredManyTiles tiles or more): 16 entries; thread (entry, part) adds the tiles
 // part, part + 16, ... in that order, then the 16 parts are added in order (the order of k_gram_reduce).
-__global__ __launch_bounds__(256) void k_q_reduce(DevicePlan dp, const double *ws, double *ws_rw, float *Qout)
+__global__ __launch_bounds__(256) void k_q_reduce(KernelPlan dp, const double *ws, double *ws_rw, float *Qout)
 {
     __shared__ double red[16][16];
     const WorkItem it = dp.qred_items[blockIdx.x];
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256) void k_q_reduce(DevicePlan dp, const double *w
 // One wave per scale block; two sweeps over the block (max-norm, then rounding) so that any
 // block length fits.  The residual is the fp32 fma chain over c = 0..r-1.
 template <int RP>
-__device__ __forceinline__ float residual_at(const DevicePlan &dp, const MatDesc &d, const void *grads,
+__device__ __forceinline__ float residual_at(const KernelPlan &dp, const MatDesc &d, const void *grads,
                                              const uint32_t *codes, const float *scales, const float *Phat,
                                              const float *Qn, int64_t j)
 {
@@ -126,7 +126,7 @@ __device__ __forceinline__ float residual_at(const DevicePlan &dp, const MatDesc
 // (dp.i_codes = codes_first) and the second in codes / scales; the rounded residual goes back to the first vector,
 // what that rounding leaves, rounded again, to the second.  Three sweeps as in k_rb_generic.
 template <int RP, bool TWO>
-__global__ __launch_bounds__(256) void k_pass_err_generic(DevicePlan dp, const void *grads, uint32_t *codes,
+__global__ __launch_bounds__(256) void k_pass_err_generic(KernelPlan dp, const void *grads, uint32_t *codes,
                                                           float *scales, const float *Phat, const float *Qn,
                                                           uint32_t step_lo, uint32_t step_hi, uint32_t *codes_first,
                                                           float *scales_first)
@@ -233,7 +233,7 @@ constexpr bool rb_sparse() { return MODE == kModeBlock || MODE == kModeStrata ||
 
 // Is coordinate j kept by the gradient compressor at this step, and where in the Delta buffer does its value go?
 template <int MODE>
-__device__ __forceinline__ bool rb_kept(const DevicePlan &dp, const MatDesc &d, int mat, int64_t j, int64_t start,
+__device__ __forceinline__ bool rb_kept(const KernelPlan &dp, const MatDesc &d, int mat, int64_t j, int64_t start,
                                         uint32_t step_lo, uint32_t step_hi, const RkuKeys &ku, int64_t *slot)
 {
     if (MODE == kModeBlock) {
@@ -257,7 +257,7 @@ __device__ __forceinline__ bool rb_kept(const DevicePlan &dp, const MatDesc &d, 
 }
 
 template <int MODE, bool TWO>
-__device__ __forceinline__ float rb_argument(const DevicePlan &dp, const MatDesc &d, const void *grads, const uint32_t *codes,
+__device__ __forceinline__ float rb_argument(const KernelPlan &dp, const MatDesc &d, const void *grads, const uint32_t *codes,
                                              const float *scales, int64_t j, int64_t start, float *delta, bool write,
                                              float c, uint32_t *sign_words, const uint32_t *codes2, const float *scales2,
                                              int mat, uint32_t step_lo, uint32_t step_hi, int64_t e_from, int64_t e_to,
@@ -319,7 +319,7 @@ __device__ __forceinline__ float rb_argument(const DevicePlan &dp, const MatDesc
 }
 
 template <int MODE, bool TWO>
-__global__ __launch_bounds__(256) void k_rb_generic(DevicePlan dp, const void *grads, uint32_t *codes, float *scales,
+__global__ __launch_bounds__(256) void k_rb_generic(KernelPlan dp, const void *grads, uint32_t *codes, float *scales,
                                                     float *delta, uint32_t step_lo, uint32_t step_hi,
                                                     uint32_t *sign_words, const float *c_scale, double *ws,
                                                     uint32_t *codes2, float *scales2)
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(256) void k_rb_generic(DevicePlan dp, const void *g
 // c = fl32(||p||_1 / N) of every matrix from the partial sums of the norm pass: thread t adds partials t, t + 1024, ..., then the
 // 1024 sums are added over the lanes of each wave and over the waves in order.  (Thousands of partials per matrix: a chain of
 // loads per thread and then one thread's chain over the threads were 10 us; neighbouring threads' loads are neighbouring now.)
-__global__ __launch_bounds__(1024) void k_ss_scale(DevicePlan dp, const double *ws, float *c_scale)
+__global__ __launch_bounds__(1024) void k_ss_scale(KernelPlan dp, const double *ws, float *c_scale)
 {
     __shared__ double share[16];
     const MatDesc d = dp.mats[blockIdx.x];
@@ -451,7 +451,7 @@ __global__ __launch_bounds__(1024) void k_ss_scale(DevicePlan dp, const double *
 }
 
 // Clears the sign words of the matrices whose sign bits are set with atomic ORs (those off the octet paths).
-__global__ __launch_bounds__(256) void k_ss_clear(DevicePlan dp, uint32_t *sign_words)
+__global__ __launch_bounds__(256) void k_ss_clear(KernelPlan dp, uint32_t *sign_words)
 {
     const WorkItem it = dp.elem_items[blockIdx.x];
     const MatDesc d = dp.mats[it.mat];
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(256) void k_ss_clear(DevicePlan dp, uint32_t *sign_
 }
 
 // Adds the column-chunk partial sums of P in chunk order and rounds once to fp32.
-__global__ __launch_bounds__(256) void k_p_reduce(DevicePlan dp, const double *ws, float *P)
+__global__ __launch_bounds__(256) void k_p_reduce(KernelPlan dp, const double *ws, float *P)
 {
     const WorkItem it = dp.pred_items[blockIdx.x];
     const MatDesc d = dp.mats[it.mat];
@@ -474,7 +474,7 @@ __global__ __launch_bounds__(256) void k_p_reduce(DevicePlan dp, const double *w
 }
 
 // ---------------------------------------------------------------- helpers
-__global__ __launch_bounds__(256) void k_decode(DevicePlan dp, const uint32_t *codes, const float *scales, float *e_out)
+__global__ __launch_bounds__(256) void k_decode(KernelPlan dp, const uint32_t *codes, const float *scales, float *e_out)
 {
     const WorkItem it = dp.elem_items[blockIdx.x];
     const MatDesc d = dp.mats[it.mat];
@@ -689,7 +689,7 @@ namespace {
 constexpr int kUpdAPitch = kUpdRows + 4, kUpdBPitch = kUpdCols + 4;
 
 template <bool SUBTRACT, bool PREFETCH>
-__global__ __launch_bounds__(256) void k_update(DevicePlan dp, const float *__restrict__ Phat,
+__global__ __launch_bounds__(256) void k_update(KernelPlan dp, const float *__restrict__ Phat,
                                                 const float *__restrict__ Qn, float *x)
 {
     __shared__ __attribute__((aligned(16))) float sa[32 * kUpdAPitch];      // [c][row of the tile]
@@ -795,7 +795,7 @@ typedef float upd_f32x4 __attribute__((ext_vector_type(4)));
 
 // NQ: a quarter of the rank
 template <bool SUBTRACT, int NQ, bool MANY>
-__global__ __launch_bounds__(256, 2) void k_update_mfma(DevicePlan dp, const float *__restrict__ Phat,
+__global__ __launch_bounds__(256, 2) void k_update_mfma(KernelPlan dp, const float *__restrict__ Phat,
                                                         const float *__restrict__ Qn, float *x)
 {
     constexpr int R = 4 * NQ;

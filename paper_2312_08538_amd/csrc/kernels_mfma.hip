@@ -51,7 +51,7 @@ constexpr int kSStride = 33;                // scales per row in LDS (+1: rows f
 constexpr int kPModeStep = 0, kPModeCodes = 1, kPModeGrad = 2, kPModeTable = 3;
 
 template <int MODE>
-__global__ __launch_bounds__(256) void k_p_mfma(DevicePlan dp, const uint16_t *__restrict__ grads,
+__global__ __launch_bounds__(256) void k_p_mfma(KernelPlan dp, const uint16_t *__restrict__ grads,
                                                 const uint32_t *__restrict__ codes, const float *__restrict__ scales,
                                                 const float *__restrict__ Q, float *P, double *ws)
 {
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(256) void k_p_mfma(DevicePlan dp, const uint16_t *_
 // ------------------------------------------------------------------ splits of P^ and Q+
 // Column-block-major copy of the block scales (transpose_scales_tile), one workgroup per 64 rows.  The full step does
 // this inside the orthonormalisation's launches instead; this kernel serves the stage calls.
-__global__ __launch_bounds__(256) void k_transpose_scales(DevicePlan dp, const float *__restrict__ scales, double *ws, int second)
+__global__ __launch_bounds__(256) void k_transpose_scales(KernelPlan dp, const float *__restrict__ scales, double *ws, int second)
 {
     __shared__ float tile[64 * 33];
     transpose_scales_tile(dp, scales, ws, (int)blockIdx.x, second, tile);
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(256) void k_transpose_scales(DevicePlan dp, const f
 // block's operands are one contiguous 24 KB piece and tile t's 16 rows (one per octet cc) are adjacent.
 // (The reduction that ends the Q+ pass writes the same layout itself; this kernel serves the err
 // stage when it is called on its own.)
-__global__ __launch_bounds__(256) void k_split_q_new(DevicePlan dp, const float *__restrict__ Qn, double *ws)
+__global__ __launch_bounds__(256) void k_split_q_new(KernelPlan dp, const float *__restrict__ Qn, double *ws)
 {
     const WorkItem it = dp.split_qn_items[blockIdx.x];
     const MatDesc d = dp.mats[it.mat];
@@ -392,7 +392,7 @@ constexpr int kQSplit = kQRows * 32;        // bf16 entries of one split of a ch
 // 3: the table's share (1 - beta) S^T U over the table's rows (two operand tiles per entry, see the P pass), U from the
 // workspace; its row tiles follow the gradient's in the partial sums, which the reduction kernel adds in order.
 template <int MODE>
-__global__ __launch_bounds__(256, 2) void k_q_mfma(DevicePlan dp, const uint16_t *__restrict__ grads,
+__global__ __launch_bounds__(256, 2) void k_q_mfma(KernelPlan dp, const uint16_t *__restrict__ grads,
                                                    const uint32_t *__restrict__ codes, const float *__restrict__ scales,
                                                    const float *__restrict__ Phat, double *ws, float *Qout)
 {
@@ -768,7 +768,7 @@ __device__ __forceinline__ uint32_t umax(uint32_t a, uint32_t b) { return a > b 
 // residual is rounded into the first vector, what that rounding leaves is rounded again (draws of the stream
 // mat | 2^31) into the second.
 template <bool TWO>
-__global__ __launch_bounds__(512, TWO ? 2 : 4) void k_err_mfma(DevicePlan dp, const uint16_t *__restrict__ grads, uint32_t *codes,
+__global__ __launch_bounds__(512, TWO ? 2 : 4) void k_err_mfma(KernelPlan dp, const uint16_t *__restrict__ grads, uint32_t *codes,
                                                   float *scales, const float *__restrict__ Phat, const double *ws,
                                                   uint32_t step_lo, uint32_t step_hi, uint32_t *codes_first,
                                                   float *scales_first)

@@ -26,7 +26,7 @@ constexpr int larger(int a, int b) { return a > b ? a : b; }
 
 template <bool BF16, int BITS, int RH>
 __global__ __launch_bounds__(256) CONEF_P_OCTET_WAVES(false)
-void k_p_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
+void k_p_mixed(KernelPlan dp, int lead, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Q, float *P, double *ws)
 {
     __shared__ __attribute__((aligned(16))) float lds[larger(kPOctetLds, kRagLds)];
@@ -41,7 +41,7 @@ void k_p_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const ui
 
 template <bool BF16, int BITS, int R>
 __global__ __launch_bounds__(256) CONEF_Q_OCTET_WAVES(BF16, false)
-void k_q_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
+void k_q_mixed(KernelPlan dp, int lead, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Phat, double *ws, float *Qout)
 {
     __shared__ __attribute__((aligned(16))) float lds[larger(kQOctetLds, kRagLds)];
@@ -55,7 +55,7 @@ void k_q_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, const ui
 
 // WALK: the strip family's workgroups are those with Q+ in LDS
 template <bool BF16, int BITS, int R, bool WIDE, bool WALK>
-__global__ __launch_bounds__(256, 2) void k_err_mixed(DevicePlan dp, int lead, const void *__restrict__ grads, uint32_t *codes,
+__global__ __launch_bounds__(256, 2) void k_err_mixed(KernelPlan dp, int lead, const void *__restrict__ grads, uint32_t *codes,
                                                       float *scales, const float *__restrict__ Phat, const float *__restrict__ Qn,
                                                       uint32_t step_lo, uint32_t step_hi)
 {

@@ -31,7 +31,7 @@ namespace {
 // ------------------------------------------------------------------ the three passes (device code: octet_device.h)
 template <bool BF16, int BITS, int RH, bool TWO = false>
 __global__ __launch_bounds__(256) CONEF_P_OCTET_WAVES(TWO)
-void k_p_octet(DevicePlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
+void k_p_octet(KernelPlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Q, float *P, double *ws)
 {
     __shared__ __attribute__((aligned(16))) float tiles[kPOctetTiles];
@@ -45,7 +45,7 @@ void k_p_octet(DevicePlan dp, const void *__restrict__ grads, const uint32_t *__
 
 template <bool BF16, int BITS, int RH, bool TWO = false>
 __global__ __launch_bounds__(256) CONEF_Q_OCTET_WAVES(BF16, TWO)
-void k_q_octet(DevicePlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
+void k_q_octet(KernelPlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Phat, double *ws, float *Qout)
 {
     __shared__ __attribute__((aligned(16))) float lds[kQOctetLds];
@@ -54,7 +54,7 @@ void k_q_octet(DevicePlan dp, const void *__restrict__ grads, const uint32_t *__
 
 template <bool BF16, int BITS, int RP, bool WIDE, bool TWO>
 __global__ __launch_bounds__(256) CONEF_ERR_TILE_WAVES(BF16, WIDE, TWO)
-void k_err_tile(DevicePlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
+void k_err_tile(KernelPlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
                                                   const float *__restrict__ Phat, const float *__restrict__ Qn,
                                                   uint32_t step_lo, uint32_t step_hi, uint32_t *codes_first, float *scales_first)
 {
@@ -88,7 +88,7 @@ void k_err_tile(DevicePlan dp, const void *__restrict__ grads, uint32_t *codes, 
 // compressed vector is q: p = g + q, + e~ on that block; Delta = p on the kept coordinates; e~+ = p - Delta on the block
 // drawn now (to dp.i2_out, another buffer: other waves still read the old one); q+ = C(p - Delta - e~+).
 template <bool BF16, int BITS, int MODE, bool TWO, bool V2>
-__global__ __launch_bounds__(256) void k_rb_octet(DevicePlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
+__global__ __launch_bounds__(256) void k_rb_octet(KernelPlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
                                                   float *__restrict__ delta, uint32_t step_lo, uint32_t step_hi,
                                                   uint32_t *__restrict__ sign_words, const float *__restrict__ c_scale, double *ws,
                                                   uint32_t *codes2, float *scales2)

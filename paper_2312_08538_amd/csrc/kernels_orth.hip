@@ -27,7 +27,7 @@ namespace {
 // (B = (RP/4)^2 blocks, PH = 256 / B row phases).  Phases are added by a fixed butterfly inside
 // the wave and in wave order across the workgroup.
 template <int RP>
-__global__ __launch_bounds__(256) void k_gram_partial(DevicePlan dp, const float *__restrict__ P, double *ws)
+__global__ __launch_bounds__(256) void k_gram_partial(KernelPlan dp, const float *__restrict__ P, double *ws)
 {
     constexpr int NB = RP / 4, B = NB * NB, PH = 256 / B;
     constexpr int kStride = RP;
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256) void k_gram_partial(DevicePlan dp, const float
 // the workgroup takes the w-th quarter of the tile's rows; the four waves' sums are added in wave order.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void k_gram_mfma32(DevicePlan dp, const float *__restrict__ P, double *ws)
+__global__ __launch_bounds__(256) void k_gram_mfma32(KernelPlan dp, const float *__restrict__ P, double *ws)
 {
     __shared__ double red[4][3][256];
     const WorkItem it = dp.gram_items[blockIdx.x];
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void k_gram_mfma32(DevicePlan dp, const float 
 // part, part + 16, ... in that order, then the 16 parts are added in order.  (One thread per entry
 // walking all tiles is a chain of dependent memory round trips, hundreds long for a tall matrix.)
 template <int RP>
-__global__ __launch_bounds__(256) void k_gram_reduce(DevicePlan dp, double *ws)
+__global__ __launch_bounds__(256) void k_gram_reduce(KernelPlan dp, double *ws)
 {
     constexpr int kSlices = (RP * RP + 15) / 16;
     __shared__ double red[16][16];
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256) void k_gram_reduce(DevicePlan dp, double *ws)
 // first region, then n_tr tiles of tr_b into the second if tr_b is given), which fills the chip while the
 // factorisations run.
 template <int RP>
-__global__ __launch_bounds__(256) void k_cholesky_inverse(DevicePlan dp, double *ws, const float *__restrict__ tr_a,
+__global__ __launch_bounds__(256) void k_cholesky_inverse(KernelPlan dp, double *ws, const float *__restrict__ tr_a,
                                                           const float *__restrict__ tr_b, int n_tr)
 {
     __shared__ CholeskyLds<RP> lds;
@@ -237,7 +237,7 @@ __device__ __forceinline__ void apply_columns(const double (&in)[RP], const doub
 }
 
 template <int RP>
-__global__ __launch_bounds__(256) void k_apply_rinv(DevicePlan dp, float *P, const double *ws)
+__global__ __launch_bounds__(256) void k_apply_rinv(KernelPlan dp, float *P, const double *ws)
 {
     constexpr int kS = RP + 1;
     __shared__ float tin[64 * kS];
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(256) void k_apply_rinv(DevicePlan dp, float *P, con
 // column block, so that the lane ends up with the four neighbouring entries c = 16 cb + 4 kq + v of its row (one store
 // per column block).  The entries of (R^-1)^T do not depend on the rows and stay in registers.  A wave reads the 16
 // rows of a group completely before it overwrites them (P^ replaces P in place).
-__global__ __launch_bounds__(256) void k_apply_mfma32(DevicePlan dp, float *P, const double *__restrict__ ws)
+__global__ __launch_bounds__(256) void k_apply_mfma32(KernelPlan dp, float *P, const double *__restrict__ ws)
 {
     const int lane = threadIdx.x & 63;
     const int item = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(256) void k_apply_mfma32(DevicePlan dp, float *P, c
 // (+ 4)], which is both its A and its B entry, so a load is coalesced and there is no staging; the instruction's four blocks
 // are four groups of four rows.  Wave w takes the 16-row groups w, w + 4, ... of the tile.
 template <int RP, bool CHUNKS>
-__global__ __launch_bounds__(256) void k_gram_small(DevicePlan dp, float *P, double *ws)
+__global__ __launch_bounds__(256) void k_gram_small(KernelPlan dp, float *P, double *ws)
 {
     constexpr int H = RP / 4, NG = H * (H + 1) / 2, U = 4;
     __shared__ double red[4][NG][16];
@@ -453,7 +453,7 @@ __global__ __launch_bounds__(256) void k_gram_small(DevicePlan dp, float *P, dou
 // The sum of the partial Gram matrices (thread (part, entry): tiles part, part + PARTS, ... in that order, then the parts in
 // order), its factorisation, and P^ = P R^-1 for a row per thread, the products of a column in ascending k.
 template <int RP>
-__global__ __launch_bounds__(orth_threads(RP)) void k_cholesky_apply(DevicePlan dp, float *P, const double *ws)
+__global__ __launch_bounds__(orth_threads(RP)) void k_cholesky_apply(KernelPlan dp, float *P, const double *ws)
 {
     constexpr int E = RP * RP, THREADS = orth_threads(RP), PARTS = THREADS / E, U = 8;
     __shared__ double red[PARTS][E], rinv[E];
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(orth_threads(RP)) void k_cholesky_apply(DevicePlan 
 // Models of matrices of few rows (orth_most_rows): both in one launch, a workgroup per matrix and a thread per row.  Same sums in
 // the same order.  18-layer residual network, rank 4: the two 4.8 + 4.7 us, this 6.7, the step 55.1 -> 53.8.
 template <int RP, bool CHUNKS>
-__global__ __launch_bounds__(1024) void k_orth_rows(DevicePlan dp, float *P, const double *ws)
+__global__ __launch_bounds__(1024) void k_orth_rows(KernelPlan dp, float *P, const double *ws)
 {
     constexpr int H = RP / 4, NG = H * (H + 1) / 2, E = RP * RP, V = RP >= 8 ? 2 : 4;
     __shared__ __attribute__((aligned(16))) float rows[kOrthRows * RP];

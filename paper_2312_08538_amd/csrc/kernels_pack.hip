@@ -59,7 +59,7 @@ __device__ __forceinline__ float operand_unit() { return BITS == 4 ? 16.0f : 1.0
 // MODE 0: P = (g + e) Q.  MODE 1: the contribution of a compressed vector alone, added to a P that an earlier launch has
 // written (the two error vectors of Algorithm 3).
 template <int BITS, int MODE>
-__global__ __launch_bounds__(256) void k_p_pack(DevicePlan dp, const uint16_t *__restrict__ grads, const uint32_t *__restrict__ codes,
+__global__ __launch_bounds__(256) void k_p_pack(KernelPlan dp, const uint16_t *__restrict__ grads, const uint32_t *__restrict__ codes,
                                                 const float *__restrict__ scales, const float *__restrict__ Q, float *P)
 {
     constexpr bool GRAD = MODE == 0, ACCUM = MODE == 1;
@@ -256,7 +256,7 @@ constexpr int kPkQRows = 64;                 // rows per chunk
 constexpr int kPkTPitch = 128 + 32;          // bf16 per row of the gradient / code tiles: 320 bytes, conflict-free transposing reads
 
 template <int BITS, int MODE>
-__global__ __launch_bounds__(256) void k_q_pack(DevicePlan dp, const uint16_t *__restrict__ grads, const uint32_t *__restrict__ codes,
+__global__ __launch_bounds__(256) void k_q_pack(KernelPlan dp, const uint16_t *__restrict__ grads, const uint32_t *__restrict__ codes,
                                                 const float *__restrict__ scales, const float *__restrict__ Phat, double *ws,
                                                 float *Qout)
 {

@@ -19,7 +19,7 @@ namespace conef {
 namespace {
 
 template <bool BF16, int BITS, int RH, bool TWO>
-__global__ __launch_bounds__(256) void k_p_ragged(DevicePlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
+__global__ __launch_bounds__(256) void k_p_ragged(KernelPlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                                                   const float *__restrict__ scales, const float *__restrict__ Q, float *P, double *ws)
 {
     __shared__ __attribute__((aligned(16))) float lds[kRagLds];
@@ -27,7 +27,7 @@ __global__ __launch_bounds__(256) void k_p_ragged(DevicePlan dp, const void *__r
 }
 
 template <bool BF16, int BITS, int RH, bool TWO>
-__global__ __launch_bounds__(256) void k_q_ragged(DevicePlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
+__global__ __launch_bounds__(256) void k_q_ragged(KernelPlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                                                   const float *__restrict__ scales, const float *__restrict__ Phat, double *ws, float *Qout)
 {
     __shared__ __attribute__((aligned(16))) float lds[kRagLds];

@@ -39,13 +39,13 @@ __device__ __forceinline__ void table_store(void *table, int f16, int64_t idx, f
 }
 
 // (1 - beta) with the sign of the row folded in: fma(-(1 - beta), t, g) is fma(1 - beta, -t, g) exactly
-__device__ __forceinline__ float signed_omb(const DevicePlan &dp, int32_t hv) { return hv < 0 ? -dp.omb : dp.omb; }
+__device__ __forceinline__ float signed_omb(const KernelPlan &dp, int32_t hv) { return hv < 0 ? -dp.omb : dp.omb; }
 
 // ---------------------------------------------------------------- pass 3: S <- beta S + C(p - P^ Q+^T)
 // One thread per column of a column tile, a run of buckets per workgroup.  The thread keeps its row of
 // Q+ in registers; P^ rows and the bucket lists are uniform over the workgroup.
 template <int RP>
-__global__ __launch_bounds__(kCsCols) void k_cs_update_generic(DevicePlan dp, const void *grads, void *table,
+__global__ __launch_bounds__(kCsCols) void k_cs_update_generic(KernelPlan dp, const void *grads, void *table,
                                                                const float *Phat, const float *Qn)
 {
     const WorkItem it = dp.cs_err_items[blockIdx.x];
@@ -114,7 +114,7 @@ __device__ __forceinline__ void csc_load(const float *src, float (&v)[R])
 }
 
 template <int RP, int R>
-__device__ __forceinline__ void csc_rows(const DevicePlan &dp, const MatDesc &d, const WorkItem &it, float *lds, const void *__restrict__ grads,
+__device__ __forceinline__ void csc_rows(const KernelPlan &dp, const MatDesc &d, const WorkItem &it, float *lds, const void *__restrict__ grads,
                                          void *table, const float *__restrict__ Phat, const float *__restrict__ Qn)
 {
     const int r = dp.rank, m = (int)d.m, w = (int)d.w, threads = (int)blockDim.x;
@@ -208,7 +208,7 @@ __device__ __forceinline__ void csc_rows(const DevicePlan &dp, const MatDesc &d,
 }
 
 template <int RP>
-__global__ __launch_bounds__(kCscThreads) void k_csc_update(DevicePlan dp, const void *__restrict__ grads, void *table,
+__global__ __launch_bounds__(kCscThreads) void k_csc_update(KernelPlan dp, const void *__restrict__ grads, void *table,
                                                             const float *__restrict__ Phat, const float *__restrict__ Qn)
 {
     extern __shared__ __attribute__((aligned(16))) float csc_lds[];       // R (m + w) floats of the largest matrix
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_update(DevicePlan dp, const
 // as fast as the strip kernels' P pass (18-layer residual network, 20 us: the loads of a trip are one behind the sums), but a row is
 // in one workgroup: no partial sums of column chunks, and the launch that adds them and one of the orthonormalisation's fall away.
 template <int R>
-__device__ __forceinline__ void csc_p_rows(const DevicePlan &dp, const MatDesc &d, const WorkItem &it, float *s_t, double *red,
+__device__ __forceinline__ void csc_p_rows(const KernelPlan &dp, const MatDesc &d, const WorkItem &it, float *s_t, double *red,
                                            const void *__restrict__ grads, const void *__restrict__ table, const float *__restrict__ Q, float *P)
 {
     constexpr int RP = 4, V = R * RP;
@@ -301,7 +301,7 @@ __device__ __forceinline__ void csc_p_rows(const DevicePlan &dp, const MatDesc &
     }
 }
 
-__global__ __launch_bounds__(kCscThreads) void k_csc_p(DevicePlan dp, const void *__restrict__ grads, const void *__restrict__ table,
+__global__ __launch_bounds__(kCscThreads) void k_csc_p(KernelPlan dp, const void *__restrict__ grads, const void *__restrict__ table,
                                                        const float *__restrict__ Q, float *P)
 {
     extern __shared__ __attribute__((aligned(16))) float csc_p_lds[];     // R w floats of the largest table
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(kCscThreads) void k_csc_p(DevicePlan dp, const void
 }
 
 // e[i, :] = s(i) S[h(i), :] in fp32, for tests and export
-__global__ __launch_bounds__(256) void k_cs_decode(DevicePlan dp, const void *table, float *e_out)
+__global__ __launch_bounds__(256) void k_cs_decode(KernelPlan dp, const void *table, float *e_out)
 {
     const WorkItem it = dp.elem_items[blockIdx.x];
     const MatDesc d = dp.mats[it.mat];
@@ -427,7 +427,7 @@ constexpr int kCsSubCols = 32, kCsStepCols = 128, kCsTileStride = 36;
 
 template <bool BF16, bool F16, int RH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RH >= 8 ? 2 : 3)))
-void k_cs_p_octet(DevicePlan dp, const void *__restrict__ grads, const void *__restrict__ table,
+void k_cs_p_octet(KernelPlan dp, const void *__restrict__ grads, const void *__restrict__ table,
                                                     const float *__restrict__ Q, float *P, double *ws)
 {
     __shared__ __attribute__((aligned(16))) float tiles[4][kPTileRows * kCsTileStride];
@@ -585,7 +585,7 @@ constexpr int kCsQTileCols = 64, kCsQTilePitch = 80, kCsQStepRows = 32;
 
 template <bool BF16, bool F16, int RH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RH >= 8 ? 2 : 3)))
-void k_cs_q_octet(DevicePlan dp, const void *__restrict__ grads, const void *__restrict__ table,
+void k_cs_q_octet(KernelPlan dp, const void *__restrict__ grads, const void *__restrict__ table,
                                                     const float *__restrict__ Phat, double *ws)
 {
     __shared__ __attribute__((aligned(16))) float tiles[4][kCsQStepRows * kCsQTilePitch];
@@ -725,7 +725,7 @@ constexpr int kCsMaxBuckets = 256;
 
 template <bool BF16, bool F16, int CPL, int RP>
 __global__ __launch_bounds__(512 / CPL) __attribute__((amdgpu_waves_per_eu(F16 || CPL < 8 ? 4 : 3)))
-void k_cs_update_octet(DevicePlan dp, const void *__restrict__ grads, void *table,
+void k_cs_update_octet(KernelPlan dp, const void *__restrict__ grads, void *table,
                                                          const float *__restrict__ Phat, const float *__restrict__ Qn)
 {
     constexpr int THREADS = 512 / CPL;
@@ -902,7 +902,7 @@ void k_cs_update_octet(DevicePlan dp, const void *__restrict__ grads, void *tabl
 // element), so the table agrees with it to an fp16 unit in the last place, not bit for bit.
 
 // U: one workgroup per run of up to 8 buckets; thread (bucket, c) adds its bucket's rows in ascending order in fp64.
-__global__ __launch_bounds__(256) void k_cs_bucket_sums(DevicePlan dp, const float *__restrict__ Phat, double *ws)
+__global__ __launch_bounds__(256) void k_cs_bucket_sums(KernelPlan dp, const float *__restrict__ Phat, double *ws)
 {
     const WorkItem it = dp.cs_u_items[blockIdx.x];
     const MatDesc d = dp.mats[it.mat];
@@ -930,7 +930,7 @@ __global__ __launch_bounds__(256) void k_cs_bucket_sums(DevicePlan dp, const flo
 // 256 contiguous bytes) rather than in 64 registers per lane: the gather needs the waves.
 typedef float lin_f32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void k_cs_lin_update(DevicePlan dp, const uint16_t *__restrict__ grads, uint16_t *table,
+__global__ __launch_bounds__(256) void k_cs_lin_update(KernelPlan dp, const uint16_t *__restrict__ grads, uint16_t *table,
                                                        const float *__restrict__ Qn, const double *ws)
 {
     __shared__ float s_q[4][8 * 8 * 64];
@@ -1048,7 +1048,7 @@ __global__ __launch_bounds__(256) void k_cs_lin_update(DevicePlan dp, const uint
 // uniformly drawn subset (see rku_perm): the same, the value of a kept coordinate j in slot pi(j).
 
 template <bool BF16, bool F16, int MODE>
-__global__ __launch_bounds__(64) void k_cs_rb_octet(DevicePlan dp, const void *__restrict__ grads, void *table,
+__global__ __launch_bounds__(64) void k_cs_rb_octet(KernelPlan dp, const void *__restrict__ grads, void *table,
                                                     float *__restrict__ delta, uint32_t step_lo, uint32_t step_hi,
                                                     uint32_t *__restrict__ sign_words, const float *__restrict__ c_scale, double *ws)
 {
@@ -1161,7 +1161,7 @@ __global__ __launch_bounds__(64) void k_cs_rb_octet(DevicePlan dp, const void *_
 // The same for any shape: one thread per column of a 256-column tile (sign bits by atomic OR into words the
 // launcher has cleared).
 template <int MODE>
-__global__ __launch_bounds__(kCsCols) void k_cs_rb_generic(DevicePlan dp, const void *grads, void *table, float *delta,
+__global__ __launch_bounds__(kCsCols) void k_cs_rb_generic(KernelPlan dp, const void *grads, void *table, float *delta,
                                                            uint32_t step_lo, uint32_t step_hi, uint32_t *sign_words,
                                                            const float *c_scale, double *ws)
 {

@@ -33,27 +33,27 @@ namespace conef {
 namespace {
 
 template <int SRC, int RH>
-__global__ __launch_bounds__(256) void k_p_strip(DevicePlan dp, Source src, const float *__restrict__ Q, float *P, double *ws)
+__global__ __launch_bounds__(256) void k_p_strip(KernelPlan dp, Source src, const float *__restrict__ Q, float *P, double *ws)
 {
     __shared__ __attribute__((aligned(16))) float lds[kPStripLds];
     p_strip<SRC, RH>(dp, blockIdx.x, lds, src, Q, P, ws);
 }
 
 template <int SRC, int R, bool EXACT>
-__global__ __launch_bounds__(256) void k_q_strip(DevicePlan dp, Source src, const float *__restrict__ Phat, double *ws, float *Qout)
+__global__ __launch_bounds__(256) void k_q_strip(KernelPlan dp, Source src, const float *__restrict__ Phat, double *ws, float *Qout)
 {
     __shared__ double red[2 * R * 64];
     q_strip<SRC, R, EXACT>(dp, blockIdx.x, red, src, Phat, ws, Qout);
 }
 
 template <int SRC, int R, bool EXACT>
-__global__ __launch_bounds__(256) void k_q_flat(DevicePlan dp, Source src, const float *__restrict__ Phat, float *Qout)
+__global__ __launch_bounds__(256) void k_q_flat(KernelPlan dp, Source src, const float *__restrict__ Phat, float *Qout)
 {
     q_flat<SRC, R, EXACT>(dp, blockIdx.x, src, Phat, Qout);
 }
 
 template <int R, bool EXACT, bool TWO, bool GROUP>
-__global__ __launch_bounds__(256) void k_err_strip(DevicePlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
+__global__ __launch_bounds__(256) void k_err_strip(KernelPlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
                                                    uint32_t *codes2, float *scales2, const float *__restrict__ Phat,
                                                    const float *__restrict__ Qn, uint32_t step_lo, uint32_t step_hi)
 {

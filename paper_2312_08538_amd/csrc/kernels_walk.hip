@@ -14,7 +14,7 @@ namespace conef {
 namespace {
 
 template <bool BF16, int BITS, int R, bool TWO>
-__global__ __launch_bounds__(256) void k_err_walk(DevicePlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
+__global__ __launch_bounds__(256) void k_err_walk(KernelPlan dp, const void *__restrict__ grads, uint32_t *codes, float *scales,
                                                   uint32_t *codes2, float *scales2, const float *__restrict__ Phat,
                                                   const float *__restrict__ Qn, uint32_t step_lo, uint32_t step_hi)
 {

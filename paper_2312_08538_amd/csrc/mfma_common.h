@@ -70,7 +70,7 @@ __device__ __forceinline__ uint4 fields2_bf16(uint32_t h)
 // the Q+ and err passes need, per 128-column block, the scales of consecutive rows, which are a row pitch apart (a
 // 128-byte line each) in the state's own row-major order.  For one workgroup of 256 threads; `tile` is 64 x 33 floats
 // of LDS.  (second: into the region kept for the other error vector of Algorithm 3)
-__device__ __forceinline__ void transpose_scales_tile(const DevicePlan &dp, const float *__restrict__ scales, double *ws,
+__device__ __forceinline__ void transpose_scales_tile(const KernelPlan &dp, const float *__restrict__ scales, double *ws,
                                                       int item, int second, float *tile)
 {
     const WorkItem it = dp.split_p_items[item];

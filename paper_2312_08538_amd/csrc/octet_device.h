@@ -231,7 +231,7 @@ __device__ __forceinline__ void load_factor_row(const float *__restrict__ F, int
 // first vector and what that rounding leaves, rounded again with random numbers of its own, to the second
 // (see k_rb_octet).  Both are read by the lane that overwrites them, before it does.
 template <bool BF16, int BITS, int RP, bool TWO = false>
-__global__ __launch_bounds__(256) void k_err_octet(DevicePlan dp, const void *__restrict__ grads, uint32_t *codes,
+__global__ __launch_bounds__(256) void k_err_octet(KernelPlan dp, const void *__restrict__ grads, uint32_t *codes,
                                                    float *scales, const float *__restrict__ Phat,
                                                    const float *__restrict__ Qn, uint32_t step_lo, uint32_t step_hi,
                                                    uint32_t *codes_first = nullptr, float *scales_first = nullptr)
@@ -349,7 +349,7 @@ template <int RP, bool WIDE>
 constexpr int err_tile_lds() { return WIDE ? 4 * 2 * 8 * (RP / 4) * 64 : 1; }
 
 template <bool BF16, int BITS, int RP, bool WIDE, bool TWO>
-__device__ __forceinline__ void err_tile(const DevicePlan &dp, int block, float *s_bq, const void *__restrict__ grads, uint32_t *codes,
+__device__ __forceinline__ void err_tile(const KernelPlan &dp, int block, float *s_bq, const void *__restrict__ grads, uint32_t *codes,
                                          float *scales, const float *__restrict__ Phat, const float *__restrict__ Qn,
                                          uint32_t step_lo, uint32_t step_hi, uint32_t *codes_first, float *scales_first)
 {
@@ -532,7 +532,7 @@ constexpr int kQOctetLds = 4 * kQStepRows * kQTilePitch;       // floats
 // TWO: p = g + e~ + q with the plan's first error vector (dp.i_codes) decoded under the codes / scales arguments.
 // lds: kQOctetLds floats; `block`: index of the workgroup among those of this pass
 template <bool BF16, int BITS, int RH, bool TWO>
-__device__ __forceinline__ void q_octet(const DevicePlan &dp, int block, float *lds, const void *__restrict__ grads,
+__device__ __forceinline__ void q_octet(const KernelPlan &dp, int block, float *lds, const void *__restrict__ grads,
                                         const uint32_t *__restrict__ codes, const float *__restrict__ scales,
                                         const float *__restrict__ Phat, double *ws, float *Qout)
 {
@@ -702,7 +702,7 @@ struct POctetLds {
 // `block`: index of the workgroup among those of this pass
 #define CONEF_P_OCTET_WAVES(TWO) __attribute__((amdgpu_waves_per_eu(TWO ? 2 : 3, TWO ? 2 : 3)))
 template <bool BF16, int BITS, int RH, bool TWO>
-__device__ __forceinline__ void p_octet(const DevicePlan &dp, int block, const POctetLds &lds, const void *__restrict__ grads,
+__device__ __forceinline__ void p_octet(const KernelPlan &dp, int block, const POctetLds &lds, const void *__restrict__ grads,
                                         const uint32_t *__restrict__ codes, const float *__restrict__ scales,
                                         const float *__restrict__ Q, float *P, double *ws)
 {

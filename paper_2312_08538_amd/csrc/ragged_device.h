@@ -27,7 +27,7 @@ struct OctetRegs {
 };
 
 template <bool BF16, int BITS, bool TWO>
-__device__ __forceinline__ OctetBase<BF16, BITS, TWO> octet_base(const DevicePlan &dp, const MatDesc &d, const void *grads,
+__device__ __forceinline__ OctetBase<BF16, BITS, TWO> octet_base(const KernelPlan &dp, const MatDesc &d, const void *grads,
                                                                  const uint32_t *codes, const float *scales, int64_t oct)
 {
     OctetBase<BF16, BITS, TWO> b;
@@ -121,7 +121,7 @@ __device__ __forceinline__ RagLanes rag_lanes(int lane, uint32_t sh0, int rows, 
 // an eighth of an octet's loads, addresses and decode, where p_strip loads a gradient, a code word and a scale for each.
 // lds: kRagLds floats; `block`: index of the workgroup among those of this pass
 template <bool BF16, int BITS, int RH, bool TWO>
-__device__ __forceinline__ void p_ragged(const DevicePlan &dp, int block, float *lds, const void *__restrict__ grads,
+__device__ __forceinline__ void p_ragged(const KernelPlan &dp, int block, float *lds, const void *__restrict__ grads,
                                          const uint32_t *__restrict__ codes, const float *__restrict__ scales,
                                          const float *__restrict__ Q, float *P, double *ws)
 {
@@ -274,7 +274,7 @@ __device__ __forceinline__ void p_ragged(const DevicePlan &dp, int block, float 
 // four waves' sums are added as (0 + 2) + (1 + 3).  A matrix with a single row tile gets its Q+ from here.
 // lds: kRagLds floats
 template <bool BF16, int BITS, int RH, bool TWO>
-__device__ __forceinline__ void q_ragged(const DevicePlan &dp, int block, float *lds, const void *__restrict__ grads,
+__device__ __forceinline__ void q_ragged(const KernelPlan &dp, int block, float *lds, const void *__restrict__ grads,
                                          const uint32_t *__restrict__ codes, const float *__restrict__ scales,
                                          const float *__restrict__ Phat, double *ws, float *Qout)
 {

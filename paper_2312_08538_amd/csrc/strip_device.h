@@ -47,7 +47,7 @@ struct Base {
 };
 
 template <int SRC>
-__device__ __forceinline__ Base<SRC> make_base(const DevicePlan &dp, const MatDesc &d, const Source &src, int64_t start, uint32_t *rel0)
+__device__ __forceinline__ Base<SRC> make_base(const KernelPlan &dp, const MatDesc &d, const Source &src, int64_t start, uint32_t *rel0)
 {
     Base<SRC> b;
     int64_t blk = 0;
@@ -73,7 +73,7 @@ __device__ __forceinline__ Base<SRC> make_base(const DevicePlan &dp, const MatDe
 // Loads U elements of a lane, at distances rel[u] from the base; row[u] / col are their matrix row (uniform) and first
 // column of the strip (lc: the lane's offset from it), hv_col the lane's column hash: used by the sketch forms only.
 template <int SRC, int U>
-__device__ __forceinline__ void load_rows(const DevicePlan &dp, const MatDesc &d, const Source &src, const Base<SRC> &b,
+__device__ __forceinline__ void load_rows(const KernelPlan &dp, const MatDesc &d, const Source &src, const Base<SRC> &b,
                                           const uint32_t (&rel)[U], const int64_t (&row)[U], int64_t col, uint32_t lc, int32_t hv_col,
                                           Raw<SRC> (&o)[U])
 {
@@ -120,7 +120,7 @@ __device__ __forceinline__ void load_rows(const DevicePlan &dp, const MatDesc &d
 
 // p of a loaded element at distance rel.
 template <int SRC>
-__device__ __forceinline__ float form_p(const DevicePlan &dp, const Raw<SRC> &o, uint32_t rel, float omb)
+__device__ __forceinline__ float form_p(const KernelPlan &dp, const Raw<SRC> &o, uint32_t rel, float omb)
 {
     const float g = dp.dtype == 0 ? __uint_as_float(o.g) : bf16_bits_to_f32(o.g);
     if (SRC == kSrcOne || SRC == kSrcTwo) {
@@ -148,7 +148,7 @@ constexpr int kPStripLds = 4 * kStripRows * kPPitch;      // floats
 
 // lds: kPStripLds floats; `block`: index of the workgroup among those of this pass (in the other passes too)
 template <int SRC, int RH>
-__device__ __forceinline__ void p_strip(const DevicePlan &dp, int block, float *lds, const Source &src, const float *__restrict__ Q,
+__device__ __forceinline__ void p_strip(const KernelPlan &dp, int block, float *lds, const Source &src, const float *__restrict__ Q,
                                         float *P, double *ws)
 {
     constexpr bool WIDE = RH >= 4;
@@ -291,7 +291,7 @@ __device__ __forceinline__ void uniform_row(const float *__restrict__ F, int r, 
 // a single row tile gets its Q+ from here.
 // red: LDS, 2 * R * 64 doubles
 template <int SRC, int R, bool EXACT>
-__device__ __forceinline__ void q_strip(const DevicePlan &dp, int block, double *red, const Source &src, const float *__restrict__ Phat,
+__device__ __forceinline__ void q_strip(const KernelPlan &dp, int block, double *red, const Source &src, const float *__restrict__ Phat,
                                         double *ws, float *Qout)
 {
     constexpr int U = 8, kHalf = R * 64;
@@ -376,7 +376,7 @@ __device__ __forceinline__ void q_strip(const DevicePlan &dp, int block, double 
 // have no rows then, and a trip repeats what rows there are: 1 x 1000000, rank 1, 16.7 us (31 with two vectors) against 7.5
 // here; a thread per column without strips took 11.9.
 template <int SRC, int R, bool EXACT>
-__device__ __forceinline__ void q_flat(const DevicePlan &dp, int block, const Source &src, const float *__restrict__ Phat, float *Qout)
+__device__ __forceinline__ void q_flat(const KernelPlan &dp, int block, const Source &src, const float *__restrict__ Phat, float *Qout)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -437,7 +437,7 @@ __device__ __forceinline__ void q_flat(const DevicePlan &dp, int block, const So
 // Three parts with barriers between them: p into LDS in octets; the reconstruction subtracted there; octets rounded and packed
 // (every code of the run has been read by then).
 template <int BITS, bool TWO>
-__device__ __forceinline__ void quantise_run(const DevicePlan &dp, const MatDesc &d, int mat, uint32_t step_lo, uint32_t step_hi,
+__device__ __forceinline__ void quantise_run(const KernelPlan &dp, const MatDesc &d, int mat, uint32_t step_lo, uint32_t step_hi,
                                              const float *X, int64_t flat0, int count, int slots, int first, int stride,
                                              uint32_t *codes, float *scales, uint32_t *codes2, float *scales2)
 {
@@ -499,7 +499,7 @@ __device__ __forceinline__ void quantise_run(const DevicePlan &dp, const MatDesc
 // X: LDS, dp.es_lds floats
 // GROUP: the matrix is walked in groups of rows (it has no segments)
 template <int R, bool EXACT, bool TWO, bool GROUP>
-__device__ __forceinline__ void err_strip(const DevicePlan &dp, int block, float *X, const void *__restrict__ grads, uint32_t *codes,
+__device__ __forceinline__ void err_strip(const KernelPlan &dp, int block, float *X, const void *__restrict__ grads, uint32_t *codes,
                                           float *scales, uint32_t *codes2, float *scales2, const float *__restrict__ Phat,
                                           const float *__restrict__ Qn, uint32_t step_lo, uint32_t step_hi)
 {

@@ -18,7 +18,7 @@ namespace {
 // R: the rank or the next of 1, 2, 4, 8 (both factors are zero beyond the rank: such terms leave the fp32 chain as it is).
 // TWO: both error vectors are decoded and replaced (codes / scales: the first); see k_rb_octet.
 template <bool BF16, int BITS, int R, bool TWO>
-__device__ __forceinline__ void err_walk(const DevicePlan &dp, int block, float *tab, const void *__restrict__ grads, uint32_t *codes,
+__device__ __forceinline__ void err_walk(const KernelPlan &dp, int block, float *tab, const void *__restrict__ grads, uint32_t *codes,
                                          float *scales, uint32_t *codes2, float *scales2, const float *__restrict__ Phat,
                                          const float *__restrict__ Qn, uint32_t step_lo, uint32_t step_hi)
 {
