@@ -39,7 +39,7 @@ void k_p_mixed(KernelPlan dp, int lead, const void *__restrict__ grads, const ui
     }
 }
 
-template <bool BF16, int BITS, int R>
+template <bool BF16, int BITS, int R, bool JOINED>
 __global__ __launch_bounds__(256) CONEF_Q_OCTET_WAVES(BF16, false)
 void k_q_mixed(KernelPlan dp, int lead, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Phat, double *ws, float *Qout)
@@ -47,7 +47,7 @@ void k_q_mixed(KernelPlan dp, int lead, const void *__restrict__ grads, const ui
     __shared__ __attribute__((aligned(16))) float lds[larger(kQOctetLds, kRagLds)];
     const int b = blockIdx.x;
     if (b >= lead) {
-        q_octet<BF16, BITS, (R > 4 ? 2 : 1), false>(dp, b - lead, lds, grads, codes, scales, Phat, ws, Qout);
+        q_octet<BF16, BITS, (R > 4 ? 2 : 1), false, JOINED>(dp, b - lead, lds, grads, codes, scales, Phat, ws, Qout);
     } else if (b < dp.n_q) {
         q_ragged<BF16, BITS, (R > 4 ? 2 : 1), false>(dp, b, lds, grads, codes, scales, Phat, ws, Qout);
     }
@@ -114,9 +114,17 @@ bool mixed_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes
         constexpr bool BF = decltype(bf)::value;
         constexpr int B = decltype(bits)::value;
         const dim3 grid(lead + q_octet_groups(dp)), block(256);
-        if (dp.rank == 8) hipLaunchKernelGGL((k_q_mixed<BF, B, 8>), grid, block, 0, st, octet_items(dp), lead, grads, codes, scales, Phat, ws, Qout);
-        else if (dp.rank == 4) hipLaunchKernelGGL((k_q_mixed<BF, B, 4>), grid, block, 0, st, octet_items(dp), lead, grads, codes, scales, Phat, ws, Qout);
-        else hipLaunchKernelGGL((k_q_mixed<BF, B, 2>), grid, block, 0, st, octet_items(dp), lead, grads, codes, scales, Phat, ws, Qout);
+        auto go = [&](auto rank, auto joined) {
+            hipLaunchKernelGGL((k_q_mixed<BF, B, decltype(rank)::value, decltype(joined)::value>), grid, block, 0, st, octet_items(dp), lead, grads,
+                               codes, scales, Phat, ws, Qout);
+        };
+        auto form = [&](auto rank) {
+            if (dp.q_joined) go(rank, std::true_type{});
+            else go(rank, std::false_type{});
+        };
+        if (dp.rank == 8) form(std::integral_constant<int, 8>{});
+        else if (dp.rank == 4) form(std::integral_constant<int, 4>{});
+        else form(std::integral_constant<int, 2>{});
     });
     return true;
 }

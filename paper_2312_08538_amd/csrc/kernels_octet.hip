@@ -43,13 +43,13 @@ void k_p_octet(KernelPlan dp, const void *__restrict__ grads, const uint32_t *__
     p_octet<BF16, BITS, RH, TWO>(dp, blockIdx.x, lds, grads, codes, scales, Q, P, ws);
 }
 
-template <bool BF16, int BITS, int RH, bool TWO = false>
+template <bool BF16, int BITS, int RH, bool TWO, bool JOINED>
 __global__ __launch_bounds__(256) CONEF_Q_OCTET_WAVES(BF16, TWO)
 void k_q_octet(KernelPlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Phat, double *ws, float *Qout)
 {
     __shared__ __attribute__((aligned(16))) float lds[kQOctetLds];
-    q_octet<BF16, BITS, RH, TWO>(dp, blockIdx.x, lds, grads, codes, scales, Phat, ws, Qout);
+    q_octet<BF16, BITS, RH, TWO, JOINED>(dp, blockIdx.x, lds, grads, codes, scales, Phat, ws, Qout);
 }
 
 template <bool BF16, int BITS, int RP, bool WIDE, bool TWO>
@@ -526,9 +526,30 @@ void octet_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes
                   const float *Phat, double *ws, float *Qout, hipStream_t st)
 {
     if (dp.n_q_f <= 0) return;
-    const dim3 grid(q_octet_groups(dp));
-    if (dp.i_codes) CONEF_OCTET2T_DISPATCH(k_q_octet, grid, st, dp, grads, codes, scales, Phat, ws, Qout);
-    else CONEF_OCTET2_DISPATCH(k_q_octet, grid, st, dp, grads, codes, scales, Phat, ws, Qout);
+    auto go = [&](auto bf, auto bits, auto half, auto two, auto joined) {
+        hipLaunchKernelGGL((k_q_octet<decltype(bf)::value, decltype(bits)::value, decltype(half)::value, decltype(two)::value,
+                                      decltype(joined)::value>),
+                           dim3(q_octet_groups(dp)), dim3(256), 0, st, dp, grads, codes, scales, Phat, ws, Qout);
+    };
+    auto form = [&](auto bf, auto bits, auto half, auto two) {
+        if (dp.q_joined) go(bf, bits, half, two, std::true_type{});
+        else go(bf, bits, half, two, std::false_type{});
+    };
+    auto vectors = [&](auto bf, auto bits, auto half) {
+        if (dp.i_codes) form(bf, bits, half, std::true_type{});
+        else form(bf, bits, half, std::false_type{});
+    };
+    auto rank = [&](auto bf, auto bits) {
+        if (dp.rank > 4) vectors(bf, bits, std::integral_constant<int, 2>{});
+        else vectors(bf, bits, std::integral_constant<int, 1>{});
+    };
+    auto width = [&](auto bf) {
+        if (dp.bits == 2) rank(bf, std::integral_constant<int, 2>{});
+        else if (dp.bits == 4) rank(bf, std::integral_constant<int, 4>{});
+        else rank(bf, std::integral_constant<int, 8>{});
+    };
+    if (dp.dtype == 1) width(std::true_type{});
+    else width(std::false_type{});
 }
 
 // The strip kernel for the plan's err_t_items (rank 4 or 8; `first`: the first vector of Algorithm 3, or null)

@@ -51,3 +51,12 @@ def test_a_launch_carries_no_more_than_its_kernel_reads(kernels):
     """The plan that a kernel is given holds what kernels read (512 bytes at most), not what only launchers do: every line of 64
     bytes costs each launch time.  What else a kernel takes are a dozen pointers at the most."""
     assert max(k["args"] for k in kernels.values()) <= 512 + 128
+
+
+def test_octet_q_pass_holds_two_steps_at_rank_8(kernels):
+    """k_q_octet's waves load the next step's octets and rows of P^ while they work on this one.  At rank 8 that takes all the
+    registers that its occupancy leaves (168 with fp32 gradients, 128 with bf16); far fewer mean that the compiler has put the loads behind
+    the work, which costs a quarter of the pass."""
+    for bits in (2, 4, 8):
+        assert kernels[f"k_q_octet<false, {bits}, 2, false, false>"]["vgprs"] > 144
+        assert kernels[f"k_q_octet<true, {bits}, 2, false, false>"]["vgprs"] > 112
