@@ -522,15 +522,22 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         // writes Q+; nothing is left for the launch that adds partial sums.  us a step without / so: fp32 at rank 4 64 x 2048 25.6 / 21.9,
         // 256 x 8192 29.6 / 27.5, 600 x 2048 28.4 / 29.2, 1000 x 512 28.2 / 32.3; bf16, 8-bit codes, at rank 8 64 x 512 32.6 / 27.3, 256 x 2048
         // 38.0 / 35.4, 600 x 512 39.4 / 49.2, 80 of 256 x 1024 93 / 90.
-        bool q_joined = !sketch;
+        // Models of more than 112 MB of gradients and codes in rows of up to 1024 columns (512 at rank 8) have enough workgroups, and few
+        // enough partial sums, without: 400 of 256 x 512 at rank 4 152.7 / 159.6, at rank 2 143 / 152, with two vectors 256 of them 131 / 141; 500 of
+        // 64 x 1024 at rank 4 119.3 / 121.4, at rank 8 154 / 152; 128 of 256 x 2048 at rank 4 222 / 207; below, 128 of 256 x 512 at rank 4 59.3 / 59.4,
+        // 64 of them 37.9 / 37.6.
+        int64_t all_rows = 0;
+        for (const MatDesc &d : plan.mats) all_rows += d.n;
+        const int64_t model_bits = total_elems * ((dtype == 0 ? 32 : 16) + bits);
+        bool q_joined = !sketch && !(model_bits > (int64_t)7 << 27 && total_elems <= all_rows * (rank <= 4 ? 1024 : 512));
         for (const MatDesc &d : plan.mats) q_joined = q_joined && (d.path != kPathOctet || d.pack || d.n <= 256);
         plan.q_joined = q_joined;
         // Column sketch, P pass: by whole rows (k_csc_p) for ranks up to 4 where most elements are in matrices of 1024 columns or more,
         // which pay for a workgroup's table and sums, and where the rows are enough workgroups.  us a step, strips / rows: 18-layer
         // residual network of 64 channels 94.6 / 88.9, of 40 48.3 / 46.4, of 96 201 / 171, 3000 x 16000 bf16 575 / 487; 43.7 M elements in
         // matrices of 650 columns 168 / 206, 64 x 16000 57 / 62; rank 8 the network of 64 channels 154 / 192.
-        int64_t all_rows = 0, wide_elems = 0;
-        for (const MatDesc &d : plan.mats) { all_rows += d.n; wide_elems += d.m >= 1024 ? d.N : 0; }
+        int64_t wide_elems = 0;
+        for (const MatDesc &d : plan.mats) wide_elems += d.m >= 1024 ? d.N : 0;
         const bool rows_p = all_generic && rank <= 4 && 2 * wide_elems >= total_elems && all_rows >= 1024;
         plan.csc_rows_p = rows_p;
         auto lay_out = [&](int64_t chunk_cols, int64_t times) {
@@ -821,7 +828,7 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         // fp32 elements at rank 4 369.0 / 359.7, two vectors 462.8 / 457.7; 210 M bf16 at rank 8 391.3 / 389.7, the row sketch 460.3 /
         // 457.8; models many times as large the same; 28 M fp32, which fit into the cache whole, 106.5 / 107.3.  (The
         // matrix-core tables dealt to the XCDs in the P pass's order, shape by shape: 388.8, not worth its code.)
-        if (total_elems * (dtype == 0 ? 32 + bits : 16 + bits) > ((int64_t)8 << 28))
+        if (model_bits > ((int64_t)8 << 28))
             for (auto *items : {&plan.q_items, &plan.q_r_items, &plan.q_f_items, &plan.q_m_items, &plan.q_k_items})
                 std::reverse(items->begin(), items->end());
         // Decompress / update: row tiles per workgroup.  On the matrix cores a workgroup keeps its strip of Q+ for several of

@@ -1,0 +1,38 @@
+"""Which kernels the planner sends a model's passes to, on both sides of its rules: what runs fast (the figures stand beside the
+rules in plan.cpp), which no result shows."""
+import json
+import os
+import subprocess
+
+import pytest
+
+from paper_2312_08538_amd import binding as B
+from paper_2312_08538_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def route(tmp_path_factory):
+    """route(kind, layout, rank, bits, block, dtype): what tests/plan_probe.cpp prints for a model"""
+    exe = tmp_path_factory.mktemp("probe") / "plan_probe"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", build.CSRC, "-o", str(exe), os.path.join(HERE, "plan_probe.cpp"),
+                    os.path.join(build.CSRC, "plan.cpp")], check=True)
+
+    def ask(kind, layout, rank, bits=4, block=128, dtype=B.F32):
+        args = [str(exe), kind, *(str(v) for v in (rank, bits, block, dtype)), *(str(v) for mat in layout for v in mat)]
+        return json.loads(subprocess.run(args, check=True, capture_output=True, text=True).stdout)
+
+    return ask
+
+
+def test_octet_q_pass_shares_a_strip_where_that_pays(route):
+    """A workgroup per strip: no matrix of more than 256 rows, and not in large models of short rows (400 of 256 x 512 took 160
+    us a step so, 153 otherwise)."""
+    def joined(layout, rank, **k):
+        return route("step", layout, rank, **k)["q_joined"]
+
+    assert joined([(256, 512)] * 64, 4) and joined([(256, 2048)] * 64, 4) and joined([(64, 1024)] * 500, 8)
+    assert joined([(256, 512)] * 256, 4, bits=8, dtype=B.BF16)
+    assert not joined([(256, 512)] * 400, 4) and not joined([(64, 1024)] * 500, 2) and not joined([(256, 512)] * 500, 8)
+    assert not joined([(257, 512)], 4)
