@@ -36,6 +36,7 @@ struct KernelPlan {
     const WorkItem *p_f_items = nullptr, *q_f_items = nullptr, *err_f_items = nullptr;    // octet family
     const WorkItem *err_t_items = nullptr;      // octet family, err pass with the residual on the fp32 matrix cores
     int n_p_f = 0, n_q_f = 0, n_err_f = 0, n_err_t = 0;
+    int q_joined = 0;               // octet Q+ pass: a workgroup per strip, its waves the row tiles, Q+ straight from there
     int n_mats = 0;
     const WorkItem *p_m_items = nullptr, *q_m_items = nullptr, *err_m_items = nullptr;    // MFMA family
     const WorkItem *split_p_items = nullptr, *split_qn_items = nullptr;
@@ -75,7 +76,6 @@ struct DevicePlan : KernelPlan {
     int n_upd = 0, upd_many = 0;    // upd_many: its items may be of several row tiles
     int n_pred = 0, n_gram = 0, n_qred = 0, n_elem = 0;
     int rpad = 0, n_q_flat = 0, n_err_g = 0;
-    int q_joined = 0;               // octet Q+ pass: a workgroup per strip, its waves the row tiles, Q+ straight from there
     int most_p_chunks = 1;          // column chunks of P of the matrix that has the most
     int ew_lds = 0, es_lds = 0;     // floats of LDS per workgroup of the strip err passes
     long long q_elems = 0;

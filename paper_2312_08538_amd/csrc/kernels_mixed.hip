@@ -39,7 +39,7 @@ void k_p_mixed(KernelPlan dp, int lead, const void *__restrict__ grads, const ui
     }
 }
 
-template <bool BF16, int BITS, int R, bool JOINED>
+template <bool BF16, int BITS, int R, int JOINED>
 __global__ __launch_bounds__(256) CONEF_Q_OCTET_WAVES(BF16, false)
 void k_q_mixed(KernelPlan dp, int lead, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Phat, double *ws, float *Qout)
@@ -118,13 +118,10 @@ bool mixed_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes
             hipLaunchKernelGGL((k_q_mixed<BF, B, decltype(rank)::value, decltype(joined)::value>), grid, block, 0, st, octet_items(dp), lead, grads,
                                codes, scales, Phat, ws, Qout);
         };
-        auto form = [&](auto rank) {
-            if (dp.q_joined) go(rank, std::true_type{});
-            else go(rank, std::false_type{});
-        };
-        if (dp.rank == 8) form(std::integral_constant<int, 8>{});
-        else if (dp.rank == 4) form(std::integral_constant<int, 4>{});
-        else form(std::integral_constant<int, 2>{});
+        if (dp.rank == 8 && dp.q_joined) go(std::integral_constant<int, 8>{}, std::integral_constant<int, kQJoinedYes>{});
+        else if (dp.rank == 8) go(std::integral_constant<int, 8>{}, std::integral_constant<int, kQJoinedNo>{});
+        else if (dp.rank == 4) go(std::integral_constant<int, 4>{}, std::integral_constant<int, kQJoinedAtRunTime>{});
+        else go(std::integral_constant<int, 2>{}, std::integral_constant<int, kQJoinedAtRunTime>{});
     });
     return true;
 }

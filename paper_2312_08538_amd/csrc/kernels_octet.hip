@@ -43,7 +43,7 @@ void k_p_octet(KernelPlan dp, const void *__restrict__ grads, const uint32_t *__
     p_octet<BF16, BITS, RH, TWO>(dp, blockIdx.x, lds, grads, codes, scales, Q, P, ws);
 }
 
-template <bool BF16, int BITS, int RH, bool TWO, bool JOINED>
+template <bool BF16, int BITS, int RH, bool TWO, int JOINED>
 __global__ __launch_bounds__(256) CONEF_Q_OCTET_WAVES(BF16, TWO)
 void k_q_octet(KernelPlan dp, const void *__restrict__ grads, const uint32_t *__restrict__ codes,
                const float *__restrict__ scales, const float *__restrict__ Phat, double *ws, float *Qout)
@@ -532,8 +532,9 @@ void octet_pass_q(const DevicePlan &dp, const void *grads, const uint32_t *codes
                            dim3(q_octet_groups(dp)), dim3(256), 0, st, dp, grads, codes, scales, Phat, ws, Qout);
     };
     auto form = [&](auto bf, auto bits, auto half, auto two) {
-        if (dp.q_joined) go(bf, bits, half, two, std::true_type{});
-        else go(bf, bits, half, two, std::false_type{});
+        if constexpr (decltype(half)::value == 1) go(bf, bits, half, two, std::integral_constant<int, kQJoinedAtRunTime>{});
+        else if (dp.q_joined) go(bf, bits, half, two, std::integral_constant<int, kQJoinedYes>{});
+        else go(bf, bits, half, two, std::integral_constant<int, kQJoinedNo>{});
     };
     auto vectors = [&](auto bf, auto bits, auto half) {
         if (dp.i_codes) form(bf, bits, half, std::true_type{});

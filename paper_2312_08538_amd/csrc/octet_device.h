@@ -530,25 +530,28 @@ constexpr int kQStepRows = 32;
 constexpr int kQOctetLds = 4 * kQStepRows * kQTilePitch;       // floats
 
 // TWO: p = g + e~ + q with the plan's first error vector (dp.i_codes) decoded under the codes / scales arguments.
-// JOINED (dp.q_joined): the workgroup's waves are the row tiles of one strip, and Q+ is written from there.  Kernels of their own: in one
-// kernel with the other form the compiler kept neither from loading a step ahead at rank 8 (114 registers for 168; fp32 gradients,
-// 101 M elements, the pass 123 -> 157 us).
+// JOINED (dp.q_joined): the workgroup's waves are the row tiles of one strip, and Q+ is written from there.  Rank 8: kernels of their
+// own, since in one with the other form the compiler no longer loads a step ahead (114 registers instead of 168; fp32 gradients, 101 M
+// elements, the pass 157 us, so 123).  Lower ranks: one kernel for both (kQJoinedAtRunTime), which costs none, and of bf16 gradients
+// with 8-bit codes it spills two registers less (138 M elements a step of 291 us, in kernels of their own 297).
+constexpr int kQJoinedNo = 0, kQJoinedYes = 1, kQJoinedAtRunTime = 2;
 // lds: kQOctetLds floats; `block`: index of the workgroup among those of this pass
-template <bool BF16, int BITS, int RH, bool TWO, bool JOINED>
+template <bool BF16, int BITS, int RH, bool TWO, int JOINED>
 __device__ __forceinline__ void q_octet(const KernelPlan &dp, int block, float *lds, const void *__restrict__ grads,
                                         const uint32_t *__restrict__ codes, const float *__restrict__ scales,
                                         const float *__restrict__ Phat, double *ws, float *Qout)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int item = __builtin_amdgcn_readfirstlane(JOINED ? block : block * 4 + (int)(threadIdx.x >> 6));
+    const bool joined = JOINED == kQJoinedAtRunTime ? dp.q_joined != 0 : JOINED == kQJoinedYes;
+    const int item = __builtin_amdgcn_readfirstlane(joined ? block : block * 4 + (int)(threadIdx.x >> 6));
     if (item >= dp.n_q_f) return;
     float *T = lds + wave * (kQStepRows * kQTilePitch);
     const WorkItem it = dp.q_f_items[item];
     const MatDesc d = dp.mats[it.mat];
     const int r = dp.rank;
     const int col0 = it.a * kQTileCols;
-    const int64_t row0 = (int64_t)(JOINED ? wave : it.b) * d.q_tile_rows;
+    const int64_t row0 = (int64_t)(joined ? wave : it.b) * d.q_tile_rows;
     const int64_t row1 = (row0 + d.q_tile_rows < d.n) ? row0 + d.q_tile_rows : d.n;
     const int lrow = lane >> 3, loct = lane & 7;      // load layout: 8 lanes per row, rows lrow + 8 s
     const int mi = lane & 15, mk = lane >> 4;         // matrix-core roles
@@ -592,7 +595,8 @@ __device__ __forceinline__ void q_octet(const KernelPlan &dp, int block, float *
     };
 
     Step cur;
-    load_step(cur, row0);           // (a wave of JOINED may have no rows: row1 is the matrix's last one then, which it reads again)
+    // (joined: a wave may have no rows; row1 is n then, and what it loads the matrix's last row)
+    if (JOINED != kQJoinedAtRunTime || row0 < row1) load_step(cur, row0);           // uniform
     for (int64_t i0 = row0; i0 < row1; i0 += kQStepRows) {
         // decode into the tile
 #pragma unroll
@@ -625,7 +629,7 @@ __device__ __forceinline__ void q_octet(const KernelPlan &dp, int block, float *
     }
     // D of block (lane % 16) / 4, entry [lane / 16][lane % 4]: column 16 t + 4 ((lane % 16) / 4) + lane / 16 of the strip
     const int dcol = 4 * (mi >> 2) + mk;
-    if constexpr (JOINED) {
+    if (joined) {
         // the waves' sums, added in wave order
         constexpr int RC = 4 * RH;
         double *red = reinterpret_cast<double *>(lds);            // [wave][column][RC], 16 KB of the 40 KB of tiles

@@ -58,5 +58,5 @@ def test_octet_q_pass_holds_two_steps_at_rank_8(kernels):
     registers that its occupancy leaves (168 with fp32 gradients, 128 with bf16); far fewer mean that the compiler has put the loads behind
     the work, which costs a quarter of the pass."""
     for bits in (2, 4, 8):
-        assert kernels[f"k_q_octet<false, {bits}, 2, false, false>"]["vgprs"] > 144
-        assert kernels[f"k_q_octet<true, {bits}, 2, false, false>"]["vgprs"] > 112
+        assert kernels[f"k_q_octet<false, {bits}, 2, false, 0>"]["vgprs"] > 144
+        assert kernels[f"k_q_octet<true, {bits}, 2, false, 0>"]["vgprs"] > 112
