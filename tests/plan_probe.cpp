@@ -25,6 +25,6 @@ int main(int argc, char **argv)
     const int rc = step ? make_plan(plan, rows.data(), cols.data(), n, rank, bits, block, dtype, 1)
                         : make_sketch_plan(plan, rows.data(), cols.data(), buckets.data(), n, rank, 0.9f, 1, dtype, 1, !strcmp(kind, "columns"));
     if (rc != 0) return 2;
-    printf("{\"ok\": %d, \"q_joined\": %d}\n", check_plan(plan), plan.q_joined);
+    printf("{\"ok\": %d, \"q_joined\": %d, \"err_t_items\": %zu}\n", check_plan(plan), plan.q_joined, plan.err_t_items.size());
     return 0;
 }

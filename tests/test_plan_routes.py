@@ -36,3 +36,8 @@ def test_octet_q_pass_shares_a_strip_where_that_pays(route):
     assert joined([(256, 512)] * 256, 4, bits=8, dtype=B.BF16)
     assert not joined([(256, 512)] * 400, 4) and not joined([(64, 1024)] * 500, 2) and not joined([(256, 512)] * 500, 8)
     assert not joined([(257, 512)], 4)
+
+
+def test_err_items_are_cut_only_where_they_do_not_all_run_at_once(route):
+    assert route("step", [(16384, 1024)], 4)["err_t_items"] == 2048                 # 64 rows of 128 columns each
+    assert route("step", [(5000, 4096)], 4)["err_t_items"] > -(-5000 // 64) * 32
