@@ -96,6 +96,8 @@ int ensure_uploaded(conef_ctx *ctx)
     if ((rc = upload(ctx, pl.rb_items, &d.rb_items))) return rc;
     if ((rc = upload(ctx, pl.rb_g_items, &d.rb_g_items))) return rc;
     d.n_rb = (int)pl.rb_items.size();
+    d.norm_back_one = pl.norm_back ? 1 : 0;
+    d.norm_back_two = pl.norm_back_two ? 1 : 0;
     d.n_rb_g = (int)pl.rb_g_items.size();
     if ((rc = upload(ctx, pl.cs_err_items, &d.cs_err_items))) return rc;
     if ((rc = upload(ctx, pl.cs_err_f_items, &d.cs_err_f_items))) return rc;

@@ -55,6 +55,7 @@ struct KernelPlan {
     // element-wise gradient compressors
     const WorkItem *rb_items = nullptr, *rb_g_items = nullptr;
     int n_rb = 0;
+    int norm_back = 0;              // the scaled sign's norm pass goes backwards (set by its launcher)
     int n_cs_lin = 0;
     const WorkItem *cs_t_items = nullptr, *cs_qt_items = nullptr, *cs_u_items = nullptr, *cs_lin_items = nullptr;   // count sketch, linear form
     const WorkItem *err_items = nullptr;        // err pass of blocks the strip kernel does not take
@@ -78,6 +79,7 @@ struct DevicePlan : KernelPlan {
     int rpad = 0, n_q_flat = 0, n_err_g = 0;
     int most_p_chunks = 1;          // column chunks of P of the matrix that has the most
     int ew_lds = 0, es_lds = 0;     // floats of LDS per workgroup of the strip err passes
+    int norm_back_one = 0, norm_back_two = 0;
     long long q_elems = 0;
     // Strip kernels, P and Q+ passes on octets.  The launchers of those kernels put them in the place of p_items and the others
     // (octet_items).

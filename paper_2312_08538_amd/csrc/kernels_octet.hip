@@ -96,9 +96,7 @@ __global__ __launch_bounds__(256) void k_rb_octet(KernelPlan dp, const void *__r
     constexpr bool BACK = TWO || V2;
     constexpr bool SPARSE = MODE == kModeBlock || MODE == kModeStrata || MODE == kModeUniform;      // Delta keeps a few coordinates as they are
     const int lane = threadIdx.x & 63;
-    // the norm pass goes backwards: the pass behind it begins with what the 256 MB last-level cache still holds of it (the scaled sign
-    // of 210 M bf16 elements 216.8 -> 207.8 us)
-    const int block = MODE == kModeNorm ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;
+    const int block = MODE == kModeNorm && dp.norm_back ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x;     // (see Plan::norm_back)
     const int item = __builtin_amdgcn_readfirstlane(block * 4 + (int)(threadIdx.x >> 6));
     if (item >= dp.n_rb) return;
     const WorkItem it = dp.rb_items[item];
@@ -411,8 +409,10 @@ void octet_stream_step(const DevicePlan &dp, int mode, const void *grads, uint32
     const dim3 grid((dp.n_rb + 3) / 4);
     const uint32_t lo = (uint32_t)step, hi = (uint32_t)(step >> 32);
     const bool two = codes2 != nullptr, v2 = dp.i2_out != nullptr;
+    KernelPlan kp = dp;
+    kp.norm_back = two ? dp.norm_back_two : dp.norm_back_one;
 #define CONEF_STREAM_LAUNCH(BF, B, M, T, V)                                                                                        \
-    hipLaunchKernelGGL((k_rb_octet<BF, B, M, T, V>), grid, dim3(256), 0, st, dp, grads, codes, scales, delta, lo, hi, sign_words,  \
+    hipLaunchKernelGGL((k_rb_octet<BF, B, M, T, V>), grid, dim3(256), 0, st, kp, grads, codes, scales, delta, lo, hi, sign_words,  \
                        c_scale, ws, codes2, scales2)
 #define CONEF_STREAM_MODE(BF, B, M)                                                                                                \
     do {                                                                                                                           \

@@ -258,6 +258,7 @@ struct Plan {
     int64_t small_lds = 0;              // bytes of LDS of the step in one launch; 0: not for this model
     int upd_many = 0;                   // 1: the kernel that walks several row tiles takes them (else all are of one tile)
     // element-wise gradient compressors with the quantiser: stream tables (made with the plan)
+    bool norm_back = false, norm_back_two = false;      // the scaled sign's norm pass goes backwards, one and two error vectors
     size_t sign_words = 0;
     size_t rb_delta_elems = 0;      // set by configure_random_block
     size_t rk_delta_elems = 0;      // set by configure_random_k / configure_random_k_uniform

@@ -25,6 +25,7 @@ int main(int argc, char **argv)
     const int rc = step ? make_plan(plan, rows.data(), cols.data(), n, rank, bits, block, dtype, 1)
                         : make_sketch_plan(plan, rows.data(), cols.data(), buckets.data(), n, rank, 0.9f, 1, dtype, 1, !strcmp(kind, "columns"));
     if (rc != 0) return 2;
-    printf("{\"ok\": %d, \"q_joined\": %d, \"err_t_items\": %zu}\n", check_plan(plan), plan.q_joined, plan.err_t_items.size());
+    printf("{\"ok\": %d, \"q_joined\": %d, \"err_t_items\": %zu, \"norm_back\": %d, \"norm_back_two\": %d}\n",
+           check_plan(plan), plan.q_joined, plan.err_t_items.size(), plan.norm_back, plan.norm_back_two);
     return 0;
 }

@@ -41,3 +41,10 @@ def test_octet_q_pass_shares_a_strip_where_that_pays(route):
 def test_err_items_are_cut_only_where_they_do_not_all_run_at_once(route):
     assert route("step", [(16384, 1024)], 4)["err_t_items"] == 2048                 # 64 rows of 128 columns each
     assert route("step", [(5000, 4096)], 4)["err_t_items"] > -(-5000 // 64) * 32
+
+
+def test_norm_pass_of_the_scaled_sign_goes_backwards_in_large_models_only(route):
+    small, large = (route("step", [(n, 1024)], 4, bits=2, block=256, dtype=B.BF16) for n in (100000, 131072))
+    assert (small["norm_back"], large["norm_back"]) == (0, 1)                       # 18 bits an element: 230 and 302 MB
+    r = route("step", [(53000, 1024)], 4)
+    assert (r["norm_back"], r["norm_back_two"]) == (0, 1)                           # 36 and 40 bits: 244 and 271 MB
