@@ -532,13 +532,24 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         bool q_joined = !sketch && !(model_bits > (int64_t)7 << 27 && total_elems <= all_rows * (rank <= 4 ? 1024 : 512));
         for (const MatDesc &d : plan.mats) q_joined = q_joined && (d.path != kPathOctet || d.pack || d.n <= 256);
         plan.q_joined = q_joined;
-        // Column sketch, P pass: by whole rows (k_csc_p) for ranks up to 4 where most elements are in matrices of 1024 columns or more,
-        // which pay for a workgroup's table and sums, and where the rows are enough workgroups.  us a step, strips / rows: 18-layer
-        // residual network of 64 channels 94.6 / 88.9, of 40 48.3 / 46.4, of 96 201 / 171, 3000 x 16000 bf16 575 / 487; 43.7 M elements in
-        // matrices of 650 columns 168 / 206, 64 x 16000 57 / 62; rank 8 the network of 64 channels 154 / 192.
-        int64_t wide_elems = 0;
-        for (const MatDesc &d : plan.mats) wide_elems += d.m >= 1024 ? d.N : 0;
-        const bool rows_p = all_generic && rank <= 4 && 2 * wide_elems >= total_elems && all_rows >= 1024;
+        // Column sketch, P pass: by whole rows (k_csc_p) for ranks up to 4, where most elements are in matrices of 1024 columns or more and
+        //   - the rows are one workgroup of four per CU (1024), or up to some four of eight for three CUs (2048 to 3200), which the strip
+        //     kernels' launches do not get below: 1024 x 2500 strips / rows 42.3 / 40.4 us a step, 2200 x 1024 40.1 / 39.2, 3000 x 2500 59.4 / 53.9;
+        //   - or, beyond, the rows are long enough to pay for a workgroup's table and sums: 1700 columns in the mean, or most elements in
+        //     matrices of 2500 or more, whose strips are in several chunks.  6000 x 2000 72.8 / 67.9, 8000 x 4998 287.6 / 235.9, 18-layer residual
+        //     network of 64 channels 92.6 / 87.6, of 96 211 / 180, GPT layers of 1024 491 / 478; 16000 x 1024 83.1 / 88.8, 16000 x 1500 123.0 / 123.6, GPT
+        //     layers of 512 140 / 160, of 768 312 / 335, 43.7 M elements in matrices of 650 columns 168 / 206.
+        // Between, in workgroups of four rows and a second, short turn of them, from 12 M elements on: 1500 x 1024 34.0 / 41.6, 1135 x 9000
+        // 130.1 / 136.6, 1500 x 9000 153.9 / 153.0, 2000 x 9000 160.0 / 137.6.  Fewer rows: 64 x 16000 57 / 62.  Rank 8: the network of 64 channels 154 / 192.
+        int64_t wide_elems = 0, very_wide_elems = 0;
+        for (const MatDesc &d : plan.mats) {
+            wide_elems += d.m >= 1024 ? d.N : 0;
+            very_wide_elems += d.m >= 2500 ? d.N : 0;
+        }
+        const bool rows_pay = all_rows <= 1024 ? all_rows == 1024
+                            : all_rows < 2048  ? total_elems >= 12000000
+                                               : all_rows <= 3200 || total_elems >= 1700 * all_rows || 2 * very_wide_elems >= total_elems;
+        const bool rows_p = all_generic && rank <= 4 && 2 * wide_elems >= total_elems && rows_pay;
         plan.csc_rows_p = rows_p;
         auto lay_out = [&](int64_t chunk_cols, int64_t times) {
             wd = 0;

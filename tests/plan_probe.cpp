@@ -25,7 +25,8 @@ int main(int argc, char **argv)
     const int rc = step ? make_plan(plan, rows.data(), cols.data(), n, rank, bits, block, dtype, 1)
                         : make_sketch_plan(plan, rows.data(), cols.data(), buckets.data(), n, rank, 0.9f, 1, dtype, 1, !strcmp(kind, "columns"));
     if (rc != 0) return 2;
-    printf("{\"ok\": %d, \"q_joined\": %d, \"err_t_items\": %zu, \"norm_back\": %d, \"norm_back_two\": %d}\n",
-           check_plan(plan), plan.q_joined, plan.err_t_items.size(), plan.norm_back, plan.norm_back_two);
+    printf("{\"ok\": %d, \"q_joined\": %d, \"err_t_items\": %zu, \"norm_back\": %d, \"norm_back_two\": %d, \"csc_rows_p\": %d}\n",
+           check_plan(plan), plan.q_joined, plan.err_t_items.size(), plan.norm_back, plan.norm_back_two,
+           plan.csc_p_items.empty() ? 0 : plan.csc_p_items[0].c);
     return 0;
 }
