@@ -399,8 +399,9 @@ int conef_get_timing(conef_ctx *ctx, float ms[4]);
 
 /* Host-only self-check of a planned model (diagnostic; no passage of the paper): the work tables of
  * each of the three passes cover every element of every matrix exactly once, every matrix has its
- * reduction and orthonormalisation items, and the workspace regions are disjoint and inside
- * workspace_bytes.  Returns CONEF_OK, or CONEF_ESTATE if the plan is inconsistent. */
+ * reduction and orthonormalisation items, the tables and sizes that kernels index or stage by are inside
+ * those kernels' limits, and the workspace regions are disjoint and inside workspace_bytes.  Returns
+ * CONEF_OK, or CONEF_ESTATE if the plan is inconsistent. */
 int conef_check_plan(const conef_ctx *ctx);
 
 /* Which kernel family the planner has chosen for matrix `mat` (host only; diagnostic, no passage of the paper), and with

@@ -1127,6 +1127,9 @@ bool check_plan(const Plan &plan)
                     if (i >= d.n || seen[i]) return false;
                     if (k > ptr[b] && i <= (plan.bucket_rows[(size_t)(d.hash_off + k - 1)] & INT32_MAX)) return false;
                     if (plan.row_hash[(size_t)(d.hash_off + i)] != ((int32_t)b | (hv & INT32_MIN))) return false;
+                    // the octet kernels take their rows of gradient, table and factor from here
+                    if ((size_t)(d.hash_off + k) >= plan.row_order.size() || plan.row_order[(size_t)(d.hash_off + k)] != std::array<int32_t, 2>{hv, (int32_t)b})
+                        return false;
                     seen[i] = 1;
                 }
             }
@@ -1218,6 +1221,28 @@ bool check_plan(const Plan &plan)
             return l + 1 == nm && next == plan.mats[l].n;
         };
         if (!rows_once(plan.gram_s_items, gram, true) || !rows_once(plan.apply_s_items, apply, false)) return false;
+        // the orthonormalisation in one launch: an item per matrix, its first one, and no more rows or tiles than a workgroup holds
+        if (!plan.orth_first.empty()) {
+            if (plan.orth_first.size() != nm) return false;
+            int64_t first = 0;
+            for (size_t l = 0; l < nm; ++l) {
+                const MatDesc &d = plan.mats[l];
+                if (plan.orth_first[l] != first || d.n > orth_most_rows(plan.rank) || d.gram_tile_rows != 64 || d.n_gram_tiles > 16) return false;
+                first += d.n_gram_tiles;
+            }
+        }
+    } else if (!plan.orth_first.empty()) {
+        return false;
+    }
+    // the step in one launch: every matrix inside the kernel's limits and the launch's LDS
+    if (plan.small_lds > 0) {
+        if (plan.sketch || plan.rank > 8 || plan.rank > plan.rpad || plan.small_lds > kSmallLds || plan.block % 8 != 0 ||
+            plan.block / 8 > 64 || plan.block != 8 << plan.lb_shift)
+            return false;
+        for (const MatDesc &d : plan.mats)
+            if (d.n > kSmallMaxRows || d.N > kSmallMaxElems || d.m % 8 != 0 || d.m8 * 8 != d.m || d.pack || d.lb_shift != plan.lb_shift ||
+                small_lds_bytes(d.n, d.m, plan.rpad) > plan.small_lds)
+                return false;
     }
     for (const WorkItem &it : plan.qred_items) qred[it.mat] += 1;
     for (const WorkItem &it : plan.pred_items) pred[it.mat] += 1;

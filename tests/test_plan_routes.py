@@ -64,3 +64,23 @@ def test_column_sketch_takes_whole_rows_where_that_pays(route):
     import test_gpu_sketch_col_rows as gpu
     for (layout, buckets, rank), want in zip(gpu.CASES, gpu.ROWS):
         assert route("columns", [(n, m, w) for (n, m), w in zip(layout, buckets)], rank)["csc_rows_p"] == want, layout
+
+
+PLANTED = [
+    # (kind, layout, rank, bits, block, dtype): models with the tables, and models just beyond the limits of the kernels behind them
+    ("step", [(256, 128), (40, 64)], 2, 8, 64, B.F32),
+    ("step", [(1025, 33), (64, 65)], 3, 4, 64, B.F32),
+    ("step", [(257, 1100)], 8, 4, 256, B.F32),
+    ("step", [(300, 300)], 16, 4, 128, B.F32),
+    ("step", [(200, 170)], 4, 4, 128, B.F32),
+    ("rows", [(500, 256, 100), (77, 64, 13), (40, 33, 8)], 4, 8, 4, B.F32),
+    ("rows", [(500, 256, 100), (70, 40, 9)], 32, 8, 4, B.BF16),
+    ("columns", [(64, 147, 29)], 4, 8, 4, B.F32),
+]
+
+
+@pytest.mark.parametrize("case", range(len(PLANTED)))
+def test_check_plan_sees_mistakes_in_what_kernels_index_and_stage_by(route, case):
+    kind, layout, rank, bits, block, dtype = PLANTED[case]
+    r = route(kind, layout, rank, bits=bits, block=block, dtype=dtype)
+    assert r["ok"] and r["missed"] == []
