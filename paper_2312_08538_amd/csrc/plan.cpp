@@ -320,7 +320,9 @@ int make_sketch_plan(Plan &plan, const int64_t *rows, const int64_t *cols, const
         while (cs_rows < 256 && total_elems / (cs_rows * 2 * 512) >= min_items) cs_rows *= 2;
         plan.row_hash.assign((size_t)h, 0);
         plan.bucket_rows.assign((size_t)h, 0);
-        plan.row_order.reserve((size_t)h);
+        // (entries of the matrices whose P and Q+ passes read them, up to the last one of those)
+        for (const MatDesc &d : plan.mats)
+            if (reads_row_order(d)) plan.row_order.resize((size_t)(d.hash_off + d.n));
         plan.bucket_ptr.assign((size_t)bp, 0);
         for (int l = 0; l < n_mats; ++l) {
             const MatDesc &d = plan.mats[l];
@@ -339,8 +341,8 @@ int make_sketch_plan(Plan &plan, const int64_t *rows, const int64_t *cols, const
                 const int32_t b = hv & INT32_MAX;
                 plan.bucket_rows[(size_t)(d.hash_off + fill[b]++)] = (int32_t)i | (hv & INT32_MIN);
             }
-            for (int64_t b = 0; b < d.w; ++b)
-                for (int32_t k = ptr[b]; k < ptr[b + 1]; ++k) plan.row_order.push_back({plan.bucket_rows[(size_t)(d.hash_off + k)], (int32_t)b});
+            for (int64_t b = 0; b < d.w && reads_row_order(d); ++b)
+                for (int32_t k = ptr[b]; k < ptr[b + 1]; ++k) plan.row_order[(size_t)(d.hash_off + k)] = {plan.bucket_rows[(size_t)(d.hash_off + k)], (int32_t)b};
             // buckets per item: about 16 rows of the matrix each (at most 64 buckets); on the octet path, where
             // a workgroup first loads 512 rows of Q+, `cs_rows` rows (at most 256 buckets)
             const bool fast = d.path == kPathOctet;
@@ -1039,6 +1041,9 @@ bool check_plan(const Plan &plan)
             if (plan.sketch || d.m > kRaggedMaxCols || it.c > kStripRows) return false;
             c.add(plan, it, it.a, it.c, (int64_t)it.b * d.p_chunk_cols, d.p_chunk_cols);
         }
+        for (const std::vector<WorkItem> *items : {&plan.p_f_items, &plan.q_f_items})
+            for (const WorkItem &it : *items)
+                if (plan.sketch && !reads_row_order(plan.mats[it.mat])) return false;
         for (const WorkItem &it : plan.p_f_items)
             c.add(plan, it, it.a, kPTileRows, (int64_t)it.b * plan.mats[it.mat].p_chunk_cols, plan.mats[it.mat].p_chunk_cols);
         if (plan.p_m_items.size() % 8 != 0) return false;                  // eight lists of one length
@@ -1128,7 +1133,8 @@ bool check_plan(const Plan &plan)
                     if (k > ptr[b] && i <= (plan.bucket_rows[(size_t)(d.hash_off + k - 1)] & INT32_MAX)) return false;
                     if (plan.row_hash[(size_t)(d.hash_off + i)] != ((int32_t)b | (hv & INT32_MIN))) return false;
                     // the octet kernels take their rows of gradient, table and factor from here
-                    if ((size_t)(d.hash_off + k) >= plan.row_order.size() || plan.row_order[(size_t)(d.hash_off + k)] != std::array<int32_t, 2>{hv, (int32_t)b})
+                    if (reads_row_order(d) && ((size_t)(d.hash_off + k) >= plan.row_order.size() ||
+                                               plan.row_order[(size_t)(d.hash_off + k)] != std::array<int32_t, 2>{hv, (int32_t)b}))
                         return false;
                     seen[i] = 1;
                 }

@@ -199,7 +199,7 @@ struct Plan {
     size_t table_elems = 0;
     std::vector<int32_t> row_hash;      // per row: bucket, bit 31 set for sign -1
     std::vector<int32_t> bucket_ptr;    // per matrix w + 1 entries: rows of bucket b are bucket_rows[ptr[b] .. ptr[b+1])
-    std::vector<std::array<int32_t, 2>> row_order;  // row sketch, per matrix n entries: bucket_rows' entry, its bucket
+    std::vector<std::array<int32_t, 2>> row_order;  // row sketch, n entries per matrix of reads_row_order: bucket_rows' entry, its bucket
     std::vector<int32_t> bucket_rows;   // per matrix n entries: row index (bit 31: sign -1), ascending within a bucket
     std::vector<WorkItem> cs_err_items; // sketch update: (mat, first bucket, buckets, column tile of cs_cols); column form: (mat, first row, rows, 0)
     std::vector<WorkItem> cs_err_f_items;  // the same for matrices of the octet path (wider tiles)
@@ -275,6 +275,8 @@ struct Plan {
 // matrix has its reduction, Gram and apply items, and that the workspace regions do not overlap.
 // Returns true if so.
 bool check_plan(const Plan &plan);
+// row sketch: the matrix's P and Q+ passes walk its rows bucket by bucket (the octet kernels; the linear form does not)
+inline bool reads_row_order(const MatDesc &d) { return d.path == kPathOctet && !d.cs_lin; }
 
 // Returns 0 or a negative CONEF_E* code.  `rows`/`cols` have n_mats entries.
 int make_plan(Plan &plan, const int64_t *rows, const int64_t *cols, int n_mats, int rank, int bits,

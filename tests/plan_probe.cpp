@@ -38,10 +38,10 @@ int main(int argc, char **argv)
         change(bad);
         if (check_plan(bad)) printf("%s\"%s\"", comma, what), comma = ", ";
     };
-    if (!plan.row_order.empty()) {
-        plant("a row of row_order", [](Plan &p) { p.row_order[p.mats[0].hash_off][0] ^= 1; });
-        plant("a bucket of row_order", [](Plan &p) { p.row_order[p.mats[0].hash_off][1] += 1; });
-        plant("the length of row_order", [](Plan &p) { p.row_order.resize(p.mats[0].hash_off + p.mats[0].n - 1); });
+    if (!plan.row_order.empty()) {          // (its last entry is one of a matrix that reads it)
+        plant("a row of row_order", [](Plan &p) { p.row_order.back()[0] ^= 1; });
+        plant("a bucket of row_order", [](Plan &p) { p.row_order.back()[1] += 1; });
+        plant("the length of row_order", [](Plan &p) { p.row_order.pop_back(); });
     }
     if (!plan.orth_first.empty()) {
         plant("an entry of orth_first", [](Plan &p) { p.orth_first.back() += 1; });

@@ -84,3 +84,10 @@ def test_check_plan_sees_mistakes_in_what_kernels_index_and_stage_by(route, case
     kind, layout, rank, bits, block, dtype = PLANTED[case]
     r = route(kind, layout, rank, bits=bits, block=block, dtype=dtype)
     assert r["ok"] and r["missed"] == []
+
+
+def test_row_order_is_made_for_the_matrices_that_read_it(route):
+    """The row sketch's octet kernels walk a matrix's rows bucket by bucket; the linear form and the kernels for any shape do not."""
+    assert route("rows", [(500, 256, 100), (70, 40, 9), (64, 33, 9)], 4)["row_order"] == 570
+    assert route("rows", [(500, 33, 100), (70, 41, 9)], 4)["row_order"] == 0
+    assert route("rows", [(500, 256, 100), (70, 128, 9)], 32, dtype=B.BF16)["row_order"] == 0
