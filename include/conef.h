@@ -113,7 +113,10 @@ int conef_step_static(conef_ctx *ctx, const void *grads, uint32_t *err_codes, fl
 
 /* The same step in its four stages, for callers that all-reduce P and Q between them
  * (the two exchange points of an all-reducable compressor, Section 2 "How gradients are
- * communicated") and for per-stage testing.  conef_step == p, orthonormalise, q, err. */
+ * communicated") and for per-stage testing.  conef_step == p, orthonormalise, q, err: the same kernels and bits, except
+ * that a model of small matrices only takes the whole step in one kernel, which adds the same fp64 products of P and of Q+
+ * in another order.  A factor's entry then differs, by the last bit of its fp32 value, where the two sums lie on either side
+ * of a rounding boundary (about one entry in 10^8), and with it what follows from that entry. */
 int conef_step_p(conef_ctx *ctx, const void *grads, const uint32_t *err_codes,
                  const float *err_scales, const float *Q_state, float *P_raw_out,
                  void *workspace, void *hip_stream);              /* P = (g + e) * Q_state          */
@@ -392,7 +395,8 @@ int conef_i_step(conef_ctx *ctx, const void *grads, uint32_t *err_codes, float *
  * 64 conef_step calls are kept (a ring); stage calls made on their own share one slot.
  * conef_get_timing waits for the recorded events and returns the mean duration per stage in
  * milliseconds over the kept calls: ms[4] = {p, orthonormalise, q, err}.  While timing is on, models of
- * small matrices take the stages one by one, too (the same results).  Switching timing on
+ * small matrices take the stages one by one, too: the stages' times are those of their own launches, together about
+ * twice the one launch of an untimed step, and the results are the stage calls' (see there).  Switching timing on
  * again clears the ring.  Errors: CONEF_ESTATE if timing is off, CONEF_EHIP. */
 int conef_set_timing(conef_ctx *ctx, int on);
 int conef_get_timing(conef_ctx *ctx, float ms[4]);

@@ -6,7 +6,8 @@
 // one CU.  One matrix of 256 x 128 at rank 2, fp32, 8-bit codes: 23 - 28 us a step in six launches, 14.8 so, of which in the kernel
 // fetch and decode 2.1, P 2.2 and Q+ 3.2 (LDS reads, conversions to fp64), Gram matrix and factor 1.4, P^ 0.3, residual and
 // rounding 2.4.
-// The sums are the octet family's: fp64 matrix cores for P and Q+ (v_mfma_f64_4x4x4_4b_f64, layout at the octet P pass), the
+// The sums are the octet family's: fp64 matrix cores for P and Q+ (v_mfma_f64_4x4x4_4b_f64, layout at the octet P pass; in an order
+// of their own, so that an entry in some 10^8 rounds to the other side of its last fp32 bit than in the stages' launches), the
 // Gram matrix in the order of k_gram_small and k_cholesky_apply, the residual as the fp32 fma chain.
 #include <type_traits>
 

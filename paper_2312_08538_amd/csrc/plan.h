@@ -70,7 +70,7 @@ constexpr int64_t walk_lds(int64_t m, int rank) { return (m + 8) * walk_rank(ran
 constexpr int kFlatRows = 8;        // matrices of at most so many rows: a wave of the strip Q+ pass takes all of them
 // The step in one launch, a workgroup per matrix (kernels_small.hip): matrices whose p = g + e and factors fit into the LDS of a
 // CU, rows of whole octets, blocks of 8 * 2^j elements, ranks up to 8, no matrix of the packed-split family (whose stages add up in
-// fp32, and the step keeps the bits of its stages).  Up to 256 matrices, a CU each; more, which take turns, only if they are worth
+// fp32; fp64 sums in another order are the stages' but for a last bit of an fp32 entry now and then).  Up to 256 matrices, a CU each; more, which take turns, only if they are worth
 // a CU.  us a step, in one launch / in the stages' six: 8 x 8 at rank 4, bf16 7.9 / 19.6, at rank 8 10.3 / 19.6, 300 of them 15.3 /
 // 19.6 and 20.1 / 19.6, 1000 29 / 19 and 39 / 25; 64 x 64 at rank 8 11.1 / 21.1, 300 of them 22.0 / 25.8, 1000 42.6 / 47, 4000 167 / 134;
 // 16 x 1024 at rank 8 17.0 / 30.1, 300 of them 38.6 / 66.6, 4000 346 / 648; 256 x 128 at rank 2 14.6 / 23.1, at rank 4, bf16 16.6 / 22.5, 256
