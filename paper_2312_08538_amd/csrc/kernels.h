@@ -40,31 +40,34 @@ struct KernelPlan {
     int n_mats = 0;
     const WorkItem *p_m_items = nullptr, *q_m_items = nullptr, *err_m_items = nullptr;    // MFMA family
     const WorkItem *split_p_items = nullptr, *split_qn_items = nullptr;
-    int n_p_m = 0, n_q_m = 0, n_err_m = 0, n_apply = 0;
-    const WorkItem *p_k_items = nullptr, *q_k_items = nullptr;                            // packed-split passes
-    int n_p_k = 0, n_q_k = 0;
+    int n_p_m = 0, n_q_m = 0, n_err_m = 0;
+    int n_p_k = 0;
+    const WorkItem *p_k_items = nullptr;        // packed-split passes
+    // element-wise gradient compressors
+    const WorkItem *rb_items = nullptr, *rb_g_items = nullptr;
+    int n_rb = 0;
+    int norm_back = 0;              // the scaled sign's norm pass goes backwards (set by its launcher)
+    // Algorithm 3, version 2, around an element-wise gradient compressor: the first error vector (a random block of
+    // every matrix, MatDesc::i2_k values at i2_off) as it comes in and where the new one goes (another buffer)
+    const float *i2_in = nullptr;
+    float *i2_out = nullptr;
     // Improved contractive error feedback around the rank-r compressor: the FIRST error vector, laid out like the
     // codes / scales arguments of the pass kernels (which then hold the second one): p = g + first + second.  Null in
     // every other call; set in a copy of the plan by the launchers of the two-vector passes.
     const uint32_t *i_codes = nullptr;
     const float *i_scales = nullptr;
-    // Algorithm 3, version 2, around an element-wise gradient compressor: the first error vector (a random block of
-    // every matrix, MatDesc::i2_k values at i2_off) as it comes in and where the new one goes (another buffer)
-    const float *i2_in = nullptr;
-    float *i2_out = nullptr;
-    // element-wise gradient compressors
-    const WorkItem *rb_items = nullptr, *rb_g_items = nullptr;
-    int n_rb = 0;
-    int norm_back = 0;              // the scaled sign's norm pass goes backwards (set by its launcher)
-    int n_cs_lin = 0;
+    int n_apply = 0, n_cs_lin = 0;
+    const WorkItem *q_k_items = nullptr;
+    int n_q_k = 0;
     const WorkItem *cs_t_items = nullptr, *cs_qt_items = nullptr, *cs_u_items = nullptr, *cs_lin_items = nullptr;   // count sketch, linear form
     const WorkItem *err_items = nullptr;        // err pass of blocks the strip kernel does not take
     const WorkItem *pred_items = nullptr, *gram_items = nullptr, *apply_items = nullptr, *qred_items = nullptr,
                    *elem_items = nullptr;
     const OrthItem *gram_s_items = nullptr, *apply_s_items = nullptr;      // orthonormalisation, ranks up to 8
     const int32_t *orth_first = nullptr;        // both in one launch: each matrix's first gram_s_items entry; null: two launches
+    uint64_t pad = 0;               // a kernel's other arguments start a line
 };
-static_assert(sizeof(KernelPlan) <= 8 * 64, "a line of arguments more for every launch");
+static_assert(sizeof(KernelPlan) == 8 * 64, "whole lines, and a line more for every launch");
 
 // ... and what only their launchers read
 struct DevicePlan : KernelPlan {
