@@ -929,10 +929,10 @@ int make_plan_impl(Plan &plan, const int64_t *rows, const int64_t *cols, int n_m
         // few thousand equal items on a chip that holds two or three thousand waves, the last items to start run on a
         // nearly empty chip for a whole item's duration.  So the items at the end of the table are cut into shorter ones
         // (rows stay multiples of the 16 of a trip): halves from 75 % of the work on, quarters from 90 % (measured on 124 M
-        // and 210 M elements: 6 - 7 % on the pass; cutting earlier or finer costs more in short items than it gains).  Up to some
-        // 2400 items start side by side, and there is no end to fill (16384 x 1024 at rank 4, 2048 items, cut / whole: fp32 65.9 / 63.5, bf16
-        // 54.0 / 52.9; 5000 x 4096, 2528: 78.1 / 79.5, bf16 66.8 / 68.4).
-        if (plan.err_t_items.size() >= 2400) {
+        // and 210 M elements: 6 - 7 % on the pass; cutting earlier or finer costs more in short items than it gains).  Up to
+        // 2048 items, two workgroups per CU, start side by side, and there is no end to fill (16384 x 1024 at rank 4, 2048 items, cut / whole:
+        // fp32 65.9 / 63.5, bf16 54.0 / 52.9; 130 of 256 x 512, 2080: 63.0 / 65.9; 5000 x 4096, 2528: 78.1 / 79.5, bf16 66.8 / 68.4).
+        if (plan.err_t_items.size() > 2048) {
             int64_t total = 0, done = 0;
             for (const WorkItem &it : plan.err_t_items) total += it.c;
             std::vector<WorkItem> cut;
