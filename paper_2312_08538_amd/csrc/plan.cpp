@@ -321,8 +321,10 @@ int make_sketch_plan(Plan &plan, const int64_t *rows, const int64_t *cols, const
         plan.row_hash.assign((size_t)h, 0);
         plan.bucket_rows.assign((size_t)h, 0);
         // (entries of the matrices whose P and Q+ passes read them, up to the last one of those)
+        size_t ordered = 0;
         for (const MatDesc &d : plan.mats)
-            if (reads_row_order(d)) plan.row_order.resize((size_t)(d.hash_off + d.n));
+            if (reads_row_order(d)) ordered = (size_t)(d.hash_off + d.n);
+        plan.row_order.resize(ordered);
         plan.bucket_ptr.assign((size_t)bp, 0);
         for (int l = 0; l < n_mats; ++l) {
             const MatDesc &d = plan.mats[l];
@@ -339,10 +341,10 @@ int make_sketch_plan(Plan &plan, const int64_t *rows, const int64_t *cols, const
             for (int64_t i = 0; i < d.n; ++i) {
                 const int32_t hv = plan.row_hash[(size_t)(d.hash_off + i)];
                 const int32_t b = hv & INT32_MAX;
-                plan.bucket_rows[(size_t)(d.hash_off + fill[b]++)] = (int32_t)i | (hv & INT32_MIN);
+                const size_t at = (size_t)(d.hash_off + fill[b]++);
+                plan.bucket_rows[at] = (int32_t)i | (hv & INT32_MIN);
+                if (reads_row_order(d)) plan.row_order[at] = {plan.bucket_rows[at], b};
             }
-            for (int64_t b = 0; b < d.w && reads_row_order(d); ++b)
-                for (int32_t k = ptr[b]; k < ptr[b + 1]; ++k) plan.row_order[(size_t)(d.hash_off + k)] = {plan.bucket_rows[(size_t)(d.hash_off + k)], (int32_t)b};
             // buckets per item: about 16 rows of the matrix each (at most 64 buckets); on the octet path, where
             // a workgroup first loads 512 rows of Q+, `cs_rows` rows (at most 256 buckets)
             const bool fast = d.path == kPathOctet;
