@@ -17,16 +17,12 @@ CASES = [
     (4, 4, 128, wl.F32, [(256, 384), (200, 147), (31, 576)]),                # beside the strip family
     (3, 4, 64, wl.F32, [(1024, 33), (1000, 130), (64, 65), (63, 64), (3, 20)]),      # one launch, up to all of its threads
     (3, 4, 64, wl.F32, [(1025, 33), (64, 65)]),                              # two launches
-    (4, 4, 128, wl.F32, [(240, 4000), (40, 2048)]),                          # column chunks of P added in it
+    (4, 4, 128, wl.F32, [(300, 5000), (40, 2048)]),                          # column chunks of P added in it
     (8, 4, 256, wl.F32, [(256, 1100), (65, 512)]),
     (8, 4, 256, wl.F32, [(257, 1100), (65, 512)]),
     (8, 4, 128, wl.F32, [(300, 640), (1500, 384)]),                          # err pass: items of 16 rows
-    (8, 2, 256, wl.BF16, [(3300, 2048), (33, 256)]),                         # ... of 32
+    (8, 2, 256, wl.BF16, [(2100, 2048), (33, 256)]),                         # ... of 32
 ]
-# (shared strips of Q+, orthonormalisation in one launch, rows of the err pass's first item, column chunks of P);
-# tests/test_plan_routes.py holds the planner to them
-ROUTES = [(1, 1, 4, 1), (1, 1, 0, 1), (1, 1, 0, 4), (0, 1, 16, 1), (1, 1, 16, 3), (1, 1, 0, 1), (1, 0, 0, 1), (1, 1, 16, 16), (1, 1, 16, 5),
-          (1, 0, 16, 5), (0, 0, 16, 2), (0, 0, 32, 4)]
 
 
 @pytest.fixture(scope="module")

@@ -1,4 +1,4 @@
-"""GPU tests of the column sketch's P pass by whole rows (ranks up to 4, wide matrices, as many rows as pay for it): eight, four, two
+"""GPU tests of the column sketch's P pass by whole rows (ranks up to 4, wide matrices, 1024 rows or more in the model): eight, four, two
 and one row per workgroup, short last groups, narrow matrices beside wide ones, fewer columns than a trip's threads and several trips;
 through the column sketch's own checks of the factor stages and of whole steps against the oracle."""
 import pytest
@@ -9,14 +9,12 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     ([(2100, 1024), (7, 147)], [204, 29], 4),              # eight rows, the last group of four
-    ([(959, 1100), (60, 33), (5, 4608)], [220, 7, 922], 3),      # four
-    ([(2049, 1025)], [1], 1),                              # one bucket
-    ([(2050, 2300)], [2300], 2),                           # as many buckets as columns
-    ([(1019, 6400), (5, 64)], [6000, 13], 4),              # two rows: the table fills the LDS
+    ([(1003, 1100), (60, 33), (5, 4608)], [220, 7, 922], 3),     # four
+    ([(1030, 1025)], [1], 1),                              # one bucket
+    ([(1026, 2300)], [2300], 2),                           # as many buckets as columns
+    ([(1025, 6400)], [6000], 4),                           # two rows: the table fills the LDS
     ([(1024, 12100)], [12000], 2),                         # one
 ]
-# rows per workgroup of the first matrix; tests/test_plan_routes.py holds the planner to it
-ROWS = [8, 4, 8, 8, 2, 1]
 
 
 @pytest.fixture(scope="module")

@@ -9,16 +9,15 @@ from paper_2312_08538_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # (layout, rank, bits, block); tests/test_plan_routes.py holds the planner to the one launch for each
-    ([(256, 128)], 2, 8, 64),                                    # most elements
-    ([(1024, 16)], 4, 4, 128),                                   # most rows: P in several trips, 16 Gram tiles; blocks across rows
-    ([(8, 1024)], 8, 4, 64),                                     # few rows, as many tiles of columns as waves
-    ([(4, 1288), (12, 1032)], 2, 8, 64),                         # more of them
+    # (layout, rank, bits, block)
+    ([(256, 128)], 2, 8, 64),                                    # all of a CU's LDS
+    ([(1024, 24)], 4, 4, 128),                                   # most rows; blocks across rows
+    ([(8, 2240)], 8, 4, 64),                                     # few rows, most tiles of columns
     ([(1, 8), (8, 8), (16, 16)], 1, 2, 16),                      # one octet; N no multiple of a code word
     ([(5, 8), (17, 24), (63, 40), (65, 8)], 5, 2, 32),           # remainders of 16 rows, 64 rows, 16 columns; rank 5
-    ([(100, 136), (33, 264), (560, 40), (129, 72)], 3, 8, 512),  # more scale block than row, short last blocks
-    ([(31, 520), (240, 104), (7, 56)], 7, 4, 8),
-    ([(128, 64)] * 300, 4, 4, 64),                               # more workgroups than CUs
+    ([(100, 136), (33, 264), (600, 40), (129, 72)], 3, 8, 512),  # more scale block than row, short last blocks
+    ([(31, 1000), (240, 104), (7, 56)], 7, 4, 8),
+    ([(40, 64)] * 300, 4, 4, 64),                                # more workgroups than CUs
 ]
 
 

@@ -61,18 +61,18 @@ def test_column_sketch_takes_whole_rows_where_that_pays(route):
     gpt = lambda d: [(3000, d)] + [(d, 3 * d), (d, d), (d, 4 * d), (4 * d, d)] * 8
     assert not rows(gpt(512)) and not rows(gpt(768)) and rows(gpt(1024))
     assert not rows([(20000, 1024)] + [(4096, 1024)] * 4) and not rows([(1024, 2500)], 8)
-    import test_gpu_sketch_col_rows as gpu
+    import test_gpu_planned_routes as gpu
 
-    for (layout, buckets, rank), want in zip(gpu.CASES, gpu.ROWS):
+    for (layout, buckets, rank), want in gpu.COLUMN_ROWS:
         assert route("columns", [(n, m, w) for (n, m), w in zip(layout, buckets)], rank)["csc_rows_p"] == want, layout
 
 
 def test_step_in_one_launch(route):
-    """... for every model of its GPU test (a second column would be noise in that test's rank-one gradients: rank 1 there), and not
+    """... for every model of its GPU tests (a second column would be noise in that test's rank-one gradients: rank 1 there), and not
     just beyond the kernel's limits."""
-    import test_gpu_small_step as gpu
+    import test_gpu_planned_routes as gpu
 
-    for layout, rank, bits, block in gpu.CASES:
+    for layout, rank, bits, block in gpu.SMALL:
         for r in {rank, 1}:
             for dtype in (B.F32, B.BF16):
                 assert route("step", layout, r, bits, block, dtype)["one_launch"], (layout, r, dtype)
@@ -82,18 +82,18 @@ def test_step_in_one_launch(route):
 
 
 def test_few_rows(route, monkeypatch):
-    import test_gpu_few_rows as gpu
+    import test_gpu_planned_routes as gpu
 
     monkeypatch.setenv("CONEF_PACK", "0")
-    for (rank, bits, block, dtype, layout), want in zip(gpu.CASES, gpu.ROUTES, strict=True):
+    for (rank, bits, block, dtype, layout), want in gpu.FEW_ROWS:
         r = route("step", layout, rank, bits, block, dtype)
         assert (r["q_joined"], r["orth_rows"], r["err_rows"], r["p_chunks"]) == want, layout
 
 
 def test_err_pass_with_q_in_lds(route):
-    import test_gpu_walk as gpu
+    import test_gpu_planned_routes as gpu
 
-    for i, (rank, bits, block, dtype, layout) in enumerate(gpu.CASES):
+    for i, (rank, bits, block, dtype, layout) in enumerate(gpu.WALK):
         assert (route("step", layout, rank, bits, block, dtype)["walk"] > 0) == (i not in gpu.ON_STRIPS), layout
 
 
